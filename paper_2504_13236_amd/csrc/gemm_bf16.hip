@@ -27,6 +27,36 @@ namespace nnt {
 
 namespace {
 
+// Eight elements at any address that an element may have: global memory takes 16-byte accesses at every multiple of 2
+// bytes, so odd leading dimensions and operands that start anywhere are read with vectors too (read one element at a
+// time, operands of odd extents kept these kernels at 50 to 80 TFLOP/s).
+typedef uint32_t u32x4u __attribute__((ext_vector_type(4), aligned(2)));
+__device__ __forceinline__ uint4 load8(const uint16_t* p) {
+    const u32x4u x = *reinterpret_cast<const u32x4u*>(p);
+    return make_uint4(x[0], x[1], x[2], x[3]);
+}
+
+// A vector that had to be moved back by `over` elements (0 .. 7) to stay inside its operand: its elements in their
+// places, zeros behind them; all zeros from 8 on.
+__device__ __forceinline__ uint4 moved_back(const uint4& x, int over) {
+    if (over <= 0) return x;
+    uint32_t w[5] = {x.x, x.y, x.z, x.w, 0u};
+    const int d = over >> 1;
+    uint32_t y[5];
+#pragma unroll
+    for (int i = 0; i < 5; i++) {
+        uint32_t t = 0u;
+#pragma unroll
+        for (int s = 0; i + s < 4; s++) t = d == s ? w[i + s] : t;
+        y[i] = t;
+    }
+    if (over & 1) {
+#pragma unroll
+        for (int i = 0; i < 4; i++) y[i] = (y[i] >> 16) | (y[i + 1] << 16);
+    }
+    return make_uint4(y[0], y[1], y[2], y[3]);
+}
+
 __device__ __forceinline__ uint4 load8_guarded(const uint16_t* p, int cnt) {
     uint16_t e[8];
 #pragma unroll
@@ -46,8 +76,11 @@ struct LoaderK {
     static constexpr int TOTAL = ROWS * BKT / 8;
     static constexpr int KP = BKT + 8;
     uint4 v[NV];
-    __device__ __forceinline__ void load(const uint16_t* base, int ld, int row0, int nrows, int k0, int kc,
-                                         bool vec_ok, int tid) {
+    // A step that reaches beyond the operand's rows or the chunk's k: every lane fetches eight elements that exist (rows
+    // beyond the edge stand in for the last one, a vector that crosses the end of the chunk is moved back until it ends
+    // there), so that these loads too stay in flight under the matrix instructions; mend() then puts the elements in
+    // place.  Chunks shorter than a vector are read one element at a time.
+    __device__ __forceinline__ void load(const uint16_t* base, int ld, int row0, int nrows, int k0, int kc, int tid) {
 #pragma unroll
         for (int i = 0; i < NV; i++) {
             const int idx = tid + 256 * i;
@@ -55,22 +88,29 @@ struct LoaderK {
             if (TOTAL >= 256 || idx < TOTAL) {
                 const int r = idx / (BKT / 8), k = (idx % (BKT / 8)) * 8;
                 const int gr = row0 + r, gk = k0 + k;
-                const uint16_t* p = base + gk + (int64_t)gr * ld;
-                const int cnt = gr < nrows ? kc - gk : 0;
-                if (cnt >= 8 && vec_ok) x = *reinterpret_cast<const uint4*>(p);
-                else if (cnt > 0) x = load8_guarded(p, cnt);
+                if (kc >= 8) x = load8(base + min(gk, kc - 8) + (int64_t)min(gr, nrows - 1) * ld);
+                else if (gr < nrows && gk < kc) x = load8_guarded(base + gk + (int64_t)gr * ld, kc - gk);
             }
             v[i] = x;
         }
     }
-    // interior k-step of an aligned operand; `base` points at (row0, k0)
+    // zeros for k beyond the chunk; what stands for missing rows only reaches results that are never stored
+    __device__ __forceinline__ void mend(int, int, int k0, int kc, int tid) {
+        if (kc < 8 || k0 + BKT <= kc) return;
+#pragma unroll
+        for (int i = 0; i < NV; i++) {
+            const int k = ((tid + 256 * i) % (BKT / 8)) * 8;
+            v[i] = moved_back(v[i], k0 + k + 8 - kc);
+        }
+    }
+    // interior k-step; `base` points at (row0, k0)
     __device__ __forceinline__ void load_fast(const uint16_t* base, int ld, int tid) {
 #pragma unroll
         for (int i = 0; i < NV; i++) {
             const int idx = tid + 256 * i;
             if (TOTAL >= 256 || idx < TOTAL) {
                 const int r = idx / (BKT / 8), k = (idx % (BKT / 8)) * 8;
-                v[i] = *reinterpret_cast<const uint4*>(base + k + (int64_t)r * ld);
+                v[i] = load8(base + k + (int64_t)r * ld);
             }
         }
     }
@@ -93,25 +133,33 @@ struct LoaderR {
     static constexpr int NB = TOTAL / 256 > 0 ? TOTAL / 256 : 1;
     static constexpr int KP = BKT + 8;
     uint4 v[NB][4];
-    __device__ __forceinline__ void load(const uint16_t* base, int ld, int row0, int nrows, int k0, int kc,
-                                         bool vec_ok, int tid) {
+    // (as LoaderK's, with the vectors along the rows)
+    __device__ __forceinline__ void load(const uint16_t* base, int ld, int row0, int nrows, int k0, int kc, int tid) {
 #pragma unroll
         for (int i = 0; i < NB; i++) {
             const int idx = tid + 256 * i;
             const int kq = idx % (BKT / 4), rg = idx / (BKT / 4);
             const int gr = row0 + rg * 8;
-            const int cnt = (TOTAL >= 256 || idx < TOTAL) ? nrows - gr : 0;
 #pragma unroll
             for (int kk = 0; kk < 4; kk++) {
                 const int gk = k0 + kq * 4 + kk;
                 uint4 x = {0u, 0u, 0u, 0u};
-                if (gk < kc && cnt > 0) {
-                    const uint16_t* p = base + gr + (int64_t)gk * ld;
-                    if (cnt >= 8 && vec_ok) x = *reinterpret_cast<const uint4*>(p);
-                    else x = load8_guarded(p, cnt);
+                if (TOTAL >= 256 || idx < TOTAL) {
+                    if (nrows >= 8) x = load8(base + min(gr, nrows - 8) + (int64_t)min(gk, kc - 1) * ld);
+                    else if (gk < kc && gr < nrows) x = load8_guarded(base + gr + (int64_t)gk * ld, nrows - gr);
                 }
                 v[i][kk] = x;
             }
+        }
+    }
+    __device__ __forceinline__ void mend(int row0, int nrows, int k0, int kc, int tid) {
+        if (nrows < 8) return;
+#pragma unroll
+        for (int i = 0; i < NB; i++) {
+            const int idx = tid + 256 * i;
+            const int kq = idx % (BKT / 4), over = row0 + (idx / (BKT / 4)) * 8 + 8 - nrows;
+#pragma unroll
+            for (int kk = 0; kk < 4; kk++) v[i][kk] = moved_back(v[i][kk], k0 + kq * 4 + kk < kc ? over : 8);
         }
     }
     __device__ __forceinline__ void load_fast(const uint16_t* base, int ld, int tid) {
@@ -122,7 +170,7 @@ struct LoaderR {
                 const int kq = idx % (BKT / 4), rg = idx / (BKT / 4);
 #pragma unroll
                 for (int kk = 0; kk < 4; kk++)
-                    v[i][kk] = *reinterpret_cast<const uint4*>(base + rg * 8 + (int64_t)(kq * 4 + kk) * ld);
+                    v[i][kk] = load8(base + rg * 8 + (int64_t)(kq * 4 + kk) * ld);
             }
         }
     }
@@ -211,12 +259,11 @@ __global__ void __launch_bounds__(256) gemm_bf16_kernel(const GemmArgs g) {
 
     if (T > 0) {
         // position of the next k-step to load; uniform state lives in scalar registers
-        int c = 0, k0 = 0, chk = 0, chvec = 0, lda = 0, ldb = 0;
+        int c = 0, k0 = 0, chk = 0, lda = 0, ldb = 0;
         const uint16_t* Ab = nullptr;
         const uint16_t* Bb = nullptr;
         auto set_chunk = [&](const GemmChunk& ch) {
             chk = __builtin_amdgcn_readfirstlane(ch.k);
-            chvec = __builtin_amdgcn_readfirstlane(ch.vec_ok);
             lda = __builtin_amdgcn_readfirstlane((int)ch.lda);
             ldb = __builtin_amdgcn_readfirstlane((int)ch.ldb);
             Ab = uniform_ptr(static_cast<const uint16_t*>(ch.A) + (int64_t)bat_lo * ch.strideA + (int64_t)bat_hi * ch.strideA2);
@@ -227,13 +274,18 @@ __global__ void __launch_bounds__(256) gemm_bf16_kernel(const GemmArgs g) {
         typename LoaderSel<BKF, BN, BKT>::type lb;
         const bool inside = m0 + BM <= task.m && n0 + BN <= task.n;
         // loads the k-step at the current position into registers and moves the position on
+        bool edge = false;              // of the step in the registers: whether it has to be mended, its k0 and chunk length
+        int ek0 = 0, ekc = 0;
         auto load_step = [&]() {
-            if (inside && k0 + BKT <= chk && chvec == 3) {
+            edge = !(inside && k0 + BKT <= chk);
+            ek0 = k0;
+            ekc = chk;
+            if (!edge) {
                 la.load_fast(AKF ? Ab + k0 + (int64_t)m0 * lda : Ab + m0 + (int64_t)k0 * lda, lda, tid);
                 lb.load_fast(BKF ? Bb + k0 + (int64_t)n0 * ldb : Bb + n0 + (int64_t)k0 * ldb, ldb, tid);
             } else {
-                la.load(Ab, lda, m0, task.m, k0, chk, chvec & 1, tid);
-                lb.load(Bb, ldb, n0, task.n, k0, chk, chvec & 2, tid);
+                la.load(Ab, lda, m0, task.m, k0, chk, tid);
+                lb.load(Bb, ldb, n0, task.n, k0, chk, tid);
             }
             k0 += BKT;
             if (k0 >= chk) {
@@ -244,6 +296,10 @@ __global__ void __launch_bounds__(256) gemm_bf16_kernel(const GemmArgs g) {
         };
         auto store_step = [&](int stage) {
             uint16_t* s = lds + stage * ST_SZ;
+            if (edge) {
+                la.mend(m0, task.m, ek0, ekc, tid);
+                lb.mend(n0, task.n, ek0, ekc, tid);
+            }
             la.store(s, tid);
             lb.store(s + A_SZ, tid);
         };

@@ -27,11 +27,14 @@ __device__ __forceinline__ float load_out(const float* p) { return *p; }
 __device__ __forceinline__ float load_out(const uint16_t* p) { return __uint_as_float((uint32_t)*p << 16); }
 
 typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef float f32x4_any __attribute__((ext_vector_type(4), aligned(4)));          // at any address of a float
+typedef uint32_t u32x4_any __attribute__((ext_vector_type(4), aligned(2)));       // at any address of a bf16 element
 
 // Writes one wave's (32 WMB) x (32 WNB) block of C = alpha * acc + bias + beta * C[+ cin_off].  `stage` is
 // 32 rows of 32 WMB + 4 floats of LDS owned by the wave; every wave of the workgroup must call
-// this (it synchronises the workgroup between the passes).  Vector stores need a 16-byte
-// aligned tile and leading dimension; anything else, and the ragged edge, goes element by element.
+// this (it synchronises the workgroup between the passes).  The vectors may start at any element (global
+// memory takes 16-byte accesses at every multiple of 2 bytes), so tiles of odd leading dimensions
+// leave as vectors too; only the ragged edge goes element by element.
 template <typename TO, int WMB, int WNB>
 __device__ __forceinline__ void write_tile(float* stage, const f32x16 (&acc)[WNB][WMB], TO* C, int64_t ldc,
                                            const float* bias, float alpha, float beta, int m_base, int n_base,
@@ -42,7 +45,6 @@ __device__ __forceinline__ void write_tile(float* stage, const f32x16 (&acc)[WNB
     static_assert(CH <= 64 && 32 % RPI == 0, "row shape");
     const int r32 = lane & 31, half = lane >> 5;
     // (the beta term comes from C + cin_off: the tile itself, or the tile of a residual input with the same geometry)
-    const bool vec_ok = (reinterpret_cast<uintptr_t>(C) % 16 == 0) && (ldc % V == 0) && (cin_off % V == 0);
 #pragma unroll
     for (int bn = 0; bn < WNB; bn++) {
 #pragma unroll
@@ -61,14 +63,14 @@ __device__ __forceinline__ void write_tile(float* stage, const f32x16 (&acc)[WNB
         // asked for before the pass's first store: a load placed after a store to what may be the same
         // tile waits for that store
         constexpr int NIT = 32 / RPI;
-        uint4 cin[NIT];
-        if (beta != 0.f && vec_ok) {
+        u32x4_any cin[NIT];
+        if (beta != 0.f) {
 #pragma unroll
             for (int it = 0; it < NIT; it++) {
                 const int row = it * RPI + lane / CH, mc = (lane % CH) * V;
                 const int gn = n_base + bn * 32 + row, gm = m_base + mc;
-                cin[it] = make_uint4(0u, 0u, 0u, 0u);
-                if (gn < n_lim && gm + V <= m_lim) cin[it] = *reinterpret_cast<const uint4*>(C + gm + (int64_t)gn * ldc + cin_off);
+                cin[it] = u32x4_any{0u, 0u, 0u, 0u};
+                if (gn < n_lim && gm + V <= m_lim) cin[it] = *reinterpret_cast<const u32x4_any*>(C + gm + (int64_t)gn * ldc + cin_off);
             }
         }
 #pragma unroll
@@ -83,26 +85,25 @@ __device__ __forceinline__ void write_tile(float* stage, const f32x16 (&acc)[WNB
             const int gn = n_base + bn * 32 + row, gm = m_base + mc;
             if (gn < n_lim && gm < m_lim) {
                 TO* p = C + gm + (int64_t)gn * ldc;
-                if (vec_ok && gm + V <= m_lim) {
+                if (gm + V <= m_lim) {
                     if (bias) {
 #pragma unroll
                         for (int j = 0; j < V; j += 4) {
-                            const f32x4 bv = *reinterpret_cast<const f32x4*>(bias + gm + j);
+                            const f32x4_any bv = *reinterpret_cast<const f32x4_any*>(bias + gm + j);
                             v[j] += bv[0]; v[j + 1] += bv[1]; v[j + 2] += bv[2]; v[j + 3] += bv[3];
                         }
                     }
                     if constexpr (sizeof(TO) == 4) {
                         if (beta != 0.f) {
-                            const uint4 c = cin[it];
-                            v[0] += beta * __uint_as_float(c.x); v[1] += beta * __uint_as_float(c.y);
-                            v[2] += beta * __uint_as_float(c.z); v[3] += beta * __uint_as_float(c.w);
+                            const u32x4_any c = cin[it];
+                            v[0] += beta * __uint_as_float(c[0]); v[1] += beta * __uint_as_float(c[1]);
+                            v[2] += beta * __uint_as_float(c[2]); v[3] += beta * __uint_as_float(c[3]);
                         }
-                        f32x4 o = {v[0], v[1], v[2], v[3]};
-                        *reinterpret_cast<f32x4*>(p) = o;
+                        const f32x4_any o = {v[0], v[1], v[2], v[3]};
+                        *reinterpret_cast<f32x4_any*>(p) = o;
                     } else {
                         if (beta != 0.f) {
-                            const uint4 c = cin[it];
-                            const uint32_t w[4] = {c.x, c.y, c.z, c.w};
+                            const uint32_t w[4] = {cin[it][0], cin[it][1], cin[it][2], cin[it][3]};
 #pragma unroll
                             for (int j = 0; j < 4; j++) {
                                 v[2 * j] += beta * __uint_as_float(w[j] << 16);
@@ -115,7 +116,7 @@ __device__ __forceinline__ void write_tile(float* stage, const f32x16 (&acc)[WNB
                             const __bf16 lo = (__bf16)v[2 * j], hi = (__bf16)v[2 * j + 1];
                             w[j] = (uint32_t)__builtin_bit_cast(uint16_t, lo) | ((uint32_t)__builtin_bit_cast(uint16_t, hi) << 16);
                         }
-                        *reinterpret_cast<uint4*>(p) = make_uint4(w[0], w[1], w[2], w[3]);
+                        *reinterpret_cast<u32x4_any*>(p) = u32x4_any{w[0], w[1], w[2], w[3]};
                     }
                 } else {
 #pragma unroll

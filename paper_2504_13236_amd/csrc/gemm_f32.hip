@@ -36,43 +36,83 @@ __device__ __forceinline__ const T* uniform_ptr(const T* p) {
 constexpr int BK = 16;
 constexpr int KP = BK + 4;   // padded k extent of a k-fast LDS row (conflict-free 128-bit reads)
 
+// Four floats at any address that a float may have: global memory takes 16-byte accesses at every multiple of 4 bytes,
+// so odd leading dimensions and operands that start anywhere are read with vectors too (read one element at a time,
+// an operand of odd extents kept these kernels at 20 to 35 TFLOP/s).
+typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));
+
+// Where vector i of this thread lies in a step's block: row r, first k.
 template <bool KF, int ROWS>
-__device__ __forceinline__ void gload(f32x4 (&v)[ROWS / 64], const float* base, int ld, int row0,
-                                      int nrows, int k0, int kc, bool vec_ok, int tid) {
-#pragma unroll
-    for (int i = 0; i < ROWS / 64; i++) {
-        const int idx = tid + 256 * i;
-        int r, k;
-        if (KF) { r = idx >> 2; k = (idx & 3) << 2; }
-        else { k = idx / (ROWS / 4); r = (idx % (ROWS / 4)) << 2; }
-        const int gr = row0 + r, gk = k0 + k;
-        const float* p = KF ? base + gk + (int64_t)gr * ld : base + gr + (int64_t)gk * ld;
-        const int cnt = KF ? (gr < nrows ? kc - gk : 0) : (gk < kc ? nrows - gr : 0);
-        f32x4 x = {0.f, 0.f, 0.f, 0.f};
-        if (cnt >= 4 && vec_ok) {
-            x = *reinterpret_cast<const f32x4*>(p);
-        } else {
-            if (cnt > 0) x[0] = p[0];
-            if (cnt > 1) x[1] = p[1];
-            if (cnt > 2) x[2] = p[2];
-            if (cnt > 3) x[3] = p[3];
-        }
-        v[i] = x;
-    }
+__device__ __forceinline__ void vec_at(int tid, int i, int& r, int& k) {
+    const int idx = tid + 256 * i;
+    if (KF) { r = idx >> 2; k = (idx & 3) << 2; }
+    else { k = idx / (ROWS / 4); r = (idx % (ROWS / 4)) << 2; }
 }
 
-// Interior k-step of an aligned operand: no predicates, no branches, so the loads stay in
-// flight across the matrix-core work that follows.  `base` points at (row0, k0).
+// Interior k-step: no predicates, no branches, so the loads stay in flight across the
+// matrix-core work that follows.  `base` points at (row0, k0).
 template <bool KF, int ROWS>
 __device__ __forceinline__ void gload_fast(f32x4 (&v)[ROWS / 64], const float* base, int ld, int tid) {
 #pragma unroll
     for (int i = 0; i < ROWS / 64; i++) {
-        const int idx = tid + 256 * i;
         int r, k;
-        if (KF) { r = idx >> 2; k = (idx & 3) << 2; }
-        else { k = idx / (ROWS / 4); r = (idx % (ROWS / 4)) << 2; }
+        vec_at<KF, ROWS>(tid, i, r, k);
         const float* p = KF ? base + k + (int64_t)r * ld : base + r + (int64_t)k * ld;
-        v[i] = *reinterpret_cast<const f32x4*>(p);
+        v[i] = *reinterpret_cast<const f32x4u*>(p);
+    }
+}
+
+// A step that reaches beyond the operand's `nrows` rows or the chunk's `kc` k (both counted from `base`): every lane
+// fetches four elements that exist, whole rows (or lines) beyond the edge standing in for the last one, and a vector
+// that crosses the edge along its own direction being moved back until it ends there (mend_edge puts its elements in
+// place).  Like the interior form it branches only on scalars, so these loads stay in flight as well.  Operands with
+// fewer than four elements along the vectors' direction are read one by one.
+template <bool KF, int ROWS>
+__device__ __forceinline__ void gload_edge(f32x4 (&v)[ROWS / 64], const float* base, int ld, int row0, int nrows, int k0, int kc, int tid) {
+    const bool vectors = (KF ? kc : nrows) >= 4;
+#pragma unroll
+    for (int i = 0; i < ROWS / 64; i++) {
+        int r, k;
+        vec_at<KF, ROWS>(tid, i, r, k);
+        const int gr = row0 + r, gk = k0 + k;
+        if (vectors) {
+            const float* p = KF ? base + min(gk, kc - 4) + (int64_t)min(gr, nrows - 1) * ld
+                                : base + min(gr, nrows - 4) + (int64_t)min(gk, kc - 1) * ld;
+            v[i] = *reinterpret_cast<const f32x4u*>(p);
+        } else {
+            const float* p = KF ? base + gk + (int64_t)gr * ld : base + gr + (int64_t)gk * ld;
+            const int cnt = KF ? (gr < nrows ? kc - gk : 0) : (gk < kc ? nrows - gr : 0);
+            f32x4 x = {0.f, 0.f, 0.f, 0.f};
+            if (cnt > 0) x[0] = p[0];
+            if (cnt > 1) x[1] = p[1];
+            if (cnt > 2) x[2] = p[2];
+            v[i] = x;
+        }
+    }
+}
+
+// What gload_edge left in the registers, put in place once it has arrived: elements of a moved vector shifted back,
+// zeros for k beyond the chunk (in both operands: whatever stands for a missing k must not meet an infinity).  Rows
+// beyond the edge keep what was fetched for them: it only reaches results that are never stored.
+template <bool KF, int ROWS>
+__device__ __forceinline__ void mend_edge(f32x4 (&v)[ROWS / 64], int row0, int nrows, int k0, int kc, int tid) {
+    if ((KF ? kc : nrows) < 4) return;
+#pragma unroll
+    for (int i = 0; i < ROWS / 64; i++) {
+        int r, k;
+        vec_at<KF, ROWS>(tid, i, r, k);
+        const int over = KF ? k0 + k + 4 - kc : row0 + r + 4 - nrows;      // elements of the vector beyond the edge
+        const bool gone = !KF && k0 + k >= kc;
+        const f32x4 x = v[i];
+        f32x4 y;
+#pragma unroll
+        for (int e = 0; e < 4; e++) {
+            float t = over <= 0 ? x[e] : 0.f;
+#pragma unroll
+            for (int s = 1; e + s < 4; s++) t = over == s ? x[e + s] : t;
+            y[e] = gone ? 0.f : t;
+        }
+        v[i] = y;
     }
 }
 
@@ -151,12 +191,11 @@ __global__ void __launch_bounds__(256) gemm_f32_kernel(const GemmArgs g) {
         // Loop state that is the same for every lane is kept in scalar registers on purpose
         // (readfirstlane): the k-loop then branches on the scalar unit and the loads address
         // memory as scalar base + per-lane offset.
-        int c = 0, k0 = 0, chk = 0, chvec = 0, lda = 0, ldb = 0;
+        int c = 0, k0 = 0, chk = 0, lda = 0, ldb = 0;
         const float* Ab = nullptr;
         const float* Bb = nullptr;
         auto set_chunk = [&](const GemmChunk& ch) {
             chk = __builtin_amdgcn_readfirstlane(ch.k);
-            chvec = __builtin_amdgcn_readfirstlane(ch.vec_ok);
             lda = __builtin_amdgcn_readfirstlane((int)ch.lda);
             ldb = __builtin_amdgcn_readfirstlane((int)ch.ldb);
             Ab = uniform_ptr(static_cast<const float*>(ch.A) + (int64_t)bat_lo * ch.strideA + (int64_t)bat_hi * ch.strideA2);
@@ -164,21 +203,33 @@ __global__ void __launch_bounds__(256) gemm_f32_kernel(const GemmArgs g) {
         };
         set_chunk(table ? g.chunks[task.chunk0] : g.one_chunk);
         f32x4 va[BM / 64], vb[BN / 64];
-        // whole macro-tile inside the C tile: k-steps that are also whole take the branch-free loads
+        // whole macro-tile inside the C tile: k-steps that are also whole need no look at the edges
         const bool inside = m0 + BM <= task.m && n0 + BN <= task.n;
+        bool edge = false;              // of the step in the registers: whether it has to be mended, its k0 and chunk length
+        int ek0 = 0, ekc = 0;
         auto load_step = [&]() {
-            if (inside && k0 + BK <= chk && chvec == 3) {
+            edge = !(inside && k0 + BK <= chk);
+            ek0 = k0;
+            ekc = chk;
+            if (!edge) {
                 gload_fast<AKF, BM>(va, AKF ? Ab + k0 + (int64_t)m0 * lda : Ab + m0 + (int64_t)k0 * lda, lda, tid);
                 gload_fast<BKF, BN>(vb, BKF ? Bb + k0 + (int64_t)n0 * ldb : Bb + n0 + (int64_t)k0 * ldb, ldb, tid);
             } else {
-                gload<AKF, BM>(va, Ab, lda, m0, task.m, k0, chk, chvec & 1, tid);
-                gload<BKF, BN>(vb, Bb, ldb, n0, task.n, k0, chk, chvec & 2, tid);
+                gload_edge<AKF, BM>(va, Ab, lda, m0, task.m, k0, chk, tid);
+                gload_edge<BKF, BN>(vb, Bb, ldb, n0, task.n, k0, chk, tid);
             }
+        };
+        auto store_step = [&](float* l) {
+            if (edge) {
+                mend_edge<AKF, BM>(va, m0, task.m, ek0, ekc, tid);
+                mend_edge<BKF, BN>(vb, n0, task.n, ek0, ekc, tid);
+            }
+            lstore<AKF, BM>(l, va, tid);
+            lstore<BKF, BN>(l + A_SZ, vb, tid);
         };
         load_step();
         int cur = 0;
-        lstore<AKF, BM>(lds, va, tid);
-        lstore<BKF, BN>(lds + A_SZ, vb, tid);
+        store_step(lds);
         __syncthreads();
         bool more = true;
         while (more) {
@@ -205,11 +256,7 @@ __global__ void __launch_bounds__(256) gemm_f32_kernel(const GemmArgs g) {
 #pragma unroll
                     for (int bm = 0; bm < WMB; bm++)
                         acc[bn][bm] = __builtin_amdgcn_mfma_f32_32x32x2f32(pf[bn][j], qf[bm][j], acc[bn][bm], 0, 0, 0);
-            if (more) {
-                float* nA = lds + (cur ^ 1) * (A_SZ + B_SZ);
-                lstore<AKF, BM>(nA, va, tid);
-                lstore<BKF, BN>(nA + A_SZ, vb, tid);
-            }
+            if (more) store_step(lds + (cur ^ 1) * (A_SZ + B_SZ));
             __syncthreads();
             cur ^= 1;
         }

@@ -515,3 +515,34 @@ def test_tile_calls_reject_bad_arguments(capi):
     assert capi.nnt_tile_gemm.raw(st, 0, 0, 0, 0, 4, 4, 4, 1, 1.0, x.data_ptr(), 2, 16, x.data_ptr(), 4, 16, 0.0,
                                   x.data_ptr(), 4, 16) == capi.NNT_EINVAL        # lda < m
     assert capi.nnt_tile_softmax_stats.raw(st, 0, 4, 4, 1, -1, 0, 1, 1.0, x.data_ptr(), x.data_ptr(), 1) == capi.NNT_EINVAL
+
+
+@pytest.mark.parametrize("din,dout", [("f32", "f32"), ("bf16", "bf16"), ("bf16", "f32")])
+@pytest.mark.parametrize("opA,opB", list(itertools.product("NT", "NT")))
+@pytest.mark.parametrize("m,n,k", [(1, 1, 1), (3, 5, 2), (4, 8, 4), (9, 7, 3), (65, 131, 17), (130, 67, 33), (301, 129, 39)])
+def test_gemm_edges_at_any_alignment(capi, din, dout, opA, opB, m, n, k):
+    """Operands and results that start at any element and have odd leading dimensions: the general kernels read and write
+    them in vectors that are moved back from the edges.  Whatever lies between and around the columns is NaN, so a
+    vector that takes in an element of the padding shows; tolerances as above (fp32 sums, one bf16 rounding)."""
+    r = rng(m + 3 * n + 7 * k)
+    a_shape, b_shape = ((m, k) if opA == "N" else (k, m)), ((k, n) if opB == "N" else (n, k))
+    A, B = quant(r.standard_normal(a_shape), din), quant(r.standard_normal(b_shape), din)
+    C0 = quant(r.standard_normal((m, n)), dout)
+    for pad, shift in ((0, 0), (1, 1), (3, 5)):
+        def dev(M, dt):
+            P = np.full((M.shape[0] + pad, M.shape[1]), np.nan, np.float32)
+            P[:M.shape[0]] = M
+            t = to_dev(P, dt)
+            s = torch.full((t.numel() + shift + 16,), float("nan"), dtype=t.dtype, device=t.device)
+            s[shift:shift + t.numel()] = t
+            return s, s.data_ptr() + shift * t.element_size(), M.shape[0] + pad
+        (sA, pA, lda), (sB, pB, ldb), (sC, pC, ldc) = dev(A, din), dev(B, din), dev(C0, dout)
+        before = sC.clone()
+        capi.nnt_tile_gemm(stream_ptr(), code(din), code(dout), 0 if opA == "N" else 1, 0 if opB == "N" else 1,
+                           m, n, k, 1, 0.5, pA, lda, 0, pB, ldb, 0, 2.0, pC, ldc, 0)
+        torch.cuda.synchronize()
+        got = from_dev(sC[shift:shift + ldc * n], (ldc, n))[:m]
+        e = relerr(got, D.matmul2d(0.5, opA, A[:, :, None], opB, B[:, :, None], 2.0, C0[:, :, None])[:, :, 0])
+        assert e <= (1e-5 if dout == "f32" else 2e-2), (pad, shift, e)
+        keep = torch.isnan(before)
+        assert torch.equal(torch.isnan(sC), keep), "an element outside the result was written"
