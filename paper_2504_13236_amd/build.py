@@ -73,13 +73,15 @@ def _vregs(text: str) -> set:
 def registers_touched_in_flight(asm_text: str) -> list:
     """[(kernel, line number, register, line of the read)]: instructions of a device assembly listing that name a
     vector register while an LDS read into it is still in flight, i.e. between the ds_read that targets it and
-    the next `s_waitcnt lgkmcnt(0)`.
+    the `s_waitcnt lgkmcnt(n)` that covers it (LDS operations complete in order, so such a wait leaves at most the
+    last n of them in flight; scalar loads only make a wait cover more than is assumed here).
 
     The compiler believes such a register holds its value from the read's asm statement on, so a copy, a move to
     an accumulation register or any other use it schedules before the hand-placed wait would see stale data.
-    The scan is linear per kernel (listing order); only a full wait clears the reads in flight."""
+    The scan is linear per kernel (listing order)."""
     hits = []
     kernel, pending = None, {}
+    issued = 0                                      # LDS operations so far; pending: register -> (line, number of its read)
     for no, line in enumerate(asm_text.splitlines(), 1):
         t = line.split(";")[0].strip()
         if not t:
@@ -91,8 +93,9 @@ def registers_touched_in_flight(asm_text: str) -> list:
             continue
         op, _, rest = t.partition(" ")
         if op == "s_waitcnt":
-            if "lgkmcnt(0)" in rest:
-                pending = {}
+            m = re.search(r"lgkmcnt\((\d+)\)", rest)
+            if m:
+                pending = {r: p for r, p in pending.items() if p[1] >= issued - int(m.group(1))}
             continue
         if op == "s_endpgm":
             pending = {}
@@ -102,13 +105,15 @@ def registers_touched_in_flight(asm_text: str) -> list:
             for o in ops[1:]:                       # the address is read now
                 for r in _vregs(o):
                     if r in pending:
-                        hits.append((kernel, no, "v%d" % r, pending[r]))
+                        hits.append((kernel, no, "v%d" % r, pending[r][0]))
             for r in _vregs(ops[0]):
-                pending[r] = no
+                pending[r] = (no, issued)
+            issued += 1
             continue
         for r in _vregs(rest):
             if r in pending:
-                hits.append((kernel, no, "v%d" % r, pending[r]))
+                hits.append((kernel, no, "v%d" % r, pending[r][0]))
+        issued += op.startswith("ds_")
     return hits
 
 

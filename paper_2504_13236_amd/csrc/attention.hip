@@ -86,15 +86,15 @@ __device__ __forceinline__ Slab slab_of(const AttnGeom& g, const Pair& p, int l)
 
 template <typename T>
 __device__ __forceinline__ T* rows_of(void* const* tiles, const Slab& s, int width) {
-    return static_cast<T*>(tiles[s.tile]) + s.off * width;
+    return global_as<T>(tiles[s.tile]) + s.off * width;
 }
 // Row 0 of (batch b, head j) in sequence tile `s` of a data operand; its rows are g.pitch elements apart.
 template <typename T>
 __device__ __forceinline__ T* rows_win(void* const* tiles, const AttnGeom& g, const Win& w, const Pair& pr, const Slab& s, int b, int j) {
-    if (!g.win) return static_cast<T*>(tiles[s.tile]) + s.off * g.H;
+    if (!g.win) return global_as<T>(tiles[s.tile]) + s.off * g.H;
     const int tb = b / g.bb, l = s.tile - pr.tile, hl = j / g.hp;
     const int tile = (w.im0 + hl) + w.g0 * (l + g.gs * tb);
-    return static_cast<T*>(tiles[tile]) + (j - hl * g.hp) * g.H + (int64_t)g.pitch * ((int64_t)s.ext * (b - tb * g.bb));
+    return global_as<T>(tiles[tile]) + (j - hl * g.hp) * g.H + (int64_t)g.pitch * ((int64_t)s.ext * (b - tb * g.bb));
 }
 
 // ---------------------------------------------------------------- element-type traits

@@ -46,7 +46,7 @@ __device__ __forceinline__ int ext0_of(const TiledView& v, int l) { return min(v
 
 template <typename T>
 __device__ __forceinline__ T* col_ptr(const TiledView& v, const Column& c, int l, int ext0) {
-    T* base = static_cast<T*>(v.tiles[c.tile0 + l]);
+    T* base = global_as<T>(v.tiles[c.tile0 + l]);
     return base ? base + (int64_t)c.colidx * ext0 : nullptr;
 }
 

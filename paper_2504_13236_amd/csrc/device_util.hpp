@@ -4,6 +4,7 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "global_ptr.hpp"
 #include "internal.hpp"
 
 namespace nnt {

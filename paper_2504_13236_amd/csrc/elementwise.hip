@@ -84,8 +84,8 @@ __global__ void __launch_bounds__(256) head_kernel(HeadArgs a) {
         const int64_t zoff = zr + (int64_t)zext0 * ((s - zls) + zes * (b - zlb));
         const int ptile = pt0 + q.grid[0] * (qs + q.grid[1] * (qb + q.grid[2] * ptj));
         const int64_t poff = pi + (int64_t)pext0 * ((s - qls) + (int64_t)qes * ((b - qlb) + qeb * pj));
-        T* zp = static_cast<T*>(a.z.tiles[ztile]) + zoff;
-        T* pp = static_cast<T*>(pv.tiles[ptile]) + poff;
+        T* zp = global_as<T>(a.z.tiles[ztile]) + zoff;
+        T* pp = global_as<T>(pv.tiles[ptile]) + poff;
         src[t] = a.to_parts ? zp : pp;
         dst[t] = a.to_parts ? pp : zp;
     }

@@ -80,9 +80,9 @@ __global__ void __launch_bounds__(256) embedding_fwd_kernel(const int32_t* token
         int tw;
         int64_t ow;
         locate(W, cw, tw, ow);
-        ldw<VE>(static_cast<const TW*>(W.tiles[tw]) + ow, v);
+        ldw<VE>(global_as<const TW>(W.tiles[tw]) + ow, v);
     }
-    stw<VE>(static_cast<TY*>(Y.tiles[tile]) + off, v);
+    stw<VE>(global_as<TY>(Y.tiles[tile]) + off, v);
 }
 
 // one thread per group of VE elements of dY; rows of dW that several positions share are summed with hardware
@@ -100,12 +100,12 @@ __global__ void __launch_bounds__(256) embedding_bwd_kernel(const int32_t* token
     int64_t off;
     locate(dY, c, tile, off);
     float g[VE];
-    ldw<VE>(static_cast<const TY*>(dY.tiles[tile]) + off, g);
+    ldw<VE>(global_as<const TY>(dY.tiles[tile]) + off, g);
     const int cw[kMaxDim] = {c[0], tok, 0, 0};
     int tw;
     int64_t ow;
     locate(dW, cw, tw, ow);
-    float* dst = static_cast<float*>(dW.tiles[tw]) + ow;
+    float* dst = global_as<float>(dW.tiles[tw]) + ow;
 #pragma unroll
     for (int k = 0; k < VE; k++) unsafeAtomicAdd(dst + k, g[k]);
 }
@@ -124,7 +124,7 @@ __global__ void __launch_bounds__(256) ce_logit_kernel(const int32_t* labels, Ti
         int tile;
         int64_t off;
         locate(X, c, tile, off);
-        x = ldf(static_cast<const T*>(X.tiles[tile]) + off);
+        x = ldf(global_as<const T>(X.tiles[tile]) + off);
     }
     logit[i] = x;
 }
@@ -144,12 +144,12 @@ __global__ void __launch_bounds__(256) ce_label_kernel(const int32_t* labels, Ti
         int tile;
         int64_t off;
         locate(P, c, tile, off);
-        T* p = static_cast<T*>(P.tiles[tile]) + off;
+        T* p = global_as<T>(P.tiles[tile]) + off;
         const int cs[kMaxDim] = {0, c[1], c[2], 0};
         int ts;
         int64_t os;
         locate(S, cs, ts, os);
-        const float* st = static_cast<const float*>(S.tiles[ts]) + os;      // (maximum, sum of shifted exponentials)
+        const float* st = global_as<const float>(S.tiles[ts]) + os;      // (maximum, sum of shifted exponentials)
         loss = -(losses[i] - st[0] - logf(st[1]));
         stf(p, ldf(p) - 1.f);
     }

@@ -31,7 +31,7 @@ struct Operand {
 
 template <typename T>
 __device__ __forceinline__ T* pick(const Operand& o, int tile) {
-    return static_cast<T*>(o.table ? o.table[tile] : o.single);
+    return global_as<T>(o.table ? o.table[tile] : o.single);
 }
 
 // F provides: V (vector width), NIN (values loaded per element), Ctx, setup(),
@@ -223,10 +223,10 @@ struct BiasAddF {
             int tc[kMaxDim], ext[kMaxDim];
             tile_geometry(g.v, tile, tc, ext);
             c.m = ext[0];
-            c.b = static_cast<const float*>(b.table[tc[0]]);
+            c.b = global_as<const float>(b.table[tc[0]]);
         } else {
             c.m = (int)m_single;
-            c.b = static_cast<const float*>(b.single);
+            c.b = global_as<const float>(b.single);
         }
         return c.y != nullptr;
     }

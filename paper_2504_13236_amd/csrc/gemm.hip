@@ -23,7 +23,9 @@ struct SplitReduce {
 
 template <typename TO>
 __global__ void __launch_bounds__(256) splitk_reduce(const SplitReduce* tab, float alpha, float beta) {
-    const SplitReduce t = tab[blockIdx.y];
+    SplitReduce t = tab[blockIdx.y];
+    t.ws = in_global(t.ws);
+    t.bias = in_global(t.bias);
     const int q = t.ldw >> 2;
     const int idx = blockIdx.x * 256 + threadIdx.x;
     const int i = (idx % q) << 2, j = idx / q;
@@ -46,7 +48,7 @@ __global__ void __launch_bounds__(256) splitk_reduce(const SplitReduce* tab, flo
         const float4 v = *reinterpret_cast<const float4*>(p + (int64_t)sl * t.slice);
         acc[0] += v.x; acc[1] += v.y; acc[2] += v.z; acc[3] += v.w;
     }
-    TO* c = static_cast<TO*>(t.C) + (t.m0 + i) + (int64_t)(t.n0 + j) * t.ldc;
+    TO* c = global_as<TO>(t.C) + (t.m0 + i) + (int64_t)(t.n0 + j) * t.ldc;
     if constexpr (sizeof(TO) == 4) {
         // four whole rows at a 16-byte aligned address: one vector access instead of four
         if (n == 4 && (reinterpret_cast<uintptr_t>(c) & 15) == 0 && (t.cin_off & 3) == 0) {

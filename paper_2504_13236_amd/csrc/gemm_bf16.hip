@@ -370,10 +370,10 @@ __global__ void __launch_bounds__(256) gemm_bf16_kernel(const GemmArgs g) {
     const int m_base = m0 + wm * WMB * 32, n_base = n0 + wn * WNB * 32;
     if (task.partial) {
         // one k-slice of a split product: raw fp32 sums into the scratch tile
-        write_tile<float, WMB, WNB>(stage, acc, static_cast<float*>(task.C) + (int64_t)bat_lo * task.strideC + (int64_t)bat_hi * task.strideC2, task.ldc, nullptr,
+        write_tile<float, WMB, WNB, true>(stage, acc, global_as<float>(task.C) + (int64_t)bat_lo * task.strideC + (int64_t)bat_hi * task.strideC2, task.ldc, nullptr,
                                     1.f, 0.f, m_base, n_base, task.m, task.n, lane);
     } else {
-        write_tile<TO, WMB, WNB>(stage, acc, static_cast<TO*>(task.C) + (int64_t)bat_lo * task.strideC + (int64_t)bat_hi * task.strideC2, task.ldc, task.bias,
+        write_tile<TO, WMB, WNB, true>(stage, acc, global_as<TO>(task.C) + (int64_t)bat_lo * task.strideC + (int64_t)bat_hi * task.strideC2, task.ldc, in_global(task.bias),
                                  g.alpha, g.beta, m_base, n_base, task.m, task.n, lane, task.cin_off);
     }
 }

@@ -4,6 +4,10 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <type_traits>
+
+#include "global_ptr.hpp"
+
 namespace nnt {
 
 typedef float f32x16 __attribute__((ext_vector_type(16)));
@@ -15,7 +19,7 @@ __device__ __forceinline__ const T* uniform_ptr(const T* p) {
     const uint64_t v = reinterpret_cast<uint64_t>(p);
     const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)v);
     const uint32_t hi = __builtin_amdgcn_readfirstlane((uint32_t)(v >> 32));
-    return reinterpret_cast<const T*>(((uint64_t)hi << 32) | lo);
+    return in_global(reinterpret_cast<const T*>(((uint64_t)hi << 32) | lo));
 }
 
 __device__ __forceinline__ void store_out(float* p, float v) { *p = v; }
@@ -30,12 +34,26 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef float f32x4_any __attribute__((ext_vector_type(4), aligned(4)));          // at any address of a float
 typedef uint32_t u32x4_any __attribute__((ext_vector_type(4), aligned(2)));       // at any address of a bf16 element
 
+// 16 bytes at a 16-byte aligned address, or (ANY) at any address of an element.
+template <bool ANY>
+__device__ __forceinline__ uint4 get16(const void* p) {
+    if constexpr (ANY) {
+        const u32x4_any x = *static_cast<const u32x4_any*>(p);
+        return make_uint4(x[0], x[1], x[2], x[3]);
+    } else {
+        return *static_cast<const uint4*>(p);
+    }
+}
+
 // Writes one wave's (32 WMB) x (32 WNB) block of C = alpha * acc + bias + beta * C[+ cin_off].  `stage` is
 // 32 rows of 32 WMB + 4 floats of LDS owned by the wave; every wave of the workgroup must call
-// this (it synchronises the workgroup between the passes).  The vectors may start at any element (global
+// this (it synchronises the workgroup between the passes).  ANY: the vectors may start at any element (global
 // memory takes 16-byte accesses at every multiple of 2 bytes), so tiles of odd leading dimensions
-// leave as vectors too; only the ragged edge goes element by element.
-template <typename TO, int WMB, int WNB>
+// leave as vectors too, and only the ragged edge goes element by element.  The direct-load kernels, whose tiles
+// are nearly always aligned, use the form that tests for alignment: the other makes the compiler spill nine
+// more registers of the 256 x 256 kernel with an fp32 result, which then takes 2.22 instead of 2.11 ms for
+// 8192 x 32768 over 4096 tokens.
+template <typename TO, int WMB, int WNB, bool ANY = false>
 __device__ __forceinline__ void write_tile(float* stage, const f32x16 (&acc)[WNB][WMB], TO* C, int64_t ldc,
                                            const float* bias, float alpha, float beta, int m_base, int n_base,
                                            int m_lim, int n_lim, int lane, int64_t cin_off = 0) {
@@ -45,6 +63,7 @@ __device__ __forceinline__ void write_tile(float* stage, const f32x16 (&acc)[WNB
     static_assert(CH <= 64 && 32 % RPI == 0, "row shape");
     const int r32 = lane & 31, half = lane >> 5;
     // (the beta term comes from C + cin_off: the tile itself, or the tile of a residual input with the same geometry)
+    const bool vec_ok = ANY || ((reinterpret_cast<uintptr_t>(C) % 16 == 0) && (ldc % V == 0) && (cin_off % V == 0));
 #pragma unroll
     for (int bn = 0; bn < WNB; bn++) {
 #pragma unroll
@@ -63,14 +82,14 @@ __device__ __forceinline__ void write_tile(float* stage, const f32x16 (&acc)[WNB
         // asked for before the pass's first store: a load placed after a store to what may be the same
         // tile waits for that store
         constexpr int NIT = 32 / RPI;
-        u32x4_any cin[NIT];
-        if (beta != 0.f) {
+        uint4 cin[NIT];
+        if (beta != 0.f && vec_ok) {
 #pragma unroll
             for (int it = 0; it < NIT; it++) {
                 const int row = it * RPI + lane / CH, mc = (lane % CH) * V;
                 const int gn = n_base + bn * 32 + row, gm = m_base + mc;
-                cin[it] = u32x4_any{0u, 0u, 0u, 0u};
-                if (gn < n_lim && gm + V <= m_lim) cin[it] = *reinterpret_cast<const u32x4_any*>(C + gm + (int64_t)gn * ldc + cin_off);
+                cin[it] = make_uint4(0u, 0u, 0u, 0u);
+                if (gn < n_lim && gm + V <= m_lim) cin[it] = get16<ANY>(C + gm + (int64_t)gn * ldc + cin_off);
             }
         }
 #pragma unroll
@@ -85,25 +104,26 @@ __device__ __forceinline__ void write_tile(float* stage, const f32x16 (&acc)[WNB
             const int gn = n_base + bn * 32 + row, gm = m_base + mc;
             if (gn < n_lim && gm < m_lim) {
                 TO* p = C + gm + (int64_t)gn * ldc;
-                if (gm + V <= m_lim) {
+                if (vec_ok && gm + V <= m_lim) {
                     if (bias) {
 #pragma unroll
                         for (int j = 0; j < V; j += 4) {
-                            const f32x4_any bv = *reinterpret_cast<const f32x4_any*>(bias + gm + j);
+                            const std::conditional_t<ANY, f32x4_any, f32x4> bv = *reinterpret_cast<const std::conditional_t<ANY, f32x4_any, f32x4>*>(bias + gm + j);
                             v[j] += bv[0]; v[j + 1] += bv[1]; v[j + 2] += bv[2]; v[j + 3] += bv[3];
                         }
                     }
                     if constexpr (sizeof(TO) == 4) {
                         if (beta != 0.f) {
-                            const u32x4_any c = cin[it];
-                            v[0] += beta * __uint_as_float(c[0]); v[1] += beta * __uint_as_float(c[1]);
-                            v[2] += beta * __uint_as_float(c[2]); v[3] += beta * __uint_as_float(c[3]);
+                            const uint4 c = cin[it];
+                            v[0] += beta * __uint_as_float(c.x); v[1] += beta * __uint_as_float(c.y);
+                            v[2] += beta * __uint_as_float(c.z); v[3] += beta * __uint_as_float(c.w);
                         }
-                        const f32x4_any o = {v[0], v[1], v[2], v[3]};
-                        *reinterpret_cast<f32x4_any*>(p) = o;
+                        f32x4 o = {v[0], v[1], v[2], v[3]};
+                        *reinterpret_cast<std::conditional_t<ANY, f32x4_any, f32x4>*>(p) = o;
                     } else {
                         if (beta != 0.f) {
-                            const uint32_t w[4] = {cin[it][0], cin[it][1], cin[it][2], cin[it][3]};
+                            const uint4 c = cin[it];
+                            const uint32_t w[4] = {c.x, c.y, c.z, c.w};
 #pragma unroll
                             for (int j = 0; j < 4; j++) {
                                 v[2 * j] += beta * __uint_as_float(w[j] << 16);
@@ -116,7 +136,8 @@ __device__ __forceinline__ void write_tile(float* stage, const f32x16 (&acc)[WNB
                             const __bf16 lo = (__bf16)v[2 * j], hi = (__bf16)v[2 * j + 1];
                             w[j] = (uint32_t)__builtin_bit_cast(uint16_t, lo) | ((uint32_t)__builtin_bit_cast(uint16_t, hi) << 16);
                         }
-                        *reinterpret_cast<u32x4_any*>(p) = u32x4_any{w[0], w[1], w[2], w[3]};
+                        if constexpr (ANY) *reinterpret_cast<u32x4_any*>(p) = u32x4_any{w[0], w[1], w[2], w[3]};
+                        else *reinterpret_cast<uint4*>(p) = make_uint4(w[0], w[1], w[2], w[3]);
                     }
                 } else {
 #pragma unroll

@@ -10,6 +10,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "global_ptr.hpp"
+
 namespace nnt {
 
 struct GemmTask {

@@ -30,7 +30,7 @@ __device__ __forceinline__ const T* uniform_ptr(const T* p) {
     const uint64_t v = reinterpret_cast<uint64_t>(p);
     const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)v);
     const uint32_t hi = __builtin_amdgcn_readfirstlane((uint32_t)(v >> 32));
-    return reinterpret_cast<const T*>(((uint64_t)hi << 32) | lo);
+    return in_global(reinterpret_cast<const T*>(((uint64_t)hi << 32) | lo));
 }
 
 constexpr int BK = 16;
@@ -263,13 +263,13 @@ __global__ void __launch_bounds__(256) gemm_f32_kernel(const GemmArgs g) {
     }
 
     // epilogue: lane holds row m = r32, columns n = 8 * (i / 4) + 4 * half + i % 4 of each 32 x 32 block
-    float* C = static_cast<float*>(task.C) + (int64_t)bat_lo * task.strideC + (int64_t)bat_hi * task.strideC2;
+    float* C = global_as<float>(task.C) + (int64_t)bat_lo * task.strideC + (int64_t)bat_hi * task.strideC2;
     const float alpha = task.partial ? 1.f : g.alpha, beta = task.partial ? 0.f : g.beta;
 #pragma unroll
     for (int bm = 0; bm < WMB; bm++) {
         const int gm = m0 + (wm * WMB + bm) * 32 + r32;
         if (gm >= task.m) continue;
-        const float bias = task.bias ? task.bias[gm] : 0.f;
+        const float bias = task.bias ? in_global(task.bias)[gm] : 0.f;
         // (the beta term of the whole row block is read before its first store: a load behind a store to
         // what may be the same tile would wait for it)
         float cin[WNB][16];

@@ -124,14 +124,14 @@ __global__ void __launch_bounds__(256) ln_fwd_fused(TiledView X, TiledView Y, Ti
         } else {
             ldv<V>(col_ptr<const T>(X, c, l, ext) + e, x);
         }
-        ldv<V>(static_cast<const float*>(G.tiles[l]) + e, g);
-        ldv<V>(static_cast<const float*>(Bt.tiles[l]) + e, b);
+        ldv<V>(global_as<const float>(G.tiles[l]) + e, g);
+        ldv<V>(global_as<const float>(Bt.tiles[l]) + e, b);
 #pragma unroll
         for (int k = 0; k < V; k++) x[k] = g[k] * ((x[k] - mean) * rstd) + b[k];
         stv<V>(col_ptr<T>(Y, c, l, ext) + e, x);
     }, w);
     if (lane == 0 && w == 0) {
-        float* s = static_cast<float*>(S.tiles[c.stat_tile]) + 2 * (int64_t)c.colidx;
+        float* s = global_as<float>(S.tiles[c.stat_tile]) + 2 * (int64_t)c.colidx;
         s[0] = mean;
         s[1] = rstd;
     }
@@ -148,7 +148,7 @@ __global__ void __launch_bounds__(256) ln_bwd_fused(TiledView X, TiledView S, Ti
     if (col >= ncols) return;
     const Column c = column_of(X, col);
     const int N = X.shape[0];
-    const float* st = static_cast<const float*>(S.tiles[c.stat_tile]) + 2 * (int64_t)c.colidx;
+    const float* st = global_as<const float>(S.tiles[c.stat_tile]) + 2 * (int64_t)c.colidx;
     const float mean = st[0], rstd = st[1];
     float cg[NV > 0 ? NV : 1][V], ch[NV > 0 ? NV : 1][V];   // g = dy * gamma, xhat
     float a = 0.f, b = 0.f;
@@ -156,7 +156,7 @@ __global__ void __launch_bounds__(256) ln_bwd_fused(TiledView X, TiledView S, Ti
         float x[V], d[V], g[V];
         ldv<V>(col_ptr<const T>(X, c, l, ext) + e, x);
         ldv<V>(col_ptr<const T>(dY, c, l, ext) + e, d);
-        ldv<V>(static_cast<const float*>(G.tiles[l]) + e, g);
+        ldv<V>(global_as<const float>(G.tiles[l]) + e, g);
 #pragma unroll
         for (int k = 0; k < V; k++) {
             const float gg = d[k] * g[k], xh = (x[k] - mean) * rstd;
@@ -176,7 +176,7 @@ __global__ void __launch_bounds__(256) ln_bwd_fused(TiledView X, TiledView S, Ti
             float x[V], d[V], g[V];
             ldv<V>(col_ptr<const T>(X, c, l, ext) + e, x);
             ldv<V>(col_ptr<const T>(dY, c, l, ext) + e, d);
-            ldv<V>(static_cast<const float*>(G.tiles[l]) + e, g);
+            ldv<V>(global_as<const float>(G.tiles[l]) + e, g);
 #pragma unroll
             for (int k = 0; k < V; k++) { gg[k] = d[k] * g[k]; xh[k] = (x[k] - mean) * rstd; }
         }
@@ -341,11 +341,11 @@ __global__ void __launch_bounds__(256) rowsum_stage1(RowsumGeom g, float* part) 
         ext0 = ext[0];
         ncol = (int64_t)ext[1] * ext[2] * ext[3];
         row0 = tc[0] * g.y.base[0];
-        y = static_cast<const T*>(g.ytab[tile]);
+        y = global_as<const T>(g.ytab[tile]);
         const int rest = tile / g.y.grid[0];
         if (MODE == 1) {
-            x = static_cast<const T*>(g.xtab[tile]);
-            st = static_cast<const float*>(g.stab[rest]);
+            x = global_as<const T>(g.xtab[tile]);
+            st = global_as<const float>(g.stab[rest]);
         }
         slot = (int64_t)rest * g.splits + blockIdx.y;
     } else {
@@ -443,7 +443,7 @@ __global__ void __launch_bounds__(256) rowsum_stage2(const float* part, int64_t 
         float s = 0.f;
 #pragma unroll
         for (int q = 0; q < 16; q++) s += red[q][rl];
-        float* o = otab ? static_cast<float*>(otab[r / base0]) + (r % base0) : o1 + r;
+        float* o = otab ? global_as<float>(otab[r / base0]) + (r % base0) : o1 + r;
         *o = accumulate ? *o + s : s;
     }
 }

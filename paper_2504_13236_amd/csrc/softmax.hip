@@ -164,7 +164,7 @@ __global__ void __launch_bounds__(256) softmax_fwd_fused(TiledView A, TiledView 
         stv<V>(p + e, x);
     });
     if (lane == 0) {
-        float* s = static_cast<float*>(S.tiles[c.stat_tile]) + 2 * (int64_t)c.colidx;
+        float* s = global_as<float>(S.tiles[c.stat_tile]) + 2 * (int64_t)c.colidx;
         s[0] = mx;
         s[1] = sum;
     }
@@ -295,7 +295,7 @@ __global__ void __launch_bounds__(256) softmax_fwd_multi(TiledView A, TiledView 
         }
     });
     if (lane < CPW) {
-        float* s = static_cast<float*>(S.tiles[c.stat_tile]) + 2 * (int64_t)(c.colidx + lane);
+        float* s = global_as<float>(S.tiles[c.stat_tile]) + 2 * (int64_t)(c.colidx + lane);
         float m = mx[0], d = sum[0];
 #pragma unroll
         for (int q = 1; q < CPW; q++)
