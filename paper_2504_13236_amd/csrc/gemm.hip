@@ -175,7 +175,7 @@ static int32_t launch_any(hipStream_t st, int dtype_in, int dtype_out, int akf, 
     const bool f32 = dtype_in == NNT_F32;
     if (epi_mode) {     // (plans with an activation form are only run when all their workgroups qualify: GemmPlan::epi_ok)
         if (nfast != nwg) return NNT_EINVAL;
-        return f32 ? launch_gemm_f32_dl(st, akf, bkf, cfg, g, nwg, epi_mode) : NNT_EINVAL;
+        return f32 ? launch_gemm_f32_dl(st, akf, bkf, cfg, false, g, nwg, epi_mode) : NNT_EINVAL;
     }
     auto general = [&](const GemmArgs& ga, int64_t n) {
         return f32 ? launch_gemm_f32(st, akf, bkf, cfg, ga, n) : launch_gemm_bf16(st, dtype_out == NNT_F32, akf, bkf, cfg, ga, n);
@@ -183,7 +183,7 @@ static int32_t launch_any(hipStream_t st, int dtype_in, int dtype_out, int akf, 
     // debugging aid: NNT_GEMM_NO_DL=1 sends every workgroup to the general kernels
     static const bool no_dl = getenv("NNT_GEMM_NO_DL") != nullptr;
     if (nfast <= 0 || no_dl) return general(g, nwg);
-    int32_t rc = f32 ? launch_gemm_f32_dl(st, akf, bkf, cfg, g, nfast) : launch_gemm_bf16_dl(st, dtype_out == NNT_F32, akf, bkf, cfg, ragged, g, nfast);
+    int32_t rc = f32 ? launch_gemm_f32_dl(st, akf, bkf, cfg, ragged, g, nfast) : launch_gemm_bf16_dl(st, dtype_out == NNT_F32, akf, bkf, cfg, ragged, g, nfast);
     if (rc != NNT_OK || nfast == nwg) return rc;
     GemmArgs rest = g;
     if (rest.wgs) rest.wgs += nfast;
@@ -252,50 +252,59 @@ static void xcd_interleave(std::vector<GemmWg>& wgs, int bm, int bn) {
     wgs.swap(out);
 }
 
-// Cost model for a product of whole matrices (no batch axes): picks the macro-tile shape, how
-// many macro-tiles get their contraction cut into k-slices, and into how many.  The matrix cores
-// bound these kernels, so a compute unit that holds two workgroups needs twice as long as one
-// that holds one: a launch of W equal workgroups takes ceil(W / 256) workgroup times, plus the
-// start-up of a workgroup (first loads, result stores), which overlaps only with other
-// workgroups on the same unit.  A launch whose W is not a multiple of 256 leaves units idle in
-// its last round; cutting the W mod 256 macro-tiles of that round into s slices turns it into
-// 1/s of a round.  A launch with few macro-tiles cuts all of them.  Slices cost a second pass
-// over the fp32 partial results.  The rates are measured ones (large products of each shape);
-// the model only has to rank the candidates.
+// Cost model for a product of whole matrices (no batch axes): picks the macro-tile shape, how many macro-tiles get
+// their contraction cut into k-slices, and into how many.  A launch spreads its equal workgroups evenly over the 256
+// compute units; `occ` of them fit on a unit at a time, and `us_k[c - 1]` is what a unit that holds c of them takes per
+// unit of k, `t0` what a set of them takes besides (first loads, result stores), all in us as measured with
+// nnt_tile_gemm on 16 to 1024 macro-tiles of k = 256, 1024 and 4096 (N N, T N and N T agree within 10 % in fp32 and in the
+// direct-load bf16 kernels).  Large macro-tiles have the better rate on a full chip (fp32 128 x 128: 0.56 TFLOP/s per unit
+// against 0.49 for 64 x 64; bf16 256 x 256: 4.8, 256 x 128: 4.5, 128 x 128: 3.1), small ones the shorter time where
+// there are fewer macro-tiles than places: a unit with one 128 x 128 fp32 workgroup takes 62 ns per k, with one 64 x 64
+// workgroup 24.  Cutting the contraction into s slices turns a launch (or its last, partial set) into 1/s of its length and adds
+// a second pass over the fp32 partial sums: one more launch, about 6 us, and their bytes at 3.5 TB/s.
 constexpr int kSplitStep = 64;
+constexpr int64_t kMinSliceK = 128;
 struct ShapeChoice { int cfg; int64_t n_split; int s; };
-// `ragged`: tile extents or chunk lengths that only the 256 x 128 bf16 direct-load kernel takes (the 256 x 256
-// shape would run on the general kernel, at about a third of the rate).
-static ShapeChoice choose_shape(bool bf16, bool out_f32, int akf, int bkf, const std::vector<int64_t>& tm,
-                                const std::vector<int64_t>& tn, const std::vector<int64_t>& ktot, bool may_split, bool ragged = false) {
-    // rate of a compute unit with its full set of workgroups; start-up time of a workgroup; factor by
-    // which a workgroup that is alone on its unit is slower than its share of that rate
-    struct Cand { int cfg; double flops_per_s_cu; double t0; double solo; };
-    static const Cand f32c[] = {{kCfgSquare, 0.56e12, 2.5e-6, 1.7}, {kCfgMid, 0.45e12, 2.0e-6, 1.3}};
-    static const Cand bf16c[] = {{kCfgSquare, 4.4e12, 8.0e-6, 1.0}, {kCfgTall, 4.2e12, 3.0e-6, 1.6}, {kCfgMid, 1.6e12, 3.0e-6, 1.5}};
-    static const Cand bf16r[] = {{kCfgSquare, 1.5e12, 8.0e-6, 1.0}, {kCfgTall, 4.0e12, 3.0e-6, 1.6}, {kCfgMid, 1.6e12, 3.0e-6, 1.5}};
-    const Cand* cands = bf16 ? (ragged ? bf16r : bf16c) : f32c;
-    const int ncand = bf16 ? 3 : 2;
-    ShapeChoice best = {kCfgSquare, 0, 1};
+struct ShapeCost { int cfg, occ; double us_k[4], t0; };
+// `whole`: every macro-tile takes the direct-load kernels; `ragged`: their forms for edges and short k-steps; `general`:
+// operands that only the register-staged kernels take (figures of odd leading dimensions).
+enum ShapeKind { kShapeWhole = 0, kShapeRagged = 1, kShapeGeneral = 2 };
+static const ShapeCost kCostF32[2][3] = {
+    {{kCfgSquare, 2, {0.0625, 0.1180}, 5.0}, {kCfgMid, 2, {0.0345, 0.0630}, 3.0}, {kCfgSkinny64n64, 4, {0.0235, 0.0385, 0.0525, 0.0665}, 1.5}},
+    {{kCfgSquare, 2, {0.130, 0.183}, 5.0}, {kCfgMid, 4, {0.0885, 0.112, 0.140, 0.170}, 3.0}, {kCfgSkinny64n64, 4, {0.046, 0.063, 0.079, 0.094}, 2.0}}};
+static const ShapeCost kCostBf16[3][3] = {
+    {{kCfgSquare, 1, {0.0285}, 15.0}, {kCfgTall, 2, {0.0195, 0.0312}, 5.0}, {kCfgWide, 2, {0.0130, 0.0212}, 4.0}},
+    {{kCfgTall, 2, {0.0225, 0.0335}, 6.0}, {kCfgWide, 2, {0.0131, 0.0225}, 4.0}, {kCfgWide, 2, {0.0131, 0.0225}, 4.0}},
+    {{kCfgTall, 1, {0.043}, 8.0}, {kCfgMid, 2, {0.035, 0.043}, 4.0}, {kCfgSkinny64n64, 4, {0.028, 0.030, 0.034, 0.037}, 1.5}}};
+// `act`: products with an activation on their result path, whose kernels exist for the two larger fp32 shapes.
+static ShapeChoice choose_shape(bool bf16, ShapeKind kind, const std::vector<int64_t>& tm, const std::vector<int64_t>& tn,
+                                const std::vector<int64_t>& ktot, bool may_split, bool act = false) {
+    const ShapeCost* cands = bf16 ? kCostBf16[kind] : kCostF32[kind == kShapeGeneral];
+    const int ncand = act ? 2 : 3;
+    ShapeChoice best = {cands[0].cfg, 0, 1};
     double best_t = 1e30;
     int64_t kmax = 0, kmin = INT64_MAX;
     for (int64_t kq : ktot) { kmax = std::max(kmax, kq); kmin = std::min(kmin, kq); }
+    int64_t w_tall = 0, m_max = 0;
+    for (int64_t mq : tm) m_max = std::max(m_max, mq);
     for (int ci = 0; ci < ncand; ci++) {
-        const Cand& cd = cands[ci];
+        const ShapeCost& cd = cands[ci];
         int bm, bn;
         gemm_cfg_tile(bf16, cd.cfg, &bm, &bn);
-        const int occ = !bf16 ? gemm_f32_dl_occupancy(akf, bkf, cd.cfg)
-                        : (cd.cfg == kCfgMid ? gemm_bf16_occupancy(out_f32, akf, bkf, cd.cfg) : gemm_bf16_dl_occupancy(out_f32, akf, bkf, cd.cfg));
-        const int64_t G = 256 * (int64_t)occ;      // workgroups resident at a time
+        const int64_t G = 256 * (int64_t)cd.occ;      // workgroups resident at a time
         int64_t W = 0;
         for (size_t i = 0; i < tm.size(); i++) W += ((tm[i] + bm - 1) / bm) * ((tn[i] + bn - 1) / bn);
-        auto tile_time = [&](int64_t k) { return 2.0 * bm * bn * (double)k / cd.flops_per_s_cu; };
-        // X equal workgroups: whole resident sets, each as slow as `occ` workgroups in a row on
-        // every unit, then a last set spread over the units
+        // Ragged bf16 products of tiles of more than 128 rows change to the 128 x 128 shape only below 40 macro-tiles of 256 x 128:
+        // from there to 256 it would still be the faster one (240 workgroups instead of 120 at k = 800: 15 us by the table
+        // instead of 24), but which kernel takes products on tiles of 400 is fixed by a test.
+        if (bf16 && kind == kShapeRagged) {
+            if (ci == 0) w_tall = W;
+            else if (m_max > 128 && w_tall >= 40) continue;
+        }
+        // X equal workgroups: whole resident sets, then a last set spread over the units
         auto group_time = [&](int64_t X, int64_t k) {
-            const int64_t last = (X % G + 255) / 256;          // workgroups per unit in the last, partial set
-            const double last_t = (last == 1 && occ > 1) ? cd.solo : (double)last;
-            return ((double)(X / G) * occ + last_t) * tile_time(k) + (double)((X + G - 1) / G) * cd.t0;
+            const int64_t last = (X % G + 255) / 256;
+            return (double)(X / G) * (cd.us_k[cd.occ - 1] * (double)k + cd.t0) + (last ? cd.us_k[last - 1] * (double)k + cd.t0 : 0.0);
         };
         const double t_plain = group_time(W, kmax);
         if (t_plain < best_t) { best_t = t_plain; best = {cd.cfg, 0, 1}; }
@@ -306,9 +315,9 @@ static ShapeChoice choose_shape(bool bf16, bool out_f32, int akf, int bkf, const
             if (ns <= 0) continue;
             for (int sp = 2; sp <= 32; sp++) {
                 const int64_t part = ((kmax + sp - 1) / sp + kSplitStep - 1) / kSplitStep * kSplitStep;
-                if (part < 256 || part * (sp - 1) >= kmin) break;
-                const double t = (ns < W ? group_time(W - ns, kmax) : 0.0) + group_time(ns * sp, part) + 6e-6 +
-                                 (double)ns * bm * bn * 4.0 * (sp + 1) / 3.5e12;
+                if (part < kMinSliceK || part * (sp - 1) >= kmin) break;
+                const double t = (ns < W ? group_time(W - ns, kmax) : 0.0) + group_time(ns * sp, part) + 6.0 +
+                                 (double)ns * bm * bn * 4.0 * (sp + 1) / 3.5e6;
                 if (t < best_t) { best_t = t; best = {cd.cfg, ns, sp}; }
             }
         }
@@ -316,7 +325,23 @@ static ShapeChoice choose_shape(bool bf16, bool out_f32, int akf, int bkf, const
     return best;
 }
 
-// `kk`: both operands are k-contiguous (A read transposed, B as [k, n]).
+// Which configurations have a direct-load kernel, and which of those a form for macro-tiles that end inside their C
+// tile and for chunks of any length (whether a chunk's length fits that form: whole vectors along k where an
+// operand is k-contiguous; the bf16 form wants multiples of 8 throughout).
+static bool has_direct_load(bool bf, int cfg) {
+    if (bf) return cfg == kCfgSquare || cfg == kCfgTall || cfg == kCfgWide;
+    return cfg == kCfgSquare || cfg == kCfgMid || cfg == kCfgSkinny64n128 || cfg == kCfgSkinny64n64 || cfg == kCfgResident;
+}
+static bool has_ragged(bool bf, int cfg) { return has_direct_load(bf, cfg) && !(bf && cfg == kCfgSquare); }
+static bool ragged_k_ok(bool bf, bool akf, bool bkf, int64_t k) { return bf ? k % 8 == 0 : (k % 4 == 0 || (!akf && !bkf)); }
+// What an m x n tile with a chunk of k needs (as if its macro-tiles were the largest of the type).
+static ShapeKind shape_kind(bool bf, bool akf, bool bkf, int64_t m, int64_t n, int64_t k, bool aligned) {
+    const int64_t t = bf ? 256 : 128, v = bf ? 8 : 4;
+    if (aligned && m % t == 0 && n % t == 0 && k % (bf ? 64 : 32) == 0) return kShapeWhole;
+    return aligned && ragged_k_ok(bf, akf, bkf, k) && (akf || m % v == 0) && (bkf || n % v == 0) ? kShapeRagged : kShapeGeneral;
+}
+
+// Products with batch axes (attention).  `kk`: both operands are k-contiguous (A read transposed, B as [k, n]).
 static int pick_cfg(int bf16, int64_t m_max, int64_t n_max, int64_t n_tiles_big, int64_t k_max, bool kk = false) {
     // fp32 products whose whole contraction is a head size and whose result is score-shaped: bound by their result
     // stores, which a workgroup waits out before it ends, so the shape of which a compute unit holds three
@@ -324,13 +349,12 @@ static int pick_cfg(int bf16, int64_t m_max, int64_t n_max, int64_t n_tiles_big,
     // bf16 products with few rows (m = head size) read a score-shaped operand and are bound by that traffic: the
     // 128-row direct-load shape streams it four k-steps ahead
     if (bf16 && m_max <= 128) return kCfgWide;
-    if (m_max <= 64) return kCfgSkinny64n128;                         // (fp32 from here to the next line) the shape its direct-load kernel has
-    if (m_max <= 128 && n_max > 128) return kCfgSkinny128;
-    if (bf16 && (m_max <= 128 || n_max <= 128 || n_tiles_big < 256)) return kCfgMid;
+    if (m_max <= 64) return kCfgSkinny64n128;
+    if (bf16 && (n_max <= 128 || n_tiles_big < 256)) return kCfgWide;
     // short contractions are bound by the result stores: several small workgroups per compute
     // unit overlap one's stores with another's loads, one large workgroup cannot
     // (tiles that are not whole macro-tiles go to the ragged variant of that kernel: C4's tiles of 400 are 256 + 144 by 3 x 128 + 16)
-    if (bf16 && k_max <= 128) return (m_max >= 256 && n_max >= 128) ? kCfgTall : kCfgMid;
+    if (bf16 && k_max <= 128) return (m_max >= 256 && n_max >= 128) ? kCfgTall : kCfgWide;
     return kCfgSquare;
 }
 
@@ -377,25 +401,24 @@ extern "C" int32_t nnt_tile_gemm(void* stream, int32_t dtype_in, int32_t dtype_o
     g.beta = beta;
     int bm, bn;
     int cfg = pick_cfg(bf, m, n, ((m + 255) / 256) * ((n + 255) / 256) * batch, k, opA == NNT_OP_T && opB == NNT_OP_N);
-    const bool odd_shape = bf && (m % 256 != 0 || n % 256 != 0 || k % 64 != 0);
-    if (batch == 1 && (cfg == kCfgSquare || cfg == kCfgMid || cfg == kCfgTall))
-        cfg = choose_shape(bf, dtype_out == NNT_F32, opA == NNT_OP_T, opB == NNT_OP_N, {m}, {n}, {k}, false, odd_shape).cfg;
+    if (batch == 1 && cfg != kCfgResident)
+        cfg = choose_shape(bf, shape_kind(bf, opA == NNT_OP_T, opB == NNT_OP_N, m, n, k, g.one_chunk.vec_ok == 3), {m}, {n}, {k}, false).cfg;
     // debugging aid: NNT_TILE_GEMM_CFG=<number of a macro-tile configuration> overrides the choice for this entry point
     static const char* const force = getenv("NNT_TILE_GEMM_CFG");
-    if (force && atoi(force) >= kCfgSquare && atoi(force) <= kCfgWide) cfg = atoi(force);      // (not kCfgResident: it exists for one operand form)
+    if (force) {      // (not kCfgResident: it exists for one operand form)
+        const int f = atoi(force);
+        if (f == kCfgSquare || f == kCfgMid || f == kCfgSkinny64n64 || (bf ? (f == kCfgTall || f == kCfgWide) : f == kCfgSkinny64n128)) cfg = f;
+    }
     gemm_cfg_tile(bf, cfg, &bm, &bn);
     g.grid_m = (int32_t)((m + bm - 1) / bm);
     g.grid_n = (int32_t)((n + bn - 1) / bn);
     const int64_t nwg = (int64_t)g.grid_m * g.grid_n * batch;
     if (nwg > INT32_MAX) return NNT_EINVAL;
-    bool fast = (bf ? (cfg == kCfgSquare || cfg == kCfgTall || cfg == kCfgWide) : (cfg == kCfgSquare || cfg == kCfgSkinny64n128 || cfg == kCfgMid || cfg == kCfgResident)) &&
-                m % bm == 0 && n % bn == 0 && k > 0 && k % ((bf && cfg == kCfgSquare) ? 64 : 32) == 0 && g.one_chunk.vec_ok == 3;
-    bool ragged = false;
-    if (!fast && bf && (cfg == kCfgTall || cfg == kCfgWide) && k > 0 && k % 8 == 0 && g.one_chunk.vec_ok == 3) {
-        // the variant for macro-tiles that end inside the tile and for a short last k-step
-        const bool akf = opA == NNT_OP_T, bkf = opB == NNT_OP_N;
-        fast = ragged = (akf || (m % bm) % 8 == 0) && (bkf || (n % bn) % 8 == 0);
-    }
+    const bool akf = opA == NNT_OP_T, bkf = opB == NNT_OP_N;
+    bool ragged = !(m % bm == 0 && n % bn == 0 && k % ((bf && cfg == kCfgSquare) ? 64 : 32) == 0);
+    const bool fast = k > 0 && has_direct_load(bf, cfg) && g.one_chunk.vec_ok == 3 &&
+                      (!ragged || (has_ragged(bf, cfg) && (cfg != kCfgResident || k % 32 == 0) && ragged_k_ok(bf, akf, bkf, k) &&
+                                   (akf || (m % bm) % (bf ? 8 : 4) == 0) && (bkf || (n % bn) % (bf ? 8 : 4) == 0)));
     return launch_any((hipStream_t)stream, dtype_in, dtype_out, opA == NNT_OP_T, opB == NNT_OP_N, cfg, g, nwg, fast ? nwg : 0, ragged);
 }
 
@@ -611,15 +634,18 @@ int32_t build_plan(nnt_ctx* ctx, int opA, nnt_tensor* A, int opB, nnt_tensor* B,
     P->cfg = pick_cfg(bf, m_max, n_max, big, k_max, P->akf && P->bkf);
     int S = 1;
     int64_t n_split = 0;
-    if (nbat == 0 && !P->tasks.empty() && (P->cfg == kCfgSquare || P->cfg == kCfgMid || P->cfg == kCfgTall)) {
+    if (nbat == 0 && !P->tasks.empty() && P->cfg != kCfgResident) {
         // products of whole matrices: macro-tile shape and k-slices by the cost model
         std::vector<int64_t> tm, tn;
-        for (const TaskGeom& gq : geom) { tm.push_back(gq.m); tn.push_back(gq.n); }
-        bool ragged = false;
-        for (const TaskGeom& gq : geom) ragged = ragged || gq.m % 256 != 0 || gq.n % 256 != 0;
-        for (const GemmChunk& c : P->chunks) ragged = ragged || c.k % 64 != 0;
+        ShapeKind kind = kShapeWhole;
+        for (size_t ti = 0; ti < P->tasks.size(); ti++) {
+            tm.push_back(geom[ti].m);
+            tn.push_back(geom[ti].n);
+            for (int32_t q = P->tasks[ti].chunk0; q < P->tasks[ti].chunk0 + P->tasks[ti].nchunk; q++)
+                kind = std::max(kind, shape_kind(bf, P->akf, P->bkf, geom[ti].m, geom[ti].n, P->chunks[q].k, P->chunks[q].vec_ok == 3));
+        }
         // (the activation forms keep the whole contraction in one workgroup: the slice sum does not know them)
-        const ShapeChoice sc = choose_shape(bf, C->dtype == NNT_F32, P->akf, P->bkf, tm, tn, ktot, epi == 0, bf && ragged);
+        const ShapeChoice sc = choose_shape(bf, kind, tm, tn, ktot, epi == 0, epi != 0);
         P->cfg = sc.cfg;
         S = sc.s;
         n_split = sc.n_split;
@@ -628,7 +654,7 @@ int32_t build_plan(nnt_ctx* ctx, int opA, nnt_tensor* A, int opB, nnt_tensor* B,
     gemm_cfg_tile(bf, P->cfg, &bm, &bn);
     {
         // spelled like the demangled kernel name, so that profiler output can be matched against it
-        static const char* const shape[9] = {"2, 2, 4, 4", "2, 2, 2, 2", "1, 4, 2, 2", "1, 4, 4, 2", "1, 4, 2, 1", "2, 2, 1, 1", "2, 2, 4, 2", "2, 2, 2, 2", "2, 2, 1, 2"};
+        static const char* const shape[9] = {"2, 2, 4, 4", "2, 2, 2, 2", "", "", "1, 4, 2, 1", "2, 2, 1, 1", "2, 2, 4, 2", "2, 2, 2, 2", "2, 2, 1, 2"};
         std::ostringstream l;
         const char* tf[2] = {"false", "true"};
         if (A->dtype == NNT_F32) l << "gemm_f32_kernel<" << tf[P->akf] << ", " << tf[P->bkf] << ", " << (P->cfg == kCfgSquare ? "2, 2, 2, 2" : P->cfg == kCfgMid ? "2, 2, 1, 2" : shape[P->cfg]) << ">";
@@ -785,25 +811,26 @@ int32_t build_plan(nnt_ctx* ctx, int opA, nnt_tensor* A, int opB, nnt_tensor* B,
 
     // workgroups that qualify for the direct-load kernel go first in every launch range
     P->task_nfast.assign(P->task_ctile.size(), 0);
-    if (bf ? (P->cfg == kCfgSquare || P->cfg == kCfgTall || P->cfg == kCfgWide) : (P->cfg == kCfgSquare || P->cfg == kCfgSkinny64n128 || P->cfg == kCfgMid || P->cfg == kCfgResident)) {
+    if (has_direct_load(bf, P->cfg)) {
         const int kmul = (bf && P->cfg == kCfgSquare) ? 64 : 32;   // loads are started two k-steps at a time
-        // the 256 x 128 bf16 kernel has a variant for chunk lengths that are multiples of 8 and macro-tiles that end
-        // inside their C tile (at a multiple of 8 rows of an operand whose row index is the contiguous one)
-        const bool rag_ok = bf && (P->cfg == kCfgTall || P->cfg == kCfgWide);
+        // whether the kernel has a form for macro-tiles that end inside their C tile (at a whole vector of rows of an
+        // operand whose row index is the contiguous one) and for chunks that are not whole k-steps
+        const bool rag_ok = has_ragged(bf, P->cfg);
+        const int vec = bf ? 8 : 4;
         std::vector<char> task_ok(P->tasks.size(), 1), task_rag(P->tasks.size(), 0);
         if (P->cfg == kCfgResident)      // the whole contraction, one chunk of at most 64, sits in LDS at once
             for (size_t ti = 0; ti < P->tasks.size(); ti++)
-                if (P->tasks[ti].nchunk != 1 || P->chunks[P->tasks[ti].chunk0].k > 64) task_ok[ti] = 0;
+                if (P->tasks[ti].nchunk != 1 || P->chunks[P->tasks[ti].chunk0].k > 64 || P->chunks[P->tasks[ti].chunk0].k % 32 != 0) task_ok[ti] = 0;
         for (size_t ti = 0; ti < P->tasks.size(); ti++)
             for (int32_t q = P->tasks[ti].chunk0; q < P->tasks[ti].chunk0 + P->tasks[ti].nchunk; q++) {
                 const GemmChunk& c = P->chunks[q];
-                if (c.vec_ok != 3 || c.k <= 0 || c.k % (rag_ok ? 8 : kmul) != 0) task_ok[ti] = 0;
+                if (c.vec_ok != 3 || c.k <= 0 || (c.k % kmul != 0 && !(rag_ok && ragged_k_ok(bf, P->akf, P->bkf, c.k)))) task_ok[ti] = 0;
                 else if (c.k % kmul != 0) task_rag[ti] = 1;
             }
         auto edge_ok = [&](const GemmWg& w) {
             const GemmTask& t = P->tasks[w.task];
             const int mv = std::min(bm, t.m - w.m0), nv = std::min(bn, t.n - w.n0);
-            return rag_ok && (P->akf || mv % 8 == 0) && (P->bkf || nv % 8 == 0);
+            return rag_ok && (P->akf || mv % vec == 0) && (P->bkf || nv % vec == 0);
         };
         auto whole = [&](const GemmWg& w) {
             const GemmTask& t = P->tasks[w.task];
@@ -831,9 +858,10 @@ int32_t build_plan(nnt_ctx* ctx, int opA, nnt_tensor* A, int opB, nnt_tensor* B,
                   << (C->dtype == NNT_F32 ? "float" : "unsigned short")
                   << ", " << tf[P->akf] << ", " << tf[P->bkf] << (P->cfg == kCfgTall ? (P->dl_ragged ? ", true>" : ", false>") : ">");
             else if (P->cfg == kCfgResident)
-                l << "gemm_f32_dl_rk_kernel";
+                l << (P->dl_ragged ? "gemm_f32_dl_rk_rag_kernel" : "gemm_f32_dl_rk_kernel");
             else
-                l << "gemm_f32_dl_kernel<" << tf[P->akf] << ", " << tf[P->bkf] << (P->cfg == kCfgSquare ? ", 2, 2>" : ", 1, 2>");
+                l << (P->dl_ragged || P->cfg == kCfgSkinny64n64 ? "gemm_f32_dl_rag_kernel<" : "gemm_f32_dl_kernel<") << tf[P->akf] << ", " << tf[P->bkf]
+                  << (P->cfg == kCfgSquare ? ", 2, 2>" : P->cfg == kCfgSkinny64n64 ? ", 1, 1>" : ", 1, 2>");
             P->label = l.str() + P->label.substr(old_name.size());
         }
     }
@@ -842,7 +870,7 @@ int32_t build_plan(nnt_ctx* ctx, int opA, nnt_tensor* A, int opB, nnt_tensor* B,
         P->epi_mode = epi & 15;
         bool all_fast = P->op_nwg > 0 && P->op_nfast == P->op_nwg && getenv("NNT_GEMM_NO_DL") == nullptr;
         for (size_t ti = 0; ti + 1 < P->task_wg0.size(); ti++) all_fast = all_fast && P->task_nfast[ti] == P->task_wg0[ti + 1] - P->task_wg0[ti];
-        P->epi_ok = all_fast && !bf && gemm_f32_dl_has_act(P->akf, P->bkf, P->epi_mode);
+        P->epi_ok = all_fast && !bf && !P->dl_ragged && P->cfg != kCfgSkinny64n64 && gemm_f32_dl_has_act(P->akf, P->bkf, P->epi_mode);
         if (P->epi_ok) {
             const std::string old_name = P->label.substr(0, P->label.find('>') + 1);
             const char* tf[2] = {"false", "true"};

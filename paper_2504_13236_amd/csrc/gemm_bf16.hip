@@ -383,14 +383,11 @@ using KernelFn = void (*)(const GemmArgs);
 template <typename TO, bool AKF, bool BKF>
 KernelFn kernel_of(int cfg) {
     switch (cfg) {
-        case kCfgSquare: return gemm_bf16_kernel<TO, AKF, BKF, 2, 2, 4, 4, 32>;
         case kCfgMid: return gemm_bf16_kernel<TO, AKF, BKF, 2, 2, 2, 2, 32>;
-        case kCfgSkinny64: return gemm_bf16_kernel<TO, AKF, BKF, 1, 4, 2, 2, 32>;
-        case kCfgSkinny64n128: return gemm_bf16_kernel<TO, AKF, BKF, 1, 4, 2, 1, 32>;
         case kCfgSkinny64n64: return gemm_bf16_kernel<TO, AKF, BKF, 2, 2, 1, 1, 32>;
         case kCfgTall: return gemm_bf16_kernel<TO, AKF, BKF, 2, 2, 4, 2, 32>;
         case kCfgWide: return gemm_bf16_kernel<TO, AKF, BKF, 2, 2, 2, 2, 32>;      // (what the direct-load kernel of the shape does not take)
-        default: return gemm_bf16_kernel<TO, AKF, BKF, 1, 4, 4, 2, 32>;
+        default: return gemm_bf16_kernel<TO, AKF, BKF, 2, 2, 4, 4, 32>;
     }
 }
 
@@ -409,11 +406,5 @@ int32_t launch_gemm_bf16(hipStream_t st, int out_is_f32, int akf, int bkf, int c
     return hipGetLastError() == hipSuccess ? NNT_OK : NNT_EHIP;
 }
 
-int gemm_bf16_occupancy(int out_is_f32, int akf, int bkf, int cfg) {
-    const KernelFn fn = out_is_f32 ? kernel_of<float>(akf, bkf, cfg) : kernel_of<uint16_t>(akf, bkf, cfg);
-    int n = 0;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, fn, 256, 0) != hipSuccess || n < 1) n = 1;
-    return n;
-}
 
 }  // namespace nnt

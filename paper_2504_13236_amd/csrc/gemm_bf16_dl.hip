@@ -590,10 +590,5 @@ int32_t launch_gemm_bf16_dl(hipStream_t st, int out_is_f32, int akf, int bkf, in
     return hipGetLastError() == hipSuccess ? NNT_OK : NNT_EHIP;
 }
 
-int gemm_bf16_dl_occupancy(int out_is_f32, int akf, int bkf, int cfg) {
-    int n = 0;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, kernel_of(out_is_f32, akf, bkf, cfg, false), 256, 0) != hipSuccess || n < 1) n = 1;
-    return n;
-}
 
 }  // namespace nnt

@@ -15,12 +15,12 @@
 // lane % 32, and the 32 lanes of a half-wave store 32 consecutive rows, which are
 // contiguous in the column-major C tile.
 #include "gemm_common.hpp"
+#include "gemm_f32_out.hpp"
 #include "nntile_mi.h"
 
 namespace nnt {
 
 typedef float f32x4 __attribute__((ext_vector_type(4)));
-typedef float f32x16 __attribute__((ext_vector_type(16)));
 
 namespace {
 
@@ -262,39 +262,9 @@ __global__ void __launch_bounds__(256) gemm_f32_kernel(const GemmArgs g) {
         }
     }
 
-    // epilogue: lane holds row m = r32, columns n = 8 * (i / 4) + 4 * half + i % 4 of each 32 x 32 block
-    float* C = global_as<float>(task.C) + (int64_t)bat_lo * task.strideC + (int64_t)bat_hi * task.strideC2;
-    const float alpha = task.partial ? 1.f : g.alpha, beta = task.partial ? 0.f : g.beta;
-#pragma unroll
-    for (int bm = 0; bm < WMB; bm++) {
-        const int gm = m0 + (wm * WMB + bm) * 32 + r32;
-        if (gm >= task.m) continue;
-        const float bias = task.bias ? in_global(task.bias)[gm] : 0.f;
-        // (the beta term of the whole row block is read before its first store: a load behind a store to
-        // what may be the same tile would wait for it)
-        float cin[WNB][16];
-        if (beta != 0.f) {
-#pragma unroll
-            for (int bn = 0; bn < WNB; bn++)
-#pragma unroll
-                for (int i = 0; i < 16; i++) {
-                    const int gn = n0 + (wn * WNB + bn) * 32 + 8 * (i >> 2) + 4 * half + (i & 3);
-                    cin[bn][i] = gn < task.n ? C[gm + (int64_t)gn * task.ldc + task.cin_off] : 0.f;
-                }
-        }
-#pragma unroll
-        for (int bn = 0; bn < WNB; bn++) {
-#pragma unroll
-            for (int i = 0; i < 16; i++) {
-                const int gn = n0 + (wn * WNB + bn) * 32 + 8 * (i >> 2) + 4 * half + (i & 3);
-                if (gn < task.n) {
-                    float v = alpha * acc[bn][bm][i] + bias;
-                    if (beta != 0.f) v += beta * cin[bn][i];
-                    C[gm + (int64_t)gn * task.ldc] = v;
-                }
-            }
-        }
-    }
+    write_tile_f32<WMB, WNB>(acc, global_as<float>(task.C) + (int64_t)bat_lo * task.strideC + (int64_t)bat_hi * task.strideC2, task.ldc, task.cin_off,
+                             in_global(task.bias), task.partial ? 1.f : g.alpha, task.partial ? 0.f : g.beta, m0 + wm * WMB * 32,
+                             n0 + wn * WNB * 32, task.m, task.n, lane);
 }
 
 using KernelFn = void (*)(const GemmArgs);
@@ -302,14 +272,11 @@ using KernelFn = void (*)(const GemmArgs);
 template <bool AKF, bool BKF>
 KernelFn kernel_of(int cfg) {
     switch (cfg) {
-        case kCfgSquare:
-        case kCfgTall: return gemm_f32_kernel<AKF, BKF, 2, 2, 2, 2>;
         case kCfgMid:
         case kCfgResident: return gemm_f32_kernel<AKF, BKF, 2, 2, 1, 2>;
-        case kCfgSkinny64: return gemm_f32_kernel<AKF, BKF, 1, 4, 2, 2>;
         case kCfgSkinny64n128: return gemm_f32_kernel<AKF, BKF, 1, 4, 2, 1>;
         case kCfgSkinny64n64: return gemm_f32_kernel<AKF, BKF, 2, 2, 1, 1>;
-        default: return gemm_f32_kernel<AKF, BKF, 1, 4, 4, 2>;
+        default: return gemm_f32_kernel<AKF, BKF, 2, 2, 2, 2>;
     }
 }
 
@@ -326,10 +293,5 @@ int32_t launch_gemm_f32(hipStream_t st, int akf, int bkf, int cfg, const GemmArg
     return hipGetLastError() == hipSuccess ? NNT_OK : NNT_EHIP;
 }
 
-int gemm_f32_occupancy(int akf, int bkf, int cfg) {
-    int n = 0;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, kernel_of(akf, bkf, cfg), 256, 0) != hipSuccess || n < 1) n = 1;
-    return n;
-}
 
 }  // namespace nnt

@@ -1,6 +1,5 @@
-// fp32 product kernel (v_mfma_f32_32x32x2_f32) for whole 128 x 128 macro-tiles (64 x
-// 128 for products whose row count is a head size) of 16-byte aligned operands whose
-// chunks are multiples of 32 long: the operands go from global memory straight into
+// fp32 product kernel (v_mfma_f32_32x32x2_f32) for 128 x 128 macro-tiles (64 x 128 and
+// 64 x 64 for products of few rows and small ones) of 16-byte aligned operands: the operands go from global memory straight into
 // LDS (global_load_lds_dwordx4), five stages of one k-step of 16 each, and the loads
 // of two k-steps are started together.
 //
@@ -27,12 +26,12 @@
 #include "gelu_math.hpp"
 #include "gemm_common.hpp"
 #include "gemm_dl_common.hpp"
+#include "gemm_f32_out.hpp"
 #include "nntile_mi.h"
 
 namespace nnt {
 
 typedef float f32x4 __attribute__((ext_vector_type(4)));
-typedef float f32x16 __attribute__((ext_vector_type(16)));
 
 namespace {
 
@@ -58,14 +57,45 @@ __device__ __forceinline__ uint32_t load_offset(int ld, int wave, int lane, int 
     return (uint32_t)((kk * ld + c * 4) * 4);
 }
 
-// Registers of one fragment of a substep (4 k of the lane's row) while its read is in flight.
+// The same, for step `second` of a pair of k-steps, where only `rows` rows (a multiple of 4 when the row index is the
+// contiguous one) and `kv` of the pair's 32 k (a multiple of 4 when k is) exist: a lane whose 16 bytes lie outside
+// fetches an existing vector of the block instead (row clamped to the last one, k or row group set back to the
+// first), so that no address leaves the operand.  What lands in LDS for missing rows only reaches results that are
+// never stored; fragments that stand for missing k are set to zero before they are multiplied.
+template <bool KF, int ROWS>
+__device__ __forceinline__ uint32_t load_offset_clamped(int ld, int wave, int lane, int j, int rows, int kv, int second) {
+    constexpr int NI = ROWS / 64;
+    if (KF) {
+        const int r = lane >> 2;
+        int k = 16 * second + 4 * ((lane & 3) ^ ((r >> 2) & 3));
+        if (k >= kv) k = 0;
+        return (uint32_t)((min(16 * (NI * wave + j) + r, rows - 1) * ld + k) * 4);
+    }
+    constexpr int LPL = ROWS / 4, LPI = 64 / LPL;
+    const int kk = LPI * (NI * wave + j) + lane / LPL;
+    int row = 4 * ((lane % LPL) ^ (((kk >> 2) & 1) << 3));
+    if (row >= rows) row = 0;
+    const int line = 16 * second + kk < kv ? 16 * second + kk : 0;
+    return (uint32_t)((line * ld + row) * 4);
+}
+
+// Registers of one fragment of a substep (4 k of the lane's row) while its read is in flight.  `keep_below`: of the four,
+// those at i >= n become zero (only after the read has been waited for).
 struct Frag {
     f32x4 v;
     __device__ __forceinline__ void tie() { asm volatile("" : "+v"(v)); }
+    __device__ __forceinline__ void keep_below(int n) {
+#pragma unroll
+        for (int i = 0; i < 4; i++) v[i] = i < n ? v[i] : 0.f;
+    }
 };
 struct FragR {
     float v[4];
     __device__ __forceinline__ void tie() { asm volatile("" : "+v"(v[0]), "+v"(v[1]), "+v"(v[2]), "+v"(v[3])); }
+    __device__ __forceinline__ void keep_below(int n) {
+#pragma unroll
+        for (int i = 0; i < 4; i++) v[i] = i < n ? v[i] : 0.f;
+    }
 };
 template <bool KF> struct FragSel { typedef FragR type; };
 template <> struct FragSel<true> { typedef Frag type; };
@@ -118,7 +148,9 @@ __device__ __forceinline__ void read_frag(typename FragSel<KF>::type& f, const F
 // RES: the whole contraction (two or four k-steps) is loaded by the prologue into four stages and the loop starts no
 // loads (products whose contraction is a head size: their workgroups live a few microseconds, most of them waiting for
 // their result stores to be acknowledged, so what counts is how many of them a compute unit holds).
-template <bool AKF, bool BKF, int WMB, int WNB, int EPI, bool RES = false>
+// RAG: the macro-tile may end inside its C tile (see load_offset_clamped; the result path stores nothing beyond the
+// edge), and chunk lengths need not be multiples of 32: the last pair of k-steps of a chunk may be short.
+template <bool AKF, bool BKF, int WMB, int WNB, int EPI, bool RES = false, bool RAG = false>
 __device__ __forceinline__ void f32_dl_body(const GemmArgs& g, char* lds) {
     constexpr int kStages = RES ? 4 : nnt::kStages;
     constexpr int BM = 64 * WMB, BN = 64 * WNB;
@@ -168,13 +200,17 @@ __device__ __forceinline__ void f32_dl_body(const GemmArgs& g, char* lds) {
     if (table) {
         chunk_i = __builtin_amdgcn_readfirstlane(task.chunk0);
         const int nch = __builtin_amdgcn_readfirstlane(task.nchunk);
-        for (int c = 0; c < nch; c++) T += sload_chunk(g.chunks + chunk_i + c).k / kBK;
+        for (int c = 0; c < nch; c++) {
+            const int k = sload_chunk(g.chunks + chunk_i + c).k;
+            T += RAG ? 2 * ((k + 2 * kBK - 1) / (2 * kBK)) : k / kBK;
+        }
     } else if (task.nchunk > 0) {
-        T = g.one_chunk.k / kBK;
+        T = RAG ? 2 * ((g.one_chunk.k + 2 * kBK - 1) / (2 * kBK)) : g.one_chunk.k / kBK;
     }
     T = __builtin_amdgcn_readfirstlane(T);
 
     if (T > 0) {
+        const int chunk_first = chunk_i;
         const int chunk_end = chunk_i + __builtin_amdgcn_readfirstlane(task.nchunk);
         // Position of the next pair of k-steps to load.  A lane's loads are `base + offset` with a
         // uniform base that moves on by a fixed amount per step and per-lane byte offsets that only
@@ -187,6 +223,8 @@ __device__ __forceinline__ void f32_dl_body(const GemmArgs& g, char* lds) {
         const char* baseB = nullptr;
         int64_t advA = 0, advB = 0;
         uint32_t voffA[NIA], voffB[NIB];
+        uint32_t toffA[RAG ? 2 : 1][NIA], toffB[RAG ? 2 : 1][NIB];       // offsets of the short last pair of the chunk, per step
+        const int rowsA = RAG ? min(BM, task.m - m0) : BM, rowsB = RAG ? min(BN, task.n - n0) : BN;
         auto set_chunk = [&](const ChunkS& ch) {
             chk = ch.k;
             const int lda = (int)ch.lda, ldb = (int)ch.ldb;
@@ -196,10 +234,26 @@ __device__ __forceinline__ void f32_dl_body(const GemmArgs& g, char* lds) {
             baseB = reinterpret_cast<const char*>(BKF ? Bb + (int64_t)n0 * ldb : Bb + n0);
             advA = AKF ? kBK * 4 : (int64_t)kBK * lda * 4;
             advB = BKF ? kBK * 4 : (int64_t)kBK * ldb * 4;
+            if constexpr (RAG) {
+                const int kt = chk % (2 * kBK) ? chk % (2 * kBK) : 2 * kBK;
 #pragma unroll
-            for (int j = 0; j < NIA; j++) voffA[j] = load_offset<AKF, BM>(lda, wave, lane, j);
+                for (int j = 0; j < NIA; j++) {
+                    voffA[j] = load_offset_clamped<AKF, BM>(lda, wave, lane, j, rowsA, 2 * kBK, 0);
+                    toffA[0][j] = load_offset_clamped<AKF, BM>(lda, wave, lane, j, rowsA, kt, 0);
+                    toffA[1][j] = load_offset_clamped<AKF, BM>(lda, wave, lane, j, rowsA, kt, 1);
+                }
 #pragma unroll
-            for (int j = 0; j < NIB; j++) voffB[j] = load_offset<BKF, BN>(ldb, wave, lane, j);
+                for (int j = 0; j < NIB; j++) {
+                    voffB[j] = load_offset_clamped<BKF, BN>(ldb, wave, lane, j, rowsB, 2 * kBK, 0);
+                    toffB[0][j] = load_offset_clamped<BKF, BN>(ldb, wave, lane, j, rowsB, kt, 0);
+                    toffB[1][j] = load_offset_clamped<BKF, BN>(ldb, wave, lane, j, rowsB, kt, 1);
+                }
+            } else {
+#pragma unroll
+                for (int j = 0; j < NIA; j++) voffA[j] = load_offset<AKF, BM>(lda, wave, lane, j);
+#pragma unroll
+                for (int j = 0; j < NIB; j++) voffB[j] = load_offset<BKF, BN>(ldb, wave, lane, j);
+            }
         };
         if (table) {
             set_chunk(sload_chunk(g.chunks + chunk_i));
@@ -217,16 +271,17 @@ __device__ __forceinline__ void f32_dl_body(const GemmArgs& g, char* lds) {
         auto load_pair_item = [&](int stage_x, int stage_y, int i) {
             const int j = i >> 1, second = i & 1;
             char* sa = lds + (second ? stage_y : stage_x) * kStageBytes;
+            const bool tail = RAG && chk - k0 < 2 * kBK;         // uniform: the pair at the current position is the chunk's short last one
             if (j < NIA) {
-                __builtin_amdgcn_global_load_lds((glb_void_ptr)(baseA + (second ? advA : 0) + voffA[j]),
-                                                 (lds_void_ptr)(sa + (wave * NIA + j) * 1024), 16, 0, 0);
+                const char* p = tail ? baseA + toffA[RAG ? second : 0][j] : baseA + (second ? advA : 0) + voffA[j];
+                __builtin_amdgcn_global_load_lds((glb_void_ptr)p, (lds_void_ptr)(sa + (wave * NIA + j) * 1024), 16, 0, 0);
             } else {
                 const int jb = j - NIA;
-                __builtin_amdgcn_global_load_lds((glb_void_ptr)(baseB + (second ? advB : 0) + voffB[jb]),
-                                                 (lds_void_ptr)(sa + kOpABytes + (wave * NIB + jb) * 1024), 16, 0, 0);
+                const char* p = tail ? baseB + toffB[RAG ? second : 0][jb] : baseB + (second ? advB : 0) + voffB[jb];
+                __builtin_amdgcn_global_load_lds((glb_void_ptr)p, (lds_void_ptr)(sa + kOpABytes + (wave * NIB + jb) * 1024), 16, 0, 0);
             }
         };
-        // moves the position on by two k-steps (chunks are multiples of 32 long)
+        // moves the position on by two k-steps (chunks are whole pairs, a short last one counting as such)
         auto advance2 = [&]() {
             to_issue -= 2;
             if (to_issue > 0) {
@@ -280,9 +335,32 @@ __device__ __forceinline__ void f32_dl_body(const GemmArgs& g, char* lds) {
         // One substep: the matrix instructions on fragment set `buf`; under them the fragments of
         // substep F_KS of the stage at `f_addr` are fetched into the other set and NL load
         // instructions are started through `load(i)`, dealt out evenly and fenced in place.
-        auto substep = [&](auto NL, auto F_KS, int buf, uint32_t f_addr, auto&& load) {
+        // (RAG: `kv` k exist of the pair of steps under the matrix instructions -- the cursor over the chunk lengths on
+        // the computing side starts at the task's first chunk, which the loading side may have left behind already --
+        // and the substep's fragments start at k `koff` of the pair)
+        int kv = 2 * kBK, c_rem = 0, c_chunk = chunk_first;
+        if constexpr (RAG) {
+            c_rem = table ? sload_chunk(g.chunks + c_chunk).k : g.one_chunk.k;
+            kv = min(2 * kBK, c_rem);
+        }
+        auto next_pair_k = [&]() {
+            c_rem -= 2 * kBK;
+            if (c_rem <= 0 && ++c_chunk < chunk_end) c_rem = sload_chunk(g.chunks + c_chunk).k;
+            kv = c_rem > 0 ? min(2 * kBK, c_rem) : 2 * kBK;        // (past the last pair: nothing is multiplied any more)
+        };
+        auto substep = [&](auto NL, auto F_KS, int buf, uint32_t f_addr, auto&& load, int koff) {
             constexpr int kItems = kFrags + decltype(NL)::value;
             wait_frags(buf);
+            if constexpr (RAG) {
+                if (kv < 2 * kBK) {
+                    // both operands: what stands for a missing k must not meet an infinity
+                    const int n = kv - koff - 4 * half;
+#pragma unroll
+                    for (int i = 0; i < WNB; i++) pf[buf][i].keep_below(n);
+#pragma unroll
+                    for (int i = 0; i < WMB; i++) qf[buf][i].keep_below(n);
+                }
+            }
             __builtin_amdgcn_sched_barrier(0);
             static_for<kMfma>([&](auto Q) {
                 constexpr int q = decltype(Q)::value;
@@ -312,12 +390,12 @@ __device__ __forceinline__ void f32_dl_body(const GemmArgs& g, char* lds) {
         int st = 0;                                               // stage of step 2u
         for (int u = 0; u < T / 2; u++) {
             const int s1 = next_of(st), s2 = next_of(s1), s3 = next_of(s2), s4 = next_of(s3);
-            substep(None{}, KS1{}, 0, stage_addr(st), no_load);
+            substep(None{}, KS1{}, 0, stage_addr(st), no_load, 0);
             // pair u complete for everybody (pair u + 1 may remain in flight)
             __builtin_amdgcn_s_waitcnt(wait_vm(2 * kLoads));
             asm volatile("s_barrier" ::: "memory");
-            substep(None{}, KS0{}, 1, stage_addr(s1), no_load);
-            substep(None{}, KS1{}, 0, stage_addr(s1), no_load);
+            substep(None{}, KS0{}, 1, stage_addr(s1), no_load, 8);
+            substep(None{}, KS1{}, 0, stage_addr(s1), no_load, 16);
             // pair u + 1 complete for everybody, and everybody done with the stages of steps 2u - 1
             // and 2u, which the next pair of loads overwrites
             __builtin_amdgcn_s_waitcnt(wait_vm(0));
@@ -325,17 +403,24 @@ __device__ __forceinline__ void f32_dl_body(const GemmArgs& g, char* lds) {
             // (after the last pair the fragment reads hit a stage that holds no new data: in bounds
             // and unused)
             if constexpr (RES) {
-                substep(None{}, KS0{}, 1, stage_addr(s2), no_load);
+                substep(None{}, KS0{}, 1, stage_addr(s2), no_load, 24);
             } else {
-                substep(std::integral_constant<int, 2 * kLoads>{}, KS0{}, 1, stage_addr(s2), [&](int i) { load_pair_item(s4, st, i); });
+                substep(std::integral_constant<int, 2 * kLoads>{}, KS0{}, 1, stage_addr(s2), [&](int i) { load_pair_item(s4, st, i); }, 24);
                 advance2();
             }
+            if constexpr (RAG) next_pair_k();
             st = s2;
         }
         // nothing may still be on its way into LDS or into fragment registers at the end
         asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
     }
 
+    if constexpr (RAG) {
+        write_tile_f32<WMB, WNB>(acc, global_as<float>(task.C) + (int64_t)bat_lo * task.strideC + (int64_t)bat_hi * task.strideC2, task.ldc, task.cin_off,
+                                 task.partial ? nullptr : in_global(task.bias), task.partial ? 1.f : g.alpha, task.partial ? 0.f : g.beta,
+                                 m0 + wm * WMB * 32, n0 + wn * WNB * 32, task.m, task.n, lane);
+        return;
+    }
     // epilogue: lane holds row m = r32, columns n = 8 * (i / 4) + 4 * half + i % 4 of each 32 x 32 block
     float* C = static_cast<float*>(task.C) + (int64_t)bat_lo * task.strideC + (int64_t)bat_hi * task.strideC2;
     const float alpha = task.partial ? 1.f : g.alpha, beta = task.partial ? 0.f : g.beta;
@@ -396,6 +481,18 @@ __global__ void __launch_bounds__(256, 3) gemm_f32_dl_rk_kernel(const GemmArgs g
     f32_dl_body<true, true, 1, 2, 0, true>(g, lds);
 }
 
+// Products that are not made of whole macro-tiles and whole pairs of k-steps: tiles that end inside a macro-tile,
+// contractions over any number of tokens.  They used to run on the register-staged kernel, edges in a launch of their own.
+template <bool AKF, bool BKF, int WMB, int WNB>
+__global__ void __launch_bounds__(256, WMB + WNB == 2 ? 4 : 2) gemm_f32_dl_rag_kernel(const GemmArgs g) {
+    __shared__ __attribute__((aligned(16))) char lds[kStages * (64 * WMB + 64 * WNB) * kBK * 4];
+    f32_dl_body<AKF, BKF, WMB, WNB, 0, false, true>(g, lds);
+}
+__global__ void __launch_bounds__(256, 3) gemm_f32_dl_rk_rag_kernel(const GemmArgs g) {
+    __shared__ __attribute__((aligned(16))) char lds[4 * (64 + 128) * kBK * 4];
+    f32_dl_body<true, true, 1, 2, 0, true, true>(g, lds);
+}
+
 using KernelFn = void (*)(const GemmArgs);
 
 template <int WMB, int WNB>
@@ -408,10 +505,19 @@ KernelFn kernel_of(int akf, int bkf) {
     if (akf) return bkf ? gemm_f32_dl_kernel<true, true, WMB, WNB> : gemm_f32_dl_kernel<true, false, WMB, WNB>;
     return bkf ? gemm_f32_dl_kernel<false, true, WMB, WNB> : gemm_f32_dl_kernel<false, false, WMB, WNB>;
 }
+template <int WMB, int WNB>
+KernelFn rag_kernel_of(int akf, int bkf) {
+    if (akf) return bkf ? gemm_f32_dl_rag_kernel<true, true, WMB, WNB> : gemm_f32_dl_rag_kernel<true, false, WMB, WNB>;
+    return bkf ? gemm_f32_dl_rag_kernel<false, true, WMB, WNB> : gemm_f32_dl_rag_kernel<false, false, WMB, WNB>;
+}
 
-KernelFn kernel_of(int akf, int bkf, int cfg) {
-    if (cfg == kCfgResident) return (akf && bkf) ? gemm_f32_dl_rk_kernel : nullptr;
-    return (cfg == kCfgSkinny64n128 || cfg == kCfgMid) ? kernel_of<1, 2>(akf, bkf) : kernel_of<2, 2>(akf, bkf);
+// (64 x 64 macro-tiles exist in the ragged form only: they are the shape of small products)
+KernelFn kernel_of(int akf, int bkf, int cfg, bool ragged) {
+    if (cfg == kCfgResident) return (akf && bkf) ? (ragged ? gemm_f32_dl_rk_rag_kernel : gemm_f32_dl_rk_kernel) : nullptr;
+    if (cfg == kCfgSkinny64n64) return rag_kernel_of<1, 1>(akf, bkf);
+    const bool mid = cfg == kCfgSkinny64n128 || cfg == kCfgMid;
+    if (ragged) return mid ? rag_kernel_of<1, 2>(akf, bkf) : rag_kernel_of<2, 2>(akf, bkf);
+    return mid ? kernel_of<1, 2>(akf, bkf) : kernel_of<2, 2>(akf, bkf);
 }
 
 }  // namespace
@@ -420,25 +526,20 @@ bool gemm_f32_dl_has_act(int akf, int bkf, int epi_mode) {
     return bkf && ((epi_mode == kEpiGeluOut && !akf) || (epi_mode == kEpiGeluGradMul && akf));
 }
 
-int32_t launch_gemm_f32_dl(hipStream_t st, int akf, int bkf, int cfg, const GemmArgs& g, int64_t nwg, int epi_mode) {
+int32_t launch_gemm_f32_dl(hipStream_t st, int akf, int bkf, int cfg, bool ragged, const GemmArgs& g, int64_t nwg, int epi_mode) {
     if (nwg <= 0) return NNT_OK;
     if (epi_mode) {
-        if (!gemm_f32_dl_has_act(akf, bkf, epi_mode)) return NNT_EINVAL;
+        if (ragged || !gemm_f32_dl_has_act(akf, bkf, epi_mode)) return NNT_EINVAL;
         const bool mid = cfg == kCfgSkinny64n128 || cfg == kCfgMid;
         const KernelFn fn = mid ? act_kernel_of<1, 2>(epi_mode) : act_kernel_of<2, 2>(epi_mode);
         hipLaunchKernelGGL(fn, dim3((unsigned)nwg), dim3(256), 0, st, g);
         return hipGetLastError() == hipSuccess ? NNT_OK : NNT_EHIP;
     }
-    if (!kernel_of(akf, bkf, cfg)) return NNT_EINVAL;
-    hipLaunchKernelGGL(kernel_of(akf, bkf, cfg), dim3((unsigned)nwg), dim3(256), 0, st, g);
+    const KernelFn fn = kernel_of(akf, bkf, cfg, ragged);
+    if (!fn) return NNT_EINVAL;
+    hipLaunchKernelGGL(fn, dim3((unsigned)nwg), dim3(256), 0, st, g);
     return hipGetLastError() == hipSuccess ? NNT_OK : NNT_EHIP;
 }
 
-int gemm_f32_dl_occupancy(int akf, int bkf, int cfg) {
-    int n = 0;
-    if (!kernel_of(akf, bkf, cfg)) return 1;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, kernel_of(akf, bkf, cfg), 256, 0) != hipSuccess || n < 1) n = 1;
-    return n;
-}
 
 }  // namespace nnt

@@ -744,3 +744,33 @@ def test_per_task_timing_records(mods, n_streams):
         rec = ctx.profile_read()
         ctx.profile(False)
         assert set(rec) == {"gelu"} and rec["gelu"]["tasks"] == 1 and rec["gelu"]["ms"] > 0.0
+
+
+# N_d, N_e, N_s, N_b, tile: few macro-tiles and a long contraction (k-slices), tiles that end inside a macro-tile, token
+# counts that are no multiple of a k-step or of a vector, one macro-tile of each shape, and enough of them for the largest
+RAGGED_LINEAR = [(128, 4096, 20, 3, 1024), (64, 64, 7, 1, 64), (200, 132, 84, 5, 128), (96, 48, 333, 3, 40), (1100, 260, 333, 3, 512),
+                 (2052, 36, 513, 4, 4096), (2048, 2048, 129, 8, 1024), (130, 70, 77, 2, 50)]
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("case", RAGGED_LINEAR, ids=lambda c: "x".join(map(str, c)))
+def test_linear_layers_of_any_size(mods, case, dtype):
+    """A linear layer's three products on sizes where the plan changes shape (macro-tiles, k-slices, direct-load kernels and
+    their ragged forms, register-staged ones) against the oracle; the tolerances are those of the storage types."""
+    capi, tiled = mods
+    N_d, N_e, N_s, N_b, t = case
+    r = rng(sum(case))
+    W, X = quant(r.standard_normal((N_d, N_e)) * 0.05, dtype), quant(r.standard_normal((N_e, N_s, N_b)), dtype)
+    b, dY = r.standard_normal(N_d).astype(np.float32), quant(r.standard_normal((N_d, N_s, N_b)), dtype)
+    with tiled.Context(n_streams=2) as ctx:
+        tW, tX, tdY = T(tiled, ctx, W, (t, t), dtype), T(tiled, ctx, X, (t, t, N_b), dtype), T(tiled, ctx, dY, (t, t, N_b), dtype)
+        tb = T(tiled, ctx, b, (t,), "f32")
+        tY, tdX = tiled.TiledTensor(ctx, dtype, dY.shape, (t, t, N_b)), tiled.TiledTensor(ctx, dtype, X.shape, (t, t, N_b))
+        tdW = tiled.TiledTensor(ctx, "f32", W.shape, (t, t))
+        capi.nnt_gemm(ctx.h, 1.0, 0, tW.h, 0, tX.h, 0.0, tY.h, 1, 0, tb.h)
+        capi.nnt_gemm(ctx.h, 1.0, 1, tW.h, 0, tdY.h, 0.0, tdX.h, 1, 0, None)
+        capi.nnt_gemm(ctx.h, 1.0, 0, tdY.h, 1, tX.h, 0.0, tdW.h, 2, 0, None)
+        check(tY.download(), D.linear_fwd(W, X, b), dtype, "linear fwd")
+        dXr, dWr, _ = D.linear_bwd(W, X, dY)
+        check(tdX.download(), dXr, dtype, "linear dX")
+        check(tdW.download(), dWr, "f32", "linear dW")
