@@ -179,13 +179,13 @@ __global__ void __launch_bounds__(256) gemm_f32_kernel(const GemmArgs g) {
         bat_lo = bat - bat_hi * task.nb1;
     }
 
-    f32x16 acc[WNB][WMB];
+    f32x16 acc[WNB][WMB], sum[WNB][WMB];
 #pragma unroll
     for (int bn = 0; bn < WNB; bn++)
 #pragma unroll
         for (int bm = 0; bm < WMB; bm++)
 #pragma unroll
-            for (int i = 0; i < 16; i++) acc[bn][bm][i] = 0.f;
+            for (int i = 0; i < 16; i++) acc[bn][bm][i] = sum[bn][bm][i] = 0.f;
 
     if (task.nchunk > 0) {
         // Loop state that is the same for every lane is kept in scalar registers on purpose
@@ -232,7 +232,7 @@ __global__ void __launch_bounds__(256) gemm_f32_kernel(const GemmArgs g) {
         store_step(lds);
         __syncthreads();
         bool more = true;
-        while (more) {
+        for (int step = 1; more; step++) {
             // advance to the next k-step (possibly the next chunk) and start its loads
             k0 += BK;
             if (k0 >= chk) {
@@ -259,8 +259,15 @@ __global__ void __launch_bounds__(256) gemm_f32_kernel(const GemmArgs g) {
             if (more) store_step(lds + (cur ^ 1) * (A_SZ + B_SZ));
             __syncthreads();
             cur ^= 1;
+            if (step % 32 == 0) move_sums<WMB, WNB>(acc, sum);       // every 512 k
         }
     }
+#pragma unroll
+    for (int bn = 0; bn < WNB; bn++)
+#pragma unroll
+        for (int bm = 0; bm < WMB; bm++)
+#pragma unroll
+            for (int i = 0; i < 16; i++) acc[bn][bm][i] += sum[bn][bm][i];
 
     write_tile_f32<WMB, WNB>(acc, global_as<float>(task.C) + (int64_t)bat_lo * task.strideC + (int64_t)bat_hi * task.strideC2, task.ldc, task.cin_off,
                              in_global(task.bias), task.partial ? 1.f : g.alpha, task.partial ? 0.f : g.beta, m0 + wm * WMB * 32,

@@ -37,6 +37,7 @@ namespace {
 
 constexpr int kBK = 16;                                  // k-step
 constexpr int kStages = 5;
+constexpr int kSumPairs = 16;                            // pairs of k-steps between two moves of the sums (512 k)
 
 // Byte offset, from (first row, first k) of an operand's ROWS x 16 block, of what this lane fetches
 // in load instruction j (0 .. ROWS / 64 - 1) of its wave; the data lands in LDS at
@@ -187,13 +188,13 @@ __device__ __forceinline__ void f32_dl_body(const GemmArgs& g, char* lds) {
         bat_lo = bat - bat_hi * task.nb1;
     }
 
-    f32x16 acc[WNB][WMB];
+    f32x16 acc[WNB][WMB], sum[WNB][WMB];
 #pragma unroll
     for (int bn = 0; bn < WNB; bn++)
 #pragma unroll
         for (int bm = 0; bm < WMB; bm++)
 #pragma unroll
-            for (int i = 0; i < 16; i++) acc[bn][bm][i] = 0.f;
+            for (int i = 0; i < 16; i++) acc[bn][bm][i] = sum[bn][bm][i] = 0.f;
 
     int T = 0;
     int chunk_i = 0;                         // index of the current chunk in g.chunks
@@ -409,10 +410,20 @@ __device__ __forceinline__ void f32_dl_body(const GemmArgs& g, char* lds) {
                 advance2();
             }
             if constexpr (RAG) next_pair_k();
+            if constexpr (!RES)
+                if (u % kSumPairs == kSumPairs - 1) move_sums<WMB, WNB>(acc, sum);
             st = s2;
         }
         // nothing may still be on its way into LDS or into fragment registers at the end
         asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
+    }
+    if constexpr (!RES) {
+#pragma unroll
+        for (int bn = 0; bn < WNB; bn++)
+#pragma unroll
+            for (int bm = 0; bm < WMB; bm++)
+#pragma unroll
+                for (int i = 0; i < 16; i++) acc[bn][bm][i] += sum[bn][bm][i];
     }
 
     if constexpr (RAG) {

@@ -9,6 +9,22 @@ namespace nnt {
 
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 
+// Takes the sums so far out of the accumulators of the matrix instructions, which start again from zero.  A chain of k
+// additions in fp32 is off by about sqrt(k) roundings of its result; cut every 512 k, with the partial sums added up on the
+// side, a contraction of 8192 is off by a quarter of that, whether or not it is cut into slices as well.
+template <int WMB, int WNB>
+__device__ __forceinline__ void move_sums(f32x16 (&acc)[WNB][WMB], f32x16 (&sum)[WNB][WMB]) {
+#pragma unroll
+    for (int bn = 0; bn < WNB; bn++)
+#pragma unroll
+        for (int bm = 0; bm < WMB; bm++)
+#pragma unroll
+            for (int i = 0; i < 16; i++) {
+                sum[bn][bm][i] += acc[bn][bm][i];
+                acc[bn][bm][i] = 0.f;
+            }
+}
+
 // Writes one wave's (32 WMB) x (32 WNB) block of C = alpha * acc + bias + beta * C[+ cin_off]: a lane holds row
 // m = lane % 32 and columns 8 * (i / 4) + 4 * (lane / 32) + i % 4 of each 32 x 32 block, so a half-wave stores 32
 // consecutive rows.  The beta terms of a row block are read before its first store and waited for once: with the loads
