@@ -10,6 +10,7 @@
 // then the probabilities in place (nnt_softmax_fwd); what is left for this file is
 // one element per column: -log of the label's probability, and minus one on that
 // entry, which turns the probabilities into the gradient of L with respect to x.
+#include "ce_column.hpp"
 #include "device_util.hpp"
 #include "internal.hpp"
 
@@ -251,6 +252,28 @@ int32_t nnt_cross_entropy(nnt_ctx* ctx, nnt_tensor* X, const int32_t* labels, nn
     const TiledView vx = X->view();
     const int dt = X->dtype;
     const dim3 grid((unsigned)((ncols + 255) / 256)), block(256);
+    // Columns that fit a workgroup's registers take one pass over the logits (one task).  The general way below reads them twice
+    // and adds a kernel before and one after: 293 + 16 us for 4096 bf16 columns of 50304, 438 + 18 us for 2048 in fp32.
+    const int64_t V = dt == NNT_F32 ? 4 : 8, vt = (X->base[0] + V - 1) / V;
+    const int64_t nvec = vt * (X->grid[0] - 1) + (X->tile_extent(0, X->grid[0] - 1) + V - 1) / V;
+    int nt = 0;
+    const CeColumnFn fn = ctx->granularity == NNT_GRAN_OP && X->grid[0] <= kCeTiles && nvec <= 16384 && ncols <= INT32_MAX
+                              ? ce_column_of(dt, (int)nvec, &nt) : nullptr;
+    if (fn) {
+        bool ok = stats->dtype == NNT_F32 && stats->ndim == 3 && stats->shape[0] == 2 && stats->base[0] == 2;
+        for (int a = 1; ok && a < 3; a++) ok = stats->shape[a] == X->shape[a] && stats->base[a] == X->base[a];
+        for (void* p : stats->tiles) ok = ok && p;
+        if (!ok) return fail(ctx, NNT_EINVAL, "nnt_cross_entropy: stats must be fp32 [2, N_s, N_b], tiled like the logits' other axes, all tiles present");
+        const TiledView vs1 = stats->view();
+        OpTag tag(ctx, "cross_entropy", 2.0 * (double)X->shape[0] * ncols * X->elem_size(), true);
+        return submit(ctx, {X->all(kReadWrite), stats->all(kWrite)}, [=](hipStream_t st) {
+            hipLaunchKernelGGL(fn, dim3((unsigned)ncols), dim3((unsigned)nt), 0, st, labels, vx, vs1, losses, (int)vt, (int)nvec);
+            if (hipGetLastError() != hipSuccess) return (int32_t)NNT_EHIP;
+            hipLaunchKernelGGL(sum_kernel, dim3(1), dim3(1024), 0, st, losses, ncols, loss);
+            return hipGetLastError() == hipSuccess ? (int32_t)NNT_OK : (int32_t)NNT_EHIP;
+        }, 2);
+    }
+    // otherwise (tile granularity, or longer columns) the SoftMax subroutines with a kernel before and one after them:
     // the label's logit of every column, kept in `losses` until the last kernel turns it into the loss
     // (ordered before the in-place softmax by its read of X, and the last kernel after it by its write)
     int32_t rc;

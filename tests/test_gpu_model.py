@@ -218,3 +218,33 @@ def test_two_block_language_model_training_step(mods, dtype):
         model.close()
         for b in blks:
             b.close()
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("N_v,tile_v", [(7, 7), (1001, 1001), (1030, 301), (4097, 1024), (16385, 4000), (50257, 8192), (70000, 9000)])
+def test_cross_entropy_column_kernels(mods, dtype, N_v, tile_v):
+    """One instance of the one-pass loss kernel after the other (and the general way for a column that no instance holds):
+    odd vocabularies, tiles that are no multiple of a vector, labels at both ends of a tile and outside the vocabulary."""
+    capi, tiled = mods
+    r = np.random.default_rng(N_v)
+    N_s, N_b = 5, 3
+    X = quant(2.0 * r.standard_normal((N_v, N_s, N_b)), dtype)
+    lab = r.integers(0, N_v, (N_s, N_b))
+    lab[0, 0], lab[1, 0], lab[2, 0], lab[3, 0] = 0, N_v - 1, min(tile_v, N_v) - 1, min(tile_v, N_v - 1)
+    _, losses, dX = D.cross_entropy(X, lab)
+    lab[4, 2] = N_v                                      # no label: no loss, the column keeps its probabilities
+    losses[4, 2] = 0.0
+    dX[:, 4, 2] = np.exp(X[:, 4, 2] - X[:, 4, 2].max())
+    dX[:, 4, 2] /= dX[:, 4, 2].sum()
+    with tiled.Context(n_streams=2) as ctx:
+        tX = T(tiled, ctx, X, (tile_v, 2, 2), dtype)
+        tS = tiled.TiledTensor(ctx, "f32", (2, N_s, N_b), (2, 2, 2))
+        dl, col, tot = dev_i32(lab), torch.empty(N_s * N_b, device="cuda"), torch.empty(1, device="cuda")
+        capi.nnt_cross_entropy(ctx.h, tX.h, dl.data_ptr(), tS.h, col.data_ptr(), tot.data_ptr())
+        ctx.wait()
+        check(tX.download(), dX, dtype, "dL/dlogits")
+        stats = tS.download()
+        check(stats[0], X.max(axis=0), "f32", "column maxima")
+        check(stats[1], np.exp(X - X.max(axis=0)).sum(axis=0), "f32", "column sums")
+        assert np.abs(col.cpu().numpy().reshape(N_b, N_s).T - losses).max() <= TOL["f32"] * np.abs(losses).max()
+        assert abs(tot.item() - losses.sum()) <= TOL["f32"] * abs(losses.sum())
