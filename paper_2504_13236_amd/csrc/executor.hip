@@ -123,7 +123,8 @@ struct TaskPlan {
 // per stream is enough because a stream runs its tasks in order.
 // `ns` streams may take the task; dependencies are looked for on all `ns_all` streams of the context (while a
 // capture is open fewer streams take tasks than exist).
-static TaskPlan plan_task(const std::vector<Access>& acc, int ns, int ns_all, bool serial, const uint64_t* tail_seq,
+// `small`: the task is over before it could be started on another stream (see submit).
+static TaskPlan plan_task(const std::vector<Access>& acc, int ns, int ns_all, bool serial, bool small, const uint64_t* tail_seq,
                           const uint64_t* synced_seq, uint64_t (*waited)[kMaxStreams], int* rr) {
     uint64_t need[kMaxStreams] = {0, 0, 0, 0, 0, 0, 0, 0};
     for (const Access& a : acc) {
@@ -151,9 +152,14 @@ static TaskPlan plan_task(const std::vector<Access>& acc, int ns, int ns_all, bo
         uint64_t best = 0;
         for (int s = 0; s < ns; s++)
             if (need[s] && need[s] == tail_seq[s] && need[s] >= best) { best = need[s]; chosen = s; }
+        // a small task stays on a stream that it depends on, the one with most behind it (the turn passes all the same, so that a
+        // flow that repeats finds its long tasks on the streams where it left them and waits for none of them)
         if (chosen < 0) {
             *rr = (*rr + 1) % ns;
             chosen = *rr;
+            uint64_t most = 0;
+            for (int s = 0; small && s < ns; s++)
+                if (need[s] && tail_seq[s] - synced_seq[s] > most) { most = tail_seq[s] - synced_seq[s]; chosen = s; }
         }
     }
     plan.chosen = chosen;
@@ -196,7 +202,14 @@ int32_t submit(nnt_ctx* ctx, const std::vector<Access>& acc,
     // While a capture is open only streams 0 and 1 take tasks: ending a capture in which two forked
     // streams wait on each other's events has crashed inside the HIP runtime on this ROCm release.
     const int ns = ctx->capturing ? std::min(ctx->n_streams, 2) : ctx->n_streams;
-    const TaskPlan plan = plan_task(acc, ns, ctx->n_streams, ctx->serial, ctx->tail_seq, ctx->synced_seq, ctx->waited, &ctx->rr);
+    // Taking a task to another stream costs the host an event and a wait, some 15 us, and the device a few; it pays only
+    // for tasks that run longer than that.  4 us at the rates of large operations (100 TFLOP/s, 4 TB/s) are 10 us and more for one this size (a threshold
+    // of 10 us serialised the bias gradients of a GPT-2-small block behind its products: 3745 -> 3800 us; without
+    // any, layer norm of few tokens, forward and backward, took 37 us instead of 26, the smallest block 327 instead of 316).  Operations that do not say what
+    // they do count as long.
+    constexpr double kSpreadSeconds = 4e-6;
+    const bool small = ctx->cur_label && ctx->cur_seconds < kSpreadSeconds;
+    const TaskPlan plan = plan_task(acc, ns, ctx->n_streams, ctx->serial, small, ctx->tail_seq, ctx->synced_seq, ctx->waited, &ctx->rr);
     const int chosen = plan.chosen;
     hipStream_t st = ctx->streams[chosen];
     for (int s = 0; s < ctx->n_streams; s++) {
@@ -313,7 +326,7 @@ int32_t nnt_sched_simulate(int32_t n_streams, int32_t serial, int32_t n_tiles, i
                 return NNT_EINVAL;
             acc.push_back(Access{&tiles[(size_t)acc_tile[i]], 1, mode, part});
         }
-        const TaskPlan plan = plan_task(acc, n_streams, n_streams, serial != 0, tail, synced, waited, &rr);
+        const TaskPlan plan = plan_task(acc, n_streams, n_streams, serial != 0, false, tail, synced, waited, &rr);
         // the waits as the executor would issue them: on the first recorded event that covers the
         // task asked for, else on a new one at the tail of that stream
         for (int s = 0; s < kMaxStreams; s++) {

@@ -143,7 +143,8 @@ struct nnt_ctx {
     // how much algorithmic work it stands for; the first task of the operation carries it
     bool profiling = false;
     const char* cur_label = nullptr;
-    double cur_work = 0.0;
+    double cur_work = 0.0;           // still to be counted by the profile
+    double cur_seconds = 0.0;        // what the whole operation takes at the rate of large ones
     bool cur_work_is_bytes = false;
     struct ProfileRec { std::string label; hipEvent_t start, stop; double work; bool bytes; int launches; };
     std::vector<ProfileRec> profile;
@@ -158,6 +159,7 @@ struct OpTag {
     OpTag(nnt_ctx* ctx, const char* label, double work, bool bytes) : c(ctx) {
         c->cur_label = label;
         c->cur_work = work;
+        c->cur_seconds = work / (bytes ? 4e12 : 100e12);
         c->cur_work_is_bytes = bytes;
     }
     ~OpTag() { c->cur_label = nullptr; c->cur_work = 0.0; }
