@@ -33,6 +33,8 @@ namespace {
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 
 constexpr int kWgRows = 128;   // rows owned by a workgroup
+constexpr int kSplitMax = 512; // workgroups of 128 rows up to which the split form is taken
+constexpr int kHalfRows = 64;  // ... in the form that splits the streamed blocks between two pairs of waves (SPLIT below)
 constexpr int kBlk = 64;       // rows streamed per iteration
 constexpr float kLog2e = 1.4426950408889634f;
 constexpr float kNegInf = -__builtin_huge_valf();
@@ -47,6 +49,7 @@ struct AttnGeom {
     int tile0;           // first sequence tile this launch covers
     int causal;
     float scale;
+    int split;           // workgroups of 64 rows whose waves share the streamed blocks (see attn_fwd)
     // Operands that are windows on tensors [parts * N_h * H, N_s, N_b] with the heads side by side along the first
     // axis (win = 1; the statistics stay an ordinary tensor, to which bh and gh then belong): `pitch` elements
     // between the rows of consecutive positions (H otherwise), `hp` heads per row tile.
@@ -317,28 +320,42 @@ struct FwdArgs {
     Win wQ, wK, wV, wO;
 };
 
+// SPLIT (all three kernels): the workgroup owns 64 rows; waves 0 and 1 take the first 32 rows of every streamed block, waves 2
+// and 3 the second 32, and their partial results meet in LDS at the end.  For launches of few workgroups: a wave that
+// owns 32 rows and walks all blocks by itself takes the same time however empty the chip is (fp32, 1024 keys: 16 blocks of
+// 3.4 us of matrix instructions), so more and shorter waves are what helps.
+
+// Registers of waves 2 and 3 to the waves of the same rows: `n` values per lane through LDS.
+template <int N, typename F>
+__device__ __forceinline__ void give(float* buf, int w, int lane, F&& value) {
+#pragma unroll
+    for (int i = 0; i < N; i++) buf[((w & 1) * N + i) * 64 + lane] = value(i);
+}
+
 // ---------------------------------------------------------------- forward
-template <class X>
+template <class X, bool SPLIT>
 __global__ void __launch_bounds__(256, 2) attn_fwd(const FwdArgs a) {
     using T = typename X::T;
     constexpr int H = X::H, LDK = X::LD, LDV = X::LD_COLS;
     constexpr int kBufElems = kBlk * LDK + kBlk * LDV;
     __shared__ __attribute__((aligned(16))) T lds[2][kBufElems];
     const AttnGeom& g = a.g;
+    constexpr int kRows = SPLIT ? kHalfRows : kWgRows;
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, hh = lane >> 5, ln = lane & 31;
+    const int wr = SPLIT ? w & 1 : w, own_sub = __builtin_amdgcn_readfirstlane(w >> 1);
     // under the causal mask the later a query block, the more key blocks it walks: the longest go first
     const int rblk = g.causal ? gridDim.y - 1 - blockIdx.y : blockIdx.y;
-    const int l = g.tile0 + rblk / g.nblk, e0 = (rblk % g.nblk) * kWgRows;
+    const int l = g.tile0 + rblk / g.nblk, e0 = (rblk % g.nblk) * kRows;
     const int b = blockIdx.x % g.Nb, j = blockIdx.x / g.Nb;
     const Pair pr = pair_of(g, b, j);
     const Slab sq = slab_of(g, pr, l);
     if (e0 >= sq.ext) return;
-    const int eq = e0 + 32 * w + ln;
+    const int eq = e0 + 32 * wr + ln;
     const bool qvalid = eq < sq.ext;
     const int qglob = l * g.bs + eq;
-    const int wave_qfirst = l * g.bs + e0 + 32 * w;
-    const int wave_qlast = l * g.bs + min(e0 + 32 * w + 31, sq.ext - 1);
-    const int wg_qlast = l * g.bs + min(e0 + kWgRows - 1, sq.ext - 1);
+    const int wave_qfirst = l * g.bs + e0 + 32 * wr;
+    const int wave_qlast = l * g.bs + min(e0 + 32 * wr + 31, sq.ext - 1);
+    const int wg_qlast = l * g.bs + min(e0 + kRows - 1, sq.ext - 1);
     const float sc2 = g.scale * kLog2e;        // scores are kept in units of log 2
 
     typename X::Own qf;
@@ -372,7 +389,45 @@ __global__ void __launch_bounds__(256, 2) attn_fwd(const FwdArgs a) {
         const int lk = it / g.nstep, kloc0 = (it % g.nstep) * kBlk;
         const int ext_k = min(g.bs, g.Ns - lk * g.bs);
         const int kglob0 = lk * g.bs + kloc0;
-        if (!(g.causal && kglob0 > wave_qlast)) {
+        if constexpr (SPLIT) {
+            const int kb = kloc0 + 32 * own_sub, kg = kglob0 + 32 * own_sub;
+            if (kb < ext_k && !(g.causal && kg > wave_qlast)) {
+                const T* Ks = lds[it & 1];
+                const T* Vs = Ks + kBlk * LDK;
+                f32x16 s = X::template rows_times_own<LDK>(Ks, own_sub, ln, hh, qf);
+                float mx = kNegInf;
+                if (!(kb + 32 <= ext_k && (!g.causal || kg + 31 <= wave_qfirst))) {
+                    int lim = ext_k - kb;
+                    if (g.causal) lim = min(lim, qglob - kg + 1);
+                    const int lim_h = lim - 4 * hh;
+#pragma unroll
+                    for (int r = 0; r < 16; r++) s[r] = acc_row0(r) < lim_h ? s[r] : kNegInf;
+                }
+#pragma unroll
+                for (int r = 0; r < 16; r++) mx = fmaxf(mx, s[r]);
+                mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
+                const float m_new = fmaxf(m, mx);
+                const float shift = m_new == kNegInf ? 0.f : m_new * sc2;
+                const float alpha = m == m_new ? 1.f : __builtin_amdgcn_exp2f(m * sc2 - shift);
+                m = m_new;
+                float rowsum = 0.f;
+#pragma unroll
+                for (int r = 0; r < 16; r++) {
+                    s[r] = __builtin_amdgcn_exp2f(fmaf(s[r], sc2, -shift));
+                    rowsum += s[r];
+                }
+                lsum = lsum * alpha + rowsum;
+                if (__any(alpha != 1.f)) {
+#pragma unroll
+                    for (int rb = 0; rb < H / 32; rb++)
+#pragma unroll
+                        for (int r = 0; r < 16; r++) O[rb][r] *= alpha;
+                }
+                typename X::Packed pk;
+                X::pack(s, pk);
+                X::template cols_times_acc<LDV>(O, Vs, own_sub, lane, pk);
+            }
+        } else if (!(g.causal && kglob0 > wave_qlast)) {
             const T* Ks = lds[it & 1];
             const T* Vs = Ks + kBlk * LDK;
             // the second half of the block may be hidden from all of this wave's queries
@@ -433,6 +488,24 @@ __global__ void __launch_bounds__(256, 2) attn_fwd(const FwdArgs a) {
         if (it + 1 < nit) stash((it + 1) & 1);
         __syncthreads();
     }
+    if constexpr (SPLIT) {
+        // two partial results per row: rescaled to the larger maximum (a wave that saw no visible key has -inf: factor 0)
+        constexpr int N = H / 2 + 2;
+        static_assert(2 * N * 64 * 4 <= sizeof(lds), "the exchange must fit the staging buffers");
+        float* buf = reinterpret_cast<float*>(&lds[0][0]);
+        if (w >= 2) give<N>(buf, w, lane, [&](int i) { return i < H / 2 ? O[i / 16][i % 16] : i == H / 2 ? m : lsum; });
+        __syncthreads();
+        if (w >= 2) return;
+        auto got = [&](int i) { return buf[(w * N + i) * 64 + lane]; };
+        const float m2 = got(H / 2), m_new = fmaxf(m, m2);
+        const float a1 = m == kNegInf ? 0.f : __builtin_amdgcn_exp2f((m - m_new) * sc2), a2 = m2 == kNegInf ? 0.f : __builtin_amdgcn_exp2f((m2 - m_new) * sc2);
+        lsum = lsum * a1 + got(H / 2 + 1) * a2;
+        m = m_new;
+#pragma unroll
+        for (int rb = 0; rb < H / 32; rb++)
+#pragma unroll
+            for (int r = 0; r < 16; r++) O[rb][r] = O[rb][r] * a1 + got(16 * rb + r) * a2;
+    }
     lsum += __shfl_xor(lsum, 32, 64);
     store_own_row<X>(rows_win<T>(a.O, g, a.wO, pr, sq, b, j), g.pitch, eq, hh, qvalid, 1.f / lsum, O);
     if (qvalid && hh == 0) {
@@ -451,25 +524,27 @@ struct BwdArgs {
 };
 
 // ---------------------------------------------------------------- dQ (also writes aux)
-template <class X>
+template <class X, bool SPLIT>
 __global__ void __launch_bounds__(256, 2) attn_dq(const BwdArgs a) {
     using T = typename X::T;
     constexpr int H = X::H, LD = X::LD;
     __shared__ __attribute__((aligned(16))) T lds[2][2 * kBlk * LD];
     const AttnGeom& g = a.g;
+    constexpr int kRows = SPLIT ? kHalfRows : kWgRows;
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, hh = lane >> 5, ln = lane & 31;
+    const int wr = SPLIT ? w & 1 : w, own_sub = __builtin_amdgcn_readfirstlane(w >> 1);
     const int rblk = g.causal ? gridDim.y - 1 - blockIdx.y : blockIdx.y;
-    const int l = g.tile0 + rblk / g.nblk, e0 = (rblk % g.nblk) * kWgRows;
+    const int l = g.tile0 + rblk / g.nblk, e0 = (rblk % g.nblk) * kRows;
     const int b = blockIdx.x % g.Nb, j = blockIdx.x / g.Nb;
     const Pair pr = pair_of(g, b, j);
     const Slab sq = slab_of(g, pr, l);
     if (e0 >= sq.ext) return;
-    const int eq = e0 + 32 * w + ln;
+    const int eq = e0 + 32 * wr + ln;
     const bool qvalid = eq < sq.ext;
     const int qglob = l * g.bs + eq;
-    const int wave_qfirst = l * g.bs + e0 + 32 * w;
-    const int wave_qlast = l * g.bs + min(e0 + 32 * w + 31, sq.ext - 1);
-    const int wg_qlast = l * g.bs + min(e0 + kWgRows - 1, sq.ext - 1);
+    const int wave_qfirst = l * g.bs + e0 + 32 * wr;
+    const int wave_qlast = l * g.bs + min(e0 + 32 * wr + 31, sq.ext - 1);
+    const int wg_qlast = l * g.bs + min(e0 + kRows - 1, sq.ext - 1);
     const float sc2 = g.scale * kLog2e;
 
     typename X::Own qf, dof;
@@ -484,7 +559,7 @@ __global__ void __launch_bounds__(256, 2) attn_dq(const BwdArgs a) {
         if (qvalid) {
             const float* st = rows_of<const float>(a.stats, sq, 2) + 2 * (int64_t)eq;
             lse = st[0] * kLog2e + log2f(st[1]);
-            if (hh == 0) {
+            if (hh == 0 && (!SPLIT || w < 2)) {
                 float* ax = a.aux + 2 * ((int64_t)qglob + (int64_t)g.Ns * (b + (int64_t)g.Nb * j));
                 ax[0] = lse;
                 ax[1] = D;
@@ -530,7 +605,7 @@ __global__ void __launch_bounds__(256, 2) attn_dq(const BwdArgs a) {
             const int lim_h = lim - 4 * hh;
             // (two copies of the body: blocks that are visible as a whole skip the mask arithmetic)
             auto body = [&](auto masked) {
-                for (int sub = 0; sub < nsub; sub++) {
+                for (int sub = SPLIT ? own_sub : 0; sub < (SPLIT ? min(nsub, own_sub + 1) : nsub); sub++) {
                     f32x16 s = X::template rows_times_own<LD>(Ks, sub, ln, hh, qf);
                     const f32x16 dp = X::template rows_times_own<LD>(Vs, sub, ln, hh, dof);
 #pragma unroll
@@ -550,30 +625,44 @@ __global__ void __launch_bounds__(256, 2) attn_dq(const BwdArgs a) {
         if (it + 1 < nit) stash((it + 1) & 1);
         __syncthreads();
     }
+    if constexpr (SPLIT) {
+        constexpr int N = H / 2;
+        static_assert(2 * N * 64 * 4 <= sizeof(lds), "the exchange must fit the staging buffers");
+        float* buf = reinterpret_cast<float*>(&lds[0][0]);
+        if (w >= 2) give<N>(buf, w, lane, [&](int i) { return dQ[i / 16][i % 16]; });
+        __syncthreads();
+        if (w >= 2) return;
+#pragma unroll
+        for (int rb = 0; rb < H / 32; rb++)
+#pragma unroll
+            for (int r = 0; r < 16; r++) dQ[rb][r] += buf[(w * N + 16 * rb + r) * 64 + lane];
+    }
     store_own_row<X>(rows_win<T>(a.dQ, g, a.wdQ, pr, sq, b, j), g.pitch, eq, hh, qvalid, g.scale, dQ);
 }
 
 // ---------------------------------------------------------------- dK and dV (reads aux)
 // (bf16 with head size 128 needs more than 256 registers per lane for its four accumulator sets and two
 // fragment sets: compiled for one workgroup per CU it keeps them all, for two it spills and runs 3x slower)
-template <class X>
+template <class X, bool SPLIT>
 __global__ void __launch_bounds__(256, X::kDkvBlocks) attn_dkv(const BwdArgs a) {
     using T = typename X::T;
     constexpr int H = X::H, LD = X::LD;
     constexpr int kAuxElems = 2 * kBlk * (int)(sizeof(float) / sizeof(T));   // 2 x 64 floats, in units of T
     __shared__ __attribute__((aligned(16))) T lds[2][2 * kBlk * LD + kAuxElems];
     const AttnGeom& g = a.g;
+    constexpr int kRows = SPLIT ? kHalfRows : kWgRows;
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, hh = lane >> 5, ln = lane & 31;
+    const int wr = SPLIT ? w & 1 : w, own_sub = __builtin_amdgcn_readfirstlane(w >> 1);
     // (under the causal mask the earliest key blocks meet the most query blocks: already first)
-    const int l = g.tile0 + blockIdx.y / g.nblk, e0 = (blockIdx.y % g.nblk) * kWgRows;
+    const int l = g.tile0 + blockIdx.y / g.nblk, e0 = (blockIdx.y % g.nblk) * kRows;
     const int b = blockIdx.x % g.Nb, j = blockIdx.x / g.Nb;
     const Pair pr = pair_of(g, b, j);
     const Slab sk = slab_of(g, pr, l);
     if (e0 >= sk.ext) return;
-    const int ek = e0 + 32 * w + ln;
+    const int ek = e0 + 32 * wr + ln;
     const bool kvalid = ek < sk.ext;
     const int kglob = l * g.bs + ek;
-    const int wave_kfirst = l * g.bs + e0 + 32 * w;
+    const int wave_kfirst = l * g.bs + e0 + 32 * wr;
     const int wave_klast = wave_kfirst + 31;
     const float sc2 = g.scale * kLog2e;
 
@@ -635,7 +724,7 @@ __global__ void __launch_bounds__(256, X::kDkvBlocks) attn_dkv(const BwdArgs a) 
             const unsigned width = (unsigned)max(hi - lo, 0);
             // (not unrolled: the second pass would keep a second set of temporaries alive and spill)
 #pragma unroll 1
-            for (int sub = sub0; sub < nsub; sub++) {
+            for (int sub = SPLIT ? max(sub0, own_sub) : sub0; sub < (SPLIT ? min(nsub, own_sub + 1) : nsub); sub++) {
                 f32x16 s = X::template rows_times_own<LD>(Qs, sub, ln, hh, kf);
                 const f32x16 dp = X::template rows_times_own<LD>(Ds, sub, ln, hh, vf);
                 // log-sum-exp and D of the 16 queries this lane's accumulator registers stand for: four runs of four
@@ -665,6 +754,21 @@ __global__ void __launch_bounds__(256, X::kDkvBlocks) attn_dkv(const BwdArgs a) 
         if (it + 1 < nit) stash((it + 1) & 1);
         __syncthreads();
     }
+    if constexpr (SPLIT) {
+        constexpr int N = H;
+        static_assert(2 * N * 64 * 4 <= sizeof(lds), "the exchange must fit the staging buffers");
+        float* buf = reinterpret_cast<float*>(&lds[0][0]);
+        if (w >= 2) give<N>(buf, w, lane, [&](int i) { return i < H / 2 ? dK[i / 16][i % 16] : dV[(i - H / 2) / 16][i % 16]; });
+        __syncthreads();
+        if (w >= 2) return;
+#pragma unroll
+        for (int rb = 0; rb < H / 32; rb++)
+#pragma unroll
+            for (int r = 0; r < 16; r++) {
+                dK[rb][r] += buf[(w * N + 16 * rb + r) * 64 + lane];
+                dV[rb][r] += buf[(w * N + H / 2 + 16 * rb + r) * 64 + lane];
+            }
+    }
     store_own_row<X>(rows_win<T>(a.dK, g, a.wdK, pr, sk, b, j), g.pitch, ek, hh, kvalid, g.scale, dK);
     store_own_row<X>(rows_win<T>(a.dV, g, a.wdV, pr, sk, b, j), g.pitch, ek, hh, kvalid, 1.f, dV);
 }
@@ -672,18 +776,21 @@ __global__ void __launch_bounds__(256, X::kDkvBlocks) attn_dkv(const BwdArgs a) 
 using FwdKernel = void (*)(const FwdArgs);
 using BwdKernel = void (*)(const BwdArgs);
 
-FwdKernel fwd_kernel(int dtype, int H) {
-    if (dtype == NNT_F32) return H == 64 ? attn_fwd<F32Traits<64>> : attn_fwd<F32Traits<128>>;
-    return H == 64 ? attn_fwd<Bf16Traits<64>> : attn_fwd<Bf16Traits<128>>;
+template <bool SPLIT> FwdKernel fwd_kernel_of(int dtype, int H) {
+    if (dtype == NNT_F32) return H == 64 ? attn_fwd<F32Traits<64>, SPLIT> : attn_fwd<F32Traits<128>, SPLIT>;
+    return H == 64 ? attn_fwd<Bf16Traits<64>, SPLIT> : attn_fwd<Bf16Traits<128>, SPLIT>;
 }
-BwdKernel dq_kernel(int dtype, int H) {
-    if (dtype == NNT_F32) return H == 64 ? attn_dq<F32Traits<64>> : attn_dq<F32Traits<128>>;
-    return H == 64 ? attn_dq<Bf16Traits<64>> : attn_dq<Bf16Traits<128>>;
+template <bool SPLIT> BwdKernel dq_kernel_of(int dtype, int H) {
+    if (dtype == NNT_F32) return H == 64 ? attn_dq<F32Traits<64>, SPLIT> : attn_dq<F32Traits<128>, SPLIT>;
+    return H == 64 ? attn_dq<Bf16Traits<64>, SPLIT> : attn_dq<Bf16Traits<128>, SPLIT>;
 }
-BwdKernel dkv_kernel(int dtype, int H) {
-    if (dtype == NNT_F32) return H == 64 ? attn_dkv<F32Traits<64>> : attn_dkv<F32Traits<128>>;
-    return H == 64 ? attn_dkv<Bf16Traits<64>> : attn_dkv<Bf16Traits<128>>;
+template <bool SPLIT> BwdKernel dkv_kernel_of(int dtype, int H) {
+    if (dtype == NNT_F32) return H == 64 ? attn_dkv<F32Traits<64>, SPLIT> : attn_dkv<F32Traits<128>, SPLIT>;
+    return H == 64 ? attn_dkv<Bf16Traits<64>, SPLIT> : attn_dkv<Bf16Traits<128>, SPLIT>;
 }
+FwdKernel fwd_kernel(int dtype, const AttnGeom& g) { return g.split ? fwd_kernel_of<true>(dtype, g.H) : fwd_kernel_of<false>(dtype, g.H); }
+BwdKernel dq_kernel(int dtype, const AttnGeom& g) { return g.split ? dq_kernel_of<true>(dtype, g.H) : dq_kernel_of<false>(dtype, g.H); }
+BwdKernel dkv_kernel(int dtype, const AttnGeom& g) { return g.split ? dkv_kernel_of<true>(dtype, g.H) : dkv_kernel_of<false>(dtype, g.H); }
 
 }  // namespace
 }  // namespace nnt
@@ -721,12 +828,21 @@ int32_t check_attn(nnt_ctx* ctx, const char* who, std::initializer_list<const nn
     return NNT_OK;
 }
 
+// Rows per workgroup: 64, with the waves sharing the streamed blocks, where workgroups of 128 would be at most kSplitMax, two for every
+// compute unit: fp32, 36 pairs of 1000 positions (288 workgroups), forward and backward 378 -> 284 us; 24 pairs of 1024
+// (192) 367 -> 290 us.  Above that the chip is full either way, and 128 rows read every streamed block half as often.
+void choose_rows(AttnGeom* g) {
+    g->nblk = (g->bs + kWgRows - 1) / kWgRows;
+    g->split = (int64_t)g->Nb * g->Nh * g->gs * g->nblk <= kSplitMax;
+    if (g->split) g->nblk = (g->bs + kHalfRows - 1) / kHalfRows;
+}
+
 AttnGeom geom_of(const nnt_tensor* q, float scale, int causal) {
     AttnGeom g;
     g.H = (int)q->shape[0]; g.Ns = (int)q->shape[1]; g.Nb = (int)q->shape[2]; g.Nh = (int)q->shape[3];
     g.bs = (int)q->base[1]; g.bb = (int)q->base[2]; g.bh = (int)q->base[3];
     g.gs = (int)q->grid[1]; g.gb = (int)q->grid[2]; g.gh = (int)q->grid[3];
-    g.nblk = (g.bs + kWgRows - 1) / kWgRows;
+    choose_rows(&g);
     g.nstep = (g.bs + kBlk - 1) / kBlk;
     g.tile0 = 0;
     g.causal = causal;
@@ -770,7 +886,7 @@ int32_t geom_of_windows(nnt_ctx* ctx, const char* who, std::initializer_list<std
     g.H = (int)H; g.Ns = (int)first->shape[1]; g.Nb = (int)first->shape[2]; g.Nh = N_h;
     g.bs = (int)first->base[1]; g.bb = (int)first->base[2]; g.bh = (int)stats->base[3];
     g.gs = (int)first->grid[1]; g.gb = (int)first->grid[2]; g.gh = (int)stats->grid[3];
-    g.nblk = (g.bs + kWgRows - 1) / kWgRows;
+    choose_rows(&g);
     g.nstep = (g.bs + kBlk - 1) / kBlk;
     g.tile0 = 0;
     g.causal = causal;
@@ -806,7 +922,7 @@ int32_t nnt_attention_fwd(nnt_ctx* ctx, nnt_tensor* Q, nnt_tensor* K, nnt_tensor
     AttnGeom g = geom_of(Q, scale, causal);
     FwdArgs a{g, Q->d_tiles, K->d_tiles, V->d_tiles, B->d_tiles, stats->d_tiles};
     const double pair_flops = 4.0 * g.H * g.Nb * g.Nh;   // two products, 2 flops per multiply-add
-    const FwdKernel kernel = fwd_kernel(Q->dtype, g.H);
+    const FwdKernel kernel = fwd_kernel(Q->dtype, g);
     auto launch = [kernel](hipStream_t st, const FwdArgs& fa, int ntile) {
         const dim3 grid((unsigned)(fa.g.Nb * fa.g.Nh), (unsigned)(ntile * fa.g.nblk)), block(256);
         hipLaunchKernelGGL(kernel, grid, block, 0, st, fa);
@@ -848,7 +964,7 @@ int32_t nnt_attention_bwd(nnt_ctx* ctx, nnt_tensor* Q, nnt_tensor* K, nnt_tensor
     const double pair_flops = 2.0 * g.H * g.Nb * g.Nh;   // per product
     const double pairs = visible_pairs(g.Ns, 0, g.Ns, causal);
     const Access scr{&ctx->red_dep, 1, kReadWrite};
-    const BwdKernel k_dq = dq_kernel(Q->dtype, g.H), k_dkv = dkv_kernel(Q->dtype, g.H);
+    const BwdKernel k_dq = dq_kernel(Q->dtype, g), k_dkv = dkv_kernel(Q->dtype, g);
     // one task, two launches: the dQ kernel leaves log-sum-exp and D per query for the dK/dV kernel
     OpTag tag(ctx, "attention_bwd_dq", 3.0 * pair_flops * pairs, false);
     return submit(ctx, {Q->all(kRead), K->all(kRead), V->all(kRead), B->all(kRead), stats->all(kRead), dB->all(kRead),
@@ -872,7 +988,7 @@ int32_t nnt_attention_fwd_heads(nnt_ctx* ctx, nnt_tensor* QKV, float scale, int3
     FwdArgs a{g, QKV->d_tiles, QKV->d_tiles, QKV->d_tiles, Bm->d_tiles, stats->d_tiles,
               window_at(QKV, 0, N_e), window_at(QKV, 1, N_e), window_at(QKV, 2, N_e), window_at(Bm, 0, N_e)};
     const double pair_flops = 4.0 * g.H * g.Nb * g.Nh;
-    const FwdKernel kernel = fwd_kernel(QKV->dtype, g.H);
+    const FwdKernel kernel = fwd_kernel(QKV->dtype, g);
     OpTag tag(ctx, "attention_fwd", pair_flops * visible_pairs(g.Ns, 0, g.Ns, causal), false);
     return submit(ctx, {QKV->all(kRead), Bm->all(kWrite), stats->all(kWrite)}, [=](hipStream_t st) {
         const dim3 grid((unsigned)(a.g.Nb * a.g.Nh), (unsigned)(a.g.gs * a.g.nblk)), block(256);
@@ -897,7 +1013,7 @@ int32_t nnt_attention_bwd_heads(nnt_ctx* ctx, nnt_tensor* QKV, nnt_tensor* Bm, n
     const double pair_flops = 2.0 * g.H * g.Nb * g.Nh;
     const double pairs = visible_pairs(g.Ns, 0, g.Ns, causal);
     const Access scr{&ctx->red_dep, 1, kReadWrite};
-    const BwdKernel k_dq = dq_kernel(QKV->dtype, g.H), k_dkv = dkv_kernel(QKV->dtype, g.H);
+    const BwdKernel k_dq = dq_kernel(QKV->dtype, g), k_dkv = dkv_kernel(QKV->dtype, g);
     OpTag tag(ctx, "attention_bwd_dq", 3.0 * pair_flops * pairs, false);
     return submit(ctx, {QKV->all(kRead), Bm->all(kRead), stats->all(kRead), dBm->all(kRead), dQKV->all(kWrite), scr},
                   [=](hipStream_t st) {

@@ -167,3 +167,29 @@ def test_fused_attention_rejects_bad_operands(mods):
         out = tiled.TiledTensor(ctx, "f32", (64, 32, 1, 1), (64, 32, 1, 1))
         capi.nnt_attention_fwd(ctx.h, q.h, q.h, q.h, 0.125, 1, out.h, s.h)
         ctx.wait()
+
+
+@pytest.mark.parametrize("causal", [1, 0])
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("h,N_s,N_b,N_h", [(64, 150, 20, 16), (128, 150, 20, 16), (64, 97, 16, 16)])
+def test_fused_attention_on_both_sides_of_the_row_split(mods, h, N_s, N_b, N_h, dtype, causal):
+    """Launches of more than 512 workgroups of 128 rows (the first two cases: 320 pairs, two row blocks each) take the kernels whose
+    waves own their rows alone, smaller ones (all cases above, and 256 pairs x 2 here) those whose waves share them."""
+    capi, tiled = mods
+    r = np.random.default_rng(h + N_s)
+    shape, base = (h, N_s, N_b, N_h), (h, 96, N_b, N_h)
+    Q, K, V, dB = (quant(r.standard_normal(shape), dtype) for _ in range(4))
+    scale = 1.0 / math.sqrt(h)
+    B, tmax, den, dQ, dK, dV = reference(Q, K, V, dB, bool(causal))
+    with tiled.Context(n_streams=2) as ctx:
+        tQ, tK, tV, tdB = (T(tiled, ctx, x, base, dtype) for x in (Q, K, V, dB))
+        tB, tdQ, tdK, tdV = (tiled.TiledTensor(ctx, dtype, shape, base) for _ in range(4))
+        tS = tiled.TiledTensor(ctx, "f32", (2, N_s, N_b, N_h), (2, 96, N_b, N_h))
+        capi.nnt_attention_fwd(ctx.h, tQ.h, tK.h, tV.h, scale, causal, tB.h, tS.h)
+        capi.nnt_attention_bwd(ctx.h, tQ.h, tK.h, tV.h, tB.h, tS.h, tdB.h, scale, causal, tdQ.h, tdK.h, tdV.h)
+        check(tB.download(), B, dtype, "attention fwd")
+        stats = tS.download()
+        check(stats[0], tmax, "f32", "running maximum")
+        check(stats[1], den, "f32", "sum of shifted exponentials")
+        for t, ref, what in ((tdQ, dQ, "dQ"), (tdK, dK, "dK"), (tdV, dV, "dV")):
+            check(t.download(), ref, dtype, "attention " + what)
