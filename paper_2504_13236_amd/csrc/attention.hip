@@ -16,7 +16,7 @@
 // Work split.  A workgroup owns 128 rows of one sequence tile (queries in the
 // forward and dQ kernels, keys in the dK/dV kernel), 32 per wavefront, and streams
 // blocks of 64 rows of the other kind through LDS, double-buffered, one barrier per
-// block.  Every product is a chain of 32x32 matrix instructions whose B operand sits
+// block.  (Launches of few workgroups: 64 rows, see attn_fwd.)  Every product is a chain of 32x32 matrix instructions whose B operand sits
 // in registers (the wavefront's own rows, or the probabilities it has just computed:
 // the accumulator layout of a 32x32 result, lane = column, is the B layout of the
 // next product) and whose A operand is read from LDS.  Rows beyond a tile's extent
