@@ -830,7 +830,7 @@ int32_t check_attn(nnt_ctx* ctx, const char* who, std::initializer_list<const nn
 
 // Rows per workgroup: 64, with the waves sharing the streamed blocks, where workgroups of 128 would be at most kSplitMax, two for every
 // compute unit: fp32, 36 pairs of 1000 positions (288 workgroups), forward and backward 378 -> 284 us; 24 pairs of 1024
-// (192) 367 -> 290 us.  Above that the chip is full either way, and 128 rows read every streamed block half as often.
+// (192) 368 -> 269 us.  Above that the chip is full either way, and 128 rows read every streamed block half as often.
 void choose_rows(AttnGeom* g) {
     g->nblk = (g->bs + kWgRows - 1) / kWgRows;
     g->split = (int64_t)g->Nb * g->Nh * g->gs * g->nblk <= kSplitMax;
