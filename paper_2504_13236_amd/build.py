@@ -38,6 +38,8 @@ FLAGS = [
 # targets it and the next full wait (registers_touched_in_flight): a copy or move the compiler
 # places there would read stale data just the same.
 IN_FLIGHT_SOURCES = ("gemm_bf16_dl.hip", "gemm_f32_dl.hip")
+# Sources with matrix instructions: their assembly is scanned for uses of a result before it is there.
+MATRIX_SOURCES = IN_FLIGHT_SOURCES + ("gemm_bf16.hip", "gemm_f32.hip", "attention.hip")
 
 
 def scratch_in_loops(asm_text: str) -> list:
@@ -117,6 +119,81 @@ def registers_touched_in_flight(asm_text: str) -> list:
     return hits
 
 
+# Wait states (instructions, an `s_nop n` counting as n + 1) that have to lie between a matrix instruction and another
+# kind of instruction that names its result: the hardware does not hold such an instruction back.  The numbers
+# are those that the compiler leaves in straight-line code.
+MATRIX_WAIT_STATES = {"v_mfma_f32_32x32x2_f32": 18, "v_mfma_f32_32x32x16_bf16": 12}
+_ANYREG = re.compile(r"\b([va])(\d+)\b|\b([va])\[(\d+):(\d+)\]")
+
+
+def _registers(text: str) -> set:
+    out = set()
+    for m in _ANYREG.finditer(text):
+        if m.group(1):
+            out.add((m.group(1), int(m.group(2))))
+        else:
+            out.update((m.group(3), r) for r in range(int(m.group(4)), int(m.group(5)) + 1))
+    return out
+
+
+def _kernels(asm_text: str) -> dict:
+    """{kernel: ([(line number, instruction, operands)], {label: index of the instruction behind it})}."""
+    out: dict = {}
+    code = labels = None
+    for no, line in enumerate(asm_text.splitlines(), 1):
+        t = line.split(";")[0].strip()
+        if t.endswith(":"):
+            if t.startswith("_Z"):
+                code, labels = out.setdefault(t[:-1], ([], {}))
+            elif t.startswith(".Lfunc_end"):
+                code = labels = None
+            elif labels is not None:
+                labels[t[:-1]] = len(code)
+        elif t and code is not None and not t.startswith("."):
+            op, _, rest = t.partition(" ") if " " in t else t.partition("\t")
+            code.append((no, op, rest.strip()))
+    return out
+
+
+def matrix_results_named_early(asm_text: str) -> list:
+    """[(kernel, line number, line of the matrix instruction, wait states between them)]: instructions of a device assembly
+    listing that name the result of a matrix instruction before it is there, on any path through the branches.
+
+    The compiler puts the wait states in itself, but counts them along one of the paths that meet in a block, which need
+    not be the shortest.  Another matrix instruction with the same result is no such use: it is held back by the hardware,
+    and what comes after it is looked at from there."""
+    hits = set()
+    for kernel, (code, labels) in _kernels(asm_text).items():
+        for first, (no, op, rest) in enumerate(code):
+            if not op.startswith(("v_mfma", "v_smfma")):
+                continue
+            if op not in MATRIX_WAIT_STATES:
+                raise RuntimeError("%s: the wait states behind %s are not on record" % (kernel, op))
+            result, best = _registers(rest.split(",")[0]), {}
+            todo = [(first + 1, 0)]
+            while todo:
+                i, waited = todo.pop()
+                while i < len(code) and waited < min(MATRIX_WAIT_STATES[op], best.get(i, 1 << 30)):
+                    best[i] = waited
+                    at, name, args = code[i]
+                    if name.startswith("v_mfma"):
+                        parts = args.split(",")
+                        if _registers(parts[1] + "," + parts[2]) & result:
+                            hits.add((kernel, at, no, waited))
+                        if _registers(parts[0]) & result:
+                            break
+                    elif _registers(args) & result:
+                        hits.add((kernel, at, no, waited))
+                        break
+                    if name == "s_endpgm" or name.startswith("s_setpc"):
+                        break
+                    waited += int(args, 0) + 1 if name == "s_nop" else 1
+                    if name.startswith("s_cbranch"):
+                        todo.append((labels[args], waited))
+                    i = labels[args] if name == "s_branch" else i + 1
+    return sorted(hits)
+
+
 _NAME = re.compile(r"remark: Function Name: (\S+)")
 _FIELD = re.compile(r"remark:\s+(TotalSGPRs|VGPRs|AGPRs|ScratchSize \[bytes/lane\]|Occupancy \[waves/SIMD\]"
                     r"|VGPRs Spill|LDS Size \[bytes/block\]): (\d+)")
@@ -148,25 +225,29 @@ def _compile(src: str, only_if_stale: bool = False) -> str:
     if only_if_stale and os.path.exists(obj) and os.path.getmtime(obj) > max(os.path.getmtime(src), _newest_header(),
                                                                               os.path.getmtime(__file__)):
         return obj
-    in_flight = os.path.basename(src) in IN_FLIGHT_SOURCES
-    cmd = ["hipcc", *FLAGS, *(["-save-temps=obj"] if in_flight else []), "-c", src, "-o", obj]
+    name = os.path.basename(src)
+    cmd = ["hipcc", *FLAGS, *(["-save-temps=obj"] if name in MATRIX_SOURCES else []), "-c", src, "-o", obj]
     r = subprocess.run(cmd, capture_output=True, text=True)
     if r.returncode != 0:
         raise RuntimeError("hipcc failed for %s:\n%s" % (src, r.stderr[-4000:]))
     usage = resource_usage(r.stderr)
-    if in_flight:
-        stem = os.path.splitext(os.path.basename(src))[0]
-        with open(os.path.join(OBJ, stem + "-hip-amdgcn-amd-amdhsa-gfx950.s")) as f:
-            hits = scratch_in_loops(f.read())
+    if name in MATRIX_SOURCES:
+        with open(os.path.join(OBJ, os.path.splitext(name)[0] + "-hip-amdgcn-amd-amdhsa-gfx950.s")) as f:
+            asm = f.read()
+        named = matrix_results_named_early(asm)
+        if named:
+            raise RuntimeError("%s: %s, assembly line %d, names the result of the matrix instruction of line %d after %d wait states (%d such uses in all)"
+                               % (name, *named[0], len(named)))
+    if name in IN_FLIGHT_SOURCES:
+        hits = scratch_in_loops(asm)
         if hits:
             raise RuntimeError("%s: scratch access inside a loop of %s (assembly line %d, %d in all): "
                                "in-flight fragment registers do not survive a spill"
-                               % (os.path.basename(src), hits[0][0], hits[0][1], len(hits)))
-        with open(os.path.join(OBJ, stem + "-hip-amdgcn-amd-amdhsa-gfx950.s")) as f:
-            early = registers_touched_in_flight(f.read())
+                               % (name, hits[0][0], hits[0][1], len(hits)))
+        early = registers_touched_in_flight(asm)
         if early:
             raise RuntimeError("%s: %s, assembly line %d, uses %s before the wait for the LDS read of line %d (%d such uses in all)"
-                               % (os.path.basename(src), early[0][0], early[0][1], early[0][2], early[0][3], len(early)))
+                               % (name, early[0][0], early[0][1], early[0][2], early[0][3], len(early)))
     with open(obj + ".usage.json", "w") as f:
         json.dump(usage, f, indent=1, sort_keys=True)
     return obj

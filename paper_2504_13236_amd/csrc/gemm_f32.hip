@@ -34,6 +34,7 @@ __device__ __forceinline__ const T* uniform_ptr(const T* p) {
 }
 
 constexpr int BK = 16;
+constexpr int kSumSteps = 32;  // k-steps between two moves of the sums (512 k)
 constexpr int KP = BK + 4;   // padded k extent of a k-fast LDS row (conflict-free 128-bit reads)
 
 // Four floats at any address that a float may have: global memory takes 16-byte accesses at every multiple of 4 bytes,
@@ -145,8 +146,10 @@ __device__ __forceinline__ void lfrag(float (&f)[8], const float* l, int row, in
     }
 }
 
+// (two workgroups per compute unit asked for: within 256 registers the compiler keeps the matrix accumulators in vector
+// registers; otherwise it takes accumulation registers and copies them out and back in every k-step)
 template <bool AKF, bool BKF, int WAVES_M, int WAVES_N, int WMB, int WNB>
-__global__ void __launch_bounds__(256) gemm_f32_kernel(const GemmArgs g) {
+__global__ void __launch_bounds__(256, 2) gemm_f32_kernel(const GemmArgs g) {
     constexpr int BM = 32 * WMB * WAVES_M, BN = 32 * WNB * WAVES_N;
     constexpr int A_SZ = AKF ? BM * KP : BK * BM;
     constexpr int B_SZ = BKF ? BN * KP : BK * BN;
@@ -179,13 +182,8 @@ __global__ void __launch_bounds__(256) gemm_f32_kernel(const GemmArgs g) {
         bat_lo = bat - bat_hi * task.nb1;
     }
 
-    f32x16 acc[WNB][WMB], sum[WNB][WMB];
-#pragma unroll
-    for (int bn = 0; bn < WNB; bn++)
-#pragma unroll
-        for (int bm = 0; bm < WMB; bm++)
-#pragma unroll
-            for (int i = 0; i < 16; i++) acc[bn][bm][i] = sum[bn][bm][i] = 0.f;
+    f32x16 sum[WNB][WMB];
+    clear<WMB, WNB>(sum);
 
     if (task.nchunk > 0) {
         // Loop state that is the same for every lane is kept in scalar registers on purpose
@@ -232,44 +230,42 @@ __global__ void __launch_bounds__(256) gemm_f32_kernel(const GemmArgs g) {
         store_step(lds);
         __syncthreads();
         bool more = true;
-        for (int step = 1; more; step++) {
-            // advance to the next k-step (possibly the next chunk) and start its loads
-            k0 += BK;
-            if (k0 >= chk) {
-                c++;
-                k0 = 0;
-                if (c < task.nchunk) set_chunk(g.chunks[task.chunk0 + c]);
+        while (more) {
+            f32x16 acc[WNB][WMB];
+            clear<WMB, WNB>(acc);
+            for (int step = 0; more && step < kSumSteps; step++) {
+                // advance to the next k-step (possibly the next chunk) and start its loads
+                k0 += BK;
+                if (k0 >= chk) {
+                    c++;
+                    k0 = 0;
+                    if (c < task.nchunk) set_chunk(g.chunks[task.chunk0 + c]);
+                }
+                more = c < task.nchunk;
+                if (more) load_step();
+                const float* lA = lds + cur * (A_SZ + B_SZ);
+                const float* lB = lA + A_SZ;
+                float pf[WNB][8], qf[WMB][8];
+#pragma unroll
+                for (int bn = 0; bn < WNB; bn++) lfrag<BKF, BN>(pf[bn], lB, (wn * WNB + bn) * 32 + r32, half);
+#pragma unroll
+                for (int bm = 0; bm < WMB; bm++) lfrag<AKF, BM>(qf[bm], lA, (wm * WMB + bm) * 32 + r32, half);
+#pragma unroll
+                for (int j = 0; j < 8; j++)
+#pragma unroll
+                    for (int bn = 0; bn < WNB; bn++)
+#pragma unroll
+                        for (int bm = 0; bm < WMB; bm++)
+                            acc[bn][bm] = __builtin_amdgcn_mfma_f32_32x32x2f32(pf[bn][j], qf[bm][j], acc[bn][bm], 0, 0, 0);
+                if (more) store_step(lds + (cur ^ 1) * (A_SZ + B_SZ));
+                __syncthreads();
+                cur ^= 1;
             }
-            more = c < task.nchunk;
-            if (more) load_step();
-            const float* lA = lds + cur * (A_SZ + B_SZ);
-            const float* lB = lA + A_SZ;
-            float pf[WNB][8], qf[WMB][8];
-#pragma unroll
-            for (int bn = 0; bn < WNB; bn++) lfrag<BKF, BN>(pf[bn], lB, (wn * WNB + bn) * 32 + r32, half);
-#pragma unroll
-            for (int bm = 0; bm < WMB; bm++) lfrag<AKF, BM>(qf[bm], lA, (wm * WMB + bm) * 32 + r32, half);
-#pragma unroll
-            for (int j = 0; j < 8; j++)
-#pragma unroll
-                for (int bn = 0; bn < WNB; bn++)
-#pragma unroll
-                    for (int bm = 0; bm < WMB; bm++)
-                        acc[bn][bm] = __builtin_amdgcn_mfma_f32_32x32x2f32(pf[bn][j], qf[bm][j], acc[bn][bm], 0, 0, 0);
-            if (more) store_step(lds + (cur ^ 1) * (A_SZ + B_SZ));
-            __syncthreads();
-            cur ^= 1;
-            if (step % 32 == 0) move_sums<WMB, WNB>(acc, sum);       // every 512 k
+            add_sums<WMB, WNB>(acc, sum);
         }
     }
-#pragma unroll
-    for (int bn = 0; bn < WNB; bn++)
-#pragma unroll
-        for (int bm = 0; bm < WMB; bm++)
-#pragma unroll
-            for (int i = 0; i < 16; i++) acc[bn][bm][i] += sum[bn][bm][i];
 
-    write_tile_f32<WMB, WNB>(acc, global_as<float>(task.C) + (int64_t)bat_lo * task.strideC + (int64_t)bat_hi * task.strideC2, task.ldc, task.cin_off,
+    write_tile_f32<WMB, WNB>(sum, global_as<float>(task.C) + (int64_t)bat_lo * task.strideC + (int64_t)bat_hi * task.strideC2, task.ldc, task.cin_off,
                              in_global(task.bias), task.partial ? 1.f : g.alpha, task.partial ? 0.f : g.beta, m0 + wm * WMB * 32,
                              n0 + wn * WNB * 32, task.m, task.n, lane);
 }

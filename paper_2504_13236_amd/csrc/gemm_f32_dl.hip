@@ -189,12 +189,8 @@ __device__ __forceinline__ void f32_dl_body(const GemmArgs& g, char* lds) {
     }
 
     f32x16 acc[WNB][WMB], sum[WNB][WMB];
-#pragma unroll
-    for (int bn = 0; bn < WNB; bn++)
-#pragma unroll
-        for (int bm = 0; bm < WMB; bm++)
-#pragma unroll
-            for (int i = 0; i < 16; i++) acc[bn][bm][i] = sum[bn][bm][i] = 0.f;
+    clear<WMB, WNB>(acc);
+    clear<WMB, WNB>(sum);
 
     int T = 0;
     int chunk_i = 0;                         // index of the current chunk in g.chunks
@@ -389,7 +385,7 @@ __device__ __forceinline__ void f32_dl_body(const GemmArgs& g, char* lds) {
         asm volatile("s_barrier" ::: "memory");
         static_for<kFrags>([&](auto I) { frag_one(I, KS0{}, 0, lds0); });
         int st = 0;                                               // stage of step 2u
-        for (int u = 0; u < T / 2; u++) {
+        auto pair_of_steps = [&]() {
             const int s1 = next_of(st), s2 = next_of(s1), s3 = next_of(s2), s4 = next_of(s3);
             substep(None{}, KS1{}, 0, stage_addr(st), no_load, 0);
             // pair u complete for everybody (pair u + 1 may remain in flight)
@@ -410,24 +406,26 @@ __device__ __forceinline__ void f32_dl_body(const GemmArgs& g, char* lds) {
                 advance2();
             }
             if constexpr (RAG) next_pair_k();
-            if constexpr (!RES)
-                if (u % kSumPairs == kSumPairs - 1) move_sums<WMB, WNB>(acc, sum);
             st = s2;
+        };
+        // (a loop over the pairs between two moves of the sums: tested for inside one loop over all pairs, the move made the
+        // 128 x 128 form spill, 256 registers and 36 bytes instead of 202 and none)
+        if constexpr (RES) {
+            for (int u = 0; u < T / 2; u++) pair_of_steps();
+        } else {
+            for (int u = 0; u < T / 2;) {
+                clear<WMB, WNB>(acc);
+                for (const int end = min(u + kSumPairs, T / 2); u < end; u++) pair_of_steps();
+                add_sums<WMB, WNB>(acc, sum);
+            }
         }
         // nothing may still be on its way into LDS or into fragment registers at the end
         asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
     }
-    if constexpr (!RES) {
-#pragma unroll
-        for (int bn = 0; bn < WNB; bn++)
-#pragma unroll
-            for (int bm = 0; bm < WMB; bm++)
-#pragma unroll
-                for (int i = 0; i < 16; i++) acc[bn][bm][i] += sum[bn][bm][i];
-    }
+    f32x16 (&res)[WNB][WMB] = RES ? acc : sum;
 
     if constexpr (RAG) {
-        write_tile_f32<WMB, WNB>(acc, global_as<float>(task.C) + (int64_t)bat_lo * task.strideC + (int64_t)bat_hi * task.strideC2, task.ldc, task.cin_off,
+        write_tile_f32<WMB, WNB>(res, global_as<float>(task.C) + (int64_t)bat_lo * task.strideC + (int64_t)bat_hi * task.strideC2, task.ldc, task.cin_off,
                                  task.partial ? nullptr : in_global(task.bias), task.partial ? 1.f : g.alpha, task.partial ? 0.f : g.beta,
                                  m0 + wm * WMB * 32, n0 + wn * WNB * 32, task.m, task.n, lane);
         return;
@@ -460,7 +458,7 @@ __device__ __forceinline__ void f32_dl_body(const GemmArgs& g, char* lds) {
 #pragma unroll
             for (int i = 0; i < 16; i++) {
                 const int gn = n0 + (wn * WNB + bn) * 32 + 8 * (i >> 2) + 4 * half + (i & 3);
-                float v = alpha * acc[bn][bm][i] + bias;
+                float v = alpha * res[bn][bm][i] + bias;
                 if (emode == kEpiGeluGradMul) v *= gelu_grad_f(cin[bn][i], evar);
                 else if (beta != 0.f) v += beta * cin[bn][i];
                 C[gm + (int64_t)gn * task.ldc] = v;

@@ -203,6 +203,40 @@ def test_build_guard_finds_registers_used_while_their_lds_read_is_in_flight():
                                                     ("_Z6kernelv", 12, "v13", 10)]
 
 
+def test_build_guard_finds_matrix_results_named_before_they_are_there():
+    """The build refuses kernels in which another kind of instruction names the result of a matrix instruction too few
+    wait states behind it, along the shortest of the paths that lead there (the compiler has counted along a longer one)."""
+    from paper_2504_13236_amd.build import matrix_results_named_early
+    listing = "\n".join([
+        "_Z6kernelv:                             ; @_Z6kernelv",
+        ".LBB0_1:                                ; =>This Inner Loop Header: Depth=1",
+        "\tv_mfma_f32_32x32x2_f32 a[0:15], v2, v74, a[0:15]",
+        "\tv_mfma_f32_32x32x2_f32 a[0:15], v3, v75, a[0:15]",           # the same result: held back by the hardware
+        "\ts_cbranch_vccnz .LBB0_3",
+        "; %bb.2:                                ;   in Loop: Header=BB0_1 Depth=1",
+        "\tds_write_b128 v2, v[18:21]",
+        "\ts_nop 15",                                                    # the long path: 19 wait states
+        ".LBB0_3:                                ;   in Loop: Header=BB0_1 Depth=1",
+        "\ts_barrier",
+        "\ts_nop 3",
+        "\tv_accvgpr_read_b32 v17, a15",                                 # 6 on the short one
+        "\tv_accvgpr_read_b32 v16, a16",                                 # another register
+        "\ts_nop 15",
+        "\tv_accvgpr_read_b32 v18, a14",                                 # 24
+        "\tv_mfma_f32_32x32x16_bf16 v[32:47], v[2:5], v[6:9], 0",
+        "\ts_nop 9",
+        "\ts_branch .LBB0_5",
+        "\tv_mov_b32_e32 v1, v40",                                       # not on the path
+        ".LBB0_5:",
+        "\tglobal_store_dword v0, v47, s[0:1]",                          # 11 of 12
+        "\tv_mfma_f32_32x32x2_f32 v[48:63], v1, v2, 0",
+        "\tv_mfma_f32_32x32x2_f32 v[64:79], v50, v2, 0",                 # a factor, not the sum: after 0
+        "\ts_endpgm",
+        ".Lfunc_end0:",
+    ])
+    assert matrix_results_named_early(listing) == [("_Z6kernelv", 12, 4, 6), ("_Z6kernelv", 21, 16, 11), ("_Z6kernelv", 23, 22, 0)]
+
+
 def _simulate(capi, n_streams, serial, n_tiles, tasks):
     import numpy as np
     first = np.zeros(len(tasks) + 1, np.int32)

@@ -248,3 +248,49 @@ def test_cross_entropy_column_kernels(mods, dtype, N_v, tile_v):
         check(stats[1], np.exp(X - X.max(axis=0)).sum(axis=0), "f32", "column sums")
         assert np.abs(col.cpu().numpy().reshape(N_b, N_s).T - losses).max() <= TOL["f32"] * np.abs(losses).max()
         assert abs(tot.item() - losses.sum()) <= TOL["f32"] * abs(losses.sum())
+
+
+def test_narrow_language_model_over_a_long_vocabulary(mods):
+    """A training step whose gradient enters through a contraction over a vocabulary that is no multiple of a vector, with few
+    columns: the fp32 product that is cut into long slices of the register-staged kernel.  Every gradient in the 2-norm, within
+    1e-5 (32-bit sums one after the other; about ten times what they show)."""
+    capi, tiled = mods
+    r = np.random.default_rng(29)
+    N_h, h, N_s, N_b, N_v = 2, 64, 154, 3, 6514
+    e, eps = N_h * h, 1e-5
+    inp = {k: (0.02 * r.standard_normal(s)).astype(np.float32) for k, s in dict(
+        W_qkv=(3 * e, e), W_o=(e, e), W_1=(4 * e, e), W_2=(e, 4 * e), b_qkv=3 * e, b_o=e, b_1=4 * e, b_2=e, gamma1=e, beta1=e, gamma2=e, beta2=e).items()}
+    for k in ("gamma1", "gamma2"):
+        inp[k] += 1.0
+    wte, wpe = (0.02 * r.standard_normal((e, N_v))).astype(np.float32), (0.01 * r.standard_normal((e, N_s))).astype(np.float32)
+    gf, bf = (1.0 + 0.02 * r.standard_normal(e)).astype(np.float32), (0.02 * r.standard_normal(e)).astype(np.float32)
+    tok, lab = r.integers(0, N_v, (N_s, N_b)), r.integers(0, N_v, (N_s, N_b))
+    # oracle
+    pos = np.repeat(np.arange(N_s)[:, None], N_b, axis=1)
+    p64 = {k: np.asarray(v, np.float64) for k, v in inp.items()}
+    W64 = wte.astype(np.float64)
+    X0 = D.embedding_fwd(W64, tok) + D.embedding_fwd(wpe.astype(np.float64), pos)
+    X, cache = D.block_forward(p64, X0, N_h, eps, "tanh")
+    Xf, mean, rstd = D.layernorm_fwd(X, gf, bf, eps)
+    L, _, dlogits = D.cross_entropy(np.tensordot(W64, Xf, (0, 0)), lab)
+    dX, dgf, dbf = D.layernorm_bwd(X, gf, mean, rstd, np.tensordot(W64, dlogits, (1, 0)))
+    dX, grads = D.block_backward(p64, cache, dX, N_h, "tanh")
+    dwte = np.tensordot(Xf, dlogits, ((1, 2), (1, 2))) + D.embedding_bwd(dX, tok, N_v)
+    want = dict(wte=dwte, wpe=D.embedding_bwd(dX, pos, N_s), gamma=dgf, beta=dbf, **grads)
+    # device
+    with tiled.Context(n_streams=2) as ctx:
+        blk = tiled.Gpt2Block(ctx, e, N_h, 4 * e, N_s, N_b, dict(e=e, m=e, s=128, b=N_b, j=N_h, i=h), dtype="f32", adam=False)
+        blk.set_params(inp)
+        model = tiled.Gpt2Model(ctx, [blk], N_v, 8192)
+        model.set_params(wte, wpe, gf, bf)
+        model.set_batch(tok, lab)
+        model.forward()
+        model.backward()
+        ctx.wait()
+        assert abs(model.loss.item() - L) <= 1e-5 * abs(L)
+        for k, ref in want.items():
+            got = (blk.grad(k) if k in grads else getattr(model, k)["g"]).download()
+            err = np.linalg.norm(got.astype(np.float64) - ref) / np.linalg.norm(ref)
+            assert err <= 1e-5, (k, err)
+        model.close()
+        blk.close()

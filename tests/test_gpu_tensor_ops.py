@@ -774,3 +774,25 @@ def test_linear_layers_of_any_size(mods, case, dtype):
         dXr, dWr, _ = D.linear_bwd(W, X, dY)
         check(tdX.download(), dXr, dtype, "linear dX")
         check(tdW.download(), dWr, "f32", "linear dW")
+
+
+@pytest.mark.parametrize("opA,opB", [(0, 0), (0, 1), (1, 0), (1, 1)])
+@pytest.mark.parametrize("m,n,k", [(128, 231, 6514), (126, 77, 3001), (500, 300, 2050), (1030, 1027, 1101), (128, 384, 6528)])
+def test_long_contractions_of_odd_extents(mods, m, n, k, opA, opB):
+    """fp32 products whose contraction is longer than the 512 after which the partial sums leave the matrix accumulators, on
+    operands that only the register-staged kernels take (the last: the direct-load ones): few macro-tiles whose slices are
+    longer than that, and many without slices.  In the 2-norm: a chain of 512 additions in random order is off by about
+    0.29 * 2^-24 * sqrt(512 / 2) of its sum, 3e-7, and so are the k / 512 chains together; 2e-6 leaves room for both roundings of
+    the slice sums and for a longer chain's tail.  One wrong register of the sixteen of a block would be 1e-2."""
+    capi, tiled = mods
+    r = rng(m + n + k)
+    A = r.standard_normal((m, k) if opA == 0 else (k, m)).astype(np.float32)
+    B = r.standard_normal((k, n) if opB == 0 else (n, k)).astype(np.float32)
+    ref = (A if opA == 0 else A.T).astype(np.float64) @ (B if opB == 0 else B.T).astype(np.float64)
+    with tiled.Context(n_streams=2) as ctx:
+        tA, tB = T(tiled, ctx, A, A.shape, "f32"), T(tiled, ctx, B, B.shape, "f32")
+        tC = tiled.TiledTensor(ctx, "f32", (m, n), (m, n))
+        capi.nnt_gemm(ctx.h, 1.0, opA, tA.h, opB, tB.h, 0.0, tC.h, 1, 0, None)
+        got = tC.download().astype(np.float64)
+    e = np.linalg.norm(got - ref) / np.linalg.norm(ref)
+    assert e <= 2e-6, e
