@@ -634,8 +634,9 @@ int32_t build_plan(nnt_ctx* ctx, int opA, nnt_tensor* A, int opB, nnt_tensor* B,
     P->cfg = pick_cfg(bf, m_max, n_max, big, k_max, P->akf && P->bkf);
     int S = 1;
     int64_t n_split = 0;
-    if (nbat == 0 && !P->tasks.empty() && P->cfg != kCfgResident) {
-        // products of whole matrices: macro-tile shape and k-slices by the cost model
+    if (nbat == 0 && !P->tasks.empty() && (P->cfg != kCfgResident || epi)) {
+        // products of whole matrices: macro-tile shape and k-slices by the cost model (with an activation on the result path also
+        // where the contraction is short: the kernels with the whole contraction in LDS have no such form)
         std::vector<int64_t> tm, tn;
         ShapeKind kind = kShapeWhole;
         for (size_t ti = 0; ti < P->tasks.size(); ti++) {

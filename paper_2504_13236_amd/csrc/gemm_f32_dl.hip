@@ -538,8 +538,9 @@ bool gemm_f32_dl_has_act(int akf, int bkf, int epi_mode) {
 int32_t launch_gemm_f32_dl(hipStream_t st, int akf, int bkf, int cfg, bool ragged, const GemmArgs& g, int64_t nwg, int epi_mode) {
     if (nwg <= 0) return NNT_OK;
     if (epi_mode) {
-        if (ragged || !gemm_f32_dl_has_act(akf, bkf, epi_mode)) return NNT_EINVAL;
+        // (these kernels do not look at edges: the shape has to be the one that the plan's workgroups were laid out for)
         const bool mid = cfg == kCfgSkinny64n128 || cfg == kCfgMid;
+        if (ragged || !(mid || cfg == kCfgSquare) || !gemm_f32_dl_has_act(akf, bkf, epi_mode)) return NNT_EINVAL;
         const KernelFn fn = mid ? act_kernel_of<1, 2>(epi_mode) : act_kernel_of<2, 2>(epi_mode);
         hipLaunchKernelGGL(fn, dim3((unsigned)nwg), dim3(256), 0, st, g);
         return hipGetLastError() == hipSuccess ? NNT_OK : NNT_EHIP;

@@ -399,6 +399,26 @@ def test_gemm_with_the_activation_on_its_way_out(mods, gran, dtype, variant, sha
             capi.nnt_gemm_gelu_bwd(ctx.h, 1.0, 1, tW.h, 0, tdY.h, tdZ.h, 1, 7, tZ.h)            # unknown variant
 
 
+@pytest.mark.parametrize("gran", GRANS)
+@pytest.mark.parametrize("n", [128, 256])
+@pytest.mark.parametrize("tm", [64, 128, 192])
+@pytest.mark.parametrize("k", [32, 64])
+def test_activation_gradient_behind_a_short_contraction(mods, k, tm, n, gran):
+    """dH = (W^T dY) * gelu'(H) where the contraction is a head size long (a narrow MLP): products for which the plain form takes
+    the kernel that holds the whole contraction in LDS, whose macro-tiles of 64 rows the activation kernels do not all have.
+    Every tile of the result, on tiles that are whole numbers of 64 rows but not of 128."""
+    capi, tiled = mods
+    r = rng(k + tm + n)
+    m = 3 * tm
+    W, dY = r.standard_normal((k, m)).astype(np.float32), r.standard_normal((k, 2 * n)).astype(np.float32)
+    Z = (1.5 * r.standard_normal((m, 2 * n))).astype(np.float32)
+    with tiled.Context(n_streams=2, granularity=gran) as ctx:
+        tW, tdY, tZ = T(tiled, ctx, W, (k, tm), "f32"), T(tiled, ctx, dY, (k, n), "f32"), T(tiled, ctx, Z, (tm, n), "f32")
+        tdZ = T(tiled, ctx, np.full((m, 2 * n), 7.0), (tm, n), "f32")
+        capi.nnt_gemm_gelu_bwd(ctx.h, 1.0, 1, tW.h, 0, tdY.h, tdZ.h, 1, 0, tZ.h)
+        check(tdZ.download(), D.contract(1.0, "T", W, "N", dY, 0.0, None, 1, 0) * D.gelu_grad(Z.astype(np.float64), "tanh"), "f32", "dZ")
+
+
 def test_device_memory_of_the_library_is_reported(mods):
     """nnt_ctx_stats: tile-pointer tables and plan tables count as table bytes, the fp32 workspace of a
     product cut into k-slices as workspace bytes; both shrink again when the tensors go."""
