@@ -190,9 +190,12 @@ static int32_t launch_any(hipStream_t st, int dtype_in, int dtype_out, int akf, 
     return general(rest, nwg - nfast);
 }
 
-static int vec_flag(const void* p, int64_t ld, int64_t stride, int elem) {
+// Whether the direct-load kernels may read an operand: 16-byte aligned lines, and, as their lanes' byte offsets from the first
+// element of a macro-tile have 32 bits, lines that lie close enough together: up to 128 fp32 (256 bf16) rows where k is the
+// contiguous index, 32 k where it is not.  (The register-staged kernels address with 64 bits.)
+static int vec_flag(const void* p, int64_t ld, int64_t stride, int elem, bool k_contiguous) {
     const int per = 16 / elem;
-    return ((uintptr_t)p % 16 == 0) && (ld % per == 0) && (stride % per == 0);
+    return ((uintptr_t)p % 16 == 0) && (ld % per == 0) && (stride % per == 0) && ld <= (k_contiguous ? (int64_t)1 << 23 : ((int64_t)1 << 27) / elem);
 }
 
 // Workgroups are handed to the 8 XCDs (each with its own L2) in turn by their linear id, so the
@@ -396,7 +399,7 @@ extern "C" int32_t nnt_tile_gemm(void* stream, int32_t dtype_in, int32_t dtype_o
     g.one_chunk.strideA = strideA;
     g.one_chunk.strideB = strideB;
     g.one_chunk.k = (int32_t)k;
-    g.one_chunk.vec_ok = vec_flag(A, lda, strideA, elem) | (vec_flag(B, ldb, strideB, elem) << 1);
+    g.one_chunk.vec_ok = vec_flag(A, lda, strideA, elem, opA == NNT_OP_T) | (vec_flag(B, ldb, strideB, elem, opB == NNT_OP_N) << 1);
     g.alpha = alpha;
     g.beta = beta;
     int bm, bn;
@@ -452,7 +455,7 @@ std::vector<std::pair<int32_t, int32_t>> cut_into_slices(GemmPlan* P, const Gemm
             c.A = static_cast<const char*>(c0.A) + used * (P->akf ? 1 : c0.lda) * elem;
             c.B = static_cast<const char*>(c0.B) + used * (P->bkf ? 1 : c0.ldb) * elem;
             c.k = (int32_t)take;
-            c.vec_ok = vec_flag(c.A, c.lda, c.strideA, elem) | (vec_flag(c.B, c.ldb, c.strideB, elem) << 1);
+            c.vec_ok = vec_flag(c.A, c.lda, c.strideA, elem, P->akf) | (vec_flag(c.B, c.ldb, c.strideB, elem, P->bkf) << 1);
             P->chunks.push_back(c);
             want -= take;
             used += take;
@@ -607,8 +610,8 @@ int32_t build_plan(nnt_ctx* ctx, int opA, nnt_tensor* A, int opB, nnt_tensor* B,
                 ch.strideA2 = view_ld[0] ? (P->akf ? k : m) : ch.strideA * nb1;
                 ch.strideB2 = view_ld[1] ? (P->bkf ? k : n) : ch.strideB * nb1;
             }
-            ch.vec_ok = (vec_flag(ch.A, ch.lda, ch.strideA, elem) && ch.strideA2 % (16 / elem) == 0 ? 1 : 0) |
-                        (vec_flag(ch.B, ch.ldb, ch.strideB, elem) && ch.strideB2 % (16 / elem) == 0 ? 2 : 0);
+            ch.vec_ok = (vec_flag(ch.A, ch.lda, ch.strideA, elem, P->akf) && ch.strideA2 % (16 / elem) == 0 ? 1 : 0) |
+                        (vec_flag(ch.B, ch.ldb, ch.strideB, elem, P->bkf) && ch.strideB2 % (16 / elem) == 0 ? 2 : 0);
             P->chunks.push_back(ch);
             atl.push_back(ai);
             btl.push_back(bi);

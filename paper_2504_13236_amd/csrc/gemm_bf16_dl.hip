@@ -50,13 +50,13 @@ __device__ __forceinline__ uint32_t load_offset(int ld, int wave, int lane, int 
         // an instruction covers 16 rows; lane -> row lane / 4, slot lane % 4
         const int r = lane >> 2;
         const int c = (lane & 3) ^ ((r >> 2) & 3);
-        return (uint32_t)(((16 * (NI * wave + j) + r) * ld + c * 8) * 2);
+        return ((uint32_t)(16 * (NI * wave + j) + r) * (uint32_t)ld + c * 8) * 2;
     }
     // an instruction covers 1024 / (2 ROWS) k-lines; lane -> line lane / LPL, slot lane % LPL
     constexpr int LPL = ROWS / 8, LPI = 64 / LPL;            // lanes per line, lines per instruction
     const int kk = LPI * j + lane / LPL;                     // line within the wave's 8; 8 * wave is 0 mod 4
     const int c = (lane % LPL) ^ ((kk & 3) << 2);
-    return (uint32_t)(((8 * wave + kk) * ld + c * 8) * 2);
+    return ((uint32_t)(8 * wave + kk) * (uint32_t)ld + c * 8) * 2;
 }
 
 // The same for a block of which only `rows` rows (a multiple of 8 when the row index is the
@@ -73,7 +73,7 @@ __device__ __forceinline__ uint32_t load_offset_clamped(int ld, int wave, int la
         int c = (lane & 3) ^ ((r >> 2) & 3);
         if (c * 8 >= kv) c = 0;
         const int row = min(16 * (NI * wave + j) + r, rows - 1);
-        return (uint32_t)((row * ld + c * 8) * 2);
+        return ((uint32_t)row * (uint32_t)ld + c * 8) * 2;
     }
     constexpr int LPL = ROWS / 8, LPI = 64 / LPL;
     const int kk = LPI * j + lane / LPL;
@@ -81,7 +81,7 @@ __device__ __forceinline__ uint32_t load_offset_clamped(int ld, int wave, int la
     if (c * 8 >= rows) c = 0;
     int line = 8 * wave + kk;
     if (line >= kv) line = 0;
-    return (uint32_t)((line * ld + c * 8) * 2);
+    return ((uint32_t)line * (uint32_t)ld + c * 8) * 2;
 }
 
 // Per-lane part of the fragment address of an operand region of ROWS rows.

@@ -47,7 +47,7 @@ struct GemmChunk {
     const void* B;
     int64_t lda, ldb, strideA, strideB;   // elements
     int32_t k;
-    int32_t vec_ok;         // bit 0: A may be read with 16-byte vectors, bit 1: B
+    int32_t vec_ok;         // bit 0: the direct-load kernels may read A (alignment, distance of its lines), bit 1: B
     int64_t strideA2, strideB2;           // second batch strides (see GemmTask::nb1), elements
 };
 

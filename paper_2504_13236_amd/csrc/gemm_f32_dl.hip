@@ -49,13 +49,13 @@ __device__ __forceinline__ uint32_t load_offset(int ld, int wave, int lane, int 
         // an instruction covers 16 rows; lane -> row lane / 4, slot lane % 4
         const int r = lane >> 2;
         const int c = (lane & 3) ^ ((r >> 2) & 3);
-        return (uint32_t)(((16 * (NI * wave + j) + r) * ld + c * 4) * 4);
+        return ((uint32_t)(16 * (NI * wave + j) + r) * (uint32_t)ld + c * 4) * 4;
     }
     // an instruction covers 256 / ROWS k-lines; lane -> line lane / LPL, slot lane % LPL
     constexpr int LPL = ROWS / 4, LPI = 64 / LPL;            // lanes per line, lines per instruction
     const int kk = LPI * (NI * wave + j) + lane / LPL;
     const int c = (lane % LPL) ^ (((kk >> 2) & 1) << 3);
-    return (uint32_t)((kk * ld + c * 4) * 4);
+    return ((uint32_t)kk * (uint32_t)ld + c * 4) * 4;
 }
 
 // The same, for step `second` of a pair of k-steps, where only `rows` rows (a multiple of 4 when the row index is the
@@ -70,14 +70,14 @@ __device__ __forceinline__ uint32_t load_offset_clamped(int ld, int wave, int la
         const int r = lane >> 2;
         int k = 16 * second + 4 * ((lane & 3) ^ ((r >> 2) & 3));
         if (k >= kv) k = 0;
-        return (uint32_t)((min(16 * (NI * wave + j) + r, rows - 1) * ld + k) * 4);
+        return ((uint32_t)min(16 * (NI * wave + j) + r, rows - 1) * (uint32_t)ld + k) * 4;
     }
     constexpr int LPL = ROWS / 4, LPI = 64 / LPL;
     const int kk = LPI * (NI * wave + j) + lane / LPL;
     int row = 4 * ((lane % LPL) ^ (((kk >> 2) & 1) << 3));
     if (row >= rows) row = 0;
     const int line = 16 * second + kk < kv ? 16 * second + kk : 0;
-    return (uint32_t)((line * ld + row) * 4);
+    return ((uint32_t)line * (uint32_t)ld + row) * 4;
 }
 
 // Registers of one fragment of a substep (4 k of the lane's row) while its read is in flight.  `keep_below`: of the four,

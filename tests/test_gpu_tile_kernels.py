@@ -546,3 +546,37 @@ def test_gemm_edges_at_any_alignment(capi, din, dout, opA, opB, m, n, k):
         assert e <= (1e-5 if dout == "f32" else 2e-2), (pad, shift, e)
         keep = torch.isnan(before)
         assert torch.equal(torch.isnan(sC), keep), "an element outside the result was written"
+
+
+@pytest.mark.parametrize("dt", ["f32", "bf16"])
+@pytest.mark.parametrize("far,op", [("A", "N"), ("A", "T"), ("B", "N"), ("B", "T")])
+def test_gemm_of_operands_whose_lines_lie_far_apart(capi, dt, far, op):
+    """One operand is a window on a matrix of 8.5 million rows (35 or 70 million where the contracted index runs along its columns), so that a macro-tile's last line starts more than 4 GiB behind its first: the direct-load kernels, which
+    address a macro-tile with 32 bits, must not take it.  Whole macro-tiles and ragged ones."""
+    r = rng(5)
+    unit, elem = (128, 4) if dt == "f32" else (256, 2)
+    k_contiguous = (far == "A") == (op == "T")
+    ld = 8_500_000 if k_contiguous else 140_000_000 // elem
+    assert ((unit - 1) * ld if k_contiguous else 31 * ld) * elem > 1 << 32
+    k = 96 if k_contiguous else 32
+    for lines in (unit, unit + 8):
+        m, n = (lines, 128) if far == "A" else (128, lines)
+        A, B = quant(r.standard_normal((m, k)), dt), quant(r.standard_normal((k, n)), dt)
+        opA, opB = (op, "N") if far == "A" else ("N", op)
+        X, Y = (A if opA == "N" else A.T), (B if opB == "N" else B.T)
+
+        def dev(M, distant):
+            t = to_dev(M, dt)
+            if not distant:
+                return t, M.shape[0]
+            s = torch.empty((M.shape[1], ld), dtype=t.dtype, device=t.device)
+            s[:, :M.shape[0]] = t.view(M.shape[1], M.shape[0])
+            return s, ld
+        (tX, lda), (tY, ldb) = dev(X, far == "A"), dev(Y, far == "B")
+        tC = torch.zeros(m * n, device="cuda")
+        capi.nnt_tile_gemm(stream_ptr(), code(dt), code("f32"), 0 if opA == "N" else 1, 0 if opB == "N" else 1, m, n, k, 1, 1.0,
+                           tX.data_ptr(), lda, 0, tY.data_ptr(), ldb, 0, 0.0, tC.data_ptr(), m, 0)
+        torch.cuda.synchronize()
+        e = relerr(from_dev(tC, (m, n)), D.matmul2d(1.0, opA, X[:, :, None], opB, Y[:, :, None], 0.0, np.zeros((m, n, 1)))[:, :, 0])
+        assert e <= 1e-5, (lines, e)
+        del tX, tY
