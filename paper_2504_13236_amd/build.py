@@ -35,28 +35,12 @@ FLAGS = [
 # between a read and its wait would hold stale data, so inside their loops these kernels
 # must not touch scratch memory.  (Spills in the prologue or after the last wait are harmless.)
 # Their assembly is also scanned for any instruction that names a register between the LDS read that
-# targets it and the next full wait (registers_touched_in_flight): a copy or move the compiler
-# places there would read stale data just the same.
+# targets it and the wait for it (registers_touched_in_flight): a copy or move the compiler
+# places there would read stale data just the same.  Both follow the branches, not the order of the listing: loop blocks
+# carry their loop's name on the line of their label or on the next one, and the compiler puts blocks out of line.
 IN_FLIGHT_SOURCES = ("gemm_bf16_dl.hip", "gemm_f32_dl.hip")
 # Sources with matrix instructions: their assembly is scanned for uses of a result before it is there.
 MATRIX_SOURCES = IN_FLIGHT_SOURCES + ("gemm_bf16.hip", "gemm_f32.hip", "attention.hip")
-
-
-def scratch_in_loops(asm_text: str) -> list:
-    """[(kernel, line number)] of scratch instructions inside loop blocks of a device assembly listing.
-
-    The listing marks each basic block that belongs to a loop in the comment on its label."""
-    hits = []
-    kernel, in_loop = None, False
-    for no, line in enumerate(asm_text.splitlines(), 1):
-        t = line.strip()
-        if t.startswith("_Z") and t.split(":")[0].isidentifier() and ":" in t:
-            kernel, in_loop = t.split(":")[0], False
-        elif t.startswith(".LBB") or t.startswith("; %bb."):
-            in_loop = "Loop" in t
-        elif in_loop and t.startswith("scratch_"):
-            hits.append((kernel, no))
-    return hits
 
 
 _VREG = re.compile(r"\bv(\d+)\b|\bv\[(\d+):(\d+)\]")
@@ -70,53 +54,6 @@ def _vregs(text: str) -> set:
         else:
             out.update(range(int(m.group(2)), int(m.group(3)) + 1))
     return out
-
-
-def registers_touched_in_flight(asm_text: str) -> list:
-    """[(kernel, line number, register, line of the read)]: instructions of a device assembly listing that name a
-    vector register while an LDS read into it is still in flight, i.e. between the ds_read that targets it and
-    the `s_waitcnt lgkmcnt(n)` that covers it (LDS operations complete in order, so such a wait leaves at most the
-    last n of them in flight; scalar loads only make a wait cover more than is assumed here).
-
-    The compiler believes such a register holds its value from the read's asm statement on, so a copy, a move to
-    an accumulation register or any other use it schedules before the hand-placed wait would see stale data.
-    The scan is linear per kernel (listing order)."""
-    hits = []
-    kernel, pending = None, {}
-    issued = 0                                      # LDS operations so far; pending: register -> (line, number of its read)
-    for no, line in enumerate(asm_text.splitlines(), 1):
-        t = line.split(";")[0].strip()
-        if not t:
-            continue
-        if t.startswith("_Z") and t.endswith(":"):
-            kernel, pending = t[:-1], {}
-            continue
-        if t.endswith(":") or t.startswith("."):
-            continue
-        op, _, rest = t.partition(" ")
-        if op == "s_waitcnt":
-            m = re.search(r"lgkmcnt\((\d+)\)", rest)
-            if m:
-                pending = {r: p for r, p in pending.items() if p[1] >= issued - int(m.group(1))}
-            continue
-        if op == "s_endpgm":
-            pending = {}
-            continue
-        if op.startswith("ds_read"):
-            ops = [o.strip() for o in rest.split(",")]
-            for o in ops[1:]:                       # the address is read now
-                for r in _vregs(o):
-                    if r in pending:
-                        hits.append((kernel, no, "v%d" % r, pending[r][0]))
-            for r in _vregs(ops[0]):
-                pending[r] = (no, issued)
-            issued += 1
-            continue
-        for r in _vregs(rest):
-            if r in pending:
-                hits.append((kernel, no, "v%d" % r, pending[r][0]))
-        issued += op.startswith("ds_")
-    return hits
 
 
 # Wait states (instructions, an `s_nop n` counting as n + 1) that have to lie between a matrix instruction and another
@@ -155,6 +92,82 @@ def _kernels(asm_text: str) -> dict:
     return out
 
 
+def _next(code: list, labels: dict, i: int) -> list:
+    """Indices of the instructions that may follow instruction i."""
+    _, op, args = code[i]
+    if op == "s_endpgm" or op.startswith("s_setpc"):
+        return []
+    to = [labels[args]] if op == "s_branch" else [i + 1] + ([labels[args]] if op.startswith("s_cbranch") else [])
+    return [j for j in to if j < len(code)]
+
+
+def scratch_in_loops(asm_text: str) -> list:
+    """[(kernel, line number)] of scratch instructions of a device assembly listing that can be reached from themselves."""
+    hits = []
+    for kernel, (code, labels) in _kernels(asm_text).items():
+        for first, (no, op, _) in enumerate(code):
+            if not op.startswith("scratch_"):
+                continue
+            seen, todo = set(), _next(code, labels, first)
+            while todo:
+                i = todo.pop()
+                if i not in seen:
+                    seen.add(i)
+                    todo += _next(code, labels, i)
+            if first in seen:
+                hits.append((kernel, no))
+    return hits
+
+
+def registers_touched_in_flight(asm_text: str) -> list:
+    """[(kernel, line number, register, line of the read)]: instructions of a device assembly listing that name a
+    vector register while an LDS read into it is still in flight on a path that leads to them, i.e. between the ds_read that
+    targets it and the `s_waitcnt lgkmcnt(n)` that covers it (LDS operations complete in order, so such a wait leaves at most
+    the last n of them in flight; scalar loads only make a wait cover more than is assumed here).
+
+    The compiler believes such a register holds its value from the read's asm statement on, so a copy, a move to
+    an accumulation register or any other use it schedules before the hand-placed wait would see stale data."""
+    hits = set()
+    for kernel, (code, labels) in _kernels(asm_text).items():
+        # in front of each instruction: register -> (LDS operations from its read on, the read included; line of the read),
+        # the fewest where paths meet
+        before: list = [None] * len(code)
+        todo = []
+
+        def reach(i, state):
+            if before[i] is None:
+                before[i] = dict(state)
+                todo.append(i)
+            else:
+                newer = {r: p for r, p in state.items() if p < before[i].get(r, (1 << 30,))}
+                if newer:
+                    before[i].update(newer)
+                    todo.append(i)
+
+        if code:
+            reach(0, {})
+        while todo:
+            i = todo.pop()
+            no, op, args = code[i]
+            state = dict(before[i])
+            if op == "s_waitcnt":
+                m = re.search(r"lgkmcnt\((\d+)\)", args)
+                if m:
+                    state = {r: p for r, p in state.items() if p[0] <= int(m.group(1))}
+            else:
+                target = set()
+                if op.startswith("ds_read"):            # its operands behind the first are the address, read now
+                    ops = args.split(",")
+                    target, args = _vregs(ops[0]), ",".join(ops[1:])
+                hits.update((kernel, no, "v%d" % r, state[r][1]) for r in _vregs(args) if r in state)
+                if op.startswith("ds_"):
+                    state = {r: (n + 1, at) for r, (n, at) in state.items()}
+                state.update((r, (1, no)) for r in target)
+            for j in _next(code, labels, i):
+                reach(j, state)
+    return sorted(hits, key=lambda h: (h[0], h[1], int(h[2][1:])))
+
+
 def matrix_results_named_early(asm_text: str) -> list:
     """[(kernel, line number, line of the matrix instruction, wait states between them)]: instructions of a device assembly
     listing that name the result of a matrix instruction before it is there, on any path through the branches.
@@ -185,12 +198,12 @@ def matrix_results_named_early(asm_text: str) -> list:
                     elif _registers(args) & result:
                         hits.add((kernel, at, no, waited))
                         break
-                    if name == "s_endpgm" or name.startswith("s_setpc"):
-                        break
                     waited += int(args, 0) + 1 if name == "s_nop" else 1
-                    if name.startswith("s_cbranch"):
-                        todo.append((labels[args], waited))
-                    i = labels[args] if name == "s_branch" else i + 1
+                    to = _next(code, labels, i)
+                    if not to:
+                        break
+                    i = to[0]
+                    todo += [(j, waited) for j in to[1:]]
     return sorted(hits)
 
 

@@ -203,6 +203,38 @@ def test_build_guard_finds_registers_used_while_their_lds_read_is_in_flight():
                                                     ("_Z6kernelv", 12, "v13", 10)]
 
 
+def test_build_guards_follow_the_branches_of_a_listing():
+    """Loop blocks whose label line names no loop, blocks that the compiler has put behind the end of the program, and
+    registers in flight around the loop's back edge."""
+    from paper_2504_13236_amd.build import registers_touched_in_flight, scratch_in_loops
+    listing = "\n".join([
+        "_Z6kernelv:                             ; @_Z6kernelv",
+        "\tds_read_b128 v[4:7], v1",
+        ".LBB0_1:                                ; %_ZN3bodyEv.exit",
+        "                                        ; =>This Inner Loop Header: Depth=1",
+        "\tv_mov_b32_e32 v9, v4",                                      # 5: in flight on the way in, and again on the way back
+        "\ts_waitcnt lgkmcnt(0)",
+        "\ts_cbranch_vccnz .LBB0_3",
+        ".LBB0_2:                                ; %_ZN4tailEv.exit",
+        "                                        ;   in Loop: Header=BB0_1 Depth=1",
+        "\tscratch_store_dword off, v3, off",                         # 10: in the loop
+        "\tds_read_b32 v8, v1",
+        "\ts_cbranch_scc0 .LBB0_1",
+        "\tv_mov_b32_e32 v10, v8",                                    # 13: behind the loop, not yet waited for
+        "\tscratch_load_dword v3, off, off",
+        "\ts_endpgm",
+        ".LBB0_3:",
+        "\tscratch_load_dword v3, off, off",                          # 17: in the loop, out of line
+        "\tv_add_u32_e32 v11, v4, v4",                                # waited for
+        "\tds_read_b32 v4, v1",
+        "\ts_branch .LBB0_2",
+        ".Lfunc_end0:",
+    ])
+    assert scratch_in_loops(listing) == [("_Z6kernelv", 10), ("_Z6kernelv", 17)]
+    # (line 5: the read of line 2 on the way in, one LDS operation back, and that of line 19 on the way back, two: the nearer is named)
+    assert registers_touched_in_flight(listing) == [("_Z6kernelv", 5, "v4", 2), ("_Z6kernelv", 13, "v8", 11)]
+
+
 def test_build_guard_finds_matrix_results_named_before_they_are_there():
     """The build refuses kernels in which another kind of instruction names the result of a matrix instruction too few
     wait states behind it, along the shortest of the paths that lead there (the compiler has counted along a longer one)."""
