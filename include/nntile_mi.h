@@ -145,7 +145,8 @@ NNT_API int32_t nnt_profile_read(nnt_ctx* ctx, nnt_profile_entry* out, int32_t c
  * acc_tile[task_first[t] .. task_first[t+1]-1] with the modes acc_mode[...]
  * (1 read, 2 write, 3 read-write, 6 + 256 * p write of part p of the tile: writers of
  * different parts of a tile are not ordered among themselves, as the attention products
- * that write the rows of Q, K and V inside one tensor) -- reports the stream each task would run on, its
+ * that write the rows of Q, K and V inside one tensor; plus 128 on any access of a task: the task
+ * counts as one of a few microseconds, which stays on a stream that it depends on) -- reports the stream each task would run on, its
  * sequence number on that stream, and per task NNT_MAX_STREAMS entries: the sequence
  * number on every other stream that it would wait for (0 = none).  Uses the same
  * code as the executor, touches no device: it lets a test check on the CPU that

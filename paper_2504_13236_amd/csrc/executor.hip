@@ -319,14 +319,16 @@ int32_t nnt_sched_simulate(int32_t n_streams, int32_t serial, int32_t n_tiles, i
     int rr = 0;
     for (int t = 0; t < n_tasks; t++) {
         std::vector<Access> acc;
+        bool small = false;
         for (int i = task_first[t]; i < task_first[t + 1]; i++) {
-            const int mode = acc_mode[i] & 0xff, part = acc_mode[i] >> 8;
+            const int mode = acc_mode[i] & 0x7f, part = acc_mode[i] >> 8;
             if (acc_tile[i] < 0 || acc_tile[i] >= n_tiles || acc_mode[i] < 0 || !((mode >= kRead && mode <= kReadWrite) || mode == kWritePart) ||
                 (mode != kWritePart && part != 0))
                 return NNT_EINVAL;
+            small = small || (acc_mode[i] & 0x80);
             acc.push_back(Access{&tiles[(size_t)acc_tile[i]], 1, mode, part});
         }
-        const TaskPlan plan = plan_task(acc, n_streams, n_streams, serial != 0, false, tail, synced, waited, &rr);
+        const TaskPlan plan = plan_task(acc, n_streams, n_streams, serial != 0, small, tail, synced, waited, &rr);
         // the waits as the executor would issue them: on the first recorded event that covers the
         // task asked for, else on a new one at the tail of that stream
         for (int s = 0; s < kMaxStreams; s++) {

@@ -287,12 +287,17 @@ def _simulate(capi, n_streams, serial, n_tiles, tasks):
     return stream, seq, waits
 
 
+SMALL = 128         # on the mode of any access: the task counts as one of a few microseconds
+
+
+@pytest.mark.parametrize("small", [False, True])
 @pytest.mark.parametrize("n_streams", [1, 2, 4, 8])
-def test_executor_orders_every_conflicting_pair(capi, n_streams):
+def test_executor_orders_every_conflicting_pair(capi, n_streams, small):
     """Host-side race check of the task executor's decisions: for random task sequences, every pair of
     tasks that touch a common tile, at least one of them writing, must be ordered by the happens-before
     relation that stream order and the event waits generate (read-after-write, write-after-read,
-    write-after-write); tasks that only share read tiles need not be."""
+    write-after-write); tasks that only share read tiles need not be.  `small`: two tasks in three, at random, count as
+    tasks of a few microseconds, for which the stream is chosen by a rule of its own."""
     import numpy as np
     r = np.random.default_rng(100 + n_streams)
     for trial in range(20):
@@ -304,7 +309,8 @@ def test_executor_orders_every_conflicting_pair(capi, n_streams):
             chosen = r.choice(n_tiles, size=k, replace=False)
             # modes: read, write, read-write, and writes of part 0, 1 or 2 of the tile (6 + 256 * part)
             tasks.append([(int(t), int(r.choice([1, 1, 2, 3, 6, 6 + 256, 6 + 512]))) for t in chosen])
-        stream, seq, waits = _simulate(capi, n_streams, 0, n_tiles, tasks)
+        told = [[(t, m | (SMALL if i == 0 else 0)) for i, (t, m) in enumerate(a)] if small and r.random() < 2 / 3 else a for a in tasks]
+        stream, seq, waits = _simulate(capi, n_streams, 0, n_tiles, told)
         assert stream.min() >= 0 and stream.max() < n_streams
         at = {(int(stream[t]), int(seq[t])): t for t in range(n_tasks)}
         assert len(at) == n_tasks                                  # sequence numbers are unique per stream
@@ -338,6 +344,24 @@ def test_executor_orders_every_conflicting_pair(capi, n_streams):
     # serial mode keeps everything on one stream
     stream, seq, waits = _simulate(capi, n_streams, 1, 3, [[(0, 2)], [(1, 2)], [(0, 1), (1, 1)], [(2, 3)]])
     assert not stream.any() and not waits.any()
+
+
+def test_executor_keeps_small_tasks_on_a_stream_they_depend_on(capi):
+    """Two chains on two streams, the second one longer; a task reads the first result of each and so is behind the tail of
+    neither stream.  A long one takes the next stream in turn; a small one the stream with more behind it, where it waits
+    for the other.  The turn passes either way: the task after it lands where it would have."""
+    import numpy as np
+    chains = [[(0, 2)], [(1, 2)], [(0, 1), (2, 2)], [(1, 1), (3, 2)], [(3, 3)], [(3, 3)]]
+    seen = []
+    for flag in (0, SMALL):
+        stream, seq, waits = _simulate(capi, 2, 0, 6, chains + [[(0, 1 | flag), (1, 1), (4, 2)], [(5, 2)]])
+        a, b = int(stream[0]), int(stream[1])
+        assert a != b and stream[:6].tolist() == [a, b, a, b, b, b] and not waits[:6].any()
+        other = b if stream[6] == a else a
+        assert waits[6, other] > 0 and np.count_nonzero(waits[6]) == 1
+        seen.append((int(stream[6]), int(stream[7])))
+    assert seen[1][0] == b and seen[0][0] == a                          # (the turn would have been the first chain's stream)
+    assert seen[0][1] == seen[1][1]
 
 
 def test_executor_lets_writers_of_different_parts_overlap(capi):
