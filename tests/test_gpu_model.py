@@ -221,7 +221,8 @@ def test_two_block_language_model_training_step(mods, dtype):
 
 
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
-@pytest.mark.parametrize("N_v,tile_v", [(7, 7), (1001, 1001), (1030, 301), (4097, 1024), (16385, 4000), (50257, 8192), (70000, 9000)])
+@pytest.mark.parametrize("N_v,tile_v", [(7, 7), (1001, 1001), (1030, 301), (4097, 1024), (16385, 4000), (50257, 8192), (60001, 7001), (65536, 8192),
+                                         (70000, 9000)])
 def test_cross_entropy_column_kernels(mods, dtype, N_v, tile_v):
     """One instance of the one-pass loss kernel after the other (and the general way for a column that no instance holds):
     odd vocabularies, tiles that are no multiple of a vector, labels at both ends of a tile and outside the vocabulary."""
