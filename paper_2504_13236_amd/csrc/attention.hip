@@ -33,7 +33,6 @@ namespace {
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 
 constexpr int kWgRows = 128;   // rows owned by a workgroup
-constexpr int kSplitMax = 512; // workgroups of 128 rows up to which the split form is taken
 constexpr int kHalfRows = 64;  // ... in the form that splits the streamed blocks between two pairs of waves (SPLIT below)
 constexpr int kBlk = 64;       // rows streamed per iteration
 constexpr float kLog2e = 1.4426950408889634f;
@@ -788,6 +787,63 @@ template <bool SPLIT> BwdKernel dkv_kernel_of(int dtype, int H) {
     if (dtype == NNT_F32) return H == 64 ? attn_dkv<F32Traits<64>, SPLIT> : attn_dkv<F32Traits<128>, SPLIT>;
     return H == 64 ? attn_dkv<Bf16Traits<64>, SPLIT> : attn_dkv<Bf16Traits<128>, SPLIT>;
 }
+enum AttnKernel { kAttnFwd = 0, kAttnDq = 1, kAttnDkv = 2 };
+
+// Where 64 rows per workgroup, with the waves sharing the streamed blocks, beat 128 rows: by the times of both forms on 16 to 512
+// workgroups of 128 rows (above that, 128 rows as ever), 1 to 32 of them for a (batch, head) pair, whole tiles and ragged
+// ones; the figures are the times with 128 rows over those with 64.
+// * Tiles of up to 64 positions fill two or fewer of the four waves with 128 rows.  fp32 gains (1.1 to 1.3), bf16 does not (0.85
+//   to 1.0); tiles of 32, which leave two waves idle either way, gain in the forward kernel only (1.0 to 1.2; 0.9 to 1.0).
+// * As many workgroups of 64 rows as compute units, or fewer: 1.3 to 1.8 in fp32, 1.0 to 1.4 in bf16.
+// * Without the mask all workgroups are equally long, and what counts is how many the fullest unit holds.  As many of 64 rows as
+//   of 128 (ragged tiles): 1.25 to 1.7, bf16 1.0 to 1.25.  Two of 64 rows instead of one of 128: 0.93 to 0.99 forward, 0.75 to
+//   0.9 with head size 128, a little more than 1 only in the backward kernels of head size 64 and in bf16, where a unit runs two
+//   workgroups in not much more than the time of one (dK and dV with head size 128, one to a unit: 0.75).  Three instead
+//   of two: fp32 0.95 to 1.2; bf16 0.7 to 0.9 except forward and dQ of head size 64 (1.0 to 1.17).  Four instead of two: 0.7 to 0.95.
+// * Under the mask the row blocks of a pair are of unequal length, and shorter ones even out the launch as long as the units are
+//   not full anyway.  The measure is the work in whole row blocks for n row blocks per (batch, head) pair: in fp32
+//   W (n + 1) / 2n for W pairs of workgroups of 64 rows, in bf16 W (n + 2) / 2n for W workgroups of 128; 1.1 to 1.8
+//   below the limits, 0.75 to 0.97 above.
+struct SplitRule {
+    int one;                        // causal, one row block per pair: most workgroups of 128 rows
+    int causal;                     // causal, more: most whole row blocks' work
+    int two_for_one, three_for_two; // not causal: row blocks per pair from which it pays
+};
+constexpr int kNever = 1 << 30;
+const SplitRule kSplitRule[2][2][3] = {      // forward, dQ, dK and dV
+    {{{512, 290, kNever, 1}, {512, 312, 4, 1}, {512, 360, 3, 1}},                      // fp32, head size 64
+     {{512, 190, kNever, 1}, {512, 192, kNever, 1}, {512, 220, kNever, 1}}},           // fp32, 128
+    {{{384, 336, 4, 4}, {0, 300, 4, 4}, {256, 288, 4, kNever}},                        // bf16, 64
+     {{256, 262, 8, kNever}, {256, 270, 8, kNever}, {0, 165, kNever, kNever}}}};       // bf16, 128
+
+bool split_rows(AttnKernel which, int dtype, const AttnGeom& g) {
+    const bool bf = dtype == NNT_BF16;
+    const SplitRule& r = kSplitRule[bf][g.H == 128][which];
+    const int last = g.Ns - (g.gs - 1) * g.bs;
+    const int64_t pairs = (int64_t)g.Nb * g.Nh;
+    const int64_t n = (int64_t)(g.gs - 1) * ((g.bs + kWgRows - 1) / kWgRows) + (last + kWgRows - 1) / kWgRows;
+    const int64_t halves = (int64_t)(g.gs - 1) * ((g.bs + kHalfRows - 1) / kHalfRows) + (last + kHalfRows - 1) / kHalfRows;
+    if (pairs * n > 512) return false;
+    if (g.bs <= 64) return g.bs <= 32 ? which == kAttnFwd : !bf;
+    if (pairs * halves <= 256) return true;
+    if (g.causal) {
+        // (head size 128 in fp32 is the form that gains least on whole row blocks; ragged tiles, a seventh of whose rows in
+        // blocks of 128 do not exist, gain 1.0 to 1.3 up to 512)
+        if (n == 1 || (!bf && g.H == 128 && 12 * n >= 7 * halves)) return pairs * n <= r.one;
+        return (bf ? pairs * n * (n + 2) : (pairs * halves + 1) / 2 * (n + 1)) <= 2 * n * r.causal;
+    }
+    const int64_t whole = (pairs * n + 255) / 256, split = (pairs * halves + 255) / 256;      // of them on the fullest unit
+    if (split <= whole) return true;
+    return split == whole + 1 && n >= (whole == 1 ? r.two_for_one : r.three_for_two);
+}
+
+// The geometry for one of the kernels: rows per workgroup chosen.
+AttnGeom rows_for(AttnKernel which, int dtype, AttnGeom g) {
+    g.split = split_rows(which, dtype, g);
+    if (g.split) g.nblk = (g.bs + kHalfRows - 1) / kHalfRows;
+    return g;
+}
+
 FwdKernel fwd_kernel(int dtype, const AttnGeom& g) { return g.split ? fwd_kernel_of<true>(dtype, g.H) : fwd_kernel_of<false>(dtype, g.H); }
 BwdKernel dq_kernel(int dtype, const AttnGeom& g) { return g.split ? dq_kernel_of<true>(dtype, g.H) : dq_kernel_of<false>(dtype, g.H); }
 BwdKernel dkv_kernel(int dtype, const AttnGeom& g) { return g.split ? dkv_kernel_of<true>(dtype, g.H) : dkv_kernel_of<false>(dtype, g.H); }
@@ -828,21 +884,13 @@ int32_t check_attn(nnt_ctx* ctx, const char* who, std::initializer_list<const nn
     return NNT_OK;
 }
 
-// Rows per workgroup: 64, with the waves sharing the streamed blocks, where workgroups of 128 would be at most kSplitMax, two for every
-// compute unit: fp32, 36 pairs of 1000 positions (288 workgroups), forward and backward 378 -> 284 us; 24 pairs of 1024
-// (192) 368 -> 269 us.  Above that the chip is full either way, and 128 rows read every streamed block half as often.
-void choose_rows(AttnGeom* g) {
-    g->nblk = (g->bs + kWgRows - 1) / kWgRows;
-    g->split = (int64_t)g->Nb * g->Nh * g->gs * g->nblk <= kSplitMax;
-    if (g->split) g->nblk = (g->bs + kHalfRows - 1) / kHalfRows;
-}
-
 AttnGeom geom_of(const nnt_tensor* q, float scale, int causal) {
     AttnGeom g;
     g.H = (int)q->shape[0]; g.Ns = (int)q->shape[1]; g.Nb = (int)q->shape[2]; g.Nh = (int)q->shape[3];
     g.bs = (int)q->base[1]; g.bb = (int)q->base[2]; g.bh = (int)q->base[3];
     g.gs = (int)q->grid[1]; g.gb = (int)q->grid[2]; g.gh = (int)q->grid[3];
-    choose_rows(&g);
+    g.nblk = (g.bs + kWgRows - 1) / kWgRows;
+    g.split = 0;
     g.nstep = (g.bs + kBlk - 1) / kBlk;
     g.tile0 = 0;
     g.causal = causal;
@@ -886,7 +934,8 @@ int32_t geom_of_windows(nnt_ctx* ctx, const char* who, std::initializer_list<std
     g.H = (int)H; g.Ns = (int)first->shape[1]; g.Nb = (int)first->shape[2]; g.Nh = N_h;
     g.bs = (int)first->base[1]; g.bb = (int)first->base[2]; g.bh = (int)stats->base[3];
     g.gs = (int)first->grid[1]; g.gb = (int)first->grid[2]; g.gh = (int)stats->grid[3];
-    choose_rows(&g);
+    g.nblk = (g.bs + kWgRows - 1) / kWgRows;
+    g.split = 0;
     g.nstep = (g.bs + kBlk - 1) / kBlk;
     g.tile0 = 0;
     g.causal = causal;
@@ -905,6 +954,20 @@ double visible_pairs(int64_t Ns, int64_t q0, int64_t q1, int causal) {
     return 0.5 * ((double)q1 * (q1 + 1) - (double)q0 * (q0 + 1));
 }
 
+// One task, two launches: the dQ kernel leaves log-sum-exp and D per query for the dK/dV kernel (by position, whatever the
+// rows per workgroup of either).
+int32_t launch_bwd(nnt_ctx* ctx, hipStream_t st, int dtype, const BwdArgs& a, double dkv_work) {
+    BwdArgs b = a;
+    for (AttnKernel which : {kAttnDq, kAttnDkv}) {
+        b.g = rows_for(which, dtype, a.g);
+        if (which == kAttnDkv) profile_mark(ctx, st, "attention_bwd_dkv", dkv_work, false);
+        const dim3 grid((unsigned)(b.g.Nb * b.g.Nh), (unsigned)(b.g.gs * b.g.nblk)), block(256);
+        hipLaunchKernelGGL(which == kAttnDq ? dq_kernel(dtype, b.g) : dkv_kernel(dtype, b.g), grid, block, 0, st, b);
+        if (hipGetLastError() != hipSuccess) return NNT_EHIP;
+    }
+    return NNT_OK;
+}
+
 // the tiles of `t` whose sequence-tile coordinate is l, any batch / head tile
 std::vector<Access> seq_tile(nnt_tensor* t, int64_t l, int mode) {
     std::vector<Access> v;
@@ -919,7 +982,7 @@ int32_t nnt_attention_fwd(nnt_ctx* ctx, nnt_tensor* Q, nnt_tensor* K, nnt_tensor
     NNT_CHECK_CTX(ctx);
     int32_t rc = check_attn(ctx, "nnt_attention_fwd", {Q, K, V, B}, stats, scale);
     if (rc != NNT_OK) return rc;
-    AttnGeom g = geom_of(Q, scale, causal);
+    const AttnGeom g = rows_for(kAttnFwd, Q->dtype, geom_of(Q, scale, causal));
     FwdArgs a{g, Q->d_tiles, K->d_tiles, V->d_tiles, B->d_tiles, stats->d_tiles};
     const double pair_flops = 4.0 * g.H * g.Nb * g.Nh;   // two products, 2 flops per multiply-add
     const FwdKernel kernel = fwd_kernel(Q->dtype, g);
@@ -964,19 +1027,11 @@ int32_t nnt_attention_bwd(nnt_ctx* ctx, nnt_tensor* Q, nnt_tensor* K, nnt_tensor
     const double pair_flops = 2.0 * g.H * g.Nb * g.Nh;   // per product
     const double pairs = visible_pairs(g.Ns, 0, g.Ns, causal);
     const Access scr{&ctx->red_dep, 1, kReadWrite};
-    const BwdKernel k_dq = dq_kernel(Q->dtype, g), k_dkv = dkv_kernel(Q->dtype, g);
-    // one task, two launches: the dQ kernel leaves log-sum-exp and D per query for the dK/dV kernel
+    const int dtype = Q->dtype;
     OpTag tag(ctx, "attention_bwd_dq", 3.0 * pair_flops * pairs, false);
     return submit(ctx, {Q->all(kRead), K->all(kRead), V->all(kRead), B->all(kRead), stats->all(kRead), dB->all(kRead),
                         dQ->all(kWrite), dK->all(kWrite), dV->all(kWrite), scr},
-                  [=](hipStream_t st) {
-                      const dim3 grid((unsigned)(a.g.Nb * a.g.Nh), (unsigned)(a.g.gs * a.g.nblk)), block(256);
-                      hipLaunchKernelGGL(k_dq, grid, block, 0, st, a);
-                      if (hipGetLastError() != hipSuccess) return (int32_t)NNT_EHIP;
-                      profile_mark(ctx, st, "attention_bwd_dkv", 4.0 * pair_flops * pairs, false);
-                      hipLaunchKernelGGL(k_dkv, grid, block, 0, st, a);
-                      return hipGetLastError() == hipSuccess ? (int32_t)NNT_OK : (int32_t)NNT_EHIP;
-                  }, 2);
+                  [=](hipStream_t st) { return launch_bwd(ctx, st, dtype, a, 4.0 * pair_flops * pairs); }, 2);
 }
 
 int32_t nnt_attention_fwd_heads(nnt_ctx* ctx, nnt_tensor* QKV, float scale, int32_t causal, nnt_tensor* Bm, nnt_tensor* stats, int32_t N_h) {
@@ -984,6 +1039,7 @@ int32_t nnt_attention_fwd_heads(nnt_ctx* ctx, nnt_tensor* QKV, float scale, int3
     AttnGeom g;
     int32_t rc = geom_of_windows(ctx, "nnt_attention_fwd_heads", {{QKV, 3}, {Bm, 1}}, stats, N_h, scale, causal, &g);
     if (rc != NNT_OK) return rc;
+    g = rows_for(kAttnFwd, QKV->dtype, g);
     const int64_t N_e = (int64_t)g.H * g.Nh;
     FwdArgs a{g, QKV->d_tiles, QKV->d_tiles, QKV->d_tiles, Bm->d_tiles, stats->d_tiles,
               window_at(QKV, 0, N_e), window_at(QKV, 1, N_e), window_at(QKV, 2, N_e), window_at(Bm, 0, N_e)};
@@ -1013,15 +1069,8 @@ int32_t nnt_attention_bwd_heads(nnt_ctx* ctx, nnt_tensor* QKV, nnt_tensor* Bm, n
     const double pair_flops = 2.0 * g.H * g.Nb * g.Nh;
     const double pairs = visible_pairs(g.Ns, 0, g.Ns, causal);
     const Access scr{&ctx->red_dep, 1, kReadWrite};
-    const BwdKernel k_dq = dq_kernel(QKV->dtype, g), k_dkv = dkv_kernel(QKV->dtype, g);
+    const int dtype = QKV->dtype;
     OpTag tag(ctx, "attention_bwd_dq", 3.0 * pair_flops * pairs, false);
     return submit(ctx, {QKV->all(kRead), Bm->all(kRead), stats->all(kRead), dBm->all(kRead), dQKV->all(kWrite), scr},
-                  [=](hipStream_t st) {
-                      const dim3 grid((unsigned)(a.g.Nb * a.g.Nh), (unsigned)(a.g.gs * a.g.nblk)), block(256);
-                      hipLaunchKernelGGL(k_dq, grid, block, 0, st, a);
-                      if (hipGetLastError() != hipSuccess) return (int32_t)NNT_EHIP;
-                      profile_mark(ctx, st, "attention_bwd_dkv", 4.0 * pair_flops * pairs, false);
-                      hipLaunchKernelGGL(k_dkv, grid, block, 0, st, a);
-                      return hipGetLastError() == hipSuccess ? (int32_t)NNT_OK : (int32_t)NNT_EHIP;
-                  }, 2);
+                  [=](hipStream_t st) { return launch_bwd(ctx, st, dtype, a, 4.0 * pair_flops * pairs); }, 2);
 }

@@ -171,20 +171,22 @@ def test_fused_attention_rejects_bad_operands(mods):
 
 @pytest.mark.parametrize("causal", [1, 0])
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
-@pytest.mark.parametrize("h,N_s,N_b,N_h", [(64, 150, 20, 16), (128, 150, 20, 16), (64, 97, 16, 16)])
-def test_fused_attention_on_both_sides_of_the_row_split(mods, h, N_s, N_b, N_h, dtype, causal):
+@pytest.mark.parametrize("h,N_s,N_b,N_h,tile", [(64, 150, 20, 16, 96), (128, 150, 20, 16, 96), (64, 97, 16, 16, 96),
+                                                (128, 100, 12, 16, 100), (64, 500, 4, 10, 500), (128, 500, 4, 10, 500), (64, 70, 9, 16, 32)])
+def test_fused_attention_on_both_sides_of_the_row_split(mods, h, N_s, N_b, N_h, tile, dtype, causal):
     """Launches of more than 512 workgroups of 128 rows (the first two cases: 320 pairs, two row blocks each) take the kernels whose
-    waves own their rows alone, smaller ones (all cases above, and 256 pairs x 2 here) those whose waves share them."""
+    waves own their rows alone, small ones (all cases above) those whose waves share them.  Between 129 and 512 each
+    of the three kernels has a rule of its own: cases in which forward, dQ and dK/dV take different forms in one call."""
     capi, tiled = mods
     r = np.random.default_rng(h + N_s)
-    shape, base = (h, N_s, N_b, N_h), (h, 96, N_b, N_h)
+    shape, base = (h, N_s, N_b, N_h), (h, tile, N_b, N_h)
     Q, K, V, dB = (quant(r.standard_normal(shape), dtype) for _ in range(4))
     scale = 1.0 / math.sqrt(h)
     B, tmax, den, dQ, dK, dV = reference(Q, K, V, dB, bool(causal))
     with tiled.Context(n_streams=2) as ctx:
         tQ, tK, tV, tdB = (T(tiled, ctx, x, base, dtype) for x in (Q, K, V, dB))
         tB, tdQ, tdK, tdV = (tiled.TiledTensor(ctx, dtype, shape, base) for _ in range(4))
-        tS = tiled.TiledTensor(ctx, "f32", (2, N_s, N_b, N_h), (2, 96, N_b, N_h))
+        tS = tiled.TiledTensor(ctx, "f32", (2, N_s, N_b, N_h), (2, tile, N_b, N_h))
         capi.nnt_attention_fwd(ctx.h, tQ.h, tK.h, tV.h, scale, causal, tB.h, tS.h)
         capi.nnt_attention_bwd(ctx.h, tQ.h, tK.h, tV.h, tB.h, tS.h, tdB.h, scale, causal, tdQ.h, tdK.h, tdV.h)
         check(tB.download(), B, dtype, "attention fwd")
