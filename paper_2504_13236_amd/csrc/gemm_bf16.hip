@@ -152,8 +152,9 @@ struct LoaderR {
             }
         }
     }
+    // (nothing to do in a step whose k all exist where the edge falls between two vectors: rows beyond it are never stored)
     __device__ __forceinline__ void mend(int row0, int nrows, int k0, int kc, int tid) {
-        if (nrows < 8) return;
+        if (nrows < 8 || (k0 + BKT <= kc && ((nrows & 7) == 0 || row0 + ROWS <= nrows))) return;
 #pragma unroll
         for (int i = 0; i < NB; i++) {
             const int idx = tid + 256 * i;

@@ -94,10 +94,13 @@ __device__ __forceinline__ void gload_edge(f32x4 (&v)[ROWS / 64], const float* b
 
 // What gload_edge left in the registers, put in place once it has arrived: elements of a moved vector shifted back,
 // zeros for k beyond the chunk (in both operands: whatever stands for a missing k must not meet an infinity).  Rows
-// beyond the edge keep what was fetched for them: it only reaches results that are never stored.
+// beyond the edge keep what was fetched for them: it only reaches results that are never stored.  So a step whose k all
+// exist needs nothing where k is the contiguous index or the edge falls between two vectors; most steps of a macro-tile on
+// an edge are such (the test is the same for every lane).
 template <bool KF, int ROWS>
 __device__ __forceinline__ void mend_edge(f32x4 (&v)[ROWS / 64], int row0, int nrows, int k0, int kc, int tid) {
     if ((KF ? kc : nrows) < 4) return;
+    if (k0 + BK <= kc && (KF || (nrows & 3) == 0 || row0 + ROWS <= nrows)) return;
 #pragma unroll
     for (int i = 0; i < ROWS / 64; i++) {
         int r, k;
