@@ -358,6 +358,8 @@ static int pick_cfg(int bf16, int64_t m_max, int64_t n_max, int64_t n_tiles_big,
     // unit overlap one's stores with another's loads, one large workgroup cannot
     // (tiles that are not whole macro-tiles go to the ragged variant of that kernel: C4's tiles of 400 are 256 + 144 by 3 x 128 + 16)
     if (bf16 && k_max <= 128) return (m_max >= 256 && n_max >= 128) ? kCfgTall : kCfgWide;
+    // (the 256 x 256 shape has no form for edges: 160 x 1152 over 1152, 64 of them, 163 us on its register-staged kernel)
+    if (bf16 && (m_max % 256 != 0 || n_max % 256 != 0 || k_max % 64 != 0)) return kCfgTall;
     return kCfgSquare;
 }
 
