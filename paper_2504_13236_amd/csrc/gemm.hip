@@ -279,6 +279,28 @@ static const ShapeCost kCostBf16[3][3] = {
     {{kCfgSquare, 1, {0.0285}, 15.0}, {kCfgTall, 2, {0.0195, 0.0312}, 5.0}, {kCfgWide, 2, {0.0130, 0.0212}, 4.0}},
     {{kCfgTall, 2, {0.0225, 0.0335}, 6.0}, {kCfgWide, 2, {0.0131, 0.0225}, 4.0}, {kCfgWide, 2, {0.0131, 0.0225}, 4.0}},
     {{kCfgTall, 1, {0.043}, 8.0}, {kCfgMid, 2, {0.035, 0.043}, 4.0}, {kCfgSkinny64n64, 4, {0.028, 0.030, 0.034, 0.037}, 1.5}}};
+// A launch of X equal workgroups with a contraction of k: whole resident sets, then a last set spread over the units.
+static double launch_us(const ShapeCost& cd, int64_t X, int64_t k) {
+    const int64_t G = 256 * (int64_t)cd.occ, last = (X % G + 255) / 256;      // G: workgroups resident at a time
+    return (double)(X / G) * (cd.us_k[cd.occ - 1] * (double)k + cd.t0) + (last ? cd.us_k[last - 1] * (double)k + cd.t0 : 0.0);
+}
+// Whether a plan of which only some workgroups can take the direct-load kernel should run as two launches, one behind the
+// other, or all on the register-staged kernel in one: by the longest contraction on either side.  Where neither fills
+// the chip, the second launch costs its whole length again (fp32, 16 pairs of 128 x 261 over 261 on tiles of 128:
+// 59 us in two launches, 34 in one).
+static bool two_launches_pay(bool bf16, int cfg, bool ragged, int64_t n_fast, int64_t k_fast, int64_t n_rest, int64_t k_rest) {
+    const int shape = cfg == kCfgSkinny64n128 || cfg == kCfgResident ? kCfgMid : cfg;
+    const int general = bf16 && cfg == kCfgWide ? kCfgMid : shape;        // (what the register-staged kernels have for it)
+    const ShapeCost *fast = nullptr, *slow = nullptr;
+    for (int i = 0; i < 3; i++) {
+        const ShapeCost& f = bf16 ? kCostBf16[ragged ? kShapeRagged : kShapeWhole][i] : kCostF32[0][i];
+        const ShapeCost& s = bf16 ? kCostBf16[kShapeGeneral][i] : kCostF32[1][i];
+        if (f.cfg == shape && !fast) fast = &f;
+        if (s.cfg == general && !slow) slow = &s;
+    }
+    if (!fast || !slow) return true;
+    return launch_us(*fast, n_fast, k_fast) + launch_us(*slow, n_rest, k_rest) < launch_us(*slow, n_fast + n_rest, std::max(k_fast, k_rest));
+}
 // `act`: products with an activation on their result path, whose kernels exist for the two larger fp32 shapes.
 static ShapeChoice choose_shape(bool bf16, ShapeKind kind, const std::vector<int64_t>& tm, const std::vector<int64_t>& tn,
                                 const std::vector<int64_t>& ktot, bool may_split, bool act = false) {
@@ -304,11 +326,7 @@ static ShapeChoice choose_shape(bool bf16, ShapeKind kind, const std::vector<int
             if (ci == 0) w_tall = W;
             else if (m_max > 128 && w_tall >= 40) continue;
         }
-        // X equal workgroups: whole resident sets, then a last set spread over the units
-        auto group_time = [&](int64_t X, int64_t k) {
-            const int64_t last = (X % G + 255) / 256;
-            return (double)(X / G) * (cd.us_k[cd.occ - 1] * (double)k + cd.t0) + (last ? cd.us_k[last - 1] * (double)k + cd.t0 : 0.0);
-        };
+        auto group_time = [&](int64_t X, int64_t k) { return launch_us(cd, X, k); };
         const double t_plain = group_time(W, kmax);
         if (t_plain < best_t) { best_t = t_plain; best = {cd.cfg, 0, 1}; }
         if (!may_split) continue;
@@ -345,7 +363,8 @@ static ShapeKind shape_kind(bool bf, bool akf, bool bkf, int64_t m, int64_t n, i
 }
 
 // Products with batch axes (attention).  `kk`: both operands are k-contiguous (A read transposed, B as [k, n]).
-static int pick_cfg(int bf16, int64_t m_max, int64_t n_max, int64_t n_tiles_big, int64_t k_max, bool kk = false) {
+// `kind`: what most of the work needs.
+static int pick_cfg(int bf16, int64_t m_max, int64_t n_max, int64_t n_tiles_big, int64_t k_max, bool kk, ShapeKind kind) {
     // fp32 products whose whole contraction is a head size and whose result is score-shaped: bound by their result
     // stores, which a workgroup waits out before it ends, so the shape of which a compute unit holds three
     if (!bf16 && kk && k_max <= 64 && m_max >= 64 && n_max >= 128) return kCfgResident;
@@ -358,8 +377,9 @@ static int pick_cfg(int bf16, int64_t m_max, int64_t n_max, int64_t n_tiles_big,
     // unit overlap one's stores with another's loads, one large workgroup cannot
     // (tiles that are not whole macro-tiles go to the ragged variant of that kernel: C4's tiles of 400 are 256 + 144 by 3 x 128 + 16)
     if (bf16 && k_max <= 128) return (m_max >= 256 && n_max >= 128) ? kCfgTall : kCfgWide;
-    // (the 256 x 256 shape has no form for edges: 160 x 1152 over 1152, 64 of them, 163 us on its register-staged kernel)
-    if (bf16 && (m_max % 256 != 0 || n_max % 256 != 0 || k_max % 64 != 0)) return kCfgTall;
+    // the 256 x 256 shape has no direct-load form for edges (160 x 1152 over 1152, 64 of them: 163 us on its register-staged
+    // kernel, 61 on the 256 x 128 one); of the register-staged kernels it is the better one (704 x 3192 over 1515, 24: 374 us, 473)
+    if (bf16 && kind == kShapeRagged) return kCfgTall;
     return kCfgSquare;
 }
 
@@ -405,9 +425,9 @@ extern "C" int32_t nnt_tile_gemm(void* stream, int32_t dtype_in, int32_t dtype_o
     g.alpha = alpha;
     g.beta = beta;
     int bm, bn;
-    int cfg = pick_cfg(bf, m, n, ((m + 255) / 256) * ((n + 255) / 256) * batch, k, opA == NNT_OP_T && opB == NNT_OP_N);
-    if (batch == 1 && cfg != kCfgResident)
-        cfg = choose_shape(bf, shape_kind(bf, opA == NNT_OP_T, opB == NNT_OP_N, m, n, k, g.one_chunk.vec_ok == 3), {m}, {n}, {k}, false).cfg;
+    const ShapeKind kind = shape_kind(bf, opA == NNT_OP_T, opB == NNT_OP_N, m, n, k, g.one_chunk.vec_ok == 3);
+    int cfg = pick_cfg(bf, m, n, ((m + 255) / 256) * ((n + 255) / 256) * batch, k, opA == NNT_OP_T && opB == NNT_OP_N, kind);
+    if (batch == 1 && cfg != kCfgResident) cfg = choose_shape(bf, kind, {m}, {n}, {k}, false).cfg;
     // debugging aid: NNT_TILE_GEMM_CFG=<number of a macro-tile configuration> overrides the choice for this entry point
     static const char* const force = getenv("NNT_TILE_GEMM_CFG");
     if (force) {      // (not kCfgResident: it exists for one operand form)
@@ -636,19 +656,26 @@ int32_t build_plan(nnt_ctx* ctx, int opA, nnt_tensor* A, int opB, nnt_tensor* B,
         for (int32_t q = P->tasks[ti].chunk0; q < P->tasks[ti].chunk0 + P->tasks[ti].nchunk; q++) ktot[ti] += P->chunks[q].k;
     int64_t k_max = 0;
     for (int64_t kq : ktot) k_max = std::max(k_max, kq);
-    P->cfg = pick_cfg(bf, m_max, n_max, big, k_max, P->akf && P->bkf);
+    // what the operands need: by the most demanding task, and by most of the work
+    ShapeKind kind = kShapeWhole;
+    double work_of[3] = {0.0, 0.0, 0.0};
+    for (size_t ti = 0; ti < P->tasks.size(); ti++)
+        for (int32_t q = P->tasks[ti].chunk0; q < P->tasks[ti].chunk0 + P->tasks[ti].nchunk; q++) {
+            const ShapeKind kq = shape_kind(bf, P->akf, P->bkf, geom[ti].m, geom[ti].n, P->chunks[q].k, P->chunks[q].vec_ok == 3);
+            kind = std::max(kind, kq);
+            work_of[kq] += (double)geom[ti].batch * geom[ti].m * geom[ti].n * P->chunks[q].k;
+        }
+    const ShapeKind most = work_of[kShapeGeneral] > work_of[kShapeWhole] + work_of[kShapeRagged] ? kShapeGeneral : std::min(kind, kShapeRagged);
+    P->cfg = pick_cfg(bf, m_max, n_max, big, k_max, P->akf && P->bkf, most);
     int S = 1;
     int64_t n_split = 0;
     if (nbat == 0 && !P->tasks.empty() && (P->cfg != kCfgResident || epi)) {
         // products of whole matrices: macro-tile shape and k-slices by the cost model (with an activation on the result path also
         // where the contraction is short: the kernels with the whole contraction in LDS have no such form)
         std::vector<int64_t> tm, tn;
-        ShapeKind kind = kShapeWhole;
         for (size_t ti = 0; ti < P->tasks.size(); ti++) {
             tm.push_back(geom[ti].m);
             tn.push_back(geom[ti].n);
-            for (int32_t q = P->tasks[ti].chunk0; q < P->tasks[ti].chunk0 + P->tasks[ti].nchunk; q++)
-                kind = std::max(kind, shape_kind(bf, P->akf, P->bkf, geom[ti].m, geom[ti].n, P->chunks[q].k, P->chunks[q].vec_ok == 3));
         }
         // (the activation forms keep the whole contraction in one workgroup: the slice sum does not know them)
         const ShapeChoice sc = choose_shape(bf, kind, tm, tn, ktot, epi == 0, epi != 0);
@@ -847,6 +874,16 @@ int32_t build_plan(nnt_ctx* ctx, int opA, nnt_tensor* A, int opB, nnt_tensor* B,
             for (const GemmWg& w : *list)
                 if (qualifies(w) && (task_rag[w.task] || !whole(w))) P->dl_ragged = true;
         P->op_nfast = std::stable_partition(P->wgs_op.begin(), P->wgs_op.end(), qualifies) - P->wgs_op.begin();
+        if (P->op_nfast > 0 && P->op_nfast < P->op_nwg) {
+            int64_t k[2] = {0, 0};
+            for (int64_t w = 0; w < P->op_nwg; w++) {
+                const GemmTask& t = P->tasks[P->wgs_op[w].task];
+                int64_t kw = 0;
+                for (int32_t q = t.chunk0; q < t.chunk0 + t.nchunk; q++) kw += P->chunks[q].k;
+                k[w >= P->op_nfast] = std::max(k[w >= P->op_nfast], kw);
+            }
+            if (!two_launches_pay(bf, P->cfg, P->dl_ragged, P->op_nfast, k[0], P->op_nwg - P->op_nfast, k[1])) P->op_nfast = 0;
+        }
         for (size_t ti = 0; ti + 1 < P->task_wg0.size(); ti++)
             P->task_nfast[ti] = std::stable_partition(P->wgs.begin() + P->task_wg0[ti], P->wgs.begin() + P->task_wg0[ti + 1], qualifies) -
                                 (P->wgs.begin() + P->task_wg0[ti]);

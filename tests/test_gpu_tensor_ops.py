@@ -816,3 +816,28 @@ def test_long_contractions_of_odd_extents(mods, m, n, k, opA, opB):
         got = tC.download().astype(np.float64)
     e = np.linalg.norm(got - ref) / np.linalg.norm(ref)
     assert e <= 2e-6, e
+
+
+# head size, positions, tile, batch members: more than 128 rows on ragged tiles (whole vectors, and tiles that are none), and
+# products of which only the tiles of whole vectors qualify for the direct-load kernels, few enough for one launch and too many
+RAGGED_BATCHED = [(160, 264, 136, 3), (192, 330, 300, 2), (64, 261, 128, 8), (128, 261, 128, 4), (64, 1301, 128, 24)]
+
+
+@pytest.mark.parametrize("gran", GRANS)
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("h,S,t,bat", RAGGED_BATCHED, ids=lambda c: str(c))
+def test_batched_products_on_ragged_tiles(mods, h, S, t, bat, dtype, gran):
+    """The attention layer's products with batch axes (scores K^T Q, V P, and the adjoint's Q P^T) where plans choose between
+    shapes and between one launch and two, against the oracle's contraction."""
+    capi, tiled = mods
+    r = rng(h + S)
+    Q, K, P = (quant(r.standard_normal(s), dtype) for s in ((h, S, bat), (h, S, bat), (S, S, bat)))
+    with tiled.Context(n_streams=2, granularity=gran) as ctx:
+        tQ, tK, tP = T(tiled, ctx, Q, (h, t, bat), dtype), T(tiled, ctx, K, (h, t, bat), dtype), T(tiled, ctx, P, (t, t, bat), dtype)
+        tS, tO, tR = (tiled.TiledTensor(ctx, dtype, s, b) for s, b in (((S, S, bat), (t, t, bat)), ((h, S, bat), (h, t, bat)), ((h, S, bat), (h, t, bat))))
+        capi.nnt_gemm(ctx.h, 0.125, 1, tK.h, 0, tQ.h, 0.0, tS.h, 1, 1, None)
+        capi.nnt_gemm(ctx.h, 1.0, 0, tK.h, 0, tP.h, 0.0, tO.h, 1, 1, None)
+        capi.nnt_gemm(ctx.h, 1.0, 0, tQ.h, 1, tP.h, 0.0, tR.h, 1, 1, None)
+        check(tS.download(), D.contract(0.125, "T", K, "N", Q, 0.0, None, 1, 1), dtype, "K^T Q")
+        check(tO.download(), D.contract(1.0, "N", K, "N", P, 0.0, None, 1, 1), dtype, "V P")
+        check(tR.download(), D.contract(1.0, "N", Q, "T", P, 0.0, None, 1, 1), dtype, "Q P^T")
