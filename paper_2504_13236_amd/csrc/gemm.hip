@@ -267,7 +267,7 @@ static void xcd_interleave(std::vector<GemmWg>& wgs, int bm, int bn) {
 // a second pass over the fp32 partial sums: one more launch, about 6 us, and their bytes at 3.5 TB/s.
 constexpr int kSplitStep = 64;
 constexpr int64_t kMinSliceK = 128;
-struct ShapeChoice { int cfg; int64_t n_split; int s; };
+struct ShapeChoice { int cfg; int64_t n_split; int s; double us; };
 struct ShapeCost { int cfg, occ; double us_k[4], t0; };
 // `whole`: every macro-tile takes the direct-load kernels; `ragged`: their forms for edges and short k-steps; `general`:
 // operands that only the register-staged kernels take (figures of odd leading dimensions).
@@ -284,30 +284,35 @@ static double launch_us(const ShapeCost& cd, int64_t X, int64_t k) {
     const int64_t G = 256 * (int64_t)cd.occ, last = (X % G + 255) / 256;      // G: workgroups resident at a time
     return (double)(X / G) * (cd.us_k[cd.occ - 1] * (double)k + cd.t0) + (last ? cd.us_k[last - 1] * (double)k + cd.t0 : 0.0);
 }
+// What the register-staged kernel of a shape takes (bf16 128 x 128: one kernel for both wave layouts; 256 x 256: 60 ns per k
+// where the operands reach it, 704 x 3192 over 1515, 24 of them).
+static const ShapeCost& staged_cost(bool bf16, int cfg) {
+    static const ShapeCost square = {kCfgSquare, 1, {0.060}, 8.0};
+    const int shape = bf16 ? (cfg == kCfgWide ? kCfgMid : cfg) : (cfg == kCfgSkinny64n128 || cfg == kCfgResident ? kCfgMid : cfg);
+    const ShapeCost* c = bf16 ? kCostBf16[kShapeGeneral] : kCostF32[1];
+    for (int i = 0; i < 3; i++)
+        if (c[i].cfg == shape) return c[i];
+    return square;
+}
 // Whether a plan of which only some workgroups can take the direct-load kernel should run as two launches, one behind the
 // other, or all on the register-staged kernel in one: by the longest contraction on either side.  Where neither fills
 // the chip, the second launch costs its whole length again (fp32, 16 pairs of 128 x 261 over 261 on tiles of 128:
 // 59 us in two launches, 34 in one).
 static bool two_launches_pay(bool bf16, int cfg, bool ragged, int64_t n_fast, int64_t k_fast, int64_t n_rest, int64_t k_rest) {
-    const int shape = cfg == kCfgSkinny64n128 || cfg == kCfgResident ? kCfgMid : cfg;
-    const int general = bf16 && cfg == kCfgWide ? kCfgMid : shape;        // (what the register-staged kernels have for it)
-    const ShapeCost *fast = nullptr, *slow = nullptr;
+    const int shape = !bf16 && (cfg == kCfgSkinny64n128 || cfg == kCfgResident) ? kCfgMid : cfg;
+    const ShapeCost& staged = staged_cost(bf16, cfg);
     for (int i = 0; i < 3; i++) {
-        const ShapeCost& f = bf16 ? kCostBf16[ragged ? kShapeRagged : kShapeWhole][i] : kCostF32[0][i];
-        const ShapeCost& s = bf16 ? kCostBf16[kShapeGeneral][i] : kCostF32[1][i];
-        if (f.cfg == shape && !fast) fast = &f;
-        if (s.cfg == general && !slow) slow = &s;
+        const ShapeCost& fast = bf16 ? kCostBf16[ragged ? kShapeRagged : kShapeWhole][i] : kCostF32[0][i];
+        if (fast.cfg == shape) return launch_us(fast, n_fast, k_fast) + launch_us(staged, n_rest, k_rest) < launch_us(staged, n_fast + n_rest, std::max(k_fast, k_rest));
     }
-    if (!fast || !slow) return true;
-    return launch_us(*fast, n_fast, k_fast) + launch_us(*slow, n_rest, k_rest) < launch_us(*slow, n_fast + n_rest, std::max(k_fast, k_rest));
+    return true;
 }
 // `act`: products with an activation on their result path, whose kernels exist for the two larger fp32 shapes.
 static ShapeChoice choose_shape(bool bf16, ShapeKind kind, const std::vector<int64_t>& tm, const std::vector<int64_t>& tn,
                                 const std::vector<int64_t>& ktot, bool may_split, bool act = false) {
     const ShapeCost* cands = bf16 ? kCostBf16[kind] : kCostF32[kind == kShapeGeneral];
     const int ncand = act ? 2 : 3;
-    ShapeChoice best = {cands[0].cfg, 0, 1};
-    double best_t = 1e30;
+    ShapeChoice best = {cands[0].cfg, 0, 1, 1e30};
     int64_t kmax = 0, kmin = INT64_MAX;
     for (int64_t kq : ktot) { kmax = std::max(kmax, kq); kmin = std::min(kmin, kq); }
     int64_t w_tall = 0, m_max = 0;
@@ -328,7 +333,7 @@ static ShapeChoice choose_shape(bool bf16, ShapeKind kind, const std::vector<int
         }
         auto group_time = [&](int64_t X, int64_t k) { return launch_us(cd, X, k); };
         const double t_plain = group_time(W, kmax);
-        if (t_plain < best_t) { best_t = t_plain; best = {cd.cfg, 0, 1}; }
+        if (t_plain < best.us) best = {cd.cfg, 0, 1, t_plain};
         if (!may_split) continue;
         const int64_t R = W % G;
         const int64_t ns_cands[2] = {W, (W > G && R > 0) ? R : 0};
@@ -339,7 +344,7 @@ static ShapeChoice choose_shape(bool bf16, ShapeKind kind, const std::vector<int
                 if (part < kMinSliceK || part * (sp - 1) >= kmin) break;
                 const double t = (ns < W ? group_time(W - ns, kmax) : 0.0) + group_time(ns * sp, part) + 6.0 +
                                  (double)ns * bm * bn * 4.0 * (sp + 1) / 3.5e6;
-                if (t < best_t) { best_t = t; best = {cd.cfg, ns, sp}; }
+                if (t < best.us) best = {cd.cfg, ns, sp, t};
             }
         }
     }
@@ -659,10 +664,12 @@ int32_t build_plan(nnt_ctx* ctx, int opA, nnt_tensor* A, int opB, nnt_tensor* B,
     // what the operands need: by the most demanding task, and by most of the work
     ShapeKind kind = kShapeWhole;
     double work_of[3] = {0.0, 0.0, 0.0};
+    std::vector<char> staged(P->tasks.size(), 0);       // tasks that only the register-staged kernels take
     for (size_t ti = 0; ti < P->tasks.size(); ti++)
         for (int32_t q = P->tasks[ti].chunk0; q < P->tasks[ti].chunk0 + P->tasks[ti].nchunk; q++) {
             const ShapeKind kq = shape_kind(bf, P->akf, P->bkf, geom[ti].m, geom[ti].n, P->chunks[q].k, P->chunks[q].vec_ok == 3);
             kind = std::max(kind, kq);
+            if (kq == kShapeGeneral) staged[ti] = 1;
             work_of[kq] += (double)geom[ti].batch * geom[ti].m * geom[ti].n * P->chunks[q].k;
         }
     const ShapeKind most = work_of[kShapeGeneral] > work_of[kShapeWhole] + work_of[kShapeRagged] ? kShapeGeneral : std::min(kind, kShapeRagged);
@@ -678,7 +685,20 @@ int32_t build_plan(nnt_ctx* ctx, int opA, nnt_tensor* A, int opB, nnt_tensor* B,
             tn.push_back(geom[ti].n);
         }
         // (the activation forms keep the whole contraction in one workgroup: the slice sum does not know them)
-        const ShapeChoice sc = choose_shape(bf, kind, tm, tn, ktot, epi == 0, epi != 0);
+        ShapeChoice sc = choose_shape(bf, kind, tm, tn, ktot, epi == 0, epi != 0);
+        if (kind == kShapeGeneral && most != kShapeGeneral) {
+            // a few tiles keep the product off the direct-load kernels as a whole (5208 x 5585 over 576 on tiles of 400, bf16: the last
+            // column of tiles has odd lines): the shape for the others, and these in a launch of their own (176 -> 120 us), where that
+            // is clearly less (the cost of two launches is less certain than that of one)
+            ShapeChoice two = choose_shape(bf, most, tm, tn, ktot, epi == 0, epi != 0);
+            int bm2, bn2;
+            gemm_cfg_tile(bf, two.cfg, &bm2, &bn2);
+            int64_t n[2] = {0, 0};          // macro-tiles, of the others and of these
+            for (size_t ti = 0; ti < P->tasks.size(); ti++) n[staged[ti]] += ((tm[ti] + bm2 - 1) / bm2) * ((tn[ti] + bn2 - 1) / bn2);
+            const int s = two.n_split == n[0] + n[1] ? two.s : 1;         // (slices of only the last macro-tiles need not be theirs)
+            two.us += launch_us(staged_cost(bf, two.cfg), n[1] * s, k_max / s);
+            if (two.us < 0.85 * sc.us) sc = two;
+        }
         P->cfg = sc.cfg;
         S = sc.s;
         n_split = sc.n_split;
