@@ -71,8 +71,10 @@ constexpr int kCeTiles = 64;         // most vocabulary tiles of a column
 // finds maximum and sum of shifted exponentials, and writes the gradient (probabilities, minus one at the label) over it,
 // the column's statistics and its loss, which comes from the label's logit.  Bound by memory: one read and one write of
 // the logits.  bf16 logits stay packed and their exponentials are taken twice: with 28 instead of 56 registers for a
-// vocabulary of 50304 a compute unit holds two such workgroups, and one's reads and writes overlap with the other's.  The vectors of all vocabulary tiles are numbered through, `vt` to a tile and `nvec` in all; the addresses of
-// the column's tiles lie in LDS, so that no store waits for a look-up in the tile table.
+// vocabulary of 50304 a compute unit holds two such workgroups, and one's reads and writes overlap with the other's (the
+// 64 registers that leaves make the instances of seven and eight vectors spill 16 and 24 bytes).  The vectors of all
+// vocabulary tiles are numbered through, `vt` to a tile and `nvec` in all; the addresses of the column's tiles lie in LDS,
+// so that no store waits for a look-up in the tile table.
 template <typename T, int SLOTS, int NT>
 __global__ void __launch_bounds__(NT, (sizeof(T) == 2 && NT == 1024) ? 8 : 1) ce_column_kernel(const int32_t* labels, TiledView X, TiledView S, float* losses, int vt, int nvec) {
     constexpr int V = RawVec<T>::V, NW = NT / 64;

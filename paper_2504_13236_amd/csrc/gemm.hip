@@ -260,8 +260,9 @@ static void xcd_interleave(std::vector<GemmWg>& wgs, int bm, int bn) {
 // compute units; `occ` of them fit on a unit at a time, and `us_k[c - 1]` is what a unit that holds c of them takes per
 // unit of k, `t0` what a set of them takes besides (first loads, result stores), all in us as measured with
 // nnt_tile_gemm on 16 to 1024 macro-tiles of k = 256, 1024 and 4096 (N N, T N and N T agree within 10 % in fp32 and in the
-// direct-load bf16 kernels).  Large macro-tiles have the better rate on a full chip (fp32 128 x 128: 0.56 TFLOP/s per unit
-// against 0.49 for 64 x 64; bf16 256 x 256: 4.8, 256 x 128: 4.5, 128 x 128: 3.1), small ones the shorter time where
+// direct-load bf16 kernels).  `occ` follows from each kernel's registers and LDS and has to be changed with them.  Large
+// macro-tiles have the better rate on a full chip (fp32 128 x 128: 0.56 TFLOP/s per unit against 0.49 for 64 x 64; bf16
+// 256 x 256: 4.6, 256 x 128: 4.2, 128 x 128: 3.1), small ones the shorter time where
 // there are fewer macro-tiles than places: a unit with one 128 x 128 fp32 workgroup takes 62 ns per k, with one 64 x 64
 // workgroup 24.  Cutting the contraction into s slices turns a launch (or its last, partial set) into 1/s of its length and adds
 // a second pass over the fp32 partial sums: one more launch, about 6 us, and their bytes at 3.5 TB/s.
@@ -277,7 +278,7 @@ static const ShapeCost kCostF32[2][3] = {
     {{kCfgSquare, 2, {0.130, 0.183}, 5.0}, {kCfgMid, 4, {0.0885, 0.112, 0.140, 0.170}, 3.0}, {kCfgSkinny64n64, 4, {0.046, 0.063, 0.079, 0.094}, 2.0}}};
 static const ShapeCost kCostBf16[3][3] = {
     {{kCfgSquare, 1, {0.0285}, 15.0}, {kCfgTall, 2, {0.0195, 0.0312}, 5.0}, {kCfgWide, 2, {0.0130, 0.0212}, 4.0}},
-    {{kCfgTall, 2, {0.0225, 0.0335}, 6.0}, {kCfgWide, 2, {0.0131, 0.0225}, 4.0}, {kCfgWide, 2, {0.0131, 0.0225}, 4.0}},
+    {{kCfgTall, 2, {0.0225, 0.0335}, 6.0}, {kCfgWide, 2, {0.0131, 0.0225}, 4.0}, {kCfgWide, 0, {}, 0.0}},       // (two shapes)
     {{kCfgTall, 1, {0.043}, 8.0}, {kCfgMid, 2, {0.035, 0.043}, 4.0}, {kCfgSkinny64n64, 4, {0.028, 0.030, 0.034, 0.037}, 1.5}}};
 // A launch of X equal workgroups with a contraction of k: whole resident sets, then a last set spread over the units.
 static double launch_us(const ShapeCost& cd, int64_t X, int64_t k) {
@@ -319,14 +320,18 @@ static ShapeChoice choose_shape(bool bf16, ShapeKind kind, const std::vector<int
     for (int64_t mq : tm) m_max = std::max(m_max, mq);
     for (int ci = 0; ci < ncand; ci++) {
         const ShapeCost& cd = cands[ci];
+        if (cd.occ == 0) continue;
         int bm, bn;
         gemm_cfg_tile(bf16, cd.cfg, &bm, &bn);
         const int64_t G = 256 * (int64_t)cd.occ;      // workgroups resident at a time
         int64_t W = 0;
         for (size_t i = 0; i < tm.size(); i++) W += ((tm[i] + bm - 1) / bm) * ((tn[i] + bn - 1) / bn);
-        // Ragged bf16 products of tiles of more than 128 rows change to the 128 x 128 shape only below 40 macro-tiles of 256 x 128:
-        // from there to 256 it would still be the faster one (240 workgroups instead of 120 at k = 800: 15 us by the table
-        // instead of 24), but which kernel takes products on tiles of 400 is fixed by a test.
+        // Ragged bf16 products of tiles of more than 128 rows change to the 128 x 128 shape only below 40 macro-tiles of 256 x 128.
+        // Alone it is often the faster one beyond that too (1200 x 2496 over 800: 24 us, 28; over 1165 random ones of 256 to 9000
+        // rows and columns on tiles of 200 to 1000 by a tenth, with 16 to 17 ns per k and 6 us for it, which chunks of odd
+        // lengths take), but twice the workgroups leave the products of the other stream no units: linear layers and
+        // MLPs, forward and backward on two streams, 203 -> 184 us (872 wide), 86 -> 98 (1696 x 5952, 896 tokens),
+        // 190 -> 205 (1280 wide, 1152 tokens).
         if (bf16 && kind == kShapeRagged) {
             if (ci == 0) w_tall = W;
             else if (m_max > 128 && w_tall >= 40) continue;
