@@ -34,7 +34,7 @@ __device__ __forceinline__ const T* uniform_ptr(const T* p) {
 }
 
 constexpr int BK = 16;
-constexpr int kSumSteps = 32;  // k-steps between two moves of the sums (512 k)
+constexpr int kSumSteps = 16;  // k-steps between two moves of the sums (256 k)
 constexpr int KP = BK + 4;   // padded k extent of a k-fast LDS row (conflict-free 128-bit reads)
 
 // Four floats at any address that a float may have: global memory takes 16-byte accesses at every multiple of 4 bytes,

@@ -37,7 +37,7 @@ namespace {
 
 constexpr int kBK = 16;                                  // k-step
 constexpr int kStages = 5;
-constexpr int kSumPairs = 16;                            // pairs of k-steps between two moves of the sums (512 k)
+constexpr int kSumPairs = 8;                             // pairs of k-steps between two moves of the sums (256 k)
 
 // Byte offset, from (first row, first k) of an operand's ROWS x 16 block, of what this lane fetches
 // in load instruction j (0 .. ROWS / 64 - 1) of its wave; the data lands in LDS at

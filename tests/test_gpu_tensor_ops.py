@@ -799,11 +799,11 @@ def test_linear_layers_of_any_size(mods, case, dtype):
 @pytest.mark.parametrize("opA,opB", [(0, 0), (0, 1), (1, 0), (1, 1)])
 @pytest.mark.parametrize("m,n,k", [(128, 231, 6514), (126, 77, 3001), (500, 300, 2050), (1030, 1027, 1101), (128, 384, 6528)])
 def test_long_contractions_of_odd_extents(mods, m, n, k, opA, opB):
-    """fp32 products whose contraction is longer than the 512 after which the partial sums leave the matrix accumulators, on
+    """fp32 products whose contraction is several times the 256 after which the partial sums leave the matrix accumulators, on
     operands that only the register-staged kernels take (the last: the direct-load ones): few macro-tiles whose slices are
-    longer than that, and many without slices.  In the 2-norm: a chain of 512 additions in random order is off by about
-    0.29 * 2^-24 * sqrt(512 / 2) of its sum, 3e-7, and so are the k / 512 chains together; 2e-6 leaves room for both roundings of
-    the slice sums and for a longer chain's tail.  One wrong register of the sixteen of a block would be 1e-2."""
+    longer than that, and many without slices.  In the 2-norm: a chain of 256 additions in random order is off by about
+    0.29 * 2^-24 * sqrt(256 / 2) of its sum, 2e-7, and so are the k / 256 chains together; 2e-6 leaves room for both roundings of
+    the slice sums and for chains twice as long.  One wrong register of the sixteen of a block would be 1e-2."""
     capi, tiled = mods
     r = rng(m + n + k)
     A = r.standard_normal((m, k) if opA == 0 else (k, m)).astype(np.float32)
