@@ -202,13 +202,15 @@ int32_t submit(nnt_ctx* ctx, const std::vector<Access>& acc,
     // While a capture is open only streams 0 and 1 take tasks: ending a capture in which two forked
     // streams wait on each other's events has crashed inside the HIP runtime on this ROCm release.
     const int ns = ctx->capturing ? std::min(ctx->n_streams, 2) : ctx->n_streams;
-    // Taking a task to another stream costs the host an event and a wait, some 15 us, and the device a few; it pays only
-    // for tasks that run longer than that.  4 us at the rates of large operations (100 TFLOP/s, 4 TB/s) are 10 us and more for one this size (a threshold
-    // of 10 us serialised the bias gradients of a GPT-2-small block behind its products: 3745 -> 3800 us; without
-    // any, layer norm of few tokens, forward and backward, took 37 us instead of 26, the smallest block 327 instead of 316).  Operations that do not say what
-    // they do count as long.
-    constexpr double kSpreadSeconds = 4e-6;
-    const bool small = ctx->cur_label && ctx->cur_seconds < kSpreadSeconds;
+    // Taking a task to another stream costs the host an event and a wait and the device a few us; a task that is over sooner
+    // stays on a stream that it depends on.  Passes over memory: 4 us at the rate of large ones, 16 MB (layer norm of few
+    // tokens, forward and backward, 46 -> 16 to 24 us; eight GELU passes of 4 MB on one result, on four streams, 60 -> 34; at this
+    // size chains that could run side by side begin to lose, two passes of 15 MB in a row, 75 -> 86).  Products: 20 MFLOP (the
+    // smallest block 300 to 360 us on two streams, 268 so); they take 5 us and more each, and above that chains of them lose
+    // (eight chains of two, 256 x 1024 over 256, on four streams: 161 us where 0.4 GFLOP still counted as small, 92 spread).
+    // Operations that do not say what they do count as long.
+    constexpr double kSmallBytes = 16e6, kSmallFlops = 2e7;
+    const bool small = ctx->cur_label && ctx->cur_op_work < (ctx->cur_work_is_bytes ? kSmallBytes : kSmallFlops);
     const TaskPlan plan = plan_task(acc, ns, ctx->n_streams, ctx->serial, small, ctx->tail_seq, ctx->synced_seq, ctx->waited, &ctx->rr);
     const int chosen = plan.chosen;
     hipStream_t st = ctx->streams[chosen];

@@ -144,7 +144,7 @@ struct nnt_ctx {
     bool profiling = false;
     const char* cur_label = nullptr;
     double cur_work = 0.0;           // still to be counted by the profile
-    double cur_seconds = 0.0;        // what the whole operation takes at the rate of large ones
+    double cur_op_work = 0.0;        // of the whole operation
     bool cur_work_is_bytes = false;
     struct ProfileRec { std::string label; hipEvent_t start, stop; double work; bool bytes; int launches; };
     std::vector<ProfileRec> profile;
@@ -159,7 +159,7 @@ struct OpTag {
     OpTag(nnt_ctx* ctx, const char* label, double work, bool bytes) : c(ctx) {
         c->cur_label = label;
         c->cur_work = work;
-        c->cur_seconds = work / (bytes ? 4e12 : 100e12);
+        c->cur_op_work = work;
         c->cur_work_is_bytes = bytes;
     }
     ~OpTag() { c->cur_label = nullptr; c->cur_work = 0.0; }
