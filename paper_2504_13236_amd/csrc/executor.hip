@@ -245,6 +245,7 @@ int32_t submit(nnt_ctx* ctx, const std::vector<Access>& acc,
         NNT_HIP(ctx, hipEventRecord(prof.start, st));
     }
     ctx->cur_prof = timed ? &prof : nullptr;
+    ctx->cur_stream = chosen;
     int32_t rc = launch(st);
     ctx->cur_prof = nullptr;
     if (timed) {
@@ -280,18 +281,23 @@ int32_t submit(nnt_ctx* ctx, const std::vector<Access>& acc,
     return NNT_OK;
 }
 
-int32_t ensure_scratch(nnt_ctx* ctx, int64_t elems) {
-    if (elems <= ctx->red_scratch_elems) return NNT_OK;
+// Makes `*buf` at least `elems` floats for each of `parts` users; contents are not kept.
+static int32_t grow_scratch(nnt_ctx* ctx, float** buf, int64_t* have, int64_t elems, int parts) {
+    if (elems <= *have) return NNT_OK;
     if (ctx->capturing) return fail(ctx, NNT_ESTATE, "reduction scratch must exist before capture: run the operation once first");
     int32_t rc = sync_all(ctx);
     if (rc != NNT_OK) return rc;
-    if (ctx->red_scratch) NNT_HIP(ctx, hipFree(ctx->red_scratch));
-    ctx->red_scratch = nullptr;
-    ctx->red_scratch_elems = 0;
-    int64_t want = std::max<int64_t>(elems, 1 << 20);
-    NNT_HIP(ctx, hipMalloc((void**)&ctx->red_scratch, want * sizeof(float)));
-    ctx->red_scratch_elems = want;
+    if (*buf) NNT_HIP(ctx, hipFree(*buf));
+    *buf = nullptr;
+    *have = 0;
+    const int64_t want = std::max<int64_t>((elems + 63) / 64 * 64, 1 << 20);
+    NNT_HIP(ctx, hipMalloc((void**)buf, parts * want * sizeof(float)));
+    *have = want;
     return NNT_OK;
+}
+int32_t ensure_scratch(nnt_ctx* ctx, int64_t elems) { return grow_scratch(ctx, &ctx->red_scratch, &ctx->red_scratch_elems, elems, 1); }
+int32_t ensure_stream_scratch(nnt_ctx* ctx, int64_t elems) {
+    return grow_scratch(ctx, &ctx->stream_scratch, &ctx->stream_scratch_elems, elems, ctx->n_streams);
 }
 
 }  // namespace nnt
@@ -392,6 +398,7 @@ int32_t nnt_ctx_destroy(nnt_ctx* ctx) {
     for (hipEvent_t e : ctx->timing_pool) (void)hipEventDestroy(e);
     ctx->gemm_plans.clear();
     if (ctx->red_scratch) (void)hipFree(ctx->red_scratch);
+    if (ctx->stream_scratch) (void)hipFree(ctx->stream_scratch);
     if (ctx->own_streams)
         for (int s = 0; s < ctx->n_streams; s++) (void)hipStreamDestroy(ctx->streams[s]);
     delete ctx;
@@ -451,7 +458,7 @@ int32_t nnt_ctx_stats(nnt_ctx* ctx, nnt_exec_stats* out) {
     *out = ctx->stats;
     out->plans = (int64_t)ctx->gemm_plans.size();
     out->device_table_bytes = ctx->table_bytes;
-    out->device_workspace_bytes = ctx->red_scratch_elems * (int64_t)sizeof(float);
+    out->device_workspace_bytes = (ctx->red_scratch_elems + ctx->n_streams * ctx->stream_scratch_elems) * (int64_t)sizeof(float);
     plan_device_bytes(ctx, &out->device_table_bytes, &out->device_workspace_bytes);
     return NNT_OK;
 }

@@ -139,6 +139,11 @@ struct nnt_ctx {
     float* red_scratch = nullptr;
     int64_t red_scratch_elems = 0;
     nnt::TileDep red_dep;
+    // the same for tasks whose kernels follow each other inside the task: one part per stream, whose order keeps the
+    // tasks that use a part apart, so that tasks on different streams do not wait for one another's partial sums
+    float* stream_scratch = nullptr;
+    int64_t stream_scratch_elems = 0;        // per stream
+    int cur_stream = 0;                      // stream of the task whose launches are being issued
     // per-task timing (nnt_profile_*): what the operation being submitted is called and
     // how much algorithmic work it stands for; the first task of the operation carries it
     bool profiling = false;
@@ -189,6 +194,9 @@ void profile_mark(nnt_ctx* ctx, hipStream_t st, const char* label, double work, 
 int32_t submit(nnt_ctx* ctx, const std::vector<Access>& acc,
                const std::function<int32_t(hipStream_t)>& launch, int n_launches = 1);
 int32_t ensure_scratch(nnt_ctx* ctx, int64_t elems);
+int32_t ensure_stream_scratch(nnt_ctx* ctx, int64_t elems);
+// inside a task's launch function: the part of the stream it has been given (as large as every ensure_stream_scratch so far)
+inline float* stream_scratch_of(const nnt_ctx* ctx) { return ctx->stream_scratch + ctx->cur_stream * ctx->stream_scratch_elems; }
 int32_t static_scratch_setup();      // looks up the current device's address of the static scratch array (norm.hip)
 
 // Adam on several parameter tensors in one launch (elementwise.hip); the group owns small device tables.

@@ -501,6 +501,38 @@ def test_layernorm_tensor(mods, gran, dtype, shape, base):
         assert e <= TOL[dtype], e
 
 
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("shape,base", [((128, 1, 1), (32, 1, 1)), ((520, 9, 1), (520, 4, 1)), ((1000, 67, 9), (400, 32, 2)), ((4096, 19, 2), (1024, 19, 2)),
+                                        ((4104, 3, 3), (4104, 3, 3)), ((8192, 5, 2), (8192, 5, 1)), ((8200, 3, 1), (8200, 3, 1)), ((512, 300, 17), (512, 300, 17)),
+                                        ((63, 5, 2), (63, 5, 2)), ((777, 130, 3), (300, 100, 3)), ((4097, 3, 1), (4097, 3, 1))])
+def test_layernorm_backward_in_one_pass(mods, dtype, shape, base):
+    """One to eight wavefronts per token, fewer and more tokens than groups of wavefronts, ragged tiles, scalar forms, and the
+    shortest tokens that are too long (4104 in fp32, 8200 in bf16, 4097 by single elements).  The input gradient in place of the
+    upstream one, twice in a row with other operations on the second stream: the partial sums of the two streams lie apart."""
+    capi, tiled = mods
+    r = rng(23)
+    X, dY, dR = [quant(r.standard_normal(shape), dtype) for _ in range(3)]
+    gamma = (1 + 0.1 * r.standard_normal(shape[0])).astype(np.float32)
+    _, mean, rstd = D.layernorm_fwd(X, gamma, 0 * gamma, 1e-5)
+    dXref, dgref, dbref = D.layernorm_bwd(X, gamma, mean, rstd, dY)
+    with tiled.Context(n_streams=2) as ctx:
+        tX, tR, tg = T(tiled, ctx, X, base, dtype), T(tiled, ctx, dR, base, dtype), T(tiled, ctx, gamma, base[:1], "f32")
+        tS = tiled.TiledTensor.from_numpy(ctx, np.stack([mean, rstd]).astype(np.float32), (2,) + base[1:])
+        runs = []
+        for _ in range(2):
+            tdY = T(tiled, ctx, dY, base, dtype)
+            out = [tiled.TiledTensor(ctx, "f32", shape[:1], base[:1]) for _ in range(3)]
+            capi.nnt_bias_grad(ctx.h, tdY.h, out[2].h)
+            capi.nnt_layernorm_bwd(ctx.h, tX.h, tS.h, tg.h, tdY.h, tR.h, tdY.h, out[0].h, out[1].h)
+            runs.append((tdY, out))
+        for tdY, out in runs:
+            e = relerr(tdY.download(), dXref + dR)
+            assert e <= TOL[dtype], e
+            check(out[0].download(), dgref, "f32", "ln dgamma")
+            check(out[1].download(), dbref, "f32", "ln dbeta")
+            check(out[2].download(), dbref, "f32", "bias grad")
+
+
 @pytest.mark.parametrize("shape,base", [((768, 6, 2), (256, 6, 2)), ((5000, 3, 1), (2500, 3, 1)), ((101, 5, 1), (37, 5, 1))])
 @pytest.mark.parametrize("gran", GRANS)
 def test_layernorm_token_with_an_outlier(mods, gran, shape, base):
