@@ -448,6 +448,59 @@ __global__ void __launch_bounds__(256) rowsum_stage2(const float* part, int64_t 
     }
 }
 
+// The whole sum of a few thousand columns at most in one launch: a block owns four vectors of rows, its 256 groups of four lanes
+// take the columns in turn and meet in shuffles and LDS.  Latency is all such a call consists of, so the second launch costs
+// as much as the first.
+constexpr int kSmallThreads = 1024;
+template <typename T, int V>
+__global__ void __launch_bounds__(kSmallThreads) rowsum_small(TiledView y, void* const* otab) {
+    __shared__ float red[kSmallThreads / 64][4][V];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, rv = threadIdx.x & 3, cg = threadIdx.x >> 2;
+    constexpr int kGroups = kSmallThreads / 4;
+    const int l = blockIdx.y, ext0 = min(y.base[0], y.shape[0] - l * y.base[0]);
+    const int e = (blockIdx.x * 4 + rv) * V;
+    float a[V];
+#pragma unroll
+    for (int k = 0; k < V; k++) a[k] = 0.f;
+    const int rest_tiles = y.grid[1] * y.grid[2] * y.grid[3];
+    for (int rest = 0; rest < rest_tiles; rest++) {
+        int tc[kMaxDim], ext[kMaxDim];
+        tile_geometry(y, l + y.grid[0] * rest, tc, ext);
+        const int ncol = ext[1] * ext[2] * ext[3];
+        const T* p = global_as<const T>(y.tiles[l + y.grid[0] * rest]);
+        if (e >= ext0) continue;
+        // eight columns per trip so that eight loads are in flight
+        for (int c = cg; c < ncol; c += 8 * kGroups) {
+            float d[8][V];
+#pragma unroll
+            for (int u = 0; u < 8; u++)
+                if (c + u * kGroups < ncol) ldv<V>(p + (int64_t)(c + u * kGroups) * ext0 + e, d[u]);
+#pragma unroll
+            for (int u = 0; u < 8; u++)
+                if (c + u * kGroups < ncol) {
+#pragma unroll
+                    for (int k = 0; k < V; k++) a[k] += d[u][k];
+                }
+        }
+    }
+#pragma unroll
+    for (int k = 0; k < V; k++) {
+#pragma unroll
+        for (int o = 32; o >= 4; o >>= 1) a[k] += __shfl_xor(a[k], o, 64);
+        if (lane < 4) red[wave][lane][k] = a[k];
+    }
+    __syncthreads();
+    if (threadIdx.x < 4 * V) {
+        const int r = threadIdx.x / V, k = threadIdx.x % V, row = (blockIdx.x * 4 + r) * V + k;
+        if (row < ext0) {
+            float s = 0.f;
+#pragma unroll
+            for (int q = 0; q < kSmallThreads / 64; q++) s += red[q][r][k];
+            global_as<float>(otab[l])[row] = s;
+        }
+    }
+}
+
 constexpr int kColsPerBlock = 128;
 
 int64_t scratch_elems(int64_t m, int64_t n, int mode) { return ((n + kColsPerBlock - 1) / kColsPerBlock) * m * (mode ? 2 : 1); }
@@ -493,6 +546,25 @@ int32_t rowsum_tensor(nnt_ctx* ctx, int mode, nnt_tensor* dY, nnt_tensor* X, nnt
     bool vec = dY->base[0] % V == 0 && dY->shape[0] % V == 0;
     for (void* p : dY->tiles) vec = vec && aligned16(p);
     if (X) for (void* p : X->tiles) vec = vec && aligned16(p);
+    // in one launch up to 1024 columns and 13 MB: 4.0 to 7.0 us where the two launches take 6.5 to 7.4 (fp32 128 x 128: 4.0, 7.2; 768 x 1024: 4.2, 6.7;
+    // 3072 x 1024: 7.0, 7.4; bf16 4.6 to 6.5, 6.6 to 7.0); beyond, its few blocks take longer (fp32 768 x 2048: 7.5, 6.7; 8192 x 512: 9.2, 7.2)
+    const int64_t ncols = n_columns(dY);
+    if (mode == 0 && ncols <= 1024 && ncols * dY->shape[0] * dY->elem_size() <= 13000000 && dY->ntiles <= 65535) {
+        const TiledView vy = dY->view();
+        void* const* ot = out0->d_tiles;
+        const int dt = dY->dtype, w = vec ? V : 1;
+        const dim3 grid((unsigned)((dY->base[0] + 4 * w - 1) / (4 * w)), (unsigned)dY->grid[0]);
+        return submit(ctx, {dY->all(kRead), out0->all(kWrite)}, [=](hipStream_t st) {
+            if (dt == NNT_F32) {
+                if (vec) hipLaunchKernelGGL((rowsum_small<float, 4>), grid, dim3(kSmallThreads), 0, st, vy, ot);
+                else hipLaunchKernelGGL((rowsum_small<float, 1>), grid, dim3(kSmallThreads), 0, st, vy, ot);
+            } else {
+                if (vec) hipLaunchKernelGGL((rowsum_small<bf16_t, 8>), grid, dim3(kSmallThreads), 0, st, vy, ot);
+                else hipLaunchKernelGGL((rowsum_small<bf16_t, 1>), grid, dim3(kSmallThreads), 0, st, vy, ot);
+            }
+            return hipGetLastError() == hipSuccess ? (int32_t)NNT_OK : (int32_t)NNT_EHIP;
+        });
+    }
     RowsumGeom g = {};
     g.tiled = 1;
     g.y = dY->view();

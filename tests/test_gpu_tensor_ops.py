@@ -533,6 +533,20 @@ def test_layernorm_backward_in_one_pass(mods, dtype, shape, base):
             check(out[2].download(), dbref, "f32", "bias grad")
 
 
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("shape,base", [((1, 1), (1, 1)), ((128, 128), (32, 32)), ((40, 1024), (16, 1000)), ((40, 1025), (16, 1000)), ((777, 31, 5), (300, 7, 2)),
+                                        ((3168, 1024), (1056, 512)), ((3176, 1024), (3176, 1024)), ((6344, 1024), (6344, 1024)), ((6352, 1024), (6352, 1024))])
+def test_bias_grad_in_one_launch(mods, dtype, shape, base):
+    """Both sides of the rule (1024 columns, 13 MB), ragged tiles on every axis, rows that are no whole vectors."""
+    capi, tiled = mods
+    r = rng(29)
+    dY = quant(r.standard_normal(shape), dtype)
+    with tiled.Context(n_streams=2) as ctx:
+        t, db = T(tiled, ctx, dY, base, dtype), tiled.TiledTensor(ctx, "f32", shape[:1], base[:1])
+        capi.nnt_bias_grad(ctx.h, t.h, db.h)
+        check(db.download(), np.asarray(dY, np.float64).reshape(shape[0], -1).sum(1), "f32", "bias grad")
+
+
 @pytest.mark.parametrize("shape,base", [((768, 6, 2), (256, 6, 2)), ((5000, 3, 1), (2500, 3, 1)), ((101, 5, 1), (37, 5, 1))])
 @pytest.mark.parametrize("gran", GRANS)
 def test_layernorm_token_with_an_outlier(mods, gran, shape, base):
