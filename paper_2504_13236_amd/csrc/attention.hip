@@ -24,6 +24,7 @@
 #include "device_util.hpp"
 #include "internal.hpp"
 
+#include <algorithm>
 #include <cmath>
 #include <type_traits>
 
@@ -49,6 +50,7 @@ struct AttnGeom {
     int causal;
     float scale;
     int split;           // workgroups of 64 rows whose waves share the streamed blocks (see attn_fwd)
+    int fold;            // end of the workgroups that are taken in reverse order (see item_of); 0: none
     // Operands that are windows on tensors [parts * N_h * H, N_s, N_b] with the heads side by side along the first
     // axis (win = 1; the statistics stay an ordinary tensor, to which bh and gh then belong): `pitch` elements
     // between the rows of consecutive positions (H otherwise), `hp` heads per row tile.
@@ -63,6 +65,19 @@ struct Slab {
     int tile;      // tile number
     int ext;       // extent of the tile along the sequence axis
 };
+
+// Which (batch, head) pair and row block a workgroup takes: pairs fastest, row blocks in the order of the launch.  Under the
+// causal mask that is the longest first, so the first 256 workgroups, one to a compute unit, are the longest, and the next 256, the
+// second ones of the units, would come in the same order: the unit with the longest also gets the longest of the rest.
+// Taken in reverse order they make the units' sums alike.
+constexpr unsigned kUnits = 256;
+struct Item { unsigned pair, row; };
+__device__ __forceinline__ Item item_of(const AttnGeom& g) {
+    if (g.fold == 0) return Item{blockIdx.x, blockIdx.y};
+    unsigned i = blockIdx.x + gridDim.x * blockIdx.y;
+    if (i >= kUnits && i < (unsigned)g.fold) i = kUnits + (unsigned)g.fold - 1 - i;
+    return Item{i % gridDim.x, i / gridDim.x};
+}
 
 // The part of a slab lookup that depends on (batch b, head j) only.
 struct Pair {
@@ -343,9 +358,10 @@ __global__ void __launch_bounds__(256, 2) attn_fwd(const FwdArgs a) {
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, hh = lane >> 5, ln = lane & 31;
     const int wr = SPLIT ? w & 1 : w, own_sub = __builtin_amdgcn_readfirstlane(w >> 1);
     // under the causal mask the later a query block, the more key blocks it walks: the longest go first
-    const int rblk = g.causal ? gridDim.y - 1 - blockIdx.y : blockIdx.y;
+    const Item item = item_of(g);
+    const int rblk = g.causal ? gridDim.y - 1 - item.row : item.row;
     const int l = g.tile0 + rblk / g.nblk, e0 = (rblk % g.nblk) * kRows;
-    const int b = blockIdx.x % g.Nb, j = blockIdx.x / g.Nb;
+    const int b = item.pair % g.Nb, j = item.pair / g.Nb;
     const Pair pr = pair_of(g, b, j);
     const Slab sq = slab_of(g, pr, l);
     if (e0 >= sq.ext) return;
@@ -532,9 +548,10 @@ __global__ void __launch_bounds__(256, 2) attn_dq(const BwdArgs a) {
     constexpr int kRows = SPLIT ? kHalfRows : kWgRows;
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, hh = lane >> 5, ln = lane & 31;
     const int wr = SPLIT ? w & 1 : w, own_sub = __builtin_amdgcn_readfirstlane(w >> 1);
-    const int rblk = g.causal ? gridDim.y - 1 - blockIdx.y : blockIdx.y;
+    const Item item = item_of(g);
+    const int rblk = g.causal ? gridDim.y - 1 - item.row : item.row;
     const int l = g.tile0 + rblk / g.nblk, e0 = (rblk % g.nblk) * kRows;
-    const int b = blockIdx.x % g.Nb, j = blockIdx.x / g.Nb;
+    const int b = item.pair % g.Nb, j = item.pair / g.Nb;
     const Pair pr = pair_of(g, b, j);
     const Slab sq = slab_of(g, pr, l);
     if (e0 >= sq.ext) return;
@@ -653,8 +670,9 @@ __global__ void __launch_bounds__(256, X::kDkvBlocks) attn_dkv(const BwdArgs a) 
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, hh = lane >> 5, ln = lane & 31;
     const int wr = SPLIT ? w & 1 : w, own_sub = __builtin_amdgcn_readfirstlane(w >> 1);
     // (under the causal mask the earliest key blocks meet the most query blocks: already first)
-    const int l = g.tile0 + blockIdx.y / g.nblk, e0 = (blockIdx.y % g.nblk) * kRows;
-    const int b = blockIdx.x % g.Nb, j = blockIdx.x / g.Nb;
+    const Item item = item_of(g);
+    const int l = g.tile0 + (int)item.row / g.nblk, e0 = ((int)item.row % g.nblk) * kRows;
+    const int b = item.pair % g.Nb, j = item.pair / g.Nb;
     const Pair pr = pair_of(g, b, j);
     const Slab sk = slab_of(g, pr, l);
     if (e0 >= sk.ext) return;
@@ -841,6 +859,17 @@ bool split_rows(AttnKernel which, int dtype, const AttnGeom& g) {
 AttnGeom rows_for(AttnKernel which, int dtype, AttnGeom g) {
     g.split = split_rows(which, dtype, g);
     if (g.split) g.nblk = (g.bs + kHalfRows - 1) / kHalfRows;
+    // reverse order for the second workgroups of the units: where two of them fit on one (not dK and dV in bf16 and any fp32 kernel
+    // of head size 128) and every row block exists (short last tiles put empty workgroups first, which shifts the order: 576 of 128
+    // rows in tiles of 300, 313 -> 335 us). fp32: 24 pairs of 1024 positions 266 -> 233 us, 36 of 1000 290 -> 263 (283 -> 269 where calls
+    // on two streams overlap), 8 of 3000 701 -> 606,
+    // 64 of 1024 (1024 workgroups) 423 -> 400; bf16 up to 512 workgroups the same or 1 % slower, 1024 of head size 128 (32 pairs of 4096) forward
+    // and dQ 437 -> 422.  Beyond 1024 the short ones even out whatever comes first.
+    const bool bf = dtype == NNT_BF16;
+    const int64_t n = (int64_t)g.Nb * g.Nh * g.gs * g.nblk;
+    const bool two = bf ? !(which == kAttnDkv && g.H == 128) : g.H == 64;
+    const int rows = g.split ? kHalfRows : kWgRows, last = g.Ns - (g.gs - 1) * g.bs;
+    if (g.causal && two && (last + rows - 1) / rows == g.nblk && n > (bf ? 2 * kUnits : kUnits) && n <= 1024) g.fold = (int)std::min<int64_t>(n, 2 * kUnits);
     return g;
 }
 
@@ -891,6 +920,7 @@ AttnGeom geom_of(const nnt_tensor* q, float scale, int causal) {
     g.gs = (int)q->grid[1]; g.gb = (int)q->grid[2]; g.gh = (int)q->grid[3];
     g.nblk = (g.bs + kWgRows - 1) / kWgRows;
     g.split = 0;
+    g.fold = 0;
     g.nstep = (g.bs + kBlk - 1) / kBlk;
     g.tile0 = 0;
     g.causal = causal;
@@ -936,6 +966,7 @@ int32_t geom_of_windows(nnt_ctx* ctx, const char* who, std::initializer_list<std
     g.gs = (int)first->grid[1]; g.gb = (int)first->grid[2]; g.gh = (int)stats->grid[3];
     g.nblk = (g.bs + kWgRows - 1) / kWgRows;
     g.split = 0;
+    g.fold = 0;
     g.nstep = (g.bs + kBlk - 1) / kBlk;
     g.tile0 = 0;
     g.causal = causal;
@@ -1008,6 +1039,7 @@ int32_t nnt_attention_fwd(nnt_ctx* ctx, nnt_tensor* Q, nnt_tensor* K, nnt_tensor
         for (const Access& x : seq_tile(stats, l, kWrite)) acc.push_back(x);
         FwdArgs al = a;
         al.g.tile0 = (int)l;
+        al.g.fold = 0;          // (the order is the whole launch's)
         rc = submit(ctx, acc, [=](hipStream_t st) { return launch(st, al, 1); });
         if (rc != NNT_OK) return rc;
     }

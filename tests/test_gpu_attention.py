@@ -41,6 +41,13 @@ CASES = [
     ((64, 1, 1, 1), 1, 1, 1),              # a single position: P = 1, B = V
     ((64, 33, 2, 1), 7, 1, 1),             # tiles far smaller than a streamed block
     ((128, 200, 2, 1), 72, 2, 1),          # head size 128 on ragged tiles
+    # causal launches of 260, 512, 516, 1020 and 1026 workgroups of 64 rows (fp32) or 128, some in reverse order
+    ((64, 128, 5, 26), 128, 5, 26),
+    ((64, 64, 16, 32), 64, 4, 32),
+    ((64, 160, 4, 43), 64, 4, 43),
+    ((64, 256, 5, 51), 128, 1, 51),
+    ((64, 384, 3, 57), 192, 3, 57),
+    ((128, 256, 4, 65), 256, 4, 65),
 ]
 
 
