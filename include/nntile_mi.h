@@ -20,10 +20,13 @@
  *  - The caller owns all tile memory.  On the device the library allocates only
  *    (a) descriptor tables: the tile-pointer table of every tensor, the tables of
  *    cached product plans and of grouped optimiser steps; (b) the fp32 scratch of
- *    the two-stage column sums (grows on demand, at least 4 MiB once used); (c)
+ *    the two-stage column sums, shared and one part per stream (grows on demand, at
+ *    least 4 MiB each once used); (c)
  *    for products whose contraction is cut into k-slices, an fp32 workspace of
- *    slices x macro-tile partial sums per cached plan (at most 2 GiB each; a plan
- *    whose workspace would be larger is built without slices).  nnt_ctx_stats
+ *    slices x macro-tile partial sums per cached plan, and for bf16 products whose
+ *    operands have odd leading dimensions or tiles a padded copy of both operands
+ *    per cached plan (at most 2 GiB each; a plan that would need more is built
+ *    without them).  nnt_ctx_stats
  *    reports the bytes held for (a) and for (b) + (c).  Tables and workspaces of a
  *    plan are released when one of its tensors or the context is destroyed, the
  *    rest in the matching destroy call.

@@ -38,7 +38,7 @@ FLAGS = [
 # targets it and the wait for it (registers_touched_in_flight): a copy or move the compiler
 # places there would read stale data just the same.  Both follow the branches, not the order of the listing: loop blocks
 # carry their loop's name on the line of their label or on the next one, and the compiler puts blocks out of line.
-IN_FLIGHT_SOURCES = ("gemm_bf16_dl.hip", "gemm_f32_dl.hip")
+IN_FLIGHT_SOURCES = ("gemm_bf16_dl.hip", "gemm_bf16_span.hip", "gemm_f32_dl.hip")
 # Sources with matrix instructions: their assembly is scanned for uses of a result before it is there.
 MATRIX_SOURCES = IN_FLIGHT_SOURCES + ("gemm_bf16.hip", "gemm_f32.hip", "attention.hip")
 

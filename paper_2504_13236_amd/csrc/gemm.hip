@@ -6,6 +6,7 @@
 
 #include <algorithm>
 #include <cstdlib>
+#include <cstring>
 #include <sstream>
 
 namespace nnt {
@@ -21,6 +22,9 @@ struct SplitReduce {
     int64_t cin_off;        // the beta term is read at C + cin_off elements (0: C itself; else a residual input's tile)
 };
 
+typedef float f4_any __attribute__((ext_vector_type(4), aligned(4)));           // at any address of a float
+typedef uint32_t u2_any __attribute__((ext_vector_type(2), aligned(2)));         // at any address of a bf16 element
+
 template <typename TO>
 __global__ void __launch_bounds__(256) splitk_reduce(const SplitReduce* tab, float alpha, float beta) {
     SplitReduce t = tab[blockIdx.y];
@@ -32,46 +36,43 @@ __global__ void __launch_bounds__(256) splitk_reduce(const SplitReduce* tab, flo
     if (j >= t.cols || i >= t.rows) return;
     const int n = t.rows - i < 4 ? t.rows - i : 4;
     float acc[4] = {0.f, 0.f, 0.f, 0.f};
-    const float* p = t.ws + (int64_t)j * t.ldw + i;       // 16-byte aligned: ldw is a multiple of 4
+    const float* p = t.ws + (int64_t)j * t.ldw + i;       // (16-byte aligned unless the macro-tile crosses an edge of C's tiles)
     // slices are added in their fixed order; four loads are started before the first of them is used
     int sl = 0;
     for (; sl + 4 <= t.nsplit; sl += 4) {
-        float4 v[4];
+        f4_any v[4];
 #pragma unroll
-        for (int u = 0; u < 4; u++) v[u] = *reinterpret_cast<const float4*>(p + (int64_t)(sl + u) * t.slice);
+        for (int u = 0; u < 4; u++) v[u] = *reinterpret_cast<const f4_any*>(p + (int64_t)(sl + u) * t.slice);
 #pragma unroll
         for (int u = 0; u < 4; u++) {
-            acc[0] += v[u].x; acc[1] += v[u].y; acc[2] += v[u].z; acc[3] += v[u].w;
+            acc[0] += v[u][0]; acc[1] += v[u][1]; acc[2] += v[u][2]; acc[3] += v[u][3];
         }
     }
     for (; sl < t.nsplit; sl++) {
-        const float4 v = *reinterpret_cast<const float4*>(p + (int64_t)sl * t.slice);
-        acc[0] += v.x; acc[1] += v.y; acc[2] += v.z; acc[3] += v.w;
+        const f4_any v = *reinterpret_cast<const f4_any*>(p + (int64_t)sl * t.slice);
+        acc[0] += v[0]; acc[1] += v[1]; acc[2] += v[2]; acc[3] += v[3];
     }
     TO* c = global_as<TO>(t.C) + (t.m0 + i) + (int64_t)(t.n0 + j) * t.ldc;
     if constexpr (sizeof(TO) == 4) {
-        // four whole rows at a 16-byte aligned address: one vector access instead of four
-        if (n == 4 && (reinterpret_cast<uintptr_t>(c) & 15) == 0 && (t.cin_off & 3) == 0) {
-            float4 o = make_float4(alpha * acc[0], alpha * acc[1], alpha * acc[2], alpha * acc[3]);
+        // four whole rows: one vector access instead of four, at any alignment
+        if (n == 4) {
+            f4_any o = {alpha * acc[0], alpha * acc[1], alpha * acc[2], alpha * acc[3]};
             if (t.bias) {
                 const float* bp = t.bias + t.m0 + i;
-                o.x += bp[0]; o.y += bp[1]; o.z += bp[2]; o.w += bp[3];
+                o[0] += bp[0]; o[1] += bp[1]; o[2] += bp[2]; o[3] += bp[3];
             }
-            float4* c4 = reinterpret_cast<float4*>(c);
             if (beta != 0.f) {
-                const float4 old = *reinterpret_cast<const float4*>(c + t.cin_off);
-                o.x += beta * old.x; o.y += beta * old.y; o.z += beta * old.z; o.w += beta * old.w;
+                const f4_any old = *reinterpret_cast<const f4_any*>(c + t.cin_off);
+                o[0] += beta * old[0]; o[1] += beta * old[1]; o[2] += beta * old[2]; o[3] += beta * old[3];
             }
-            *c4 = o;
+            *reinterpret_cast<f4_any*>(c) = o;
             return;
         }
     } else {
-        if (n == 4 && (reinterpret_cast<uintptr_t>(c) & 7) == 0 && (t.cin_off & 3) == 0) {
+        if (n == 4) {
             float o[4];
-            uint2* c2 = reinterpret_cast<uint2*>(c);
-            uint2 old = make_uint2(0u, 0u);
-            if (beta != 0.f) old = *reinterpret_cast<const uint2*>(c + t.cin_off);
-            const uint32_t ow[2] = {old.x, old.y};
+            u2_any ow = {0u, 0u};
+            if (beta != 0.f) ow = *reinterpret_cast<const u2_any*>(c + t.cin_off);
 #pragma unroll
             for (int jj = 0; jj < 4; jj++) {
                 o[jj] = alpha * acc[jj];
@@ -84,7 +85,7 @@ __global__ void __launch_bounds__(256) splitk_reduce(const SplitReduce* tab, flo
                 const __bf16 b = (__bf16)o[jj];
                 h[jj] = (uint32_t)__builtin_bit_cast(uint16_t, b);
             }
-            *c2 = make_uint2(h[0] | (h[1] << 16), h[2] | (h[3] << 16));
+            *reinterpret_cast<u2_any*>(c) = u2_any{h[0] | (h[1] << 16), h[2] | (h[3] << 16)};
             return;
         }
     }
@@ -144,12 +145,23 @@ struct GemmPlan {
     std::vector<TileSplit> tile_split;         // per task; nwg == 0: launched whole
     std::vector<GemmWg> wgs_ts;
     int64_t slice_elems_ts = 0;
+    // Whole-operation launches of bf16 operands that only the register-staged kernel could read as they are: the operands are
+    // laid out afresh in `d_pack` first and the macro-tiles lie on one grid over all of C, with tables of its own.  Such a plan has
+    // nothing else: launches tile by tile of the same product have a plan to themselves.
+    bool packed = false;
+    PackOperand pack[2] = {};
+    int pack_cfg = 0;
+    uint16_t* d_pack = nullptr;
+    char* d_pack_tables = nullptr;
+    GemmArgs pack_args = {};
+    const SplitReduce* pack_red = nullptr;
+    int64_t pack_nwg = 0;
     GemmWg* d_wgs_ts = nullptr;
     SplitReduce* d_red_ts = nullptr;
     float* d_ws_ts = nullptr;
     ~GemmPlan() {
         for (void* p : {(void*)d_tasks, (void*)d_chunks, (void*)d_wgs, (void*)d_wgs_op, (void*)d_red, (void*)d_ws, (void*)d_wgs_ts,
-                        (void*)d_red_ts, (void*)d_ws_ts})
+                        (void*)d_red_ts, (void*)d_ws_ts, (void*)d_pack, (void*)d_pack_tables})
             if (p) (void)hipFree(p);
     }
 };
@@ -529,6 +541,237 @@ SplitReduce add_slice_tasks(GemmPlan* P, const GemmTask& t0, const GemmWg& mw, c
     return r;
 }
 
+// Launch order of k-slices: workgroup p runs on XCD p mod 8, and the workgroups of one k-slice read
+// one k-range of both operands, so each slice is dealt to one XCD (slice s to XCD s mod 8): that XCD's
+// L2 then fetches the range once for all macro-tiles.  An XCD whose queue runs dry takes from the
+// longest one.
+void deal_slices(const std::vector<std::vector<GemmWg>>& by_slice, std::vector<GemmWg>& out) {
+    std::vector<GemmWg> q[8];
+    for (size_t sidx = 0; sidx < by_slice.size(); sidx++) q[sidx & 7].insert(q[sidx & 7].end(), by_slice[sidx].begin(), by_slice[sidx].end());
+    size_t head[8] = {0, 0, 0, 0, 0, 0, 0, 0}, left = 0;
+    for (int x = 0; x < 8; x++) left += q[x].size();
+    while (left > 0) {
+        const int x = (int)(out.size() & 7);
+        if (head[x] < q[x].size()) {
+            out.push_back(q[x][head[x]++]);
+        } else {
+            int longest = 0;
+            for (int y = 1; y < 8; y++)
+                if (q[y].size() - head[y] > q[longest].size() - head[longest]) longest = y;
+            out.push_back(q[longest].back());
+            q[longest].pop_back();
+        }
+        left--;
+    }
+}
+
+// Extents of the groups of tiles along `axes` of `t` taken together (first axis fastest), as first elements of the groups with the total
+// at the end.
+std::vector<int64_t> group_starts(const nnt_tensor* t, const std::vector<int>& axes) {
+    int64_t n = 1;
+    for (int a : axes) n *= t->grid[a];
+    std::vector<int64_t> out(1, 0);
+    for (int64_t i = 0; i < n; i++) {
+        int64_t tc[kMaxDim] = {0, 0, 0, 0}, rem = i;
+        for (int a : axes) { tc[a] = rem % t->grid[a]; rem /= t->grid[a]; }
+        out.push_back(out.back() + prod_extent(t, tc, axes));
+    }
+    return out;
+}
+
+// The form of a bf16 product that lays its operands out afresh (GemmPlan::packed), if it can take the product and promises to take
+// less than `limit_us`: nine tenths of what the model says of the register-staged kernels, with the copy priced at 14 us (10 to 12
+// measured for 13 MB, and a result path that sorts) and 3 TB/s.  At 5 us, 6 of 150 random products of 128 to 6000 rows, columns and
+// contraction became 8 to 20 % slower (632 x 4856 over 848 on tiles of 300: 29 -> 35 us); at 14 none of 300 did, and products of
+// some size are two to three times faster (2688 x 3072 over 2145 on tiles of 400: 185 -> 57; 3627 x 1880 over 2496: 174 -> 74).
+int32_t try_packed(nnt_ctx* ctx, const AxisMap& ax, nnt_tensor* A, nnt_tensor* B, nnt_tensor* C, nnt_tensor* bias, nnt_tensor* R, GemmPlan* P, double limit_us) {
+    const std::vector<int>*contig[2] = {P->akf ? &ax.a_con : &ax.a_free, P->bkf ? &ax.b_con : &ax.b_free};
+    if ((P->akf && !P->bkf) || contig[0]->size() != 1 || contig[1]->size() != 1) return NNT_OK;
+    for (const nnt_tensor* t : {A, B, C})
+        for (void* p : t->tiles) if (!p) return NNT_OK;
+    const std::vector<int64_t> rows = group_starts(A, ax.a_free), cols = group_starts(B, ax.b_free), ks = group_starts(A, ax.a_con);
+    const int64_t M = rows.back(), N = cols.back(), K = ks.back(), Kp = (K + 63) / 64 * 64;
+    const int64_t Mp = (M + 255) / 256 * 256, Np = (N + 255) / 256 * 256;
+    const int64_t a_elems = Mp * Kp, b_elems = Np * Kp;
+    // (byte offsets of a macro-tile's lines and vector numbers have 32 bits)
+    if (Kp > (1 << 23) || Mp > (1 << 23) || Np > (1 << 23) || a_elems / 8 > INT32_MAX / 2 || b_elems / 8 > INT32_MAX / 2 || (a_elems + b_elems) * 2 > ((int64_t)2 << 30)) return NNT_OK;
+    const ShapeChoice sc = choose_shape(true, kShapeWhole, {M}, {N}, {Kp}, true);
+    if (sc.us + 14.0 + (double)(M + N) * K * 4.0 / 3.0e6 >= limit_us) return NNT_OK;
+    int bm, bn;
+    gemm_cfg_tile(1, sc.cfg, &bm, &bn);
+    const int64_t gm = (M + bm - 1) / bm, gn = (N + bn - 1) / bn;
+    if (sc.s > 1 && (sc.n_split * sc.s * bm * bn * (int64_t)sizeof(float) > ((int64_t)2 << 30) || sc.n_split > 65535 / 4)) return NNT_OK;
+
+    // where the results of every macro-tile go: at most two tiles of C along either axis
+    const int64_t NR = (int64_t)rows.size() - 1;
+    const int64_t esize = C->elem_size();
+    std::vector<GemmSpan> spans((size_t)(gm * gn));
+    for (int64_t j = 0, cb = 0; j < gn; j++) {
+        while (j * bn >= cols[cb + 1]) cb++;
+        const int64_t j1 = std::min(N, (j + 1) * bn);
+        if (j1 > cols[cb + 1] && j1 > cols[cb + 2]) return NNT_OK;
+        for (int64_t i = 0, ra = 0; i < gm; i++) {
+            while (i * bm >= rows[ra + 1]) ra++;
+            const int64_t i1 = std::min(M, (i + 1) * bm);
+            if (i1 > rows[ra + 1] && i1 > rows[ra + 2]) return NNT_OK;
+            GemmSpan& s = spans[(size_t)(i + j * gm)];
+            s = GemmSpan{};
+            s.rows = (int32_t)(i1 - i * bm);
+            s.cols = (int32_t)(j1 - j * bn);
+            s.sm = i1 > rows[ra + 1] ? (int32_t)(rows[ra + 1] - i * bm) : INT32_MAX;
+            s.sn = j1 > cols[cb + 1] ? (int32_t)(cols[cb + 1] - j * bn) : INT32_MAX;
+            for (int a = 0; a < 2; a++) {
+                const int64_t r = ra + (a && s.sm != INT32_MAX);
+                s.ldc[a] = rows[r + 1] - rows[r];
+                if (bias) s.bias[a] = static_cast<const float*>(bias->tiles[r]) + (i * bm - rows[r]);
+                if (bias && !bias->tiles[r]) return NNT_OK;
+                for (int b = 0; b < 2; b++) {
+                    const int64_t c = cb + (b && s.sn != INT32_MAX), t = r + NR * c;
+                    s.C[a + 2 * b] = static_cast<char*>(C->tiles[t]) + ((i * bm - rows[r]) + (j * bn - cols[c]) * s.ldc[a]) * esize;
+                    if (R) {
+                        const ptrdiff_t delta = static_cast<const char*>(R->tiles[t]) - static_cast<const char*>(C->tiles[t]);
+                        if (!R->tiles[t] || delta % esize != 0) return NNT_OK;
+                        s.cin[a + 2 * b] = delta / esize;
+                    }
+                }
+            }
+        }
+    }
+
+    // the operands
+    std::vector<int32_t> line0;
+    const std::vector<int64_t>* lines[2] = {P->akf ? &rows : &ks, P->bkf ? &cols : &ks};
+    for (const std::vector<int64_t>* l : lines) line0.insert(line0.end(), l->begin(), l->end());
+    // (where there is no memory for them the product runs on the operands as they are)
+    const int64_t cut_part = ((Kp + sc.s - 1) / sc.s + 63) / 64 * 64, n_cut = sc.s > 1 ? std::min<int64_t>(sc.n_split, gm * gn) : 0;
+    const int S = n_cut > 0 ? (int)((Kp + cut_part - 1) / cut_part) : 1;
+    const int64_t slice = (int64_t)bm * bn;
+    // (four floats more: the sum reads whole vectors, also of parts that do not begin at one)
+    const size_t pack_bytes = (size_t)(a_elems + b_elems) * 2, cut_bytes = n_cut > 0 ? ((size_t)n_cut * S * slice + 4) * sizeof(float) : 0;
+    if (hipMalloc((void**)&P->d_pack, pack_bytes) != hipSuccess || (cut_bytes && hipMalloc((void**)&P->d_ws, cut_bytes) != hipSuccess)) {
+        (void)hipGetLastError();
+        if (P->d_pack) (void)hipFree(P->d_pack);
+        P->d_pack = nullptr;
+        P->d_ws = nullptr;
+        return NNT_OK;
+    }
+    P->ws_bytes += (int64_t)(pack_bytes + cut_bytes);
+    for (int o = 0; o < 2; o++) {
+        nnt_tensor* const t = o ? B : A;
+        const bool kf = o ? P->bkf : P->akf;
+        const int64_t free_pad = o ? Np : Mp;
+        const int cx = (*contig[o])[0];
+        PackOperand& p = P->pack[o];
+        p.tiles = t->d_tiles;
+        p.dst = P->d_pack + (o ? a_elems : 0);
+        p.ntc = (int32_t)t->grid[cx];
+        p.ntl = (int32_t)lines[o]->size() - 1;
+        p.base = (int32_t)t->base[cx];
+        p.contig = (int32_t)t->shape[cx];
+        p.pitch = (int32_t)(kf ? Kp : free_pad);
+        p.lines = (int32_t)lines[o]->back();
+        p.all_lines = kf ? p.lines : (int32_t)Kp;      // (lines of rows that do not exist are read, but only reach results that are not stored)
+    }
+
+    // tasks: the product, and one per k-slice of every macro-tile that is cut
+    GemmChunk whole = {};
+    whole.A = P->pack[0].dst;
+    whole.B = P->pack[1].dst;
+    whole.lda = P->pack[0].pitch;
+    whole.ldb = P->pack[1].pitch;
+    whole.k = (int32_t)Kp;
+    whole.vec_ok = 3;
+    std::vector<GemmChunk> chunks(1, whole);
+    GemmTask main = {};
+    main.m = (int32_t)M;
+    main.n = (int32_t)N;
+    main.nchunk = 1;
+    std::vector<GemmTask> tasks(1, main);
+    std::vector<GemmWg> wgs;
+    std::vector<SplitReduce> red;
+    for (int64_t j = 0; j < gn; j++)
+        for (int64_t i = 0; i < gm; i++) wgs.push_back(GemmWg{0, (int32_t)(i * bm), (int32_t)(j * bn), 0});
+    xcd_interleave(wgs, bm, bn);
+    if (n_cut > 0) {
+        const int64_t part = cut_part;
+        for (int q = 0; q < S; q++) {
+            GemmChunk c = whole;
+            c.A = P->pack[0].dst + q * part * (P->akf ? 1 : whole.lda);
+            c.B = P->pack[1].dst + q * part * (P->bkf ? 1 : whole.ldb);
+            c.k = (int32_t)std::min(part, Kp - q * part);
+            chunks.push_back(c);
+        }
+        const std::vector<GemmWg> cut(wgs.end() - n_cut, wgs.end());
+        wgs.resize(wgs.size() - (size_t)n_cut);
+        std::vector<std::vector<GemmWg>> by_slice(S);
+        for (int64_t w = 0; w < n_cut; w++) {
+            const GemmWg& mw = cut[(size_t)w];
+            float* const block = P->d_ws + w * S * slice;
+            for (int q = 0; q < S; q++) {
+                GemmTask t = main;
+                t.C = block + q * slice - (mw.m0 + (int64_t)mw.n0 * bm);
+                t.ldc = bm;
+                t.partial = 1;
+                t.chunk0 = 1 + q;
+                by_slice[q].push_back(GemmWg{(int32_t)tasks.size(), mw.m0, mw.n0, 0});
+                tasks.push_back(t);
+            }
+            const GemmSpan& s = spans[(size_t)(mw.m0 / bm + (mw.n0 / bn) * gm)];
+            const int32_t ie[3] = {0, std::min(s.sm, s.rows), s.rows}, je[3] = {0, std::min(s.sn, s.cols), s.cols};
+            for (int b = 0; b < 2; b++)
+                for (int a = 0; a < 2; a++) {
+                    if (ie[a + 1] == ie[a] || je[b + 1] == je[b]) continue;
+                    SplitReduce r = {};
+                    r.C = s.C[a + 2 * b];
+                    r.bias = s.bias[a];
+                    r.ws = block + ie[a] + (int64_t)je[b] * bm;
+                    r.ldc = s.ldc[a];
+                    r.slice = slice;
+                    r.m0 = ie[a];
+                    r.n0 = je[b];
+                    r.rows = ie[a + 1] - ie[a];
+                    r.cols = je[b + 1] - je[b];
+                    r.ldw = bm;
+                    r.nsplit = S;
+                    r.cin_off = s.cin[a + 2 * b];
+                    red.push_back(r);
+                }
+        }
+        deal_slices(by_slice, wgs);
+        P->splits = S;
+        P->n_split = (int64_t)red.size();
+        P->slice_elems = slice * n_cut / (int64_t)red.size();
+        P->red_blocks = (int)((slice / 4 + 255) / 256);
+    }
+    // all tables in one piece: an allocation and a copy cost some 15 us each in the first call on new tensors
+    std::vector<char> blob;
+    auto put = [&](const void* h, size_t bytes) {
+        const size_t at = (blob.size() + 15) / 16 * 16;
+        blob.resize(at + bytes);
+        if (bytes) memcpy(blob.data() + at, h, bytes);
+        return at;
+    };
+    const size_t at_lines = put(line0.data(), line0.size() * sizeof(int32_t)), at_red = put(red.data(), red.size() * sizeof(SplitReduce)),
+                 at_spans = put(spans.data(), spans.size() * sizeof(GemmSpan)), at_tasks = put(tasks.data(), tasks.size() * sizeof(GemmTask)),
+                 at_chunks = put(chunks.data(), chunks.size() * sizeof(GemmChunk)), at_wgs = put(wgs.data(), wgs.size() * sizeof(GemmWg));
+    NNT_HIP(ctx, hipMalloc((void**)&P->d_pack_tables, blob.size()));
+    P->table_bytes += (int64_t)blob.size();
+    NNT_HIP(ctx, hipMemcpy(P->d_pack_tables, blob.data(), blob.size(), hipMemcpyHostToDevice));
+    const int32_t* const d_lines = reinterpret_cast<const int32_t*>(P->d_pack_tables + at_lines);
+    P->pack[0].line0 = d_lines;
+    P->pack[1].line0 = d_lines + lines[0]->size();
+    P->pack_red = reinterpret_cast<const SplitReduce*>(P->d_pack_tables + at_red);
+    P->pack_args.spans = reinterpret_cast<const GemmSpan*>(P->d_pack_tables + at_spans);
+    P->pack_args.tasks = reinterpret_cast<const GemmTask*>(P->d_pack_tables + at_tasks);
+    P->pack_args.chunks = reinterpret_cast<const GemmChunk*>(P->d_pack_tables + at_chunks);
+    P->pack_args.wgs = reinterpret_cast<const GemmWg*>(P->d_pack_tables + at_wgs);
+    P->pack_args.grid_m = (int32_t)gm;
+    P->pack_cfg = sc.cfg;
+    P->pack_nwg = (int64_t)wgs.size();
+    P->packed = true;
+    return NNT_OK;
+}
+
 // `view_ld` (or nullptr): per operand (A, B, C) the leading dimension of a tensor that is a window on a tensor
 // with the heads side by side along its first axis (see nnt_gemm_heads), or 0 for an ordinary tensor.  With it
 // the two batch axes stay apart (batch member, head): GemmTask::nb1 and the second strides.
@@ -707,6 +950,11 @@ int32_t build_plan(nnt_ctx* ctx, int opA, nnt_tensor* A, int opB, nnt_tensor* B,
         P->cfg = sc.cfg;
         S = sc.s;
         n_split = sc.n_split;
+        static const bool no_pack = getenv("NNT_GEMM_NO_PACK") != nullptr;      // debugging aid: operands are read as they are
+        if (bf && kind == kShapeGeneral && epi == 0 && ctx->granularity == NNT_GRAN_OP && !no_pack) {
+            const int32_t rc = try_packed(ctx, ax, A, B, C, bias, R, P, 0.9 * sc.us);
+            if (rc != NNT_OK) return rc;
+        }
     }
     int bm, bn;
     gemm_cfg_tile(bf, P->cfg, &bm, &bn);
@@ -728,6 +976,13 @@ int32_t build_plan(nnt_ctx* ctx, int opA, nnt_tensor* A, int opB, nnt_tensor* B,
             l << " [" << rows << " x " << cols << ", k/tile " << kmax << ", " << n_split << " macro-tiles in " << S << " slices]";
         }
         P->label = l.str();
+    }
+    if (P->packed) {
+        const std::string old_name = P->label.substr(0, P->label.find('>') + 1);
+        const char* tf[2] = {"false", "true"};
+        P->label = std::string(P->pack_cfg == kCfgSquare ? "gemm_bf16_span_kernel<" : P->pack_cfg == kCfgTall ? "gemm_bf16_span_tall_kernel<" : "gemm_bf16_span_wide_kernel<") +
+                   (C->dtype == NNT_F32 ? "float, " : "unsigned short, ") + tf[P->akf] + ", " + tf[P->bkf] + ">" + P->label.substr(old_name.size());
+        return NNT_OK;
     }
     // Workgroup order inside a task: m index fastest, so that workgroups in flight
     // together share a column panel of B.
@@ -779,29 +1034,7 @@ int32_t build_plan(nnt_ctx* ctx, int opA, nnt_tensor* A, int opB, nnt_tensor* B,
             if (ranges[mw.task].empty()) ranges[mw.task] = cut_into_slices(P, t0, ktot[mw.task], S, elem);
             red.push_back(add_slice_tasks(P, t0, mw, ranges[mw.task], P->d_ws + (int64_t)w * S * slice, bm, bn, by_slice));
         }
-        // Launch order of the slices: workgroup p runs on XCD p mod 8, and the workgroups of one k-slice read
-        // one k-range of both operands, so each slice is dealt to one XCD (slice s to XCD s mod 8): that XCD's
-        // L2 then fetches the range once for all macro-tiles.  An XCD whose queue runs dry takes from the
-        // longest one.
-        {
-            std::vector<GemmWg> q[8];
-            for (int sidx = 0; sidx < S; sidx++) q[sidx & 7].insert(q[sidx & 7].end(), by_slice[sidx].begin(), by_slice[sidx].end());
-            size_t head[8] = {0, 0, 0, 0, 0, 0, 0, 0}, left = 0;
-            for (int x = 0; x < 8; x++) left += q[x].size();
-            while (left > 0) {
-                const int x = (int)(P->wgs_op.size() & 7);
-                if (head[x] < q[x].size()) {
-                    P->wgs_op.push_back(q[x][head[x]++]);
-                } else {
-                    int longest = 0;
-                    for (int y = 1; y < 8; y++)
-                        if (q[y].size() - head[y] > q[longest].size() - head[longest]) longest = y;
-                    P->wgs_op.push_back(q[longest].back());
-                    q[longest].pop_back();
-                }
-                left--;
-            }
-        }
+        deal_slices(by_slice, P->wgs_op);
         P->red_blocks = (int)((slice / 4 + 255) / 256);
         P->slice_elems = slice;
         NNT_HIP(ctx, hipMalloc((void**)&P->d_red, red.size() * sizeof(SplitReduce)));
@@ -972,6 +1205,12 @@ extern "C" int32_t nnt_gemm(nnt_ctx* ctx, float alpha, int32_t opA, nnt_tensor* 
 
 namespace {
 
+void launch_splitk_reduce(hipStream_t st, const GemmPlan* P, const SplitReduce* red, float alpha, float beta) {
+    const dim3 grid((unsigned)P->red_blocks, (unsigned)P->n_split), block(256);
+    if (P->dtype_out == NNT_F32) hipLaunchKernelGGL((splitk_reduce<float>), grid, block, 0, st, red, alpha, beta);
+    else hipLaunchKernelGGL((splitk_reduce<uint16_t>), grid, block, 0, st, red, alpha, beta);
+}
+
 // what gemm_core answers when the plan of a product with an activation form has workgroups that no kernel with that
 // form takes (never leaves the library: the callers then run the product and the activation as two passes)
 constexpr int32_t kNoActKernel = 1 << 20;
@@ -985,17 +1224,22 @@ int32_t gemm_core(nnt_ctx* ctx, float alpha, int32_t opA, nnt_tensor* A, int32_t
     std::ostringstream key;
     key << opA << opB << ':' << A->id << ':' << B->id << ':' << C->id << ':' << (bias ? bias->id : 0) << ':' << ncon << ':' << nbat
         << ':' << (R ? R->id : 0) << key_extra;
-    GemmPlan* P;
-    auto it = ctx->gemm_plans.find(key.str());
-    if (it == ctx->gemm_plans.end()) {
-        if (ctx->capturing) return fail(ctx, NNT_ESTATE, "nnt_gemm: plan must exist before capture (run the call once first)");
-        std::shared_ptr<GemmPlan> np(new GemmPlan());
-        int32_t rc = build_plan(ctx, opA, A, opB, B, C, ncon, nbat, bias, R, np.get(), view_ld, epi);
-        if (rc != NNT_OK) return rc;
-        P = np.get();
-        ctx->gemm_plans[key.str()] = np;
-    } else {
-        P = it->second.get();
+    GemmPlan* P = nullptr;
+    const bool by_tile = ctx->granularity == NNT_GRAN_TILE && !view_ld;
+    for (const char* which : {"", ":t"}) {
+        const std::string k = key.str() + which;
+        auto it = ctx->gemm_plans.find(k);
+        if (it == ctx->gemm_plans.end()) {
+            if (ctx->capturing) return fail(ctx, NNT_ESTATE, "nnt_gemm: plan must exist before capture (run the call once first)");
+            std::shared_ptr<GemmPlan> np(new GemmPlan());
+            int32_t rc = build_plan(ctx, opA, A, opB, B, C, ncon, nbat, bias, R, np.get(), view_ld, epi);
+            if (rc != NNT_OK) return rc;
+            P = np.get();
+            ctx->gemm_plans[k] = np;
+        } else {
+            P = it->second.get();
+        }
+        if (!(by_tile && P->packed)) break;      // (a plan that lays the operands out afresh has no tasks per tile: another one is built)
     }
     if (epi && !P->epi_ok) return kNoActKernel;
     const int epi_mode = P->epi_mode;
@@ -1016,6 +1260,22 @@ int32_t gemm_core(nnt_ctx* ctx, float alpha, int32_t opA, nnt_tensor* A, int32_t
         if (bias) acc.push_back(bias->all(kRead));
         if (R && (beta != 0.f || epi)) acc.push_back(R->all((epi & 15) == kEpiGeluOut ? kWrite : kRead));
         g.wgs = P->d_wgs_op;
+        if (P->packed) {
+            g = P->pack_args;
+            g.alpha = alpha;
+            g.beta = beta;
+            acc.push_back(Access{&P->ws_dep, 1, kReadWrite});
+            const double red_bytes = (double)P->n_split * P->slice_elems * 4.0 * (P->splits + 1);
+            return submit(ctx, acc, [=](hipStream_t st) {
+                int32_t rc = pack_operands(st, P->pack[0], P->pack[1]);
+                if (rc != NNT_OK) return rc;
+                rc = launch_gemm_bf16_span(st, P->dtype_out == NNT_F32, P->akf, P->bkf, P->pack_cfg, g, P->pack_nwg);
+                if (rc != NNT_OK || P->n_split == 0) return rc;
+                profile_mark(ctx, st, "splitk_reduce", red_bytes, true);
+                launch_splitk_reduce(st, P, P->pack_red, alpha, beta);
+                return hipGetLastError() == hipSuccess ? (int32_t)NNT_OK : (int32_t)NNT_EHIP;
+            }, P->n_split > 0 ? 3 : 2);
+        }
         const int64_t nwg = P->op_nwg;
         if (nwg == 0) return NNT_OK;
         if (P->n_split > 0) {
@@ -1025,9 +1285,7 @@ int32_t gemm_core(nnt_ctx* ctx, float alpha, int32_t opA, nnt_tensor* A, int32_t
                 int32_t rc = launch_any(st, P->dtype_in, P->dtype_out, P->akf, P->bkf, P->cfg, g, nwg, P->op_nfast, P->dl_ragged);
                 if (rc != NNT_OK) return rc;
                 profile_mark(ctx, st, "splitk_reduce", red_bytes, true);
-                const dim3 grid((unsigned)P->red_blocks, (unsigned)P->n_split), block(256);
-                if (P->dtype_out == NNT_F32) hipLaunchKernelGGL((splitk_reduce<float>), grid, block, 0, st, P->d_red, alpha, beta);
-                else hipLaunchKernelGGL((splitk_reduce<uint16_t>), grid, block, 0, st, P->d_red, alpha, beta);
+                launch_splitk_reduce(st, P, P->d_red, alpha, beta);
                 return hipGetLastError() == hipSuccess ? (int32_t)NNT_OK : (int32_t)NNT_EHIP;
             }, 2);
         }

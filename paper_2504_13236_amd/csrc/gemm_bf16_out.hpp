@@ -6,6 +6,7 @@
 
 #include <type_traits>
 
+#include "gemm_common.hpp"
 #include "global_ptr.hpp"
 
 namespace nnt {
@@ -148,6 +149,133 @@ __device__ __forceinline__ void write_tile(float* stage, const f32x16 (&acc)[WNB
                             store_out(p + j, x);
                         }
                     }
+                }
+            }
+        }
+        __syncthreads();
+    }
+}
+
+// The same for a macro-tile that may cross the edges of C's tiles (GemmSpan): every 16-byte vector goes to the part that it lies in, at any
+// alignment, and vectors that cross an edge go element by element.  m_off, n_off: the wave's block within the macro-tile.
+template <typename TO, int WMB, int WNB>
+__device__ __forceinline__ void write_span(float* stage, const f32x16 (&acc)[WNB][WMB], const GemmSpan* span, float alpha, float beta, int m_off, int n_off, int lane) {
+    constexpr int MW = 32 * WMB, ROW = MW + 4;
+    constexpr int V = 16 / (int)sizeof(TO), CH = MW / V, RPI = 64 / CH, NIT = 32 / RPI;
+    static_assert(CH <= 64 && 32 % RPI == 0, "row shape");
+    const int r32 = lane & 31, half = lane >> 5;
+    const GemmSpan s = *span;
+    const int mc = (lane % CH) * V, gm = m_off + mc;
+    // the part along m is the lane's for good; vectors that cross an edge are told apart here
+    const bool a = gm >= s.sm;
+    const bool vec = gm + V <= s.rows && (a || gm + V <= s.sm);
+    TO* const C0 = in_global(static_cast<TO*>(a ? s.C[1] : s.C[0]));
+    TO* const C1 = in_global(static_cast<TO*>(a ? s.C[3] : s.C[2]));
+    const int64_t ldc = a ? s.ldc[1] : s.ldc[0], cin0 = a ? s.cin[1] : s.cin[0], cin1 = a ? s.cin[3] : s.cin[2];
+    const float* const bias = in_global(a ? s.bias[1] : s.bias[0]);
+    const bool has_bias = s.bias[0] != nullptr;
+    float bv[V];
+#pragma unroll
+    for (int j = 0; j < V; j++) bv[j] = 0.f;
+    if (has_bias && vec) {
+#pragma unroll
+        for (int j = 0; j < V; j += 4) {
+            const f32x4_any x = *reinterpret_cast<const f32x4_any*>(bias + gm + j);
+            bv[j] = x[0]; bv[j + 1] = x[1]; bv[j + 2] = x[2]; bv[j + 3] = x[3];
+        }
+    } else if (has_bias && gm < s.rows) {
+#pragma unroll
+        for (int j = 0; j < V; j++) {
+            const int ge = min(gm + j, s.rows - 1);
+            bv[j] = (ge >= s.sm ? in_global(s.bias[1]) : in_global(s.bias[0]))[ge];
+        }
+    }
+    const bool edge = __any(!vec && gm < s.rows);          // some lane of the wave has a vector that crosses an edge
+#pragma unroll
+    for (int bn = 0; bn < WNB; bn++) {
+#pragma unroll
+        for (int bm = 0; bm < WMB; bm++)
+#pragma unroll
+            for (int q = 0; q < 4; q++) {
+                f32x4 v;
+                v[0] = alpha * acc[bn][bm][4 * q];
+                v[1] = alpha * acc[bn][bm][4 * q + 1];
+                v[2] = alpha * acc[bn][bm][4 * q + 2];
+                v[3] = alpha * acc[bn][bm][4 * q + 3];
+                *reinterpret_cast<f32x4*>(&stage[r32 * ROW + bm * 32 + 8 * q + 4 * half]) = v;
+            }
+        __syncthreads();
+        uint4 cin[NIT];                  // asked for before the pass's first store (see write_tile)
+        if (beta != 0.f) {
+#pragma unroll
+            for (int it = 0; it < NIT; it++) {
+                const int gn = n_off + bn * 32 + it * RPI + lane / CH;
+                cin[it] = make_uint4(0u, 0u, 0u, 0u);
+                if (gn < s.cols && vec) cin[it] = get16<true>((gn >= s.sn ? C1 + cin1 : C0 + cin0) + gm + (int64_t)gn * ldc);
+            }
+        }
+#pragma unroll
+        for (int it = 0; it < NIT; it++) {
+            const int row = it * RPI + lane / CH, gn = n_off + bn * 32 + row;
+            float v[V];
+#pragma unroll
+            for (int j = 0; j < V; j += 4) {
+                const f32x4 x = *reinterpret_cast<const f32x4*>(&stage[row * ROW + mc + j]);
+                v[j] = x[0]; v[j + 1] = x[1]; v[j + 2] = x[2]; v[j + 3] = x[3];
+            }
+            if (vec && gn < s.cols) {
+                TO* p = (gn >= s.sn ? C1 : C0) + gm + (int64_t)gn * ldc;
+#pragma unroll
+                for (int j = 0; j < V; j++) v[j] += bv[j];
+                if constexpr (sizeof(TO) == 4) {
+                    if (beta != 0.f) {
+                        const uint4 c = cin[it];
+                        v[0] += beta * __uint_as_float(c.x); v[1] += beta * __uint_as_float(c.y);
+                        v[2] += beta * __uint_as_float(c.z); v[3] += beta * __uint_as_float(c.w);
+                    }
+                    *reinterpret_cast<f32x4_any*>(p) = f32x4_any{v[0], v[1], v[2], v[3]};
+                } else {
+                    if (beta != 0.f) {
+                        const uint4 c = cin[it];
+                        const uint32_t w[4] = {c.x, c.y, c.z, c.w};
+#pragma unroll
+                        for (int j = 0; j < 4; j++) {
+                            v[2 * j] += beta * __uint_as_float(w[j] << 16);
+                            v[2 * j + 1] += beta * __uint_as_float(w[j] & 0xffff0000u);
+                        }
+                    }
+                    uint32_t w[4];
+#pragma unroll
+                    for (int j = 0; j < 4; j++) {
+                        const __bf16 lo = (__bf16)v[2 * j], hi = (__bf16)v[2 * j + 1];
+                        w[j] = (uint32_t)__builtin_bit_cast(uint16_t, lo) | ((uint32_t)__builtin_bit_cast(uint16_t, hi) << 16);
+                    }
+                    *reinterpret_cast<u32x4_any*>(p) = u32x4_any{w[0], w[1], w[2], w[3]};
+                }
+            }
+        }
+        if (edge && !vec && gm < s.rows) {
+            // (the passes one after the other: their vectors lie in LDS; straight code for all of them keeps the loop above from being
+            // unrolled, and with it the accumulators out of registers)
+#pragma unroll 1
+            for (int it = 0; it < NIT; it++) {
+                const int row = it * RPI + lane / CH, gn = n_off + bn * 32 + row;
+                if (gn >= s.cols) break;
+                const bool b = gn >= s.sn;
+                TO* const P0 = in_global(static_cast<TO*>(b ? s.C[2] : s.C[0])) + (int64_t)gn * s.ldc[0];
+                TO* const P1 = in_global(static_cast<TO*>(b ? s.C[3] : s.C[1])) + (int64_t)gn * s.ldc[1];
+                const int64_t c0 = b ? s.cin[2] : s.cin[0], c1 = b ? s.cin[3] : s.cin[1];
+                float x[V];
+#pragma unroll
+                for (int j = 0; j < V; j++) {
+                    const int ge = gm + j;
+                    x[j] = stage[row * ROW + mc + j] + bv[j];
+                    if (beta != 0.f && ge < s.rows) x[j] += beta * load_out(ge >= s.sm ? P1 + ge + c1 : P0 + ge + c0);
+                }
+#pragma unroll
+                for (int j = 0; j < V; j++) {
+                    const int ge = gm + j;
+                    if (ge < s.rows) store_out((ge >= s.sm ? P1 : P0) + ge, x[j]);
                 }
             }
         }

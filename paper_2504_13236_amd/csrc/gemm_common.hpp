@@ -55,6 +55,16 @@ struct GemmWg {
     int32_t task, m0, n0, batch;
 };
 
+// Where the results of a macro-tile go that lies on a grid over all of C: up to 2 x 2 tiles of C, part (a, b) the rows from `sm` on (a = 1)
+// and the columns from `sn` on (b = 1).  Element (i, j) of the macro-tile belongs at C[a + 2 b] + i + j * ldc[a], its
+// bias at bias[a] + i, its beta term cin[a + 2 b] elements behind it.
+struct GemmSpan {
+    void* C[4];
+    const float* bias[2];
+    int64_t ldc[2], cin[4];
+    int32_t sm, sn, rows, cols;
+};
+
 struct GemmArgs {
     const GemmTask* tasks;
     const GemmChunk* chunks;
@@ -63,6 +73,7 @@ struct GemmArgs {
     GemmChunk one_chunk;
     int32_t grid_m, grid_n; // macro-tile grid of the single product
     float alpha, beta;
+    const GemmSpan* spans;  // kernels on a grid over all of C: one record per macro-tile, grid_m of them per column of macro-tiles
 };
 
 // Macro-tile configurations.  M counts rows of C (first, fastest axis), N columns.
@@ -97,6 +108,22 @@ int32_t launch_gemm_bf16(hipStream_t st, int out_is_f32, int akf, int bkf, int c
 // macro-tiles may end inside their C tile (row-contiguous operands: at a multiple of 8 rows) and chunk lengths are multiples of 8.
 // kCfgWide: 128 x 128 macro-tiles, always under the rules of `ragged`.
 int32_t launch_gemm_bf16_dl(hipStream_t st, int out_is_f32, int akf, int bkf, int cfg, bool ragged, const GemmArgs& g, int64_t nwg);
+// The same kernels (kCfgSquare, kCfgTall, kCfgWide) on operands that pack_operands has laid out afresh, macro-tiles on a grid over all of C.
+// Not both operands in the forms (k-contiguous A, row-contiguous B).
+int32_t launch_gemm_bf16_span(hipStream_t st, int out_is_f32, int akf, int bkf, int cfg, const GemmArgs& g, int64_t nwg);
+
+// One bf16 operand as the product kernels would like to find it: the matrix that its tiles make up, in one piece, `contig` elements
+// per line (its contiguous index) padded to `pitch`, a multiple of 64, with zeros, and `lines` lines followed by lines of zeros up to `all_lines`.
+// Tile (i, j) of the `ntc` x `ntl` tiles is tiles[i + ntc * j]; it holds `base` elements of a line (the last one what is left) and the
+// lines line0[j] .. line0[j + 1] - 1.
+struct PackOperand {
+    void* const* tiles;
+    uint16_t* dst;
+    const int32_t* line0;
+    int32_t ntc, ntl, base, contig, pitch, lines, all_lines;
+};
+int32_t pack_operands(hipStream_t st, const PackOperand& a, const PackOperand& b);
+
 // fp32: 128 x 128 (kCfgSquare), 64 x 128 (kCfgMid, kCfgSkinny64n128, kCfgResident) or 64 x 64 (kCfgSkinny64n64) macro-tiles of
 // 16-byte aligned operands.  Not `ragged`: macro-tiles wholly inside their C tile, chunk lengths that are multiples of 32.
 // `ragged`: macro-tiles may end inside their C tile (row-contiguous operands: at a multiple of 4 rows), chunk lengths are

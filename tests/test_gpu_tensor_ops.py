@@ -419,6 +419,49 @@ def test_activation_gradient_behind_a_short_contraction(mods, k, tm, n, gran):
         check(tdZ.download(), D.contract(1.0, "T", W, "N", dY, 0.0, None, 1, 0) * D.gelu_grad(Z.astype(np.float64), "tanh"), "f32", "dZ")
 
 
+@pytest.mark.parametrize("form", ["NN", "TN", "NT", "TT"])
+@pytest.mark.parametrize("m,n,k,tm,tn,tk", [
+    (1333, 1027, 777, 500, 257, 300),       # every extent odd, tiles of C crossed along both axes
+    (1281, 513, 1025, 1281, 513, 1025),     # one element beyond the macro-tiles and the k-steps, one tile
+    (2051, 1030, 1999, 1024, 515, 1000),    # k-slices
+    (300, 3100, 129, 100, 300, 50),         # tiles narrower than a macro-tile along m: operands read as they are
+    (1537, 4611, 515, 300, 2305, 257),      # many macro-tiles
+    (2816, 2560, 523, 300, 300, 300),       # whole macro-tiles, odd contraction
+])
+def test_bf16_products_of_odd_sizes(mods, m, n, k, tm, tn, tk, form):
+    """Operands that are laid out afresh: fp32 and bf16 results, bias, beta and residual input, twice in a row with other values in
+    the operands (what the first call laid out must not be seen again), and tile by tile as the comparison.  Operands hold
+    small multiples of 1/16, so fp32 results are exact up to the sums' rounding."""
+    capi, tiled = mods
+    r = rng(m + n + k)
+    opA, opB = ("NT".index(c) for c in form)
+    with tiled.Context(n_streams=2) as ctx:
+        ash, abase = ((m, k), (tm, tk)) if opA == 0 else ((k, m), (tk, tm))
+        bsh, bbase = ((k, n), (tk, tn)) if opB == 0 else ((n, k), (tn, tk))
+        draw = lambda shape: r.integers(-32, 33, shape).astype(np.float32) / 16
+        A, B, bias = draw(ash), draw(bsh), draw((m,))
+        tA, tB, tbias = T(tiled, ctx, A, abase, "bf16"), T(tiled, ctx, B, bbase, "bf16"), T(tiled, ctx, bias, (tm,), "f32")
+        for dt in ("f32", "bf16"):
+            C0, R = draw((m, n)), draw((m, n))
+            tC, tR, tD = (T(tiled, ctx, x, (tm, tn), dt) for x in (C0, R, C0))
+            for _ in range(2):
+                A, B = draw(ash), draw(bsh)
+                tA.upload(A)
+                tB.upload(B)
+                want = (A.T if opA else A).astype(np.float64) @ (B.T if opB else B).astype(np.float64)
+                capi.nnt_gemm(ctx.h, 1.0, opA, tA.h, opB, tB.h, 0.0, tC.h, 1, 0, tbias.h)
+                check(tC.download(), want + bias[:, None], dt, form + " + bias")
+                capi.nnt_gemm(ctx.h, 0.5, opA, tA.h, opB, tB.h, 2.0, tD.h, 1, 0, None)
+                C0 = 0.5 * want + 2.0 * C0
+                check(tD.download(), C0, dt, form + " + beta C")
+                C0 = tD.download().astype(np.float64)
+                capi.nnt_gemm_res(ctx.h, 1.0, opA, tA.h, opB, tB.h, 1.0, tC.h, 1, 0, tbias.h, tR.h)
+                check(tC.download(), want + bias[:, None] + R, dt, form + " + bias + R")
+        ctx.set_granularity(1)
+        capi.nnt_gemm(ctx.h, 1.0, opA, tA.h, opB, tB.h, 0.0, tD.h, 1, 0, None)
+        check(tD.download(), want, "bf16", form + ", tile by tile")
+
+
 def test_device_memory_of_the_library_is_reported(mods):
     """nnt_ctx_stats: tile-pointer tables and plan tables count as table bytes, the fp32 workspace of a
     product cut into k-slices as workspace bytes; both shrink again when the tensors go."""
