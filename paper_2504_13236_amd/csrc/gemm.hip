@@ -145,13 +145,13 @@ struct GemmPlan {
     std::vector<TileSplit> tile_split;         // per task; nwg == 0: launched whole
     std::vector<GemmWg> wgs_ts;
     int64_t slice_elems_ts = 0;
-    // Whole-operation launches of bf16 operands that only the register-staged kernel could read as they are: the operands are
+    // Whole-operation launches of operands that only the register-staged kernels could read as they are: the operands are
     // laid out afresh in `d_pack` first and the macro-tiles lie on one grid over all of C, with tables of its own.  Such a plan has
     // nothing else: launches tile by tile of the same product have a plan to themselves.
     bool packed = false;
     PackOperand pack[2] = {};
     int pack_cfg = 0;
-    uint16_t* d_pack = nullptr;
+    char* d_pack = nullptr;
     char* d_pack_tables = nullptr;
     GemmArgs pack_args = {};
     const SplitReduce* pack_red = nullptr;
@@ -579,26 +579,28 @@ std::vector<int64_t> group_starts(const nnt_tensor* t, const std::vector<int>& a
     return out;
 }
 
-// The form of a bf16 product that lays its operands out afresh (GemmPlan::packed), if it can take the product and promises to take
+// The form of a product that lays its operands out afresh (GemmPlan::packed), if it can take the product and promises to take
 // less than `limit_us`: nine tenths of what the model says of the register-staged kernels, with the copy priced at 14 us (10 to 12
 // measured for 13 MB, and a result path that sorts) and 3 TB/s.  At 5 us, 6 of 150 random products of 128 to 6000 rows, columns and
 // contraction became 8 to 20 % slower (632 x 4856 over 848 on tiles of 300: 29 -> 35 us); at 14 none of 300 did, and products of
 // some size are two to three times faster (2688 x 3072 over 2145 on tiles of 400: 185 -> 57; 3627 x 1880 over 2496: 174 -> 74).
 int32_t try_packed(nnt_ctx* ctx, const AxisMap& ax, nnt_tensor* A, nnt_tensor* B, nnt_tensor* C, nnt_tensor* bias, nnt_tensor* R, GemmPlan* P, double limit_us) {
+    const bool bf = A->dtype == NNT_BF16;
+    const int64_t elem = A->elem_size(), pad = bf ? 256 : 128;      // (pad: the most rows of a macro-tile)
     const std::vector<int>*contig[2] = {P->akf ? &ax.a_con : &ax.a_free, P->bkf ? &ax.b_con : &ax.b_free};
     if ((P->akf && !P->bkf) || contig[0]->size() != 1 || contig[1]->size() != 1) return NNT_OK;
     for (const nnt_tensor* t : {A, B, C})
         for (void* p : t->tiles) if (!p) return NNT_OK;
     const std::vector<int64_t> rows = group_starts(A, ax.a_free), cols = group_starts(B, ax.b_free), ks = group_starts(A, ax.a_con);
     const int64_t M = rows.back(), N = cols.back(), K = ks.back(), Kp = (K + 63) / 64 * 64;
-    const int64_t Mp = (M + 255) / 256 * 256, Np = (N + 255) / 256 * 256;
+    const int64_t Mp = (M + pad - 1) / pad * pad, Np = (N + pad - 1) / pad * pad;
     const int64_t a_elems = Mp * Kp, b_elems = Np * Kp;
     // (byte offsets of a macro-tile's lines and vector numbers have 32 bits)
-    if (Kp > (1 << 23) || Mp > (1 << 23) || Np > (1 << 23) || a_elems / 8 > INT32_MAX / 2 || b_elems / 8 > INT32_MAX / 2 || (a_elems + b_elems) * 2 > ((int64_t)2 << 30)) return NNT_OK;
-    const ShapeChoice sc = choose_shape(true, kShapeWhole, {M}, {N}, {Kp}, true);
-    if (sc.us + 14.0 + (double)(M + N) * K * 4.0 / 3.0e6 >= limit_us) return NNT_OK;
+    if (Kp > (1 << 23) || Mp > (1 << 23) || Np > (1 << 23) || a_elems > INT32_MAX || b_elems > INT32_MAX || (a_elems + b_elems) * elem > ((int64_t)2 << 30)) return NNT_OK;
+    const ShapeChoice sc = choose_shape(bf, kShapeWhole, {M}, {N}, {Kp}, true);
+    if (sc.us + (bf || K < 512 ? 14.0 : 3.5) + (double)(M + N) * K * 2.0 * elem / 3.0e6 >= limit_us) return NNT_OK;
     int bm, bn;
-    gemm_cfg_tile(1, sc.cfg, &bm, &bn);
+    gemm_cfg_tile(bf, sc.cfg, &bm, &bn);
     const int64_t gm = (M + bm - 1) / bm, gn = (N + bn - 1) / bn;
     if (sc.s > 1 && (sc.n_split * sc.s * bm * bn * (int64_t)sizeof(float) > ((int64_t)2 << 30) || sc.n_split > 65535 / 4)) return NNT_OK;
 
@@ -647,7 +649,7 @@ int32_t try_packed(nnt_ctx* ctx, const AxisMap& ax, nnt_tensor* A, nnt_tensor* B
     const int S = n_cut > 0 ? (int)((Kp + cut_part - 1) / cut_part) : 1;
     const int64_t slice = (int64_t)bm * bn;
     // (four floats more: the sum reads whole vectors, also of parts that do not begin at one)
-    const size_t pack_bytes = (size_t)(a_elems + b_elems) * 2, cut_bytes = n_cut > 0 ? ((size_t)n_cut * S * slice + 4) * sizeof(float) : 0;
+    const size_t pack_bytes = (size_t)((a_elems + b_elems) * elem), cut_bytes = n_cut > 0 ? ((size_t)n_cut * S * slice + 4) * sizeof(float) : 0;
     if (hipMalloc((void**)&P->d_pack, pack_bytes) != hipSuccess || (cut_bytes && hipMalloc((void**)&P->d_ws, cut_bytes) != hipSuccess)) {
         (void)hipGetLastError();
         if (P->d_pack) (void)hipFree(P->d_pack);
@@ -663,7 +665,7 @@ int32_t try_packed(nnt_ctx* ctx, const AxisMap& ax, nnt_tensor* A, nnt_tensor* B
         const int cx = (*contig[o])[0];
         PackOperand& p = P->pack[o];
         p.tiles = t->d_tiles;
-        p.dst = P->d_pack + (o ? a_elems : 0);
+        p.dst = P->d_pack + (o ? a_elems * elem : 0);
         p.ntc = (int32_t)t->grid[cx];
         p.ntl = (int32_t)lines[o]->size() - 1;
         p.base = (int32_t)t->base[cx];
@@ -696,8 +698,8 @@ int32_t try_packed(nnt_ctx* ctx, const AxisMap& ax, nnt_tensor* A, nnt_tensor* B
         const int64_t part = cut_part;
         for (int q = 0; q < S; q++) {
             GemmChunk c = whole;
-            c.A = P->pack[0].dst + q * part * (P->akf ? 1 : whole.lda);
-            c.B = P->pack[1].dst + q * part * (P->bkf ? 1 : whole.ldb);
+            c.A = static_cast<const char*>(whole.A) + q * part * (P->akf ? 1 : whole.lda) * elem;
+            c.B = static_cast<const char*>(whole.B) + q * part * (P->bkf ? 1 : whole.ldb) * elem;
             c.k = (int32_t)std::min(part, Kp - q * part);
             chunks.push_back(c);
         }
@@ -951,7 +953,7 @@ int32_t build_plan(nnt_ctx* ctx, int opA, nnt_tensor* A, int opB, nnt_tensor* B,
         S = sc.s;
         n_split = sc.n_split;
         static const bool no_pack = getenv("NNT_GEMM_NO_PACK") != nullptr;      // debugging aid: operands are read as they are
-        if (bf && kind == kShapeGeneral && epi == 0 && ctx->granularity == NNT_GRAN_OP && !no_pack) {
+        if (kind == kShapeGeneral && epi == 0 && ctx->granularity == NNT_GRAN_OP && !no_pack) {
             const int32_t rc = try_packed(ctx, ax, A, B, C, bias, R, P, 0.9 * sc.us);
             if (rc != NNT_OK) return rc;
         }
@@ -980,7 +982,9 @@ int32_t build_plan(nnt_ctx* ctx, int opA, nnt_tensor* A, int opB, nnt_tensor* B,
     if (P->packed) {
         const std::string old_name = P->label.substr(0, P->label.find('>') + 1);
         const char* tf[2] = {"false", "true"};
-        P->label = std::string(P->pack_cfg == kCfgSquare ? "gemm_bf16_span_kernel<" : P->pack_cfg == kCfgTall ? "gemm_bf16_span_tall_kernel<" : "gemm_bf16_span_wide_kernel<") +
+        if (!bf) P->label = std::string("gemm_f32_span_kernel<") + tf[P->akf] + ", " + tf[P->bkf] +
+                            (P->pack_cfg == kCfgSquare ? ", 2, 2>" : P->pack_cfg == kCfgMid ? ", 1, 2>" : ", 1, 1>") + P->label.substr(old_name.size());
+        else P->label = std::string(P->pack_cfg == kCfgSquare ? "gemm_bf16_span_kernel<" : P->pack_cfg == kCfgTall ? "gemm_bf16_span_tall_kernel<" : "gemm_bf16_span_wide_kernel<") +
                    (C->dtype == NNT_F32 ? "float, " : "unsigned short, ") + tf[P->akf] + ", " + tf[P->bkf] + ">" + P->label.substr(old_name.size());
         return NNT_OK;
     }
@@ -1267,9 +1271,11 @@ int32_t gemm_core(nnt_ctx* ctx, float alpha, int32_t opA, nnt_tensor* A, int32_t
             acc.push_back(Access{&P->ws_dep, 1, kReadWrite});
             const double red_bytes = (double)P->n_split * P->slice_elems * 4.0 * (P->splits + 1);
             return submit(ctx, acc, [=](hipStream_t st) {
-                int32_t rc = pack_operands(st, P->pack[0], P->pack[1]);
+                const bool bf16 = P->dtype_in == NNT_BF16;
+                int32_t rc = pack_operands(st, bf16, P->pack[0], P->pack[1]);
                 if (rc != NNT_OK) return rc;
-                rc = launch_gemm_bf16_span(st, P->dtype_out == NNT_F32, P->akf, P->bkf, P->pack_cfg, g, P->pack_nwg);
+                rc = bf16 ? launch_gemm_bf16_span(st, P->dtype_out == NNT_F32, P->akf, P->bkf, P->pack_cfg, g, P->pack_nwg)
+                          : launch_gemm_f32_span(st, P->akf, P->bkf, P->pack_cfg, g, P->pack_nwg);
                 if (rc != NNT_OK || P->n_split == 0) return rc;
                 profile_mark(ctx, st, "splitk_reduce", red_bytes, true);
                 launch_splitk_reduce(st, P, P->pack_red, alpha, beta);

@@ -111,18 +111,19 @@ int32_t launch_gemm_bf16_dl(hipStream_t st, int out_is_f32, int akf, int bkf, in
 // The same kernels (kCfgSquare, kCfgTall, kCfgWide) on operands that pack_operands has laid out afresh, macro-tiles on a grid over all of C.
 // Not both operands in the forms (k-contiguous A, row-contiguous B).
 int32_t launch_gemm_bf16_span(hipStream_t st, int out_is_f32, int akf, int bkf, int cfg, const GemmArgs& g, int64_t nwg);
+int32_t launch_gemm_f32_span(hipStream_t st, int akf, int bkf, int cfg, const GemmArgs& g, int64_t nwg);      // kCfgSquare, kCfgMid, kCfgSkinny64n64
 
-// One bf16 operand as the product kernels would like to find it: the matrix that its tiles make up, in one piece, `contig` elements
+// One operand as the product kernels would like to find it: the matrix that its tiles make up, in one piece, `contig` elements
 // per line (its contiguous index) padded to `pitch`, a multiple of 64, with zeros, and `lines` lines followed by lines of zeros up to `all_lines`.
 // Tile (i, j) of the `ntc` x `ntl` tiles is tiles[i + ntc * j]; it holds `base` elements of a line (the last one what is left) and the
 // lines line0[j] .. line0[j + 1] - 1.
 struct PackOperand {
     void* const* tiles;
-    uint16_t* dst;
+    void* dst;
     const int32_t* line0;
     int32_t ntc, ntl, base, contig, pitch, lines, all_lines;
 };
-int32_t pack_operands(hipStream_t st, const PackOperand& a, const PackOperand& b);
+int32_t pack_operands(hipStream_t st, bool bf16, const PackOperand& a, const PackOperand& b);
 
 // fp32: 128 x 128 (kCfgSquare), 64 x 128 (kCfgMid, kCfgSkinny64n128, kCfgResident) or 64 x 64 (kCfgSkinny64n64) macro-tiles of
 // 16-byte aligned operands.  Not `ragged`: macro-tiles wholly inside their C tile, chunk lengths that are multiples of 32.

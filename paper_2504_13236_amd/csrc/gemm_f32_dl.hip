@@ -151,7 +151,8 @@ __device__ __forceinline__ void read_frag(typename FragSel<KF>::type& f, const F
 // their result stores to be acknowledged, so what counts is how many of them a compute unit holds).
 // RAG: the macro-tile may end inside its C tile (see load_offset_clamped; the result path stores nothing beyond the
 // edge), and chunk lengths need not be multiples of 32: the last pair of k-steps of a chunk may be short.
-template <bool AKF, bool BKF, int WMB, int WNB, int EPI, bool RES = false, bool RAG = false>
+// SPAN: the macro-tile lies on a grid over all of C and may cross the edges of C's tiles; where its results go stands in g.spans.
+template <bool AKF, bool BKF, int WMB, int WNB, int EPI, bool RES = false, bool RAG = false, bool SPAN = false>
 __device__ __forceinline__ void f32_dl_body(const GemmArgs& g, char* lds) {
     constexpr int kStages = RES ? 4 : nnt::kStages;
     constexpr int BM = 64 * WMB, BN = 64 * WNB;
@@ -424,6 +425,13 @@ __device__ __forceinline__ void f32_dl_body(const GemmArgs& g, char* lds) {
     }
     f32x16 (&res)[WNB][WMB] = RES ? acc : sum;
 
+    if constexpr (SPAN) {
+        if (!task.partial) {
+            write_span_f32<WMB, WNB>(res, g.spans + (m0 / BM + (n0 / BN) * g.grid_m), g.alpha, g.beta, wm * WMB * 32, wn * WNB * 32, lane);
+            return;
+        }
+    }
+
     if constexpr (RAG) {
         write_tile_f32<WMB, WNB>(res, global_as<float>(task.C) + (int64_t)bat_lo * task.strideC + (int64_t)bat_hi * task.strideC2, task.ldc, task.cin_off,
                                  task.partial ? nullptr : in_global(task.bias), task.partial ? 1.f : g.alpha, task.partial ? 0.f : g.beta,
@@ -502,7 +510,19 @@ __global__ void __launch_bounds__(256, 3) gemm_f32_dl_rk_rag_kernel(const GemmAr
     f32_dl_body<true, true, 1, 2, 0, true, true>(g, lds);
 }
 
+// Products of operands that pack_operands has laid out afresh: whole macro-tiles and pairs of k-steps, results sorted into C's tiles.
+template <bool AKF, bool BKF, int WMB, int WNB>
+__global__ void __launch_bounds__(256, WMB + WNB == 2 ? 4 : 2) gemm_f32_span_kernel(const GemmArgs g) {
+    __shared__ __attribute__((aligned(16))) char lds[kStages * (64 * WMB + 64 * WNB) * kBK * 4];
+    f32_dl_body<AKF, BKF, WMB, WNB, 0, false, false, true>(g, lds);
+}
+
 using KernelFn = void (*)(const GemmArgs);
+
+template <int WMB, int WNB>
+KernelFn span_kernel_of(int akf, int bkf) {
+    return akf ? gemm_f32_span_kernel<true, true, WMB, WNB> : bkf ? gemm_f32_span_kernel<false, true, WMB, WNB> : gemm_f32_span_kernel<false, false, WMB, WNB>;
+}
 
 template <int WMB, int WNB>
 KernelFn act_kernel_of(int epi_mode) {
@@ -530,6 +550,13 @@ KernelFn kernel_of(int akf, int bkf, int cfg, bool ragged) {
 }
 
 }  // namespace
+
+int32_t launch_gemm_f32_span(hipStream_t st, int akf, int bkf, int cfg, const GemmArgs& g, int64_t nwg) {
+    if ((cfg != kCfgSquare && cfg != kCfgMid && cfg != kCfgSkinny64n64) || (akf && !bkf)) return NNT_EINVAL;
+    const KernelFn fn = cfg == kCfgSquare ? span_kernel_of<2, 2>(akf, bkf) : cfg == kCfgMid ? span_kernel_of<1, 2>(akf, bkf) : span_kernel_of<1, 1>(akf, bkf);
+    hipLaunchKernelGGL(fn, dim3((unsigned)nwg), dim3(256), 0, st, g);
+    return hipGetLastError() == hipSuccess ? NNT_OK : NNT_EHIP;
+}
 
 bool gemm_f32_dl_has_act(int akf, int bkf, int epi_mode) {
     return bkf && ((epi_mode == kEpiGeluOut && !akf) || (epi_mode == kEpiGeluGradMul && akf));

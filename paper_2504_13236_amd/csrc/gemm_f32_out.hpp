@@ -3,6 +3,7 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "gemm_common.hpp"
 #include "global_ptr.hpp"
 
 namespace nnt {
@@ -90,6 +91,41 @@ __device__ __forceinline__ void write_tile_f32(const f32x16 (&acc)[WNB][WMB], fl
 #pragma unroll
                 for (int i = 0; i < 16; i++)
                     if (8 * (i >> 2) + (i & 3) < left) p[(int64_t)(8 * (i >> 2) + (i & 3)) * ldc] = v[i];
+            }
+        }
+    }
+}
+
+// The same for a macro-tile that may cross the edges of C's tiles (GemmSpan).  m_off, n_off: the wave's block within the macro-tile.
+template <int WMB, int WNB>
+__device__ __forceinline__ void write_span_f32(const f32x16 (&acc)[WNB][WMB], const GemmSpan* span, float alpha, float beta, int m_off, int n_off, int lane) {
+    const GemmSpan s = *span;
+    const int r32 = lane & 31, half = lane >> 5;
+#pragma unroll
+    for (int bm = 0; bm < WMB; bm++) {
+        const int gm = m_off + 32 * bm + r32;
+        if (gm >= s.rows) continue;
+        const bool a = gm >= s.sm;
+        float* const C0 = in_global(static_cast<float*>(a ? s.C[1] : s.C[0])) + gm;
+        float* const C1 = in_global(static_cast<float*>(a ? s.C[3] : s.C[2])) + gm;
+        const int64_t ldc = a ? s.ldc[1] : s.ldc[0], cin0 = a ? s.cin[1] : s.cin[0], cin1 = a ? s.cin[3] : s.cin[2];
+        const float bias = s.bias[0] ? (a ? in_global(s.bias[1]) : in_global(s.bias[0]))[gm] : 0.f;
+#pragma unroll
+        for (int bn = 0; bn < WNB; bn++) {
+            float cin[16];
+#pragma unroll
+            for (int i = 0; i < 16; i++) {
+                const int gn = n_off + 32 * bn + 8 * (i >> 2) + 4 * half + (i & 3);
+                cin[i] = 0.f;
+                if (beta != 0.f && gn < s.cols) cin[i] = (gn >= s.sn ? C1 + cin1 : C0 + cin0)[(int64_t)gn * ldc];
+            }
+            __builtin_amdgcn_s_waitcnt(0x0F70);        // vmcnt(0): no load is pending at the stores below (see write_tile_f32)
+#pragma unroll
+            for (int i = 0; i < 16; i++) {
+                const int gn = n_off + 32 * bn + 8 * (i >> 2) + 4 * half + (i & 3);
+                float v = alpha * acc[bn][bm][i] + bias;
+                if (beta != 0.f) v += beta * cin[i];
+                if (gn < s.cols) (gn >= s.sn ? C1 : C0)[(int64_t)gn * ldc] = v;
             }
         }
     }

@@ -419,6 +419,7 @@ def test_activation_gradient_behind_a_short_contraction(mods, k, tm, n, gran):
         check(tdZ.download(), D.contract(1.0, "T", W, "N", dY, 0.0, None, 1, 0) * D.gelu_grad(Z.astype(np.float64), "tanh"), "f32", "dZ")
 
 
+@pytest.mark.parametrize("din", ["bf16", "f32"])
 @pytest.mark.parametrize("form", ["NN", "TN", "NT", "TT"])
 @pytest.mark.parametrize("m,n,k,tm,tn,tk", [
     (1333, 1027, 777, 500, 257, 300),       # every extent odd, tiles of C crossed along both axes
@@ -428,7 +429,7 @@ def test_activation_gradient_behind_a_short_contraction(mods, k, tm, n, gran):
     (1537, 4611, 515, 300, 2305, 257),      # many macro-tiles
     (2816, 2560, 523, 300, 300, 300),       # whole macro-tiles, odd contraction
 ])
-def test_bf16_products_of_odd_sizes(mods, m, n, k, tm, tn, tk, form):
+def test_products_of_odd_sizes(mods, m, n, k, tm, tn, tk, form, din):
     """Operands that are laid out afresh: fp32 and bf16 results, bias, beta and residual input, twice in a row with other values in
     the operands (what the first call laid out must not be seen again), and tile by tile as the comparison.  Operands hold
     small multiples of 1/16, so fp32 results are exact up to the sums' rounding."""
@@ -440,8 +441,8 @@ def test_bf16_products_of_odd_sizes(mods, m, n, k, tm, tn, tk, form):
         bsh, bbase = ((k, n), (tk, tn)) if opB == 0 else ((n, k), (tn, tk))
         draw = lambda shape: r.integers(-32, 33, shape).astype(np.float32) / 16
         A, B, bias = draw(ash), draw(bsh), draw((m,))
-        tA, tB, tbias = T(tiled, ctx, A, abase, "bf16"), T(tiled, ctx, B, bbase, "bf16"), T(tiled, ctx, bias, (tm,), "f32")
-        for dt in ("f32", "bf16"):
+        tA, tB, tbias = T(tiled, ctx, A, abase, din), T(tiled, ctx, B, bbase, din), T(tiled, ctx, bias, (tm,), "f32")
+        for dt in ("f32", "bf16") if din == "bf16" else ("f32",):
             C0, R = draw((m, n)), draw((m, n))
             tC, tR, tD = (T(tiled, ctx, x, (tm, tn), dt) for x in (C0, R, C0))
             for _ in range(2):
@@ -459,7 +460,7 @@ def test_bf16_products_of_odd_sizes(mods, m, n, k, tm, tn, tk, form):
                 check(tC.download(), want + bias[:, None] + R, dt, form + " + bias + R")
         ctx.set_granularity(1)
         capi.nnt_gemm(ctx.h, 1.0, opA, tA.h, opB, tB.h, 0.0, tD.h, 1, 0, None)
-        check(tD.download(), want, "bf16", form + ", tile by tile")
+        check(tD.download(), want, dt, form + ", tile by tile")
 
 
 def test_device_memory_of_the_library_is_reported(mods):
