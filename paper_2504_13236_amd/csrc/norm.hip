@@ -22,7 +22,11 @@ namespace {
 // along axis 0, e the first row inside it and ext the tile's extent.  With NV > 0
 // the loop is fully unrolled and `slot` is a compile-time index into a per-lane
 // register cache; with NV == 0 it is a plain loop and slot is 0.
-template <int V, int NV, int WPT = 1, typename Fn>
+// ANY (only with NV > 0): tiles of any extent and alignment.  A vector that would pass the tile's end is moved back to end there, and
+// fn(slot, l, e, ext, own) is told which of its elements are the vector's own (the others belong to its neighbour, or do not exist in tiles shorter
+// than a vector).
+struct Own { int lo, hi; __device__ __forceinline__ bool operator()(int k) const { return k >= lo && k < hi; } };
+template <int V, int NV, int WPT = 1, bool ANY = false, typename Fn>
 __device__ __forceinline__ void walk(const TiledView& v, int lane, Fn fn, int w = 0) {
     const int g0 = v.grid[0];
     if constexpr (NV > 0) {
@@ -37,7 +41,14 @@ __device__ __forceinline__ void walk(const TiledView& v, int lane, Fn fn, int w 
             if (l < g0) {
                 const int ext = ext0_of(v, l);
                 const int e = (j * 64 + lane) * V;
-                if (e < ext) fn(it, l, e, ext);
+                if constexpr (ANY) {
+                    if (e < ext) {
+                        const int at = max(min(e, ext - V), 0);
+                        fn(it, l, at, ext, Own{e - at, min(V, ext - at)});
+                    }
+                } else {
+                    if (e < ext) fn(it, l, e, ext, Own{0, V});
+                }
             }
             if constexpr (WPT == 1) {
                 if (++j == vpt) {
@@ -55,8 +66,61 @@ __device__ __forceinline__ void walk(const TiledView& v, int lane, Fn fn, int w 
     } else {
         for (int l = 0; l < g0; l++) {
             const int ext = ext0_of(v, l);
-            for (int e = (w * 64 + lane) * V; e < ext; e += 64 * V * WPT) fn(0, l, e, ext);
+            for (int e = (w * 64 + lane) * V; e < ext; e += 64 * V * WPT) fn(0, l, e, ext, Own{0, V});
         }
+    }
+}
+
+// V elements at any address of an element; `n` < V of them where a tile is shorter than a vector (the same in every lane of a wave).
+typedef float f4_any __attribute__((ext_vector_type(4), aligned(4)));
+typedef uint32_t u4_any __attribute__((ext_vector_type(4), aligned(2)));
+template <bool ANY, int V> __device__ __forceinline__ void ldn(const float* p, int n, float (&f)[V]) {
+    if constexpr (!ANY || V == 1) {
+        ldv<V>(p, f);
+    } else if (n >= V) {
+#pragma unroll
+        for (int i = 0; i < V; i += 4) {
+            const f4_any x = *reinterpret_cast<const f4_any*>(p + i);
+            f[i] = x[0]; f[i + 1] = x[1]; f[i + 2] = x[2]; f[i + 3] = x[3];
+        }
+    } else {
+#pragma unroll
+        for (int i = 0; i < V; i++) f[i] = i < n ? p[i] : 0.f;
+    }
+}
+template <bool ANY, int V> __device__ __forceinline__ void ldn(const bf16_t* p, int n, float (&f)[V]) {
+    if constexpr (!ANY || V == 1) {
+        ldv<V>(p, f);
+    } else if (n >= V) {
+        const u4_any x = *reinterpret_cast<const u4_any*>(p);
+#pragma unroll
+        for (int i = 0; i < 4; i++) { f[2 * i] = __uint_as_float(x[i] << 16); f[2 * i + 1] = __uint_as_float(x[i] & 0xffff0000u); }
+    } else {
+#pragma unroll
+        for (int i = 0; i < V; i++) f[i] = i < n ? bf2f(p[i]) : 0.f;
+    }
+}
+template <bool ANY, int V> __device__ __forceinline__ void stn(float* p, int n, const float (&f)[V]) {
+    if constexpr (!ANY || V == 1) {
+        stv<V>(p, f);
+    } else if (n >= V) {
+        *reinterpret_cast<f4_any*>(p) = f4_any{f[0], f[1], f[2], f[3]};
+    } else {
+#pragma unroll
+        for (int i = 0; i < V; i++) if (i < n) p[i] = f[i];
+    }
+}
+template <bool ANY, int V> __device__ __forceinline__ void stn(bf16_t* p, int n, const float (&f)[V]) {
+    if constexpr (!ANY || V == 1) {
+        stv<V>(p, f);
+    } else if (n >= V) {
+        u4_any x;
+#pragma unroll
+        for (int i = 0; i < 4; i++) x[i] = (uint32_t)f2bf(f[2 * i]) | ((uint32_t)f2bf(f[2 * i + 1]) << 16);
+        *reinterpret_cast<u4_any*>(p) = x;
+    } else {
+#pragma unroll
+        for (int i = 0; i < V; i++) if (i < n) p[i] = f2bf(f[i]);
     }
 }
 
@@ -76,7 +140,7 @@ __device__ __forceinline__ float column_sum(float x, float* red, int w, int lane
 
 // WPT = 1: one wavefront per token, four tokens per workgroup.  WPT = 4: the workgroup's four wavefronts share
 // one token (long tokens: a quarter of the registers per wave, four times the waves in flight).
-template <typename T, int V, int NV, int WPT = 1>
+template <typename T, int V, int NV, int WPT = 1, bool ANY = false>
 __global__ void __launch_bounds__(256) ln_fwd_fused(TiledView X, TiledView Y, TiledView S, TiledView G, TiledView Bt,
                                                      float eps, int64_t ncols) {
     __shared__ float red[4];
@@ -92,43 +156,43 @@ __global__ void __launch_bounds__(256) ln_fwd_fused(TiledView X, TiledView Y, Ti
     // element of the token lies far from the rest).  The second pass runs over the register cache when
     // the token fits there and re-reads the token otherwise (it is still in the L2 of this wave's XCD).
     float s1 = 0.f;
-    walk<V, NV, WPT>(X, lane, [&](int slot, int l, int e, int ext) {
+    walk<V, NV, WPT, ANY>(X, lane, [&](int slot, int l, int e, int ext, Own own) {
         float x[V];
-        ldv<V>(col_ptr<const T>(X, c, l, ext) + e, x);
+        ldn<ANY, V>(col_ptr<const T>(X, c, l, ext) + e, ext, x);
 #pragma unroll
         for (int k = 0; k < V; k++) {
-            s1 += x[k];
+            s1 += !ANY || own(k) ? x[k] : 0.f;
             if constexpr (NV > 0) cache[slot][k] = x[k];
         }
     }, w);
     const float mean = column_sum<WPT>(s1, red, w, lane) / (float)N;
     float s2 = 0.f;
-    walk<V, NV, WPT>(X, lane, [&](int slot, int l, int e, int ext) {
+    walk<V, NV, WPT, ANY>(X, lane, [&](int slot, int l, int e, int ext, Own own) {
         float x[V];
         if constexpr (NV > 0) {
 #pragma unroll
             for (int k = 0; k < V; k++) x[k] = cache[slot][k];
         } else {
-            ldv<V>(col_ptr<const T>(X, c, l, ext) + e, x);
+            ldn<ANY, V>(col_ptr<const T>(X, c, l, ext) + e, ext, x);
         }
 #pragma unroll
-        for (int k = 0; k < V; k++) s2 += (x[k] - mean) * (x[k] - mean);
+        for (int k = 0; k < V; k++) s2 += !ANY || own(k) ? (x[k] - mean) * (x[k] - mean) : 0.f;
     }, w);
     const float var = column_sum<WPT>(s2, red, w, lane) / (float)N;
     const float rstd = 1.f / sqrtf(var + eps);
-    walk<V, NV, WPT>(X, lane, [&](int slot, int l, int e, int ext) {
+    walk<V, NV, WPT, ANY>(X, lane, [&](int slot, int l, int e, int ext, Own own) {
         float x[V], g[V], b[V];
         if constexpr (NV > 0) {
 #pragma unroll
             for (int k = 0; k < V; k++) x[k] = cache[slot][k];
         } else {
-            ldv<V>(col_ptr<const T>(X, c, l, ext) + e, x);
+            ldn<ANY, V>(col_ptr<const T>(X, c, l, ext) + e, ext, x);
         }
-        ldv<V>(global_as<const float>(G.tiles[l]) + e, g);
-        ldv<V>(global_as<const float>(Bt.tiles[l]) + e, b);
+        ldn<ANY, V>(global_as<const float>(G.tiles[l]) + e, ext, g);
+        ldn<ANY, V>(global_as<const float>(Bt.tiles[l]) + e, ext, b);
 #pragma unroll
         for (int k = 0; k < V; k++) x[k] = g[k] * ((x[k] - mean) * rstd) + b[k];
-        stv<V>(col_ptr<T>(Y, c, l, ext) + e, x);
+        stn<ANY, V>(col_ptr<T>(Y, c, l, ext) + e, ext, x);
     }, w);
     if (lane == 0 && w == 0) {
         float* s = global_as<float>(S.tiles[c.stat_tile]) + 2 * (int64_t)c.colidx;
@@ -152,7 +216,7 @@ __global__ void __launch_bounds__(256) ln_bwd_fused(TiledView X, TiledView S, Ti
     const float mean = st[0], rstd = st[1];
     float cg[NV > 0 ? NV : 1][V], ch[NV > 0 ? NV : 1][V];   // g = dy * gamma, xhat
     float a = 0.f, b = 0.f;
-    walk<V, NV, WPT>(X, lane, [&](int slot, int l, int e, int ext) {
+    walk<V, NV, WPT>(X, lane, [&](int slot, int l, int e, int ext, Own) {
         float x[V], d[V], g[V];
         ldv<V>(col_ptr<const T>(X, c, l, ext) + e, x);
         ldv<V>(col_ptr<const T>(dY, c, l, ext) + e, d);
@@ -167,7 +231,7 @@ __global__ void __launch_bounds__(256) ln_bwd_fused(TiledView X, TiledView S, Ti
     }, w);
     a = column_sum<WPT>(a, red, w, lane) / (float)N;
     b = column_sum<WPT>(b, red, w, lane) / (float)N;
-    walk<V, NV, WPT>(X, lane, [&](int slot, int l, int e, int ext) {
+    walk<V, NV, WPT>(X, lane, [&](int slot, int l, int e, int ext, Own) {
         float gg[V], xh[V], r[V];
         if constexpr (NV > 0) {
 #pragma unroll
@@ -659,18 +723,32 @@ bool tensors_vec_ok(std::initializer_list<const nnt_tensor*> ts, int V) {
     return true;
 }
 
+// Whether vectors may be read and written at the tiles' own alignment: every tile begins at an element.
+bool any_vec(std::initializer_list<const nnt_tensor*> ts) {
+    for (const nnt_tensor* t : ts)
+        if (t)
+            for (void* p : t->tiles)
+                if ((uintptr_t)p % (uintptr_t)t->elem_size() != 0) return false;
+    return true;
+}
+
 // Tokens of more vectors per lane than this are shared by the four wavefronts of a workgroup (measured: shorter
 // tokens lose to the two workgroup barriers, longer ones gain from four times the loads in flight).
 constexpr int kLnShareAbove = 4;
 
 template <typename T>
-int32_t launch_ln_fwd(hipStream_t st, bool vec, int nv_needed, const TiledView& X, const TiledView& Y, const TiledView& S,
+int32_t launch_ln_fwd(hipStream_t st, bool vec, bool any, int nv_needed, const TiledView& X, const TiledView& Y, const TiledView& S,
                       const TiledView& G, const TiledView& B, float eps, int64_t ncols) {
     constexpr int V = VecOf<T>::V;
     // tokens of more than `kLnShareAbove` vectors per lane are shared by the four wavefronts of a workgroup
-    const bool shared = vec && nv_needed > kLnShareAbove;
+    any = any && !vec && nv_needed <= 64;
+    const bool shared = (vec || any) && nv_needed > kLnShareAbove;
     const dim3 grid((unsigned)(shared ? ncols : (ncols + 3) / 4)), block(256);
-    if (!vec) hipLaunchKernelGGL((ln_fwd_fused<T, 1, 0>), grid, block, 0, st, X, Y, S, G, B, eps, ncols);
+    // (odd extents: vectors at any alignment, the last one of a tile moved back to end there)
+    if (any && !shared) hipLaunchKernelGGL((ln_fwd_fused<T, V, 4, 1, true>), grid, block, 0, st, X, Y, S, G, B, eps, ncols);
+    else if (any && nv_needed <= 16) hipLaunchKernelGGL((ln_fwd_fused<T, V, 4, 4, true>), grid, block, 0, st, X, Y, S, G, B, eps, ncols);
+    else if (any) hipLaunchKernelGGL((ln_fwd_fused<T, V, 16, 4, true>), grid, block, 0, st, X, Y, S, G, B, eps, ncols);
+    else if (!vec) hipLaunchKernelGGL((ln_fwd_fused<T, 1, 0>), grid, block, 0, st, X, Y, S, G, B, eps, ncols);
     else if (!shared && nv_needed <= 4) hipLaunchKernelGGL((ln_fwd_fused<T, V, 4>), grid, block, 0, st, X, Y, S, G, B, eps, ncols);
     else if (!shared && nv_needed <= 16) hipLaunchKernelGGL((ln_fwd_fused<T, V, 16>), grid, block, 0, st, X, Y, S, G, B, eps, ncols);
     else if (!shared) hipLaunchKernelGGL((ln_fwd_fused<T, V, 0>), grid, block, 0, st, X, Y, S, G, B, eps, ncols);
@@ -681,12 +759,11 @@ int32_t launch_ln_fwd(hipStream_t st, bool vec, int nv_needed, const TiledView& 
 }
 
 template <typename T>
-int32_t launch_ln_bwd(hipStream_t st, bool vec, int nv_needed, const TiledView& X, const TiledView& S, const TiledView& G,
+int32_t launch_ln_bwd(hipStream_t st, bool vec, const TiledView& X, const TiledView& S, const TiledView& G,
                       const TiledView& dY, const TiledView& dR, const TiledView& dX, int has_res, int64_t ncols) {
     constexpr int V = VecOf<T>::V;
     // (what is too long for ln_bwd_onepass: the four wavefronts of a workgroup share a token)
     if (!vec) hipLaunchKernelGGL((ln_bwd_fused<T, 1, 0>), dim3((unsigned)((ncols + 3) / 4)), dim3(256), 0, st, X, S, G, dY, dR, dX, has_res, ncols);
-    else if (nv_needed <= 32) hipLaunchKernelGGL((ln_bwd_fused<T, V, 8, 4>), dim3((unsigned)ncols), dim3(256), 0, st, X, S, G, dY, dR, dX, has_res, ncols);
     else hipLaunchKernelGGL((ln_bwd_fused<T, V, 0, 4>), dim3((unsigned)ncols), dim3(256), 0, st, X, S, G, dY, dR, dX, has_res, ncols);
     return hipGetLastError() == hipSuccess ? NNT_OK : NNT_EHIP;
 }
@@ -698,13 +775,10 @@ int32_t launch_ln_bwd(hipStream_t st, bool vec, int nv_needed, const TiledView& 
 // and the vectors of the next token in registers while it works on the present one, so that memory is never idle.
 // At the end the groups' sums meet in LDS and the workgroup leaves one partial row per gradient (at most
 // 256 rows, which rowsum_stage2 adds in a fixed order): 8192 x 4096 in bf16 with a residual 95 -> 89 us,
-// 1024 x 16384 50 -> 38, 768 x 2048 20 -> 15; forward and backward with the calls before and behind them 115 -> 107, 63 -> 53, 36 -> 17.
+// 1024 x 16384 50 -> 38, 768 x 2048 20 -> 15, odd extents (vectors at any alignment instead of single elements) 3001 x 2004 72 -> 32; forward and backward with the calls before and behind them 115 -> 107, 63 -> 53, 36 -> 17.
 template <typename T, int V> struct RawVec;
-template <typename T> struct RawVec<T, 1> { using R = T; };
 template <> struct RawVec<float, 4> { using R = float4; };
 template <> struct RawVec<bf16_t, 8> { using R = uint4; };
-__device__ __forceinline__ void unpack(const float& r, float (&f)[1]) { f[0] = r; }
-__device__ __forceinline__ void unpack(const bf16_t& r, float (&f)[1]) { f[0] = bf2f(r); }
 __device__ __forceinline__ void unpack(const float4& r, float (&f)[4]) { f[0] = r.x; f[1] = r.y; f[2] = r.z; f[3] = r.w; }
 __device__ __forceinline__ void unpack(const uint4& r, float (&f)[8]) {
     const uint32_t w[4] = {r.x, r.y, r.z, r.w};
@@ -713,15 +787,41 @@ __device__ __forceinline__ void unpack(const uint4& r, float (&f)[8]) {
 }
 
 // the compiler takes the value as changed here
-__device__ __forceinline__ void keep(float& r) { asm volatile("" : "+v"(r)); }
-__device__ __forceinline__ void keep(bf16_t& r) { asm volatile("" : "+v"(r)); }
 __device__ __forceinline__ void keep(float4& r) { asm volatile("" : "+v"(r.x), "+v"(r.y), "+v"(r.z), "+v"(r.w)); }
 __device__ __forceinline__ void keep(uint4& r) { asm volatile("" : "+v"(r.x), "+v"(r.y), "+v"(r.z), "+v"(r.w)); }
+
+// a vector as it lies in memory
+template <bool ANY, typename T, typename R> __device__ __forceinline__ void raw(const T* p, int n, R& r) {
+    constexpr int V = (int)(sizeof(R) / sizeof(T));
+    if constexpr (!ANY) {
+        r = *reinterpret_cast<const R*>(p);
+    } else {
+        uint32_t w[4] = {0u, 0u, 0u, 0u};
+        if (n >= V) {
+            if constexpr (V == 4) {
+                const f4_any x = *reinterpret_cast<const f4_any*>(p);
+                for (int i = 0; i < 4; i++) w[i] = __float_as_uint(x[i]);
+            } else {
+                const u4_any x = *reinterpret_cast<const u4_any*>(p);
+                for (int i = 0; i < 4; i++) w[i] = x[i];
+            }
+        } else {
+#pragma unroll
+            for (int i = 0; i < V; i++)
+                if (i < n) {
+                    if constexpr (V == 4) w[i] = __float_as_uint(p[i]);
+                    else w[i / 2] |= (uint32_t)p[i] << (16 * (i & 1));
+                }
+        }
+        if constexpr (V == 4) r = make_float4(__uint_as_float(w[0]), __uint_as_float(w[1]), __uint_as_float(w[2]), __uint_as_float(w[3]));
+        else r = make_uint4(w[0], w[1], w[2], w[3]);
+    }
+}
 
 constexpr int kOnepassWaves = 8;
 constexpr int kOnepassGroups = 256;      // workgroups at most: one per compute unit (512: 101 us instead of 89 for 8192 x 4096, twice the partial rows)
 
-template <typename T, int V, int NV, int WPT, bool RES>
+template <typename T, int V, int NV, int WPT, bool RES, bool ANY>
 __global__ void __launch_bounds__(64 * kOnepassWaves, 2) ln_bwd_onepass(TiledView X, TiledView S, TiledView G, TiledView dY, TiledView dR,
                                                                      TiledView dX, unsigned ncols, unsigned rounds, float* part) {
     using R = typename RawVec<T, V>::R;
@@ -736,6 +836,7 @@ __global__ void __launch_bounds__(64 * kOnepassWaves, 2) ln_bwd_onepass(TiledVie
     int l[NV], ext[NV];
     unsigned e[NV];
     bool ok[NV];
+    Own own[NV];          // (ANY: see walk)
     float ag[NV][V], ab[NV][V];
     // the gain lies in LDS (read twice per token): registers are what the kernel is short of
     float* const gam = sums + w * kWave + lane * V;
@@ -746,13 +847,18 @@ __global__ void __launch_bounds__(64 * kOnepassWaves, 2) ln_bwd_onepass(TiledVie
         ext[it] = ext0_of(X, l[it]);
         e[it] = (unsigned)(((s - ll * vpt) * 64 + lane) * V);
         ok[it] = ll < g0 && (int)e[it] < ext[it];
+        if constexpr (ANY) {
+            const int at = max(min((int)e[it], ext[it] - V), 0);
+            own[it] = Own{(int)e[it] - at, min(V, ext[it] - at)};
+            if (ok[it]) e[it] = (unsigned)at;
+        }
 #pragma unroll
         for (int k = 0; k < V; k++) ag[it][k] = ab[it][k] = 0.f;
         if (grp == 0) {
             float gm[V];
 #pragma unroll
             for (int k = 0; k < V; k++) gm[k] = 0.f;
-            if (ok[it]) ldv<V>(global_as<const float>(G.tiles[l[it]]) + e[it], gm);
+            if (ok[it]) ldn<ANY, V>(global_as<const float>(G.tiles[l[it]]) + e[it], ext[it], gm);
 #pragma unroll
             for (int k = 0; k < V; k++) gam[it * 64 * V + k] = gm[k];
         }
@@ -779,9 +885,9 @@ __global__ void __launch_bounds__(64 * kOnepassWaves, 2) ln_bwd_onepass(TiledVie
         for (int it = 0; it < NV; it++)
             if (ok[it]) {
                 const int64_t at = (int64_t)c.colidx * ext[it];
-                t.x[it] = *reinterpret_cast<const R*>(global_as<const T>(X.tiles[c.tile0 + l[it]]) + at + e[it]);
-                t.d[it] = *reinterpret_cast<const R*>(global_as<const T>(dY.tiles[c.tile0 + l[it]]) + at + e[it]);
-                if constexpr (RES) t.q[it] = *reinterpret_cast<const R*>(global_as<const T>(dR.tiles[c.tile0 + l[it]]) + at + e[it]);
+                raw<ANY>(global_as<const T>(X.tiles[c.tile0 + l[it]]) + at + e[it], ext[it], t.x[it]);
+                raw<ANY>(global_as<const T>(dY.tiles[c.tile0 + l[it]]) + at + e[it], ext[it], t.d[it]);
+                if constexpr (RES) raw<ANY>(global_as<const T>(dR.tiles[c.tile0 + l[it]]) + at + e[it], ext[it], t.q[it]);
             }
     };
     // (the same number of rounds for every group: the waves of a workgroup meet once per token)
@@ -803,6 +909,7 @@ __global__ void __launch_bounds__(64 * kOnepassWaves, 2) ln_bwd_onepass(TiledVie
             ldv<V>(gam + it * 64 * V, gm);
 #pragma unroll
             for (int k = 0; k < V; k++) {
+                if constexpr (ANY) d[k] = own[it](k) ? d[k] : 0.f;
                 const float gg = d[k] * gm[k], xh = (x[k] - cur.mean) * cur.rstd;
                 a += gg;
                 b += gg * xh;
@@ -845,7 +952,7 @@ __global__ void __launch_bounds__(64 * kOnepassWaves, 2) ln_bwd_onepass(TiledVie
 #pragma unroll
                         for (int k = 0; k < V; k++) o[k] += q[k];
                     }
-                    stv<V>(global_as<T>(dX.tiles[cur.tile0 + l[it]]) + (int64_t)cur.colidx * ext[it] + e[it], o);
+                    stn<ANY, V>(global_as<T>(dX.tiles[cur.tile0 + l[it]]) + (int64_t)cur.colidx * ext[it] + e[it], ext[it], o);
                     __builtin_amdgcn_sched_barrier(0);
                 }
         }
@@ -864,8 +971,17 @@ __global__ void __launch_bounds__(64 * kOnepassWaves, 2) ln_bwd_onepass(TiledVie
         float* out = part + ((int64_t)which * gridDim.x + blockIdx.x) * rows;
         for (int p = threadIdx.x; p < WPT * kWave; p += 64 * kOnepassWaves) {
             const int ww = p / kWave, q = p - ww * kWave, it = q / (64 * V);
-            const int s = ww + WPT * it, ll = s / vpt, el = (s - ll * vpt) * 64 * V + (q - it * 64 * V);
-            if (ll >= g0 || el >= ext0_of(X, ll)) continue;
+            const int s = ww + WPT * it, ll = s / vpt;
+            int el = (s - ll * vpt) * 64 * V + (q - it * 64 * V);
+            if (ll >= g0) continue;
+            const int ex = ext0_of(X, ll);
+            if constexpr (ANY) {      // (where the vector was moved to, and whether the element is its own)
+                const int k = el % V, first = el - k, at = max(min(first, ex - V), 0);
+                if (first >= ex || k < first - at || at + k >= ex) continue;
+                el = at + k;
+            } else if (el >= ex) {
+                continue;
+            }
             float t = 0.f;
 #pragma unroll
             for (int gq = 0; gq < GR; gq++) t += sums[gq * WPT * kWave + p];
@@ -883,33 +999,47 @@ inline int onepass_wpt(int nv_needed) {
 }
 // (two vectors of 16 bytes per lane: up to 161 registers, the next token's included; sixteen waves per workgroup would have to make do with
 // 128, and the spilled ones' reloads wait for the next token's loads: 113 us for 8192 x 4096)
-constexpr int kOnepassVecs = 2, kOnepassScalars = 8;
-inline int onepass_waves(bool vec, int nv_needed) { return vec ? onepass_wpt<kOnepassVecs>(nv_needed) : onepass_wpt<kOnepassScalars>(nv_needed); }
+// Longer tokens (8192 fp32 elements, 16384 in bf16): all eight waves on one with four vectors per lane, up to 256 registers (fp32 8192 x 4096
+// 169 -> 142 us; odd extents, bf16 8200 x 4096 253 -> 199).
+constexpr int kOnepassVecs = 2, kOnepassLong = 4;
+inline int onepass_waves(int nv_needed) { const int w = onepass_wpt<kOnepassVecs>(nv_needed); return w ? w : onepass_wpt<kOnepassLong>(nv_needed); }
 inline int64_t onepass_wgs(int wpt, int64_t ncols) { const int64_t gr = kOnepassWaves / wpt; return std::min<int64_t>(kOnepassGroups, (ncols + gr - 1) / gr); }
 
-template <typename T, int V, int NV, bool RES>
+template <typename T, int V, int NV, bool RES, bool ANY>
 int32_t launch_onepass_v(hipStream_t st, int wpt, const TiledView& X, const TiledView& S, const TiledView& G, const TiledView& dY,
                          const TiledView& dR, const TiledView& dX, int64_t ncols, float* part) {
     const int64_t wgs = onepass_wgs(wpt, ncols), per = wgs * (kOnepassWaves / wpt);
     const unsigned n = (unsigned)ncols, rounds = (unsigned)((ncols + per - 1) / per);
     const dim3 grid((unsigned)wgs), block(64 * kOnepassWaves);
     switch (wpt) {
-        case 1: hipLaunchKernelGGL((ln_bwd_onepass<T, V, NV, 1, RES>), grid, block, 0, st, X, S, G, dY, dR, dX, n, rounds, part); break;
-        case 2: hipLaunchKernelGGL((ln_bwd_onepass<T, V, NV, 2, RES>), grid, block, 0, st, X, S, G, dY, dR, dX, n, rounds, part); break;
-        case 4: hipLaunchKernelGGL((ln_bwd_onepass<T, V, NV, 4, RES>), grid, block, 0, st, X, S, G, dY, dR, dX, n, rounds, part); break;
-        case 8: hipLaunchKernelGGL((ln_bwd_onepass<T, V, NV, 8, RES>), grid, block, 0, st, X, S, G, dY, dR, dX, n, rounds, part); break;
+        case 1: hipLaunchKernelGGL((ln_bwd_onepass<T, V, NV, 1, RES, ANY>), grid, block, 0, st, X, S, G, dY, dR, dX, n, rounds, part); break;
+        case 2: hipLaunchKernelGGL((ln_bwd_onepass<T, V, NV, 2, RES, ANY>), grid, block, 0, st, X, S, G, dY, dR, dX, n, rounds, part); break;
+        case 4: hipLaunchKernelGGL((ln_bwd_onepass<T, V, NV, 4, RES, ANY>), grid, block, 0, st, X, S, G, dY, dR, dX, n, rounds, part); break;
+        case 8: hipLaunchKernelGGL((ln_bwd_onepass<T, V, NV, 8, RES, ANY>), grid, block, 0, st, X, S, G, dY, dR, dX, n, rounds, part); break;
         default: return NNT_EINVAL;
     }
     return hipGetLastError() == hipSuccess ? NNT_OK : NNT_EHIP;
 }
 template <typename T>
-int32_t launch_onepass(hipStream_t st, bool vec, int wpt, const TiledView& X, const TiledView& S, const TiledView& G, const TiledView& dY,
+int32_t launch_onepass(hipStream_t st, bool vec, int wpt, int nv_needed, const TiledView& X, const TiledView& S, const TiledView& G, const TiledView& dY,
                        const TiledView& dR, const TiledView& dX, int has_res, int64_t ncols, float* part) {
     constexpr int V = VecOf<T>::V;
-    if (vec) return has_res ? launch_onepass_v<T, V, kOnepassVecs, true>(st, wpt, X, S, G, dY, dR, dX, ncols, part)
-                            : launch_onepass_v<T, V, kOnepassVecs, false>(st, wpt, X, S, G, dY, dR, dX, ncols, part);
-    return has_res ? launch_onepass_v<T, 1, kOnepassScalars, true>(st, wpt, X, S, G, dY, dR, dX, ncols, part)
-                   : launch_onepass_v<T, 1, kOnepassScalars, false>(st, wpt, X, S, G, dY, dR, dX, ncols, part);
+    if (wpt * kOnepassVecs < nv_needed) {
+        // (only the longest: every wave of the workgroup, twice the vectors)
+        const int64_t wgs = onepass_wgs(wpt, ncols);
+        const unsigned n = (unsigned)ncols, rounds = (unsigned)((ncols + wgs - 1) / wgs);
+        const dim3 grid((unsigned)wgs), block(64 * kOnepassWaves);
+        if (wpt != kOnepassWaves) return NNT_EINVAL;
+        if (vec && has_res) hipLaunchKernelGGL((ln_bwd_onepass<T, V, kOnepassLong, kOnepassWaves, true, false>), grid, block, 0, st, X, S, G, dY, dR, dX, n, rounds, part);
+        else if (vec) hipLaunchKernelGGL((ln_bwd_onepass<T, V, kOnepassLong, kOnepassWaves, false, false>), grid, block, 0, st, X, S, G, dY, dR, dX, n, rounds, part);
+        else if (has_res) hipLaunchKernelGGL((ln_bwd_onepass<T, V, kOnepassLong, kOnepassWaves, true, true>), grid, block, 0, st, X, S, G, dY, dR, dX, n, rounds, part);
+        else hipLaunchKernelGGL((ln_bwd_onepass<T, V, kOnepassLong, kOnepassWaves, false, true>), grid, block, 0, st, X, S, G, dY, dR, dX, n, rounds, part);
+        return hipGetLastError() == hipSuccess ? NNT_OK : NNT_EHIP;
+    }
+    if (vec) return has_res ? launch_onepass_v<T, V, kOnepassVecs, true, false>(st, wpt, X, S, G, dY, dR, dX, ncols, part)
+                            : launch_onepass_v<T, V, kOnepassVecs, false, false>(st, wpt, X, S, G, dY, dR, dX, ncols, part);
+    return has_res ? launch_onepass_v<T, V, kOnepassVecs, true, true>(st, wpt, X, S, G, dY, dR, dX, ncols, part)
+                   : launch_onepass_v<T, V, kOnepassVecs, false, true>(st, wpt, X, S, G, dY, dR, dX, ncols, part);
 }
 
 int32_t check_ln_shapes(nnt_ctx* ctx, const nnt_tensor* X, const nnt_tensor* gamma, const nnt_tensor* stats, const char* who) {
@@ -1123,15 +1253,15 @@ int32_t nnt_layernorm_fwd(nnt_ctx* ctx, nnt_tensor* X, nnt_tensor* gamma, nnt_te
     OpTag tag(ctx, "layernorm_fwd", numel * X->elem_size() * (ctx->granularity == NNT_GRAN_OP ? 2 : 3), true);
     if (ctx->granularity == NNT_GRAN_OP) {
         const int V = dtype == NNT_F32 ? 4 : 8;
-        const bool vec = tensors_vec_ok({X, Y, gamma, beta}, V);
+        const bool vec = tensors_vec_ok({X, Y, gamma, beta}, V), any = any_vec({X, Y, gamma, beta});
         const int nv = (int)(((X->base[0] + 64 * V - 1) / (64 * V)) * X->grid[0]);
         const TiledView vx = X->view(), vy = Y->view(), vs = stats->view(), vg = gamma->view(), vb = beta->view();
         const int64_t ncols = n_columns(X);
         if (ncols > INT32_MAX) return fail(ctx, NNT_EINVAL, "nnt_layernorm_fwd: tensor too large");
         std::vector<Access> acc = {X->all(kRead), gamma->all(kRead), beta->all(kRead), Y->all(kWrite), stats->all(kWrite)};
         return submit(ctx, acc, [=](hipStream_t st) {
-            return dtype == NNT_F32 ? launch_ln_fwd<float>(st, vec, nv, vx, vy, vs, vg, vb, eps, ncols)
-                                    : launch_ln_fwd<bf16_t>(st, vec, nv, vx, vy, vs, vg, vb, eps, ncols);
+            return dtype == NNT_F32 ? launch_ln_fwd<float>(st, vec, any, nv, vx, vy, vs, vg, vb, eps, ncols)
+                                    : launch_ln_fwd<bf16_t>(st, vec, any, nv, vx, vy, vs, vg, vb, eps, ncols);
         });
     }
     // the paper's steps, tile by tile
@@ -1195,7 +1325,7 @@ int32_t nnt_layernorm_bwd(nnt_ctx* ctx, nnt_tensor* X, nnt_tensor* stats, nnt_te
         if (dRes) acc.push_back(dRes->all(kRead));
         // one pass over the tokens wherever the eight waves of a workgroup can hold one (measured no slower at any size, from 128 tokens
         // of 128 to 4096 of 8192); longer ones take the column sums and the input gradient one after the other
-        const int wpt = onepass_waves(vec, vec ? nv : (int)(((X->base[0] + 63) / 64) * X->grid[0]));
+        const int wpt = vec || any_vec({X, dY, dX, dRes, gamma}) ? onepass_waves(nv) : 0;
         if (wpt > 0 && ncols > 0 && ncols < INT32_MAX / 2 && X->ntiles <= 65535) {
             const int64_t wgs = onepass_wgs(wpt, ncols), rows = X->shape[0];
             rc = ensure_stream_scratch(ctx, 2 * wgs * rows);
@@ -1207,8 +1337,8 @@ int32_t nnt_layernorm_bwd(nnt_ctx* ctx, nnt_tensor* X, nnt_tensor* stats, nnt_te
             acc.push_back(dbeta->all(kWrite));
             return submit(ctx, acc, [=](hipStream_t st) {
                 float* part = stream_scratch_of(ctx);
-                const int32_t r = dtype == NNT_F32 ? launch_onepass<float>(st, vec, wpt, vx, vs, vg, vdy, vr, vdx, has_res, ncols, part)
-                                                   : launch_onepass<bf16_t>(st, vec, wpt, vx, vs, vg, vdy, vr, vdx, has_res, ncols, part);
+                const int32_t r = dtype == NNT_F32 ? launch_onepass<float>(st, vec, wpt, nv, vx, vs, vg, vdy, vr, vdx, has_res, ncols, part)
+                                                   : launch_onepass<bf16_t>(st, vec, wpt, nv, vx, vs, vg, vdy, vr, vdx, has_res, ncols, part);
                 if (r != NNT_OK) return r;
                 return launch_stage2(st, part, wgs, rows, og, ob, base0);
             }, 2);
@@ -1216,8 +1346,8 @@ int32_t nnt_layernorm_bwd(nnt_ctx* ctx, nnt_tensor* X, nnt_tensor* stats, nnt_te
         rc = rowsum_tensor(ctx, 1, dY, X, stats, dgamma, dbeta);
         if (rc != NNT_OK) return rc;
         return submit(ctx, acc, [=](hipStream_t st) {
-            return dtype == NNT_F32 ? launch_ln_bwd<float>(st, vec, nv, vx, vs, vg, vdy, vr, vdx, has_res, ncols)
-                                    : launch_ln_bwd<bf16_t>(st, vec, nv, vx, vs, vg, vdy, vr, vdx, has_res, ncols);
+            return dtype == NNT_F32 ? launch_ln_bwd<float>(st, vec, vx, vs, vg, vdy, vr, vdx, has_res, ncols)
+                                    : launch_ln_bwd<bf16_t>(st, vec, vx, vs, vg, vdy, vr, vdx, has_res, ncols);
         });
     }
     // tile by tile.  The per-token sums live in the reduction scratch: [2][columns] per group of tiles.

@@ -512,7 +512,11 @@ def test_gemm_rejects_mismatched_tilings(mods):
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
 @pytest.mark.parametrize("shape,base", [((768, 40, 3), (256, 16, 3)), ((100, 37, 2), (48, 10, 1)), ((1600, 12, 2), (400, 12, 2)),
                                         # long tokens, shared by the wavefronts of a workgroup: register-cached and looping forms
-                                        ((8192, 5, 2), (1024, 5, 1)), ((2560, 7, 1), (512, 7, 1)), ((20000, 3, 1), (5000, 3, 1))])
+                                        ((8192, 5, 2), (1024, 5, 1)), ((2560, 7, 1), (512, 7, 1)), ((20000, 3, 1), (5000, 3, 1)),
+                                        # odd extents: a last tile of one element, tiles shorter than a vector, tokens shared by wavefronts, the longest
+                                        # (8192 vectors of 4, 4096 of 8) and the next
+                                        ((2001, 9, 2), (500, 4, 2)), ((13, 7, 2), (5, 7, 1)), ((3001, 33, 1), (1024, 33, 1)), ((9001, 5, 1), (9001, 5, 1)),
+                                        ((16381, 3, 1), (16381, 3, 1)), ((33001, 2, 1), (33001, 2, 1))])
 def test_layernorm_tensor(mods, gran, dtype, shape, base):
     capi, tiled = mods
     r = rng(3)
@@ -547,11 +551,12 @@ def test_layernorm_tensor(mods, gran, dtype, shape, base):
 
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
 @pytest.mark.parametrize("shape,base", [((128, 1, 1), (32, 1, 1)), ((520, 9, 1), (520, 4, 1)), ((1000, 67, 9), (400, 32, 2)), ((4096, 19, 2), (1024, 19, 2)),
-                                        ((4104, 3, 3), (4104, 3, 3)), ((8192, 5, 2), (8192, 5, 1)), ((8200, 3, 1), (8200, 3, 1)), ((512, 300, 17), (512, 300, 17)),
-                                        ((63, 5, 2), (63, 5, 2)), ((777, 130, 3), (300, 100, 3)), ((4097, 3, 1), (4097, 3, 1))])
+                                        ((4104, 3, 3), (4104, 3, 3)), ((8192, 5, 2), (8192, 5, 1)), ((8200, 3, 1), (8200, 3, 1)), ((16384, 3, 1), (4096, 3, 1)), ((16392, 2, 1), (16392, 2, 1)), ((512, 300, 17), (512, 300, 17)),
+                                        ((63, 5, 2), (63, 5, 2)), ((777, 130, 3), (300, 100, 3)), ((4095, 3, 1), (4095, 3, 1)), ((4097, 3, 1), (4097, 3, 1)),
+                                        ((2001, 21, 2), (500, 9, 2)), ((13, 40, 2), (5, 7, 1)), ((8191, 5, 2), (1000, 5, 2))])
 def test_layernorm_backward_in_one_pass(mods, dtype, shape, base):
     """One to eight wavefronts per token, fewer and more tokens than groups of wavefronts, ragged tiles, scalar forms, and the
-    shortest tokens that are too long (4104 in fp32, 8200 in bf16, 4097 by single elements).  The input gradient in place of the
+    longest tokens of either form (4096, 8192 in fp32, twice that in bf16) and the next.  The input gradient in place of the
     upstream one, twice in a row with other operations on the second stream: the partial sums of the two streams lie apart."""
     capi, tiled = mods
     r = rng(23)
