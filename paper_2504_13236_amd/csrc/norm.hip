@@ -389,7 +389,8 @@ struct RowsumGeom {
     int64_t nslots;         // partial rows per output (the second output of MODE 1 follows the first)
 };
 
-template <typename T, int V, int MODE>
+// (ANY: rows of any extent and alignment, see walk)
+template <typename T, int V, int MODE, bool ANY = false>
 __global__ void __launch_bounds__(256) rowsum_stage1(RowsumGeom g, float* part) {
     __shared__ float red[2][4][64 * V];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -420,13 +421,14 @@ __global__ void __launch_bounds__(256) rowsum_stage1(RowsumGeom g, float* part) 
         if (MODE == 1) { x = static_cast<const T*>(g.x1); st = g.s1; }
         slot = blockIdx.y;
     }
-    const int e = (blockIdx.x * 64 + lane) * V;
+    const int e0 = (blockIdx.x * 64 + lane) * V, e = ANY ? max(min(e0, ext0 - V), 0) : e0;
+    const Own own{e0 - e, min(V, ext0 - e)};
     const int64_t c0 = (int64_t)blockIdx.y * g.cpb;
     const int64_t c1 = min(ncol, c0 + g.cpb);
     float a0[V], a1[V];
 #pragma unroll
     for (int k = 0; k < V; k++) a0[k] = a1[k] = 0.f;
-    if (y && e < ext0) {
+    if (y && e0 < ext0) {
         // four columns per trip so that four loads per operand are in flight
         for (int64_t cb = c0 + wave; cb < c1; cb += 16) {
             float d[4][V], f[4][V];
@@ -434,8 +436,8 @@ __global__ void __launch_bounds__(256) rowsum_stage1(RowsumGeom g, float* part) 
             for (int u = 0; u < 4; u++) {
                 const int64_t c = cb + 4 * u;
                 if (c < c1) {
-                    ldv<V>(y + c * ext0 + e, d[u]);
-                    if (MODE == 1) ldv<V>(x + c * ext0 + e, f[u]);
+                    ldn<ANY, V>(y + c * ext0 + e, ext0, d[u]);
+                    if (MODE == 1) ldn<ANY, V>(x + c * ext0 + e, ext0, f[u]);
                 }
             }
 #pragma unroll
@@ -460,9 +462,10 @@ __global__ void __launch_bounds__(256) rowsum_stage1(RowsumGeom g, float* part) 
         if (MODE == 1) red[1][wave][lane * V + k] = a1[k];
     }
     __syncthreads();
-    if (wave == 0 && e < ext0) {
+    if (wave == 0 && e0 < ext0) {
 #pragma unroll
         for (int k = 0; k < V; k++) {
+            if (ANY && !own(k)) continue;
             const int i = lane * V + k;
             part[slot * g.rows_total + row0 + e + k] = red[0][0][i] + red[0][1][i] + red[0][2][i] + red[0][3][i];
             if (MODE == 1)
@@ -516,13 +519,13 @@ __global__ void __launch_bounds__(256) rowsum_stage2(const float* part, int64_t 
 // take the columns in turn and meet in shuffles and LDS.  Latency is all such a call consists of, so the second launch costs
 // as much as the first.
 constexpr int kSmallThreads = 1024;
-template <typename T, int V>
+template <typename T, int V, bool ANY>
 __global__ void __launch_bounds__(kSmallThreads) rowsum_small(TiledView y, void* const* otab) {
     __shared__ float red[kSmallThreads / 64][4][V];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, rv = threadIdx.x & 3, cg = threadIdx.x >> 2;
     constexpr int kGroups = kSmallThreads / 4;
     const int l = blockIdx.y, ext0 = min(y.base[0], y.shape[0] - l * y.base[0]);
-    const int e = (blockIdx.x * 4 + rv) * V;
+    const int e0 = (blockIdx.x * 4 + rv) * V, e = ANY ? max(min(e0, ext0 - V), 0) : e0;
     float a[V];
 #pragma unroll
     for (int k = 0; k < V; k++) a[k] = 0.f;
@@ -532,13 +535,13 @@ __global__ void __launch_bounds__(kSmallThreads) rowsum_small(TiledView y, void*
         tile_geometry(y, l + y.grid[0] * rest, tc, ext);
         const int ncol = ext[1] * ext[2] * ext[3];
         const T* p = global_as<const T>(y.tiles[l + y.grid[0] * rest]);
-        if (e >= ext0) continue;
+        if (e0 >= ext0) continue;
         // eight columns per trip so that eight loads are in flight
         for (int c = cg; c < ncol; c += 8 * kGroups) {
             float d[8][V];
 #pragma unroll
             for (int u = 0; u < 8; u++)
-                if (c + u * kGroups < ncol) ldv<V>(p + (int64_t)(c + u * kGroups) * ext0 + e, d[u]);
+                if (c + u * kGroups < ncol) ldn<ANY, V>(p + (int64_t)(c + u * kGroups) * ext0 + e, ext0, d[u]);
 #pragma unroll
             for (int u = 0; u < 8; u++)
                 if (c + u * kGroups < ncol) {
@@ -555,8 +558,9 @@ __global__ void __launch_bounds__(kSmallThreads) rowsum_small(TiledView y, void*
     }
     __syncthreads();
     if (threadIdx.x < 4 * V) {
-        const int r = threadIdx.x / V, k = threadIdx.x % V, row = (blockIdx.x * 4 + r) * V + k;
-        if (row < ext0) {
+        const int r = threadIdx.x / V, k = threadIdx.x % V, first = (blockIdx.x * 4 + r) * V, at = ANY ? max(min(first, ext0 - V), 0) : first;
+        const int row = at + k;
+        if (first < ext0 && row >= first && row < ext0) {
             float s = 0.f;
 #pragma unroll
             for (int q = 0; q < kSmallThreads / 64; q++) s += red[q][r][k];
@@ -610,10 +614,10 @@ constexpr int kColsPerBlock = 128;
 int64_t scratch_elems(int64_t m, int64_t n, int mode) { return ((n + kColsPerBlock - 1) / kColsPerBlock) * m * (mode ? 2 : 1); }
 
 template <typename T, int MODE>
-int32_t launch_rowsum_t(hipStream_t st, const RowsumGeom& g, int vpt_v, int vpt_1, int64_t ntiles, bool vec, float* part) {
+int32_t launch_rowsum_t(hipStream_t st, const RowsumGeom& g, int vpt, int64_t ntiles, bool vec, float* part) {
     constexpr int V = VecOf<T>::V;
-    if (vec) hipLaunchKernelGGL((rowsum_stage1<T, V, MODE>), dim3(vpt_v, g.splits, (unsigned)ntiles), dim3(256), 0, st, g, part);
-    else hipLaunchKernelGGL((rowsum_stage1<T, 1, MODE>), dim3(vpt_1, g.splits, (unsigned)ntiles), dim3(256), 0, st, g, part);
+    if (vec) hipLaunchKernelGGL((rowsum_stage1<T, V, MODE>), dim3(vpt, g.splits, (unsigned)ntiles), dim3(256), 0, st, g, part);
+    else hipLaunchKernelGGL((rowsum_stage1<T, V, MODE, true>), dim3(vpt, g.splits, (unsigned)ntiles), dim3(256), 0, st, g, part);
     return hipGetLastError() == hipSuccess ? NNT_OK : NNT_EHIP;
 }
 
@@ -631,10 +635,10 @@ int32_t rowsum_single(hipStream_t st, int dtype, int mode, int64_t m, int64_t n,
     g.nslots = g.splits;
     const int V = dtype == NNT_F32 ? 4 : 8;
     const bool vec = m % V == 0 && aligned16(dy) && (!x || aligned16(x));
-    const int vv = (int)((m + 64 * V - 1) / (64 * V)), v1 = (int)((m + 63) / 64);
+    const int vv = (int)((m + 64 * V - 1) / (64 * V));
     int32_t rc;
-    if (dtype == NNT_F32) rc = mode ? launch_rowsum_t<float, 1>(st, g, vv, v1, 1, vec, scratch) : launch_rowsum_t<float, 0>(st, g, vv, v1, 1, vec, scratch);
-    else rc = mode ? launch_rowsum_t<bf16_t, 1>(st, g, vv, v1, 1, vec, scratch) : launch_rowsum_t<bf16_t, 0>(st, g, vv, v1, 1, vec, scratch);
+    if (dtype == NNT_F32) rc = mode ? launch_rowsum_t<float, 1>(st, g, vv, 1, vec, scratch) : launch_rowsum_t<float, 0>(st, g, vv, 1, vec, scratch);
+    else rc = mode ? launch_rowsum_t<bf16_t, 1>(st, g, vv, 1, vec, scratch) : launch_rowsum_t<bf16_t, 0>(st, g, vv, 1, vec, scratch);
     if (rc != NNT_OK) return rc;
     const unsigned blocks = (unsigned)((m + kStage2Rows - 1) / kStage2Rows);
     hipLaunchKernelGGL(rowsum_stage2, dim3(blocks, mode ? 2 : 1), dim3(256), 0, st, scratch, (int64_t)g.splits, m, nullptr, out0, 1,
@@ -656,15 +660,15 @@ int32_t rowsum_tensor(nnt_ctx* ctx, int mode, nnt_tensor* dY, nnt_tensor* X, nnt
     if (mode == 0 && ncols <= 1024 && ncols * dY->shape[0] * dY->elem_size() <= 13000000 && dY->ntiles <= 65535) {
         const TiledView vy = dY->view();
         void* const* ot = out0->d_tiles;
-        const int dt = dY->dtype, w = vec ? V : 1;
-        const dim3 grid((unsigned)((dY->base[0] + 4 * w - 1) / (4 * w)), (unsigned)dY->grid[0]);
+        const int dt = dY->dtype;
+        const dim3 grid((unsigned)((dY->base[0] + 4 * V - 1) / (4 * V)), (unsigned)dY->grid[0]);
         return submit(ctx, {dY->all(kRead), out0->all(kWrite)}, [=](hipStream_t st) {
             if (dt == NNT_F32) {
-                if (vec) hipLaunchKernelGGL((rowsum_small<float, 4>), grid, dim3(kSmallThreads), 0, st, vy, ot);
-                else hipLaunchKernelGGL((rowsum_small<float, 1>), grid, dim3(kSmallThreads), 0, st, vy, ot);
+                if (vec) hipLaunchKernelGGL((rowsum_small<float, 4, false>), grid, dim3(kSmallThreads), 0, st, vy, ot);
+                else hipLaunchKernelGGL((rowsum_small<float, 4, true>), grid, dim3(kSmallThreads), 0, st, vy, ot);
             } else {
-                if (vec) hipLaunchKernelGGL((rowsum_small<bf16_t, 8>), grid, dim3(kSmallThreads), 0, st, vy, ot);
-                else hipLaunchKernelGGL((rowsum_small<bf16_t, 1>), grid, dim3(kSmallThreads), 0, st, vy, ot);
+                if (vec) hipLaunchKernelGGL((rowsum_small<bf16_t, 8, false>), grid, dim3(kSmallThreads), 0, st, vy, ot);
+                else hipLaunchKernelGGL((rowsum_small<bf16_t, 8, true>), grid, dim3(kSmallThreads), 0, st, vy, ot);
             }
             return hipGetLastError() == hipSuccess ? (int32_t)NNT_OK : (int32_t)NNT_EHIP;
         });
@@ -691,7 +695,7 @@ int32_t rowsum_tensor(nnt_ctx* ctx, int mode, nnt_tensor* dY, nnt_tensor* X, nnt
     int32_t rc = ensure_scratch(ctx, need);
     if (rc != NNT_OK) return rc;
     if (dY->ntiles > 65535 || g.splits > 65535) return fail(ctx, NNT_EINVAL, "column sum: too many tiles");
-    const int vv = (int)((dY->base[0] + 64 * V - 1) / (64 * V)), v1 = (int)((dY->base[0] + 63) / 64);
+    const int vv = (int)((dY->base[0] + 64 * V - 1) / (64 * V));
     float* scratch = ctx->red_scratch;
     const int dtype = dY->dtype;
     const int64_t ntiles = dY->ntiles, rows = g.rows_total;
@@ -706,8 +710,8 @@ int32_t rowsum_tensor(nnt_ctx* ctx, int mode, nnt_tensor* dY, nnt_tensor* X, nnt
     if (out1) acc.push_back(out1->all(kWrite));
     return submit(ctx, acc, [=](hipStream_t st) {
         int32_t r;
-        if (dtype == NNT_F32) r = mode ? launch_rowsum_t<float, 1>(st, g, vv, v1, ntiles, vec, scratch) : launch_rowsum_t<float, 0>(st, g, vv, v1, ntiles, vec, scratch);
-        else r = mode ? launch_rowsum_t<bf16_t, 1>(st, g, vv, v1, ntiles, vec, scratch) : launch_rowsum_t<bf16_t, 0>(st, g, vv, v1, ntiles, vec, scratch);
+        if (dtype == NNT_F32) r = mode ? launch_rowsum_t<float, 1>(st, g, vv, ntiles, vec, scratch) : launch_rowsum_t<float, 0>(st, g, vv, ntiles, vec, scratch);
+        else r = mode ? launch_rowsum_t<bf16_t, 1>(st, g, vv, ntiles, vec, scratch) : launch_rowsum_t<bf16_t, 0>(st, g, vv, ntiles, vec, scratch);
         if (r != NNT_OK) return r;
         return launch_stage2(st, scratch, nslots, rows, o0, mode ? o1 : nullptr, base0);
     }, 2);
