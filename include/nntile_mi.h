@@ -23,7 +23,7 @@
  *    the two-stage column sums, shared and one part per stream (grows on demand, at
  *    least 4 MiB each once used); (c)
  *    for products whose contraction is cut into k-slices, an fp32 workspace of
- *    slices x macro-tile partial sums per cached plan, and for bf16 products whose
+ *    slices x macro-tile partial sums per cached plan, and for products whose
  *    operands have odd leading dimensions or tiles a padded copy of both operands
  *    per cached plan (at most 2 GiB each; a plan that would need more is built
  *    without them).  nnt_ctx_stats

@@ -1234,6 +1234,7 @@ int32_t gemm_core(nnt_ctx* ctx, float alpha, int32_t opA, nnt_tensor* A, int32_t
         const std::string k = key.str() + which;
         auto it = ctx->gemm_plans.find(k);
         if (it == ctx->gemm_plans.end()) {
+            if (ctx->capturing && P) break;      // (inside a capture, where none can be built, the one that is there runs as a whole)
             if (ctx->capturing) return fail(ctx, NNT_ESTATE, "nnt_gemm: plan must exist before capture (run the call once first)");
             std::shared_ptr<GemmPlan> np(new GemmPlan());
             int32_t rc = build_plan(ctx, opA, A, opB, B, C, ncon, nbat, bias, R, np.get(), view_ld, epi);
@@ -1257,7 +1258,7 @@ int32_t gemm_core(nnt_ctx* ctx, float alpha, int32_t opA, nnt_tensor* A, int32_t
     g.alpha = alpha;
     g.beta = beta;
     const int cmode = beta != 0.f ? kReadWrite : kWrite;
-    if (ctx->granularity == NNT_GRAN_OP || view_ld) {
+    if (!by_tile || P->packed) {
         // (a window writes the rows of its part in every tile it touches and leaves the others)
         std::vector<Access> acc = {dA->all(kRead), dB->all(kRead), dC->all((view_ld && view_ld[2]) ? kWritePart : (R ? kWrite : cmode))};
         acc[2].part = part_c;

@@ -646,10 +646,29 @@ int32_t rowsum_single(hipStream_t st, int dtype, int mode, int64_t m, int64_t n,
     return hipGetLastError() == hipSuccess ? NNT_OK : NNT_EHIP;
 }
 
-// whole tiled tensor dY [rows, ...] -> out0 / out1: 1-axis tensors tiled like dY's first axis
-int32_t rowsum_tensor(nnt_ctx* ctx, int mode, nnt_tensor* dY, nnt_tensor* X, nnt_tensor* S, nnt_tensor* out0, nnt_tensor* out1) {
+// Columns per block, column splits per tile and partial rows of the two-stage sums over a tensor: fewer columns per block when the tensor would
+// otherwise give the chip too few blocks.
+struct RowsumSplit { int32_t cpb, splits; int64_t nslots; };
+RowsumSplit split_of(const nnt_tensor* dY) {
     int64_t max_cols = 1, rest_tiles = 1;
     for (int a = 1; a < dY->ndim; a++) { max_cols *= dY->base[a]; rest_tiles *= dY->grid[a]; }
+    const int V = dY->dtype == NNT_F32 ? 4 : 8;
+    const int64_t row_blocks = (dY->base[0] + 64 * V - 1) / (64 * V);
+    int cpb = kColsPerBlock;
+    while (cpb > 32 && row_blocks * ((max_cols + cpb - 1) / cpb) * dY->ntiles < 1024) cpb /= 2;
+    const int32_t splits = (int32_t)((max_cols + cpb - 1) / cpb);
+    return RowsumSplit{cpb, splits, rest_tiles * splits};
+}
+
+// The scratch that the two-stage sums would take, also where a form without it runs: a later call inside a capture, where nothing can
+// be allocated, may need it ("run the operation once first" holds for any call of the operation that is no larger).
+int32_t keep_rowsum_scratch(nnt_ctx* ctx, int mode, const nnt_tensor* dY) {
+    if (ctx->capturing) return NNT_OK;
+    return ensure_scratch(ctx, split_of(dY).nslots * dY->shape[0] * (mode ? 2 : 1));
+}
+
+// whole tiled tensor dY [rows, ...] -> out0 / out1: 1-axis tensors tiled like dY's first axis
+int32_t rowsum_tensor(nnt_ctx* ctx, int mode, nnt_tensor* dY, nnt_tensor* X, nnt_tensor* S, nnt_tensor* out0, nnt_tensor* out1) {
     const int V = dY->dtype == NNT_F32 ? 4 : 8;
     bool vec = dY->base[0] % V == 0 && dY->shape[0] % V == 0;
     for (void* p : dY->tiles) vec = vec && aligned16(p);
@@ -658,6 +677,8 @@ int32_t rowsum_tensor(nnt_ctx* ctx, int mode, nnt_tensor* dY, nnt_tensor* X, nnt
     // 3072 x 1024: 7.0, 7.4; bf16 4.6 to 6.5, 6.6 to 7.0); beyond, its few blocks take longer (fp32 768 x 2048: 7.5, 6.7; 8192 x 512: 9.2, 7.2)
     const int64_t ncols = n_columns(dY);
     if (mode == 0 && ncols <= 1024 && ncols * dY->shape[0] * dY->elem_size() <= 13000000 && dY->ntiles <= 65535) {
+        const int32_t kept = keep_rowsum_scratch(ctx, mode, dY);
+        if (kept != NNT_OK) return kept;
         const TiledView vy = dY->view();
         void* const* ot = out0->d_tiles;
         const int dt = dY->dtype;
@@ -679,20 +700,13 @@ int32_t rowsum_tensor(nnt_ctx* ctx, int mode, nnt_tensor* dY, nnt_tensor* X, nnt
     g.ytab = dY->d_tiles;
     g.xtab = X ? X->d_tiles : nullptr;
     g.stab = S ? S->d_tiles : nullptr;
-    // columns per block: fewer when the tensor would otherwise give the chip too few blocks
-    int cpb = kColsPerBlock;
-    {
-        const int V0 = dY->dtype == NNT_F32 ? 4 : 8;
-        const int64_t row_blocks = (dY->base[0] + 64 * V0 - 1) / (64 * V0);
-        while (cpb > 32 && row_blocks * ((max_cols + cpb - 1) / cpb) * dY->ntiles < 1024) cpb /= 2;
-    }
-    g.cpb = cpb;
-    g.splits = (int32_t)((max_cols + cpb - 1) / cpb);
+    const RowsumSplit cut = split_of(dY);
+    g.cpb = cut.cpb;
+    g.splits = cut.splits;
     g.rows_total = dY->shape[0];
-    const int64_t nslots = rest_tiles * g.splits;
+    const int64_t nslots = cut.nslots;
     g.nslots = nslots;
-    const int64_t need = nslots * g.rows_total * (mode ? 2 : 1);
-    int32_t rc = ensure_scratch(ctx, need);
+    int32_t rc = ensure_scratch(ctx, nslots * g.rows_total * (mode ? 2 : 1));
     if (rc != NNT_OK) return rc;
     if (dY->ntiles > 65535 || g.splits > 65535) return fail(ctx, NNT_EINVAL, "column sum: too many tiles");
     const int vv = (int)((dY->base[0] + 64 * V - 1) / (64 * V));
@@ -1330,8 +1344,11 @@ int32_t nnt_layernorm_bwd(nnt_ctx* ctx, nnt_tensor* X, nnt_tensor* stats, nnt_te
         // one pass over the tokens wherever the eight waves of a workgroup can hold one (measured no slower at any size, from 128 tokens
         // of 128 to 4096 of 8192); longer ones take the column sums and the input gradient one after the other
         const int wpt = vec || any_vec({X, dY, dX, dRes, gamma}) ? onepass_waves(nv) : 0;
-        if (wpt > 0 && ncols > 0 && ncols < INT32_MAX / 2 && X->ntiles <= 65535) {
-            const int64_t wgs = onepass_wgs(wpt, ncols), rows = X->shape[0];
+        // (so do calls inside a capture whose partial rows have no room yet)
+        const int64_t wgs = wpt > 0 ? onepass_wgs(wpt, ncols) : 0, rows = X->shape[0];
+        if (wpt > 0 && ncols > 0 && ncols < INT32_MAX / 2 && X->ntiles <= 65535 && !(ctx->capturing && 2 * wgs * rows > ctx->stream_scratch_elems)) {
+            rc = keep_rowsum_scratch(ctx, 1, dY);
+            if (rc != NNT_OK) return rc;
             rc = ensure_stream_scratch(ctx, 2 * wgs * rows);
             if (rc != NNT_OK) return rc;
             void* const* og = dgamma->d_tiles;

@@ -829,6 +829,57 @@ def test_graph_capture_replays_task_flow(mods):
         check(want, ref + D.gelu(ref), "f32", "captured flow")
 
 
+def test_graph_capture_behind_other_forms_of_the_operation(mods):
+    """Calls inside a capture whose scratch or plan comes from an earlier call that ran another form: column sums in two launches behind
+    one in a single launch, a layer norm adjoint with more partial rows than the last one, a product of odd sizes tile by tile that
+    ran as a whole before."""
+    capi, tiled = mods
+    r = rng(31)
+    with tiled.Context(n_streams=2) as ctx:
+        def norm_case(shape, base):
+            X, dY = (r.standard_normal(shape).astype(np.float32) for _ in range(2))
+            gamma = (1 + 0.1 * r.standard_normal(shape[0])).astype(np.float32)
+            _, mean, rstd = D.layernorm_fwd(X, gamma, 0 * gamma, 1e-5)
+            ts = [T(tiled, ctx, X, base, "f32"), tiled.TiledTensor.from_numpy(ctx, np.stack([mean, rstd]).astype(np.float32), (2,) + base[1:]),
+                  T(tiled, ctx, gamma, base[:1], "f32"), T(tiled, ctx, dY, base, "f32"), tiled.TiledTensor(ctx, "f32", shape, base)]
+            ts += [tiled.TiledTensor(ctx, "f32", shape[:1], base[:1]) for _ in range(2)]
+            return ts, D.layernorm_bwd(X, gamma, mean, rstd, dY)
+
+        def norm(ts):
+            capi.nnt_layernorm_bwd(ctx.h, ts[0].h, ts[1].h, ts[2].h, ts[3].h, None, ts[4].h, ts[5].h, ts[6].h)
+
+        A, B = (r.integers(-32, 33, s).astype(np.float32) / 16 for s in ((1333, 777), (777, 1027)))
+        tA, tB, tC = T(tiled, ctx, A, (500, 300), "bf16"), T(tiled, ctx, B, (300, 257), "bf16"), tiled.TiledTensor(ctx, "f32", (1333, 1027), (500, 257))
+        product = lambda: capi.nnt_gemm(ctx.h, 1.0, 0, tA.h, 0, tB.h, 0.0, tC.h, 1, 0, None)
+        Y = r.standard_normal((256, 1500)).astype(np.float32)
+        small, large = T(tiled, ctx, Y[:, :64], (128, 64), "f32"), T(tiled, ctx, Y, (128, 500), "f32")
+        db = tiled.TiledTensor(ctx, "f32", (256,), (128,))
+        first, _ = norm_case((2050, 400, 1), (2050, 400, 1))
+        last, want = norm_case((8191, 300, 1), (8191, 300, 1))      # 2 x 256 partial rows: 4.2 million elements
+        # eager: a product as a whole, sums in one launch, a smaller layer norm
+        product()
+        capi.nnt_bias_grad(ctx.h, small.h, db.h)
+        norm(first)
+        g = C.c_void_p()
+        capi.nnt_capture_begin(ctx.h)
+        ctx.set_granularity(1)
+        product()
+        ctx.set_granularity(0)
+        capi.nnt_bias_grad(ctx.h, large.h, db.h)
+        norm(last)
+        capi.nnt_capture_end(ctx.h, C.byref(g))
+        for rep in range(3):
+            for t in (tC, db, last[4], last[5], last[6]):
+                capi.nnt_fill(ctx.h, 0.0, t.h)
+            capi.nnt_graph_launch(g)
+            check(tC.download(), A.astype(np.float64) @ B.astype(np.float64), "f32", "captured product")
+            check(db.download(), Y.astype(np.float64).sum(1), "f32", "captured bias gradient")
+            for t, ref, what in zip(last[4:], want, ("dX", "dgamma", "dbeta")):
+                e = relerr(t.download(), ref)
+                assert e <= TOL["f32"], (what, e)
+        capi.nnt_graph_destroy(g)
+
+
 @pytest.mark.parametrize("n_streams", [1, 4])
 def test_per_task_timing_records(mods, n_streams):
     """nnt_profile_*: every task is bracketed by timing events; the records come back aggregated per
