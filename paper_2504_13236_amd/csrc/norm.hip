@@ -777,11 +777,14 @@ int32_t launch_ln_fwd(hipStream_t st, bool vec, bool any, int nv_needed, const T
 }
 
 template <typename T>
-int32_t launch_ln_bwd(hipStream_t st, bool vec, const TiledView& X, const TiledView& S, const TiledView& G,
+int32_t launch_ln_bwd(hipStream_t st, bool vec, int nv_needed, const TiledView& X, const TiledView& S, const TiledView& G,
                       const TiledView& dY, const TiledView& dR, const TiledView& dX, int has_res, int64_t ncols) {
     constexpr int V = VecOf<T>::V;
-    // (what is too long for ln_bwd_onepass: the four wavefronts of a workgroup share a token)
-    if (!vec) hipLaunchKernelGGL((ln_bwd_fused<T, 1, 0>), dim3((unsigned)((ncols + 3) / 4)), dim3(256), 0, st, X, S, G, dY, dR, dX, has_res, ncols);
+    // (what ln_bwd_onepass does not take: tokens of more than `kLnShareAbove` vectors per lane are shared by the four wavefronts of a workgroup)
+    const dim3 quarter((unsigned)((ncols + 3) / 4)), block(256);
+    if (!vec) hipLaunchKernelGGL((ln_bwd_fused<T, 1, 0>), quarter, block, 0, st, X, S, G, dY, dR, dX, has_res, ncols);
+    else if (nv_needed <= kLnShareAbove) hipLaunchKernelGGL((ln_bwd_fused<T, V, 4>), quarter, block, 0, st, X, S, G, dY, dR, dX, has_res, ncols);
+    else if (nv_needed <= 16) hipLaunchKernelGGL((ln_bwd_fused<T, V, 4, 4>), dim3((unsigned)ncols), block, 0, st, X, S, G, dY, dR, dX, has_res, ncols);
     else hipLaunchKernelGGL((ln_bwd_fused<T, V, 0, 4>), dim3((unsigned)ncols), dim3(256), 0, st, X, S, G, dY, dR, dX, has_res, ncols);
     return hipGetLastError() == hipSuccess ? NNT_OK : NNT_EHIP;
 }
@@ -1343,7 +1346,12 @@ int32_t nnt_layernorm_bwd(nnt_ctx* ctx, nnt_tensor* X, nnt_tensor* stats, nnt_te
         if (dRes) acc.push_back(dRes->all(kRead));
         // one pass over the tokens wherever the eight waves of a workgroup can hold one (measured no slower at any size, from 128 tokens
         // of 128 to 4096 of 8192); longer ones take the column sums and the input gradient one after the other
-        const int wpt = vec || any_vec({X, dY, dX, dRes, gamma}) ? onepass_waves(nv) : 0;
+        // Tiles that fill less than half of a wave's lanes, more tokens than four per compute unit: two passes as well; its 256 large
+        // workgroups, most lanes idle, hold up the products of the other stream (fp32 block of 320 on tiles of 64, 1536 tokens: 418 us, 381
+        // in two passes).  With fewer tokens the launches count (128 on tiles of 32, 64 tokens, forward and backward: 17.9 -> 13.0).
+        const int lanes = 64 * V * (int)((X->base[0] + 64 * V - 1) / (64 * V));
+        const bool narrow = vec && 2 * X->base[0] < lanes && ncols > 1024;
+        const int wpt = !narrow && (vec || any_vec({X, dY, dX, dRes, gamma})) ? onepass_waves(nv) : 0;
         // (so do calls inside a capture whose partial rows have no room yet)
         const int64_t wgs = wpt > 0 ? onepass_wgs(wpt, ncols) : 0, rows = X->shape[0];
         if (wpt > 0 && ncols > 0 && ncols < INT32_MAX / 2 && X->ntiles <= 65535 && !(ctx->capturing && 2 * wgs * rows > ctx->stream_scratch_elems)) {
@@ -1367,8 +1375,8 @@ int32_t nnt_layernorm_bwd(nnt_ctx* ctx, nnt_tensor* X, nnt_tensor* stats, nnt_te
         rc = rowsum_tensor(ctx, 1, dY, X, stats, dgamma, dbeta);
         if (rc != NNT_OK) return rc;
         return submit(ctx, acc, [=](hipStream_t st) {
-            return dtype == NNT_F32 ? launch_ln_bwd<float>(st, vec, vx, vs, vg, vdy, vr, vdx, has_res, ncols)
-                                    : launch_ln_bwd<bf16_t>(st, vec, vx, vs, vg, vdy, vr, vdx, has_res, ncols);
+            return dtype == NNT_F32 ? launch_ln_bwd<float>(st, vec, nv, vx, vs, vg, vdy, vr, vdx, has_res, ncols)
+                                    : launch_ln_bwd<bf16_t>(st, vec, nv, vx, vs, vg, vdy, vr, vdx, has_res, ncols);
         });
     }
     // tile by tile.  The per-token sums live in the reduction scratch: [2][columns] per group of tiles.

@@ -553,7 +553,7 @@ def test_layernorm_tensor(mods, gran, dtype, shape, base):
 @pytest.mark.parametrize("shape,base", [((128, 1, 1), (32, 1, 1)), ((520, 9, 1), (520, 4, 1)), ((1000, 67, 9), (400, 32, 2)), ((4096, 19, 2), (1024, 19, 2)),
                                         ((4104, 3, 3), (4104, 3, 3)), ((8192, 5, 2), (8192, 5, 1)), ((8200, 3, 1), (8200, 3, 1)), ((16384, 3, 1), (4096, 3, 1)), ((16392, 2, 1), (16392, 2, 1)), ((512, 300, 17), (512, 300, 17)),
                                         ((63, 5, 2), (63, 5, 2)), ((777, 130, 3), (300, 100, 3)), ((4095, 3, 1), (4095, 3, 1)), ((4097, 3, 1), (4097, 3, 1)),
-                                        ((2001, 21, 2), (500, 9, 2)), ((13, 40, 2), (5, 7, 1)), ((8191, 5, 2), (1000, 5, 2))])
+                                        ((96, 1025, 1), (96, 1025, 1)), ((320, 513, 2), (64, 513, 2)), ((1200, 1025, 1), (48, 500, 1)), ((2001, 21, 2), (500, 9, 2)), ((13, 40, 2), (5, 7, 1)), ((8191, 5, 2), (1000, 5, 2))])
 def test_layernorm_backward_in_one_pass(mods, dtype, shape, base):
     """One to eight wavefronts per token, fewer and more tokens than groups of wavefronts, ragged tiles, scalar forms, and the
     longest tokens of either form (4096, 8192 in fp32, twice that in bf16) and the next.  The input gradient in place of the
