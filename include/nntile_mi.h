@@ -21,7 +21,8 @@
  *    (a) descriptor tables: the tile-pointer table of every tensor, the tables of
  *    cached product plans and of grouped optimiser steps; (b) the fp32 scratch of
  *    the two-stage column sums, shared and one part per stream (grows on demand, at
- *    least 4 MiB each once used); (c)
+ *    least 4 MiB each once used; a smaller one that it replaces stays as long as a
+ *    graph lives that was captured with it); (c)
  *    for products whose contraction is cut into k-slices, an fp32 workspace of
  *    slices x macro-tile partial sums per cached plan, and for products whose
  *    operands have odd leading dimensions or tiles a padded copy of both operands

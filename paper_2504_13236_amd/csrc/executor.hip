@@ -281,23 +281,30 @@ int32_t submit(nnt_ctx* ctx, const std::vector<Access>& acc,
     return NNT_OK;
 }
 
-// Makes `*buf` at least `elems` floats for each of `parts` users; contents are not kept.
-static int32_t grow_scratch(nnt_ctx* ctx, float** buf, int64_t* have, int64_t elems, int parts) {
+// Makes `*buf` (the memory of `*mem`) at least `elems` floats for each of `parts` users; contents are not kept.
+static int32_t grow_scratch(nnt_ctx* ctx, float** buf, int64_t* have, std::shared_ptr<Scratch>* mem, int64_t elems, int parts) {
     if (elems <= *have) return NNT_OK;
     if (ctx->capturing) return fail(ctx, NNT_ESTATE, "reduction scratch must exist before capture: run the operation once first");
     int32_t rc = sync_all(ctx);
     if (rc != NNT_OK) return rc;
-    if (*buf) NNT_HIP(ctx, hipFree(*buf));
     *buf = nullptr;
     *have = 0;
+    std::vector<std::weak_ptr<Scratch>>& old = ctx->replaced_mem;
+    old.erase(std::remove_if(old.begin(), old.end(), [](const std::weak_ptr<Scratch>& w) { return w.expired(); }), old.end());
+    if (mem->use_count() > 1) old.push_back(*mem);
+    mem->reset();      // freed here unless a graph holds it
     const int64_t want = std::max<int64_t>((elems + 63) / 64 * 64, 1 << 20);
-    NNT_HIP(ctx, hipMalloc((void**)buf, parts * want * sizeof(float)));
+    std::shared_ptr<Scratch> fresh(new Scratch());
+    fresh->bytes = parts * want * (int64_t)sizeof(float);
+    NNT_HIP(ctx, hipMalloc((void**)&fresh->p, (size_t)fresh->bytes));
+    *buf = fresh->p;
     *have = want;
+    *mem = std::move(fresh);
     return NNT_OK;
 }
-int32_t ensure_scratch(nnt_ctx* ctx, int64_t elems) { return grow_scratch(ctx, &ctx->red_scratch, &ctx->red_scratch_elems, elems, 1); }
+int32_t ensure_scratch(nnt_ctx* ctx, int64_t elems) { return grow_scratch(ctx, &ctx->red_scratch, &ctx->red_scratch_elems, &ctx->red_mem, elems, 1); }
 int32_t ensure_stream_scratch(nnt_ctx* ctx, int64_t elems) {
-    return grow_scratch(ctx, &ctx->stream_scratch, &ctx->stream_scratch_elems, elems, ctx->n_streams);
+    return grow_scratch(ctx, &ctx->stream_scratch, &ctx->stream_scratch_elems, &ctx->stream_mem, elems, ctx->n_streams);
 }
 
 }  // namespace nnt
@@ -308,6 +315,7 @@ struct nnt_graph {
     nnt_ctx* ctx;
     hipGraph_t graph;
     hipGraphExec_t exec;
+    std::shared_ptr<Scratch> mem[2];     // what its tasks write partial sums to: kept also where the context takes larger buffers
 };
 
 extern "C" {
@@ -397,8 +405,6 @@ int32_t nnt_ctx_destroy(nnt_ctx* ctx) {
     for (auto& r : ctx->profile) { (void)hipEventDestroy(r.start); (void)hipEventDestroy(r.stop); }
     for (hipEvent_t e : ctx->timing_pool) (void)hipEventDestroy(e);
     ctx->gemm_plans.clear();
-    if (ctx->red_scratch) (void)hipFree(ctx->red_scratch);
-    if (ctx->stream_scratch) (void)hipFree(ctx->stream_scratch);
     if (ctx->own_streams)
         for (int s = 0; s < ctx->n_streams; s++) (void)hipStreamDestroy(ctx->streams[s]);
     delete ctx;
@@ -458,7 +464,9 @@ int32_t nnt_ctx_stats(nnt_ctx* ctx, nnt_exec_stats* out) {
     *out = ctx->stats;
     out->plans = (int64_t)ctx->gemm_plans.size();
     out->device_table_bytes = ctx->table_bytes;
-    out->device_workspace_bytes = (ctx->red_scratch_elems + ctx->n_streams * ctx->stream_scratch_elems) * (int64_t)sizeof(float);
+    out->device_workspace_bytes = (ctx->red_mem ? ctx->red_mem->bytes : 0) + (ctx->stream_mem ? ctx->stream_mem->bytes : 0);
+    for (const std::weak_ptr<Scratch>& w : ctx->replaced_mem)
+        if (const std::shared_ptr<Scratch> m = w.lock()) out->device_workspace_bytes += m->bytes;
     plan_device_bytes(ctx, &out->device_table_bytes, &out->device_workspace_bytes);
     return NNT_OK;
 }
@@ -551,7 +559,7 @@ int32_t nnt_capture_end(nnt_ctx* ctx, nnt_graph** out) {
     hipGraphExec_t exec;
     NNT_HIP(ctx, hipGraphInstantiate(&exec, graph, nullptr, nullptr, 0));
     if (trace) fprintf(stderr, "nnt: capture_end: instantiated\n");
-    nnt_graph* g = new (std::nothrow) nnt_graph{ctx, graph, exec};
+    nnt_graph* g = new (std::nothrow) nnt_graph{ctx, graph, exec, {ctx->red_mem, ctx->stream_mem}};
     if (!g) return NNT_ENOMEM;
     *out = g;
     return NNT_OK;

@@ -106,6 +106,19 @@ struct nnt_tensor {
     nnt::Access one(int64_t idx, int mode) { return nnt::Access{&deps[idx], 1, mode}; }
 };
 
+namespace nnt {
+// Scratch memory of a context.  A graph keeps the addresses that its tasks were recorded with, so it holds the buffers that the
+// context had at the time: one that the context has replaced by a larger one goes with the last graph that may write to it.
+struct Scratch {
+    float* p = nullptr;
+    int64_t bytes = 0;
+    Scratch() = default;
+    Scratch(const Scratch&) = delete;
+    Scratch& operator=(const Scratch&) = delete;
+    ~Scratch() { if (p) (void)hipFree(p); }
+};
+}  // namespace nnt
+
 struct nnt_ctx {
     int device = 0;
     int n_streams = 1;
@@ -138,11 +151,14 @@ struct nnt_ctx {
     // gradients); grows on demand, guarded by its own dependency record.
     float* red_scratch = nullptr;
     int64_t red_scratch_elems = 0;
+    std::shared_ptr<nnt::Scratch> red_mem;
     nnt::TileDep red_dep;
     // the same for tasks whose kernels follow each other inside the task: one part per stream, whose order keeps the
     // tasks that use a part apart, so that tasks on different streams do not wait for one another's partial sums
     float* stream_scratch = nullptr;
     int64_t stream_scratch_elems = 0;        // per stream
+    std::shared_ptr<nnt::Scratch> stream_mem;
+    std::vector<std::weak_ptr<nnt::Scratch>> replaced_mem;      // some of it may still be held by graphs
     int cur_stream = 0;                      // stream of the task whose launches are being issued
     // per-task timing (nnt_profile_*): what the operation being submitted is called and
     // how much algorithmic work it stands for; the first task of the operation carries it

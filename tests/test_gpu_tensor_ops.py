@@ -880,6 +880,54 @@ def test_graph_capture_behind_other_forms_of_the_operation(mods):
         capi.nnt_graph_destroy(g)
 
 
+def test_graph_keeps_the_scratch_it_was_captured_with(mods):
+    """The partial sums of captured tasks lie in the scratch that the context had then.  An eager call that needs more takes a new
+    one; the old one stays until the graph goes (seen by the reported bytes), and the graph replays on it."""
+    capi, tiled = mods
+    r = rng(37)
+    with tiled.Context(n_streams=2) as ctx:
+        def case(rows, cols):
+            X, dY = (r.standard_normal((rows, cols)).astype(np.float32) for _ in range(2))
+            gamma = (1 + 0.1 * r.standard_normal(rows)).astype(np.float32)
+            _, mean, rstd = D.layernorm_fwd(X, gamma, 0 * gamma, 1e-5)
+            base = (rows, cols)
+            ts = [T(tiled, ctx, X, base, "f32"), tiled.TiledTensor.from_numpy(ctx, np.stack([mean, rstd]).astype(np.float32), (2, cols)),
+                  T(tiled, ctx, gamma, (rows,), "f32"), T(tiled, ctx, dY, base, "f32"), tiled.TiledTensor(ctx, "f32", base, base)]
+            ts += [tiled.TiledTensor(ctx, "f32", (rows,), (rows,)) for _ in range(3)]
+            return ts, D.layernorm_bwd(X, gamma, mean, rstd, dY) + (dY.astype(np.float64).sum(1),)
+
+        def run(ts):
+            capi.nnt_layernorm_bwd(ctx.h, ts[0].h, ts[1].h, ts[2].h, ts[3].h, None, ts[4].h, ts[5].h, ts[6].h)
+            capi.nnt_bias_grad(ctx.h, ts[3].h, ts[7].h)
+
+        held = lambda: ctx.stats()["device_workspace_bytes"]
+        small, want = case(512, 1100)             # both scratches at their least, 2^20 floats
+        large, _ = case(4096, 1100)               # 2 x 256 partial rows: twice that and more
+        wide = tiled.TiledTensor.zeros(ctx, (8192, 17000), (8192, 17000), "bf16")      # 133 partial rows of 8192 in the shared scratch
+        wide_db = tiled.TiledTensor(ctx, "f32", (8192,), (8192,))
+        run(small)
+        first = held()
+        assert first == (1 + 2) * 4 * 2 ** 20
+        g = C.c_void_p()
+        capi.nnt_capture_begin(ctx.h)
+        run(small)
+        capi.nnt_capture_end(ctx.h, C.byref(g))
+        run(large)
+        capi.nnt_bias_grad(ctx.h, wide.h, wide_db.h)
+        both = held()
+        assert both == first + 2 * 2 * 256 * 4096 * 4 + 133 * 8192 * 4
+        for rep in range(3):
+            for t in small[4:]:
+                capi.nnt_fill(ctx.h, 0.0, t.h)
+            capi.nnt_graph_launch(g)
+            run(large)
+            for t, ref, what in zip(small[4:], want, ("dX", "dgamma", "dbeta", "db")):
+                e = relerr(t.download(), ref)
+                assert e <= TOL["f32"], (rep, what, e)
+        capi.nnt_graph_destroy(g)
+        assert both - held() == first             # what only the graph still held, and not before
+
+
 @pytest.mark.parametrize("n_streams", [1, 4])
 def test_per_task_timing_records(mods, n_streams):
     """nnt_profile_*: every task is bracketed by timing events; the records come back aggregated per
