@@ -942,6 +942,12 @@ __global__ void __launch_bounds__(64 * kOnepassWaves, 2) ln_bwd_onepass(TiledVie
         a = wave_sum(a);
         b = wave_sum(b);
         if constexpr (WPT > 1) {
+            // (dX may be the residual: a vector that was moved back is stored over elements of the neighbour's, which lie in another
+            // wave's registers by the time the waves meet.  x and dy do, being summed; the residual is made to)
+            if constexpr (RES && ANY) {
+#pragma unroll
+                for (int it = 0; it < NV; it++) keep(cur.q[it]);
+            }
             // two buffers: a wave that is a token ahead writes the other one
             if (lane == 0) red[r & 1][wave] = make_float2(a, b);
             __syncthreads();

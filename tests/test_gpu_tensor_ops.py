@@ -583,6 +583,30 @@ def test_layernorm_backward_in_one_pass(mods, dtype, shape, base):
 
 
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("shape,base", [((8191, 150, 2), (1000, 150, 2)), ((4097, 300, 1), (4097, 300, 1)), ((1025, 700, 1), (513, 700, 1)), ((15, 40, 1), (5, 40, 1))])
+def test_layernorm_backward_in_place_of_the_residual(mods, dtype, shape, base):
+    """dX is the residual, odd extents: the last vector of a tile is moved back over elements that another lane, or another wavefront of
+    the token, adds its own copy of the residual to.  Every element gets it once."""
+    capi, tiled = mods
+    r = rng(41)
+    X, dY, dR = [quant(r.standard_normal(shape), dtype) for _ in range(3)]
+    gamma = (1 + 0.1 * r.standard_normal(shape[0])).astype(np.float32)
+    _, mean, rstd = D.layernorm_fwd(X, gamma, 0 * gamma, 1e-5)
+    dXref, _, _ = D.layernorm_bwd(X, gamma, mean, rstd, dY)
+    with tiled.Context(n_streams=2) as ctx:
+        tX, tdY, tg = T(tiled, ctx, X, base, dtype), T(tiled, ctx, dY, base, dtype), T(tiled, ctx, gamma, base[:1], "f32")
+        tS = tiled.TiledTensor.from_numpy(ctx, np.stack([mean, rstd]).astype(np.float32), (2,) + base[1:])
+        tR, apart = T(tiled, ctx, dR, base, dtype), tiled.TiledTensor(ctx, dtype, shape, base)
+        out = [tiled.TiledTensor(ctx, "f32", shape[:1], base[:1]) for _ in range(2)]
+        capi.nnt_layernorm_bwd(ctx.h, tX.h, tS.h, tg.h, tdY.h, tR.h, apart.h, out[0].h, out[1].h)
+        want = apart.download()
+        e = relerr(want, dXref + dR)
+        assert e <= TOL[dtype], e
+        capi.nnt_layernorm_bwd(ctx.h, tX.h, tS.h, tg.h, tdY.h, tR.h, tR.h, out[0].h, out[1].h)
+        assert np.array_equal(np.asarray(tR.download()), np.asarray(want))
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
 @pytest.mark.parametrize("shape,base", [((1, 1), (1, 1)), ((128, 128), (32, 32)), ((40, 1024), (16, 1000)), ((40, 1025), (16, 1000)), ((777, 31, 5), (300, 7, 2)),
                                         ((3168, 1024), (1056, 512)), ((3176, 1024), (3176, 1024)), ((6344, 1024), (6344, 1024)), ((6352, 1024), (6352, 1024))])
 def test_bias_grad_in_one_launch(mods, dtype, shape, base):
