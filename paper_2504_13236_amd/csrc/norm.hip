@@ -793,10 +793,15 @@ int32_t launch_ln_bwd(hipStream_t st, bool vec, int nv_needed, const TiledView& 
 // The input gradient and the partial gain / bias gradients from one read of x and dy.  As two kernels (ln_bwd_fused behind
 // the column sums) the adjoint reads x and dy twice; its bytes and, for few tokens, its launches are what bounds it.  A workgroup is
 // eight waves: WPT of them share a token, the 8 / WPT groups take tokens in turn, and every lane keeps its two sums
-// and the vectors of the next token in registers while it works on the present one, so that memory is never idle.
+// in registers while the vectors of the next token are on their way (all loads of a token in one piece and in every round, tile pointers through
+// the scalar memory: pointers out of the vector memory, whose loads come back in order, waited for the next token's data and for the last one's
+// stores, three to four memory latencies per token: 2664 x 8168 in fp32 on tiles of 512 129 us, 86 now; 768 x 8192 34 -> 26, bf16 4096 x 8192 75 -> 57).
 // At the end the groups' sums meet in LDS and the workgroup leaves one partial row per gradient (at most
-// 256 rows, which rowsum_stage2 adds in a fixed order): 8192 x 4096 in bf16 with a residual 95 -> 89 us,
-// 1024 x 16384 50 -> 38, 768 x 2048 20 -> 15, odd extents (vectors at any alignment instead of single elements) 3001 x 2004 72 -> 32; forward and backward with the calls before and behind them 115 -> 107, 63 -> 53, 36 -> 17.
+// 256 rows, which rowsum_stage2 adds in a fixed order).  Against the two passes, which in a captured graph run side by side on two streams,
+// adjoints back to back: fp32 1024 x 8192 37 -> 35 us, 4096 x 8192 140 -> 122, 8192 x 8192 326 -> 235, odd extents (vectors at any alignment instead of single
+// elements) 777 x 2664 27 -> 24, 1370 x 1672 35 -> 22; slower where less than half of the lanes have a vector or the longest tokens are few (bf16 768 x 8192
+// on tiles of 256 25 -> 28, 8192 x 4096 72 -> 77, fp32 5840 x 387 22 -> 28).  Called one by one, forward and backward, all of these are faster:
+// 49 -> 36, 126 -> 104, 49 -> 36; 65 sizes between 128 x 128 and 8192 x 8192: 1.24 times in graphs, 1.55 by calls.
 template <typename T, int V> struct RawVec;
 template <> struct RawVec<float, 4> { using R = float4; };
 template <> struct RawVec<bf16_t, 8> { using R = uint4; };
@@ -810,6 +815,10 @@ __device__ __forceinline__ void unpack(const uint4& r, float (&f)[8]) {
 // the compiler takes the value as changed here
 __device__ __forceinline__ void keep(float4& r) { asm volatile("" : "+v"(r.x), "+v"(r.y), "+v"(r.z), "+v"(r.w)); }
 __device__ __forceinline__ void keep(uint4& r) { asm volatile("" : "+v"(r.x), "+v"(r.y), "+v"(r.z), "+v"(r.w)); }
+
+// the value, or zeros
+__device__ __forceinline__ void only_if(bool c, float4& r) { if (!c) r = make_float4(0.f, 0.f, 0.f, 0.f); }
+__device__ __forceinline__ void only_if(bool c, uint4& r) { if (!c) r = make_uint4(0u, 0u, 0u, 0u); }
 
 // a vector as it lies in memory
 template <bool ANY, typename T, typename R> __device__ __forceinline__ void raw(const T* p, int n, R& r) {
@@ -837,6 +846,12 @@ template <bool ANY, typename T, typename R> __device__ __forceinline__ void raw(
         if constexpr (V == 4) r = make_float4(__uint_as_float(w[0]), __uint_as_float(w[1]), __uint_as_float(w[2]), __uint_as_float(w[3]));
         else r = make_uint4(w[0], w[1], w[2], w[3]);
     }
+}
+
+// Entry `i` (wave-uniform) of a table of tile pointers.  Tables do not change while a kernel runs, but behind a store the compiler does not
+// know that and would fetch the entry through the vector memory, whose loads come back in order.
+template <typename T> __device__ __forceinline__ T* table_entry(void* const* tab, int i) {
+    return in_global((T*)(uintptr_t)((const __attribute__((address_space(4))) uint64_t*)(uintptr_t)tab)[i]);
 }
 
 constexpr int kOnepassWaves = 8;
@@ -873,65 +888,65 @@ __global__ void __launch_bounds__(64 * kOnepassWaves, 2) ln_bwd_onepass(TiledVie
             own[it] = Own{(int)e[it] - at, min(V, ext[it] - at)};
             if (ok[it]) e[it] = (unsigned)at;
         }
+        if (!ok[it]) e[it] = 0;
 #pragma unroll
         for (int k = 0; k < V; k++) ag[it][k] = ab[it][k] = 0.f;
-        if (grp == 0) {
+    }
+    auto load_gain = [&]() {
+        if (grp != 0) return;
+#pragma unroll
+        for (int it = 0; it < NV; it++) {
             float gm[V];
 #pragma unroll
             for (int k = 0; k < V; k++) gm[k] = 0.f;
-            if (ok[it]) ldn<ANY, V>(global_as<const float>(G.tiles[l[it]]) + e[it], ext[it], gm);
+            if (ok[it]) ldn<ANY, V>(table_entry<const float>(G.tiles, l[it]) + e[it], ext[it], gm);
 #pragma unroll
             for (int k = 0; k < V; k++) gam[it * 64 * V + k] = gm[k];
         }
-    }
+    };
+    load_gain();
     __syncthreads();
     struct Token {
         R x[NV], d[NV], q[RES ? NV : 1];
         float mean, rstd;
-        int tile0, colidx;
+        T* o[NV];
+        bool real;
     };
+    // (lanes without a vector fetch their tile's first, groups without a token the last one: loads behind a condition would be waited for
+    // where the ways meet)
     auto fetch = [&](unsigned col, Token& t) {
-        t.mean = t.rstd = 0.f;
-        t.tile0 = -1;
-#pragma unroll
-        for (int it = 0; it < NV; it++) { t.x[it] = R{}; t.d[it] = R{}; }
-        if (col >= ncols) return;
-        const Column c = column_of(X, col);
-        t.tile0 = c.tile0;
-        t.colidx = c.colidx;
-        const float* st = global_as<const float>(S.tiles[c.stat_tile]) + 2 * (int64_t)c.colidx;
+        t.real = col < ncols;
+        const Column c = column_of(X, min(col, ncols - 1));
+        const float* st = table_entry<const float>(S.tiles, c.stat_tile) + 2 * (int64_t)c.colidx;
         t.mean = st[0];
         t.rstd = st[1];
 #pragma unroll
-        for (int it = 0; it < NV; it++)
-            if (ok[it]) {
-                const int64_t at = (int64_t)c.colidx * ext[it];
-                raw<ANY>(global_as<const T>(X.tiles[c.tile0 + l[it]]) + at + e[it], ext[it], t.x[it]);
-                raw<ANY>(global_as<const T>(dY.tiles[c.tile0 + l[it]]) + at + e[it], ext[it], t.d[it]);
-                if constexpr (RES) raw<ANY>(global_as<const T>(dR.tiles[c.tile0 + l[it]]) + at + e[it], ext[it], t.q[it]);
-            }
+        for (int it = 0; it < NV; it++) {
+            const int64_t at = (int64_t)c.colidx * ext[it];
+            t.o[it] = table_entry<T>(dX.tiles, c.tile0 + l[it]) + at;
+            raw<ANY>(table_entry<const T>(X.tiles, c.tile0 + l[it]) + at + e[it], ext[it], t.x[it]);
+            raw<ANY>(table_entry<const T>(dY.tiles, c.tile0 + l[it]) + at + e[it], ext[it], t.d[it]);
+            if constexpr (RES) raw<ANY>(table_entry<const T>(dR.tiles, c.tile0 + l[it]) + at + e[it], ext[it], t.q[it]);
+        }
     };
     // (the same number of rounds for every group: the waves of a workgroup meet once per token)
     const unsigned step = gridDim.x * GR, col0 = blockIdx.x * GR + grp;
     const float inv = 1.f / (float)X.shape[0];
-    // (one token ahead: two make it 81 us instead of 78 for 8192 x 4096 in bf16)
-    Token cur;
-    fetch(col0, cur);
-    for (unsigned r = 0; r < rounds; r++) {
-        Token next;
-        next.tile0 = -1;
-        if (r + 1 < rounds) fetch(col0 + (r + 1) * step, next);
+    auto work_on = [&](Token& t, unsigned r) {
+        const float mean = t.real ? t.mean : 0.f, rstd = t.real ? t.rstd : 0.f;
         float a = 0.f, b = 0.f;
 #pragma unroll
         for (int it = 0; it < NV; it++) {
             float x[V], d[V], gm[V];
-            unpack(cur.x[it], x);
-            unpack(cur.d[it], d);
+            only_if(t.real && ok[it], t.x[it]);
+            only_if(t.real && ok[it], t.d[it]);
+            unpack(t.x[it], x);
+            unpack(t.d[it], d);
             ldv<V>(gam + it * 64 * V, gm);
 #pragma unroll
             for (int k = 0; k < V; k++) {
                 if constexpr (ANY) d[k] = own[it](k) ? d[k] : 0.f;
-                const float gg = d[k] * gm[k], xh = (x[k] - cur.mean) * cur.rstd;
+                const float gg = d[k] * gm[k], xh = (x[k] - mean) * rstd;
                 a += gg;
                 b += gg * xh;
                 ag[it][k] += d[k] * xh;
@@ -946,7 +961,7 @@ __global__ void __launch_bounds__(64 * kOnepassWaves, 2) ln_bwd_onepass(TiledVie
             // wave's registers by the time the waves meet.  x and dy do, being summed; the residual is made to)
             if constexpr (RES && ANY) {
 #pragma unroll
-                for (int it = 0; it < NV; it++) keep(cur.q[it]);
+                for (int it = 0; it < NV; it++) keep(t.q[it]);
             }
             // two buffers: a wave that is a token ahead writes the other one
             if (lane == 0) red[r & 1][wave] = make_float2(a, b);
@@ -962,28 +977,54 @@ __global__ void __launch_bounds__(64 * kOnepassWaves, 2) ln_bwd_onepass(TiledVie
         b *= inv;
         // (unpacked again below: the unpacked values held over the sums would take another 32 registers)
 #pragma unroll
-        for (int it = 0; it < NV; it++) { keep(cur.x[it]); keep(cur.d[it]); }
-        if (cur.tile0 >= 0) {
+        for (int it = 0; it < NV; it++) { keep(t.x[it]); keep(t.d[it]); }
+        if (t.real) {
 #pragma unroll
             for (int it = 0; it < NV; it++)
                 if (ok[it]) {
                     float x[V], d[V], gm[V], o[V];
-                    unpack(cur.x[it], x);
-                    unpack(cur.d[it], d);
+                    unpack(t.x[it], x);
+                    unpack(t.d[it], d);
                     ldv<V>(gam + it * 64 * V, gm);
 #pragma unroll
-                    for (int k = 0; k < V; k++) o[k] = cur.rstd * (d[k] * gm[k] - a - (x[k] - cur.mean) * cur.rstd * b);
+                    for (int k = 0; k < V; k++) o[k] = rstd * (d[k] * gm[k] - a - (x[k] - mean) * rstd * b);
                     if constexpr (RES) {
                         float q[V];
-                        unpack(cur.q[it], q);
+                        unpack(t.q[it], q);
 #pragma unroll
                         for (int k = 0; k < V; k++) o[k] += q[k];
                     }
-                    stn<ANY, V>(global_as<T>(dX.tiles[cur.tile0 + l[it]]) + (int64_t)cur.colidx * ext[it] + e[it], ext[it], o);
+                    stn<ANY, V>(t.o[it] + e[it], ext[it], o);
                     __builtin_amdgcn_sched_barrier(0);
                 }
         }
-        cur = next;
+    };
+    // Two tokens in turn, the next one's loads started before the present one's are waited for.  (A fetch only where a token is left would be
+    // waited for where the ways meet.)  Four vectors per lane: one set of registers, the next token's copied to it at the end of a round, where they
+    // are waited for (two sets spill, 232 registers at most).
+    Token t0, t1;
+    fetch(col0, t0);
+    unsigned r = 0;
+    if constexpr (NV <= 2) {
+        for (; rounds - r > 2; r += 2) {
+            fetch(col0 + (r + 1) * step, t1);
+            work_on(t0, r);
+            fetch(col0 + (r + 2) * step, t0);
+            work_on(t1, r + 1);
+        }
+        if (rounds - r == 2) {
+            fetch(col0 + (r + 1) * step, t1);
+            work_on(t0, r);
+            work_on(t1, r + 1);
+        } else {
+            work_on(t0, r);
+        }
+    } else {
+        for (; r < rounds; r++) {
+            if (r + 1 < rounds) fetch(col0 + (r + 1) * step, t1);
+            work_on(t0, r);
+            t0 = t1;
+        }
     }
     // the groups' sums, gain first; element r of slot `it` of wave w at [it * 64 V + r]
     const int64_t rows = X.shape[0];

@@ -582,6 +582,30 @@ def test_layernorm_backward_in_one_pass(mods, dtype, shape, base):
             check(out[2].download(), dbref, "f32", "bias grad")
 
 
+@pytest.mark.parametrize("tokens", [255, 256, 257, 512, 513, 768, 769, 1025])
+@pytest.mark.parametrize("dtype,rows,base", [("f32", 2048, 128), ("bf16", 3848, 264), ("f32", 79, 5), ("bf16", 8200, 8200)])
+def test_layernorm_backward_of_one_to_five_tokens_per_workgroup(mods, dtype, rows, base, tokens):
+    """All waves of a workgroup on one token, 256 workgroups: the rounds in which a workgroup has one, two or more tokens left, workgroups without
+    one in the last round, whole vectors, odd extents and the longest form.  The last token is full of large values and the input gradient takes
+    the place of X: what the others fetch in its stead must not be seen."""
+    capi, tiled = mods
+    r = rng(43)
+    X, dY = [quant(r.standard_normal((rows, tokens)), dtype) for _ in range(2)]
+    X[:, -1] *= np.asarray(2.0, X.dtype) ** 100
+    gamma = (1 + 0.1 * r.standard_normal(rows)).astype(np.float32)
+    _, mean, rstd = D.layernorm_fwd(X.astype(np.float64), gamma, 0 * gamma, 1e-5)
+    dXref, dgref, dbref = D.layernorm_bwd(X.astype(np.float64), gamma, mean, rstd, dY.astype(np.float64))
+    with tiled.Context(n_streams=2) as ctx:
+        tX, tdY, tg = T(tiled, ctx, X, (base, 300), dtype), T(tiled, ctx, dY, (base, 300), dtype), T(tiled, ctx, gamma, (base,), "f32")
+        tS = tiled.TiledTensor.from_numpy(ctx, np.stack([mean, rstd]).astype(np.float32), (2, 300))
+        out = [tiled.TiledTensor(ctx, "f32", (rows,), (base,)) for _ in range(2)]
+        capi.nnt_layernorm_bwd(ctx.h, tX.h, tS.h, tg.h, tdY.h, None, tX.h, out[0].h, out[1].h)
+        e = relerr(tX.download(), dXref)
+        assert e <= TOL[dtype], e
+        check(out[0].download(), dgref, "f32", "ln dgamma")
+        check(out[1].download(), dbref, "f32", "ln dbeta")
+
+
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
 @pytest.mark.parametrize("shape,base", [((8191, 150, 2), (1000, 150, 2)), ((4097, 300, 1), (4097, 300, 1)), ((1025, 700, 1), (513, 700, 1)), ((15, 40, 1), (5, 40, 1))])
 def test_layernorm_backward_in_place_of_the_residual(mods, dtype, shape, base):
