@@ -584,8 +584,12 @@ __global__ void __launch_bounds__(256) rowsum_stage2_vec(const float* part, int6
             float4 x[8];
 #pragma unroll
             for (int u = 0; u < 8; u++) x[u] = k + 16 * u < nslots ? *reinterpret_cast<const float4*>(part + (k + 16 * u) * rows_total + r) : make_float4(0.f, 0.f, 0.f, 0.f);
+            // (in pairs: a chain of all of them would be the longest in the sum)
 #pragma unroll
-            for (int u = 0; u < 8; u++) { s.x += x[u].x; s.y += x[u].y; s.z += x[u].z; s.w += x[u].w; }
+            for (int d = 1; d < 8; d *= 2)
+#pragma unroll
+                for (int u = 0; u < 8; u += 2 * d) { x[u].x += x[u + d].x; x[u].y += x[u + d].y; x[u].z += x[u + d].z; x[u].w += x[u + d].w; }
+            s.x += x[0].x; s.y += x[0].y; s.z += x[0].z; s.w += x[0].w;
         }
     red[kg][rl] = s;
     __syncthreads();
@@ -593,10 +597,14 @@ __global__ void __launch_bounds__(256) rowsum_stage2_vec(const float* part, int6
         const int q = threadIdx.x >> 2, c = threadIdx.x & 3;
         const int64_t row = (int64_t)blockIdx.x * 64 + threadIdx.x;
         if (row < rows_total) {
-            float t = 0.f;
+            float t[16];
 #pragma unroll
-            for (int g = 0; g < 16; g++) t += reinterpret_cast<const float*>(&red[g][q])[c];
-            global_as<float>(otab[row / base0])[row % base0] = t;
+            for (int g = 0; g < 16; g++) t[g] = reinterpret_cast<const float*>(&red[g][q])[c];
+#pragma unroll
+            for (int d = 1; d < 16; d *= 2)
+#pragma unroll
+                for (int g = 0; g < 16; g += 2 * d) t[g] += t[g + d];
+            global_as<float>(otab[row / base0])[row % base0] = t[0];
         }
     }
 }
@@ -855,6 +863,10 @@ template <typename T> __device__ __forceinline__ T* table_entry(void* const* tab
 }
 
 constexpr int kOnepassWaves = 8;
+// Tokens of a group between two moves of its gradient sums to the partial rows (even).  The sums of one chain over all its tokens would be less
+// exact than the column sums' with their chains of 32 (256 tokens, 4096 x 65536: 3.1e-7 instead of 1.4e-7 in the 2-norm; 32 tokens, 4096 x 8192: the same
+// 1.4e-7 once the partial rows are added in pairs, 1.5e-7 before).
+constexpr unsigned kSumRounds = 32;
 constexpr int kOnepassGroups = 256;      // workgroups at most: one per compute unit (512: 101 us instead of 89 for 8192 x 4096, twice the partial rows)
 
 template <typename T, int V, int NV, int WPT, bool RES, bool ANY>
@@ -999,18 +1011,69 @@ __global__ void __launch_bounds__(64 * kOnepassWaves, 2) ln_bwd_onepass(TiledVie
                 }
         }
     };
+    // the groups' sums since the last time, gain first, added to the workgroup's partial rows; element r of slot `it` of wave w at [it * 64 V + r]
+    const int64_t rows = X.shape[0];
+    auto leave_sums = [&](bool first) {
+#pragma unroll
+        for (int which = 0; which < 2; which++) {
+            __syncthreads();
+#pragma unroll
+            for (int it = 0; it < NV; it++)
+#pragma unroll
+                for (int k = 0; k < V; k++) {
+                    float& s = which ? ab[it][k] : ag[it][k];
+                    sums[wave * kWave + it * 64 * V + lane * V + k] = s;
+                    s = 0.f;
+                }
+            __syncthreads();
+            float* out = part + ((int64_t)which * gridDim.x + blockIdx.x) * rows;
+            for (int p = threadIdx.x; p < WPT * kWave; p += 64 * kOnepassWaves) {
+                const int ww = p / kWave, q = p - ww * kWave, it = q / (64 * V);
+                const int s = ww + WPT * it, ll = s / vpt;
+                int el = (s - ll * vpt) * 64 * V + (q - it * 64 * V);
+                if (ll >= g0) continue;
+                const int ex = ext0_of(X, ll);
+                if constexpr (ANY) {      // (where the vector was moved to, and whether the element is its own)
+                    const int k = el % V, first_el = el - k, at = max(min(first_el, ex - V), 0);
+                    if (first_el >= ex || k < first_el - at || at + k >= ex) continue;
+                    el = at + k;
+                } else if (el >= ex) {
+                    continue;
+                }
+                float t = 0.f;
+#pragma unroll
+                for (int gq = 0; gq < GR; gq++) t += sums[gq * WPT * kWave + p];
+                float* const dst = out + (int64_t)ll * X.base[0] + el;
+                *dst = first ? t : *dst + t;
+            }
+        }
+    };
     // Two tokens in turn, the next one's loads started before the present one's are waited for.  (A fetch only where a token is left would be
     // waited for where the ways meet.)  Four vectors per lane: one set of registers, the next token's copied to it at the end of a round, where they
     // are waited for (two sets spill, 232 registers at most).
+    constexpr bool kTwoSets = NV <= 2;
+    auto sums_so_far = [&](bool first) {
+        leave_sums(first);
+        __syncthreads();
+        load_gain();
+        __syncthreads();
+    };
     Token t0, t1;
     fetch(col0, t0);
-    unsigned r = 0;
-    if constexpr (NV <= 2) {
-        for (; rounds - r > 2; r += 2) {
-            fetch(col0 + (r + 1) * step, t1);
-            work_on(t0, r);
-            fetch(col0 + (r + 2) * step, t0);
-            work_on(t1, r + 1);
+    unsigned r = 0, moved = 0;
+    if constexpr (kTwoSets) {
+        while (rounds - r > 2) {
+            const unsigned end = min(r + kSumRounds, (rounds - 1) & ~1u);
+            for (; r < end; r += 2) {
+                fetch(col0 + (r + 1) * step, t1);
+                work_on(t0, r);
+                fetch(col0 + (r + 2) * step, t0);
+                work_on(t1, r + 1);
+            }
+            if (r - moved == kSumRounds) {
+                sums_so_far(moved == 0);
+                moved = r;
+            }
         }
         if (rounds - r == 2) {
             fetch(col0 + (r + 1) * step, t1);
@@ -1020,42 +1083,18 @@ __global__ void __launch_bounds__(64 * kOnepassWaves, 2) ln_bwd_onepass(TiledVie
             work_on(t0, r);
         }
     } else {
-        for (; r < rounds; r++) {
-            if (r + 1 < rounds) fetch(col0 + (r + 1) * step, t1);
-            work_on(t0, r);
-            t0 = t1;
-        }
-    }
-    // the groups' sums, gain first; element r of slot `it` of wave w at [it * 64 V + r]
-    const int64_t rows = X.shape[0];
-#pragma unroll
-    for (int which = 0; which < 2; which++) {
-        __syncthreads();
-#pragma unroll
-        for (int it = 0; it < NV; it++)
-#pragma unroll
-            for (int k = 0; k < V; k++) sums[wave * kWave + it * 64 * V + lane * V + k] = which ? ab[it][k] : ag[it][k];
-        __syncthreads();
-        float* out = part + ((int64_t)which * gridDim.x + blockIdx.x) * rows;
-        for (int p = threadIdx.x; p < WPT * kWave; p += 64 * kOnepassWaves) {
-            const int ww = p / kWave, q = p - ww * kWave, it = q / (64 * V);
-            const int s = ww + WPT * it, ll = s / vpt;
-            int el = (s - ll * vpt) * 64 * V + (q - it * 64 * V);
-            if (ll >= g0) continue;
-            const int ex = ext0_of(X, ll);
-            if constexpr (ANY) {      // (where the vector was moved to, and whether the element is its own)
-                const int k = el % V, first = el - k, at = max(min(first, ex - V), 0);
-                if (first >= ex || k < first - at || at + k >= ex) continue;
-                el = at + k;
-            } else if (el >= ex) {
-                continue;
+        for (;;) {
+            for (const unsigned end = min(r + kSumRounds, rounds); r < end; r++) {
+                if (r + 1 < rounds) fetch(col0 + (r + 1) * step, t1);
+                work_on(t0, r);
+                t0 = t1;
             }
-            float t = 0.f;
-#pragma unroll
-            for (int gq = 0; gq < GR; gq++) t += sums[gq * WPT * kWave + p];
-            out[(int64_t)ll * X.base[0] + el] = t;
+            if (r >= rounds) break;
+            sums_so_far(moved == 0);
+            moved = r;
         }
     }
+    leave_sums(moved == 0);
 }
 
 // Waves that share a token so that each has at most NV vectors of it per lane; 0: too long for the kernel.

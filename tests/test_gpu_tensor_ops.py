@@ -606,6 +606,29 @@ def test_layernorm_backward_of_one_to_five_tokens_per_workgroup(mods, dtype, row
         check(out[1].download(), dbref, "f32", "ln dbeta")
 
 
+@pytest.mark.parametrize("rows,base,tokens", [(79, 5, 65536), (1152, 128, 16640), (79, 5, 8192), (79, 5, 8193), (79, 5, 8449), (79, 5, 8705), (145, 5, 16385)])
+def test_layernorm_backward_sums_over_many_tokens(mods, rows, base, tokens):
+    """All waves of a workgroup on one token, 256 workgroups: 65536 tokens are 256 rounds.  Gain and bias gradients in the 2-norm: a chain of m
+    additions in random order is off by about 0.29 * 2^-24 * sqrt(m / 2) of its sum, 6.9e-8 for the 32 tokens of a chain, 3.5e-8 for the 8 chains of a
+    workgroup, 5e-8 for its row's way through the pairs of 256, 6e-8 for the roundings of the terms: 1.1e-7 together; one chain of 256 is 2.0e-7
+    alone.  The numbers of tokens around a move of the sums as well: a token lost or counted twice would be 1e-2."""
+    capi, tiled = mods
+    r = rng(47)
+    X, dY = [r.standard_normal((rows, tokens)).astype(np.float32) for _ in range(2)]
+    gamma = (1 + 0.1 * r.standard_normal(rows)).astype(np.float32)
+    mean, rstd = [a.astype(np.float32) for a in (X.mean(0, dtype=np.float64), 1 / np.sqrt(X.var(0, dtype=np.float64) + 1e-5))]
+    xh = (X - mean.astype(np.float64)) * rstd
+    with tiled.Context(n_streams=2) as ctx:
+        tX, tdY, tg = T(tiled, ctx, X, (base, tokens), "f32"), T(tiled, ctx, dY, (base, tokens), "f32"), T(tiled, ctx, gamma, (base,), "f32")
+        tS = tiled.TiledTensor.from_numpy(ctx, np.stack([mean, rstd]), (2, tokens))
+        tdX = tiled.TiledTensor(ctx, "f32", (rows, tokens), (base, tokens))
+        out = [tiled.TiledTensor(ctx, "f32", (rows,), (base,)) for _ in range(2)]
+        capi.nnt_layernorm_bwd(ctx.h, tX.h, tS.h, tg.h, tdY.h, None, tdX.h, out[0].h, out[1].h)
+        for t, ref, what in zip(out, ((dY * xh).sum(1), dY.sum(1, dtype=np.float64)), ("dgamma", "dbeta")):
+            e = float(np.linalg.norm(t.download() - ref) / np.linalg.norm(ref))
+            assert e <= 2e-7, (what, e)
+
+
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
 @pytest.mark.parametrize("shape,base", [((8191, 150, 2), (1000, 150, 2)), ((4097, 300, 1), (4097, 300, 1)), ((1025, 700, 1), (513, 700, 1)), ((15, 40, 1), (5, 40, 1))])
 def test_layernorm_backward_in_place_of_the_residual(mods, dtype, shape, base):
