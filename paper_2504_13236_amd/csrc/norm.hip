@@ -515,9 +515,9 @@ __global__ void __launch_bounds__(256) rowsum_stage2(const float* part, int64_t 
     }
 }
 
-// The whole sum of a few thousand columns at most in one launch: a block owns four vectors of rows, its 256 groups of four lanes
-// take the columns in turn and meet in shuffles and LDS.  Latency is all such a call consists of, so the second launch costs
-// as much as the first.
+// The whole sum of up to 1024 columns in one or two tiles per row of tiles in one launch: a block owns four vectors of rows, its 256 groups of four
+// lanes take the columns in turn and meet in shuffles and LDS.  Latency is all such a call consists of, so the second launch costs
+// as much as the first; the tiles come one after the other, each a latency of its own.
 constexpr int kSmallThreads = 1024;
 template <typename T, int V, bool ANY>
 __global__ void __launch_bounds__(kSmallThreads) rowsum_small(TiledView y, void* const* otab) {
@@ -536,14 +536,14 @@ __global__ void __launch_bounds__(kSmallThreads) rowsum_small(TiledView y, void*
         const int ncol = ext[1] * ext[2] * ext[3];
         const T* p = global_as<const T>(y.tiles[l + y.grid[0] * rest]);
         if (e0 >= ext0) continue;
-        // eight columns per trip so that eight loads are in flight
-        for (int c = cg; c < ncol; c += 8 * kGroups) {
-            float d[8][V];
+        // four columns per trip, which 1024 of them fill, so that four loads are in flight
+        for (int c = cg; c < ncol; c += 4 * kGroups) {
+            float d[4][V];
 #pragma unroll
-            for (int u = 0; u < 8; u++)
+            for (int u = 0; u < 4; u++)
                 if (c + u * kGroups < ncol) ldn<ANY, V>(p + (int64_t)(c + u * kGroups) * ext0 + e, ext0, d[u]);
 #pragma unroll
-            for (int u = 0; u < 8; u++)
+            for (int u = 0; u < 4; u++)
                 if (c + u * kGroups < ncol) {
 #pragma unroll
                     for (int k = 0; k < V; k++) a[k] += d[u][k];
@@ -681,10 +681,11 @@ int32_t rowsum_tensor(nnt_ctx* ctx, int mode, nnt_tensor* dY, nnt_tensor* X, nnt
     bool vec = dY->base[0] % V == 0 && dY->shape[0] % V == 0;
     for (void* p : dY->tiles) vec = vec && aligned16(p);
     if (X) for (void* p : X->tiles) vec = vec && aligned16(p);
-    // in one launch up to 1024 columns and 13 MB: 4.0 to 7.0 us where the two launches take 6.5 to 7.4 (fp32 128 x 128: 4.0, 7.2; 768 x 1024: 4.2, 6.7;
-    // 3072 x 1024: 7.0, 7.4; bf16 4.6 to 6.5, 6.6 to 7.0); beyond, its few blocks take longer (fp32 768 x 2048: 7.5, 6.7; 8192 x 512: 9.2, 7.2)
+    // in one launch up to 1024 columns, 13 MB and two tiles along the columns: 4.3 to 6 us where the two launches take 6.5 to 8.1 (fp32 256 x 64: 4.3, 6.8;
+    // 768 x 1024: 5.0, 7.4; 3072 x 1024 in two tiles 5.6, 7.7); beyond, its few blocks take longer (fp32 768 x 2048: 7.5, 6.7;
+    // 8192 x 512: 9.2, 7.2), and every tile costs another latency: four tiles 6.7 to 9.5 (256 columns 6.9, 7.0; 1024 8.4, 7.4), sixteen 13.7, 7.1, sixty-four 43, 7.3
     const int64_t ncols = n_columns(dY);
-    if (mode == 0 && ncols <= 1024 && ncols * dY->shape[0] * dY->elem_size() <= 13000000 && dY->ntiles <= 65535) {
+    if (mode == 0 && ncols <= 1024 && ncols * dY->shape[0] * dY->elem_size() <= 13000000 && dY->ntiles <= std::min<int64_t>(2 * dY->grid[0], 65535)) {
         const int32_t kept = keep_rowsum_scratch(ctx, mode, dY);
         if (kept != NNT_OK) return kept;
         const TiledView vy = dY->view();

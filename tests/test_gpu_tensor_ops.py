@@ -667,6 +667,21 @@ def test_bias_grad_in_one_launch(mods, dtype, shape, base):
         check(db.download(), np.asarray(dY, np.float64).reshape(shape[0], -1).sum(1), "f32", "bias grad")
 
 
+@pytest.mark.parametrize("shape,base,launches", [((300, 64), (100, 64), 1), ((300, 64), (100, 33), 1), ((300, 64), (100, 30), 2), ((300, 16, 8), (300, 16, 4), 1),
+                                                 ((300, 16, 8), (300, 16, 2), 2), ((40, 1024), (40, 1), 2), ((301, 8, 64), (75, 8, 1), 2)])
+def test_bias_grad_of_many_tiles_takes_two_launches(mods, shape, base, launches):
+    """The one-launch form walks the tiles along the columns one after the other: one or two of them, however few columns they hold."""
+    capi, tiled = mods
+    r = rng(53)
+    dY = r.standard_normal(shape).astype(np.float32)
+    with tiled.Context(n_streams=2) as ctx:
+        t, db = T(tiled, ctx, dY, base, "f32"), tiled.TiledTensor(ctx, "f32", shape[:1], base[:1])
+        before = ctx.stats()["launches"]
+        capi.nnt_bias_grad(ctx.h, t.h, db.h)
+        assert ctx.stats()["launches"] - before == launches
+        check(db.download(), dY.astype(np.float64).reshape(shape[0], -1).sum(1), "f32", "bias grad")
+
+
 @pytest.mark.parametrize("shape,base", [((768, 6, 2), (256, 6, 2)), ((5000, 3, 1), (2500, 3, 1)), ((101, 5, 1), (37, 5, 1))])
 @pytest.mark.parametrize("gran", GRANS)
 def test_layernorm_token_with_an_outlier(mods, gran, shape, base):
