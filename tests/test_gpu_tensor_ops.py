@@ -629,6 +629,23 @@ def test_layernorm_backward_sums_over_many_tokens(mods, rows, base, tokens):
             assert e <= 2e-7, (what, e)
 
 
+@pytest.mark.parametrize("rows,base,tokens,passes", [(256, 256, 40, 1), (16384, 4096, 40, 2), (256, 32, 40, 1), (256, 32, 1025, 2), (255, 51, 1025, 1)])
+def test_layernorm_backward_counts_the_bytes_it_moves(mods, rows, base, tokens, passes):
+    """One pass reads x, dy (and the residual) once and writes dx, two read x and dy twice: that is what the records say."""
+    capi, tiled = mods
+    with tiled.Context(n_streams=2) as ctx:
+        z = lambda shape, b: tiled.TiledTensor.zeros(ctx, shape, b)
+        tX, tdY, tR, tdX = (z((rows, tokens), (base, tokens)) for _ in range(4))
+        tS, tg, dg, db = z((2, tokens), (2, tokens)), z((rows,), (base,)), z((rows,), (base,)), z((rows,), (base,))
+        for res in (None, tR):
+            ctx.profile(True)
+            capi.nnt_layernorm_bwd(ctx.h, tX.h, tS.h, tg.h, tdY.h, res.h if res else None, tdX.h, dg.h, db.h)
+            rec = ctx.profile_read()["layernorm_bwd"]
+            ctx.profile(False)
+            assert rec["unit"] == "bytes" and rec["tasks"] == passes
+            assert rec["work"] == rows * tokens * 4 * ((3 if passes == 1 else 5) + (1 if res else 0))
+
+
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
 @pytest.mark.parametrize("shape,base", [((8191, 150, 2), (1000, 150, 2)), ((4097, 300, 1), (4097, 300, 1)), ((1025, 700, 1), (513, 700, 1)), ((15, 40, 1), (5, 40, 1))])
 def test_layernorm_backward_in_place_of_the_residual(mods, dtype, shape, base):
