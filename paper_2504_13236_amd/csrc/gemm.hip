@@ -5,6 +5,7 @@
 #include "internal.hpp"
 
 #include <algorithm>
+#include <cmath>
 #include <cstdlib>
 #include <cstring>
 #include <sstream>
@@ -580,11 +581,12 @@ std::vector<int64_t> group_starts(const nnt_tensor* t, const std::vector<int>& a
 }
 
 // The form of a product that lays its operands out afresh (GemmPlan::packed), if it can take the product and promises to take
-// less than `limit_us`: nine tenths of what the model says of the register-staged kernels, with the copy priced at 14 us (10 to 12
+// nine tenths of what the model says of them as they are (`as_is`, of `as_is_wgs` macro-tiles), with the copy priced at 14 us (10 to 12
 // measured for 13 MB, and a result path that sorts) and 3 TB/s.  At 5 us, 6 of 150 random products of 128 to 6000 rows, columns and
 // contraction became 8 to 20 % slower (632 x 4856 over 848 on tiles of 300: 29 -> 35 us); at 14 none of 300 did, and products of
 // some size are two to three times faster (2688 x 3072 over 2145 on tiles of 400: 185 -> 57; 3627 x 1880 over 2496: 174 -> 74).
-int32_t try_packed(nnt_ctx* ctx, const AxisMap& ax, nnt_tensor* A, nnt_tensor* B, nnt_tensor* C, nnt_tensor* bias, nnt_tensor* R, GemmPlan* P, double limit_us) {
+int32_t try_packed(nnt_ctx* ctx, const AxisMap& ax, nnt_tensor* A, nnt_tensor* B, nnt_tensor* C, nnt_tensor* bias, nnt_tensor* R, GemmPlan* P, const ShapeChoice& as_is,
+                   int64_t as_is_wgs) {
     const bool bf = A->dtype == NNT_BF16;
     const int64_t elem = A->elem_size(), pad = bf ? 256 : 128;      // (pad: the most rows of a macro-tile)
     const std::vector<int>*contig[2] = {P->akf ? &ax.a_con : &ax.a_free, P->bkf ? &ax.b_con : &ax.b_free};
@@ -597,11 +599,24 @@ int32_t try_packed(nnt_ctx* ctx, const AxisMap& ax, nnt_tensor* A, nnt_tensor* B
     const int64_t a_elems = Mp * Kp, b_elems = Np * Kp;
     // (byte offsets of a macro-tile's lines and vector numbers have 32 bits)
     if (Kp > (1 << 23) || Mp > (1 << 23) || Np > (1 << 23) || a_elems > INT32_MAX || b_elems > INT32_MAX || (a_elems + b_elems) * elem > ((int64_t)2 << 30)) return NNT_OK;
-    const ShapeChoice sc = choose_shape(bf, kShapeWhole, {M}, {N}, {Kp}, true);
-    if (sc.us + (bf || K < 512 ? 14.0 : 3.5) + (double)(M + N) * K * 2.0 * elem / 3.0e6 >= limit_us) return NNT_OK;
+    ShapeChoice sc = choose_shape(bf, kShapeWhole, {M}, {N}, {Kp}, true);
     int bm, bn;
     gemm_cfg_tile(bf, sc.cfg, &bm, &bn);
     const int64_t gm = (M + bm - 1) / bm, gn = (N + bn - 1) / bn;
+    if (bf && C->dtype == NNT_F32 && sc.cfg != kCfgWide) {
+        // The larger bf16 shapes have no registers to move partial sums to, so their fp32 results are cut into slices at least as the operands as
+        // they are would have been (whole contractions in one chain instead: up to 1.8 times less exact, 4065 x 1211 over 2832 1.8e-7 -> 3.2e-7).
+        const double cut0 = (double)as_is.n_split / (double)std::max<int64_t>(as_is_wgs, 1), cut1 = (double)sc.n_split / (double)(gm * gn);
+        if (1.0 - cut1 + cut1 / sc.s > 1.0 - cut0 + cut0 / as_is.s) {
+            const ShapeCost* cd = kCostBf16[kShapeWhole];
+            while (cd->cfg != sc.cfg) cd++;
+            sc.s = as_is.s;
+            sc.n_split = std::min<int64_t>(gm * gn, (int64_t)std::ceil(cut0 * (double)(gm * gn)));
+            const int64_t part = ((Kp + sc.s - 1) / sc.s + 63) / 64 * 64, uncut = gm * gn - sc.n_split;
+            sc.us = (uncut > 0 ? launch_us(*cd, uncut, Kp) : 0.0) + launch_us(*cd, sc.n_split * sc.s, part) + 6.0 + (double)sc.n_split * bm * bn * 4.0 * (sc.s + 1) / 3.5e6;
+        }
+    }
+    if (sc.us + (bf || K < 512 ? 14.0 : 3.5) + (double)(M + N) * K * 2.0 * elem / 3.0e6 >= 0.9 * as_is.us) return NNT_OK;
     if (sc.s > 1 && (sc.n_split * sc.s * bm * bn * (int64_t)sizeof(float) > ((int64_t)2 << 30) || sc.n_split > 65535 / 4)) return NNT_OK;
 
     // where the results of every macro-tile go: at most two tiles of C along either axis
@@ -954,7 +969,11 @@ int32_t build_plan(nnt_ctx* ctx, int opA, nnt_tensor* A, int opB, nnt_tensor* B,
         n_split = sc.n_split;
         static const bool no_pack = getenv("NNT_GEMM_NO_PACK") != nullptr;      // debugging aid: operands are read as they are
         if (kind == kShapeGeneral && epi == 0 && ctx->granularity == NNT_GRAN_OP && !no_pack) {
-            const int32_t rc = try_packed(ctx, ax, A, B, C, bias, R, P, 0.9 * sc.us);
+            int bm0, bn0;
+            gemm_cfg_tile(bf, sc.cfg, &bm0, &bn0);
+            int64_t wgs = 0;
+            for (size_t ti = 0; ti < P->tasks.size(); ti++) wgs += ((tm[ti] + bm0 - 1) / bm0) * ((tn[ti] + bn0 - 1) / bn0);
+            const int32_t rc = try_packed(ctx, ax, A, B, C, bias, R, P, sc, wgs);
             if (rc != NNT_OK) return rc;
         }
     }

@@ -227,13 +227,14 @@ __device__ __forceinline__ void dl_body(const GemmArgs& g, char* lds) {
         bat_lo = bat - bat_hi * task.nb1;
     }
 
-    f32x16 acc[WNB][WMB];
-#pragma unroll
-    for (int bn = 0; bn < WNB; bn++)
-#pragma unroll
-        for (int bm = 0; bm < WMB; bm++)
-#pragma unroll
-            for (int i = 0; i < 16; i++) acc[bn][bm][i] = 0.f;
+    // kMoves: partial sums leave the matrix accumulators every 512 k (see add_sums): operands that are laid out afresh are cut into fewer slices than
+    // the register-staged kernels cut them into, and without the moves fp32 results were up to 1.8 times less exact for that (4350 x 430 over
+    // 1968 1.5e-7 -> 2.6e-7).  The larger shapes have no registers for it.
+    constexpr bool kMoves = SPAN && WNB == 1;
+    constexpr int kSumSteps = 16;
+    f32x16 acc[WNB][WMB], sum[kMoves ? WNB : 1][kMoves ? WMB : 1];
+    clear<WMB, WNB>(acc);
+    if constexpr (kMoves) clear<WMB, WNB>(sum);
 
     int T = 0;
     int chunk_i = 0;                         // index of the current chunk in g.chunks
@@ -497,7 +498,7 @@ __device__ __forceinline__ void dl_body(const GemmArgs& g, char* lds) {
             asm volatile("s_barrier" ::: "memory");
             static_for<kFrags>([&](auto I) { frag_one(I, KS0{}, 0, lds0); });
             int stage = 0, next_stage = kStages - 1;
-            for (int t = 0; t < T; t++) {
+            auto step = [&]() {
                 const int stage1 = next_of(stage);
                 substep(None{}, KS1{}, 0, stage_addr(stage), no_load, 0);
                 // step t + 1 complete for everybody (loads of steps t + 2 .. t + kStages - 2 may
@@ -511,6 +512,15 @@ __device__ __forceinline__ void dl_body(const GemmArgs& g, char* lds) {
                 advance();
                 next_stage = next_of(next_stage);
                 stage = stage1;
+            };
+            if constexpr (kMoves) {
+                for (int t = 0; t < T;) {
+                    clear<WMB, WNB>(acc);
+                    for (const int end = min(t + kSumSteps, T); t < end; t++) step();
+                    add_sums<WMB, WNB>(acc, sum);
+                }
+            } else {
+                for (int t = 0; t < T; t++) step();
             }
         }
         // nothing may still be on its way into LDS or into fragment registers when the results are staged
@@ -522,15 +532,18 @@ __device__ __forceinline__ void dl_body(const GemmArgs& g, char* lds) {
         asm volatile("s_barrier" ::: "memory");
     }
 
+    f32x16 (&res)[WNB][WMB] = [&]() -> f32x16 (&)[WNB][WMB] {
+        if constexpr (kMoves) return sum; else return acc;
+    }();
     float* stage = reinterpret_cast<float*>(lds) + wave * (32 * (32 * WMB + 4));
     const int m_base = m0 + wm * WMB * 32, n_base = n0 + wn * WNB * 32;
     if (task.partial) {
-        write_tile<float, WMB, WNB>(stage, acc, static_cast<float*>(task.C) + (int64_t)bat_lo * task.strideC + (int64_t)bat_hi * task.strideC2, task.ldc, nullptr,
+        write_tile<float, WMB, WNB>(stage, res, static_cast<float*>(task.C) + (int64_t)bat_lo * task.strideC + (int64_t)bat_hi * task.strideC2, task.ldc, nullptr,
                                     1.f, 0.f, m_base, n_base, task.m, task.n, lane);
     } else if constexpr (SPAN) {
-        write_span<TO, WMB, WNB>(stage, acc, g.spans + (m0 / BM + (n0 / BN) * g.grid_m), g.alpha, g.beta, m_base - m0, n_base - n0, lane);
+        write_span<TO, WMB, WNB>(stage, res, g.spans + (m0 / BM + (n0 / BN) * g.grid_m), g.alpha, g.beta, m_base - m0, n_base - n0, lane);
     } else {
-        write_tile<TO, WMB, WNB>(stage, acc, static_cast<TO*>(task.C) + (int64_t)bat_lo * task.strideC + (int64_t)bat_hi * task.strideC2, task.ldc, task.bias,
+        write_tile<TO, WMB, WNB>(stage, res, static_cast<TO*>(task.C) + (int64_t)bat_lo * task.strideC + (int64_t)bat_hi * task.strideC2, task.ldc, task.bias,
                                  g.alpha, g.beta, m_base, n_base, task.m, task.n, lane, task.cin_off);
     }
 }

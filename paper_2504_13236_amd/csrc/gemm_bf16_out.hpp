@@ -7,11 +7,11 @@
 #include <type_traits>
 
 #include "gemm_common.hpp"
+#include "gemm_sums.hpp"
 #include "global_ptr.hpp"
 
 namespace nnt {
 
-typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 
 // A pointer that is the same in every lane, moved to scalar registers.

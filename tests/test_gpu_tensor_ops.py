@@ -463,6 +463,30 @@ def test_products_of_odd_sizes(mods, m, n, k, tm, tn, tk, form, din):
         check(tD.download(), want, dt, form + ", tile by tile")
 
 
+@pytest.mark.parametrize("m,n,k,tile,din,bound", [
+    (3778, 896, 4736, 300, "f32", 2.4e-7),       # a move every 128 k: 2.1e-7; every 256 k 2.6e-7 to 2.9e-7
+    (2688, 3072, 2145, 400, "f32", 2.4e-7),
+    (2001, 1333, 2068, 500, "bf16", 1.7e-7),     # 128 x 128 macro-tiles, a move every 512 k: 1.3e-7; one chain 2.7e-7
+    (4065, 1211, 2832, 512, "bf16", 2.2e-7),     # 256 x 128 macro-tiles in as many slices as the operands as they are take: 1.8e-7; one chain 3.2e-7
+])
+def test_products_of_odd_sizes_are_as_exact_as_before(mods, m, n, k, tile, din, bound):
+    """fp32 results of operands that are laid out afresh, 2-norm.  A chain of c additions in random order is off by about a * sqrt(c / 2) of its sum,
+    so that halving it takes 0.7 of that; the bounds lie between what the chains are and what twice as long ones give."""
+    capi, tiled = mods
+    r = rng(m + n + k)
+    with tiled.Context(n_streams=2) as ctx:
+        A, B = quant(r.standard_normal((m, k)), din), quant(r.standard_normal((k, n)), din)
+        tA, tB, tC = T(tiled, ctx, A, (tile, tile), din), T(tiled, ctx, B, (tile, tile), din), tiled.TiledTensor(ctx, "f32", (m, n), (tile, tile))
+        ctx.profile(True)
+        capi.nnt_gemm(ctx.h, 1.0, 0, tA.h, 0, tB.h, 0.0, tC.h, 1, 0, None)
+        labels = list(ctx.profile_read())
+        ctx.profile(False)
+        assert any("_span_" in x for x in labels), labels
+        want = A.astype(np.float64) @ B.astype(np.float64)
+        e = float(np.linalg.norm(tC.download() - want) / np.linalg.norm(want))
+        assert e <= bound, e
+
+
 def test_device_memory_of_the_library_is_reported(mods):
     """nnt_ctx_stats: tile-pointer tables and plan tables count as table bytes, the fp32 workspace of a
     product cut into k-slices as workspace bytes; both shrink again when the tensors go."""
