@@ -580,11 +580,12 @@ std::vector<int64_t> group_starts(const nnt_tensor* t, const std::vector<int>& a
     return out;
 }
 
-// The form of a product that lays its operands out afresh (GemmPlan::packed), if it can take the product and promises to take
-// nine tenths of what the model says of them as they are (`as_is`, of `as_is_wgs` macro-tiles), with the copy priced at 14 us (10 to 12
-// measured for 13 MB, and a result path that sorts) and 3 TB/s.  At 5 us, 6 of 150 random products of 128 to 6000 rows, columns and
-// contraction became 8 to 20 % slower (632 x 4856 over 848 on tiles of 300: 29 -> 35 us); at 14 none of 300 did, and products of
-// some size are two to three times faster (2688 x 3072 over 2145 on tiles of 400: 185 -> 57; 3627 x 1880 over 2496: 174 -> 74).
+// The form of a product that lays its operands out afresh (GemmPlan::packed), if it can take the product and promises to take less than
+// nine tenths of what the model says of them as they are (`as_is`, of `as_is_wgs` macro-tiles).  The copy, and a result path that sorts, are priced at
+// 10 us (fp32) or 15 us (bf16) and 3 TB/s.  1217 random products of 128 to 5000 rows, columns and contraction on tiles of 256 to 1024, both forms
+// of each timed: fp32 80 of 640 take the copy, 1.29 times faster, none slower (at 7 us 3 of 104 by up to 9 %; at 3.5 us 37 of 173 by up to
+// 29 %, 1538 x 359 over 469 20 -> 24 us); bf16 57 of 577, 1.59 times (3204 x 3811 over 808 135 -> 45 us), none slower (at 10 us 7 of 73, by up to
+// 42 %).
 int32_t try_packed(nnt_ctx* ctx, const AxisMap& ax, nnt_tensor* A, nnt_tensor* B, nnt_tensor* C, nnt_tensor* bias, nnt_tensor* R, GemmPlan* P, const ShapeChoice& as_is,
                    int64_t as_is_wgs) {
     const bool bf = A->dtype == NNT_BF16;
@@ -616,7 +617,7 @@ int32_t try_packed(nnt_ctx* ctx, const AxisMap& ax, nnt_tensor* A, nnt_tensor* B
             sc.us = (uncut > 0 ? launch_us(*cd, uncut, Kp) : 0.0) + launch_us(*cd, sc.n_split * sc.s, part) + 6.0 + (double)sc.n_split * bm * bn * 4.0 * (sc.s + 1) / 3.5e6;
         }
     }
-    if (sc.us + (bf || K < 512 ? 14.0 : 3.5) + (double)(M + N) * K * 2.0 * elem / 3.0e6 >= 0.9 * as_is.us) return NNT_OK;
+    if (sc.us + (bf ? 15.0 : 10.0) + (double)(M + N) * K * 2.0 * elem / 3.0e6 >= 0.9 * as_is.us) return NNT_OK;
     if (sc.s > 1 && (sc.n_split * sc.s * bm * bn * (int64_t)sizeof(float) > ((int64_t)2 << 30) || sc.n_split > 65535 / 4)) return NNT_OK;
 
     // where the results of every macro-tile go: at most two tiles of C along either axis

@@ -487,6 +487,25 @@ def test_products_of_odd_sizes_are_as_exact_as_before(mods, m, n, k, tile, din, 
         assert e <= bound, e
 
 
+@pytest.mark.parametrize("m,n,k,tile,opA,opB,din,afresh", [
+    (1258, 1208, 686, 256, 0, 0, "f32", False), (1437, 1032, 903, 512, 0, 1, "f32", False), (1538, 359, 469, 1024, 0, 0, "f32", False),
+    (1111, 999, 777, 300, 0, 0, "f32", False), (3778, 896, 4736, 300, 0, 0, "f32", True),
+    (1605, 862, 1061, 300, 1, 0, "bf16", False), (4630, 1735, 810, 256, 1, 0, "bf16", False), (3204, 3811, 808, 400, 0, 1, "bf16", True),
+    (2001, 2068, 1333, 500, 0, 0, "bf16", True), (1333, 2068, 2001, 500, 1, 0, "bf16", True),
+])
+def test_which_products_of_odd_sizes_are_laid_out_afresh(mods, m, n, k, tile, opA, opB, din, afresh):
+    """Products on which the copy was measured to lose (by 3 to 40 %) and to win."""
+    capi, tiled = mods
+    with tiled.Context(n_streams=1) as ctx:
+        z = lambda shape, dt: tiled.TiledTensor.zeros(ctx, shape, tuple(min(x, tile) for x in shape), dt)
+        tA, tB, tC = z((k, m) if opA else (m, k), din), z((n, k) if opB else (k, n), din), z((m, n), "f32")
+        ctx.profile(True)
+        capi.nnt_gemm(ctx.h, 1.0, opA, tA.h, opB, tB.h, 0.0, tC.h, 1, 0, None)
+        labels = list(ctx.profile_read())
+        ctx.profile(False)
+        assert any("_span_" in x for x in labels) == afresh, labels
+
+
 def test_device_memory_of_the_library_is_reported(mods):
     """nnt_ctx_stats: tile-pointer tables and plan tables count as table bytes, the fp32 workspace of a
     product cut into k-slices as workspace bytes; both shrink again when the tensors go."""
