@@ -230,7 +230,7 @@ __device__ __forceinline__ void dl_body(const GemmArgs& g, char* lds) {
     // kMoves: partial sums leave the matrix accumulators every 512 k (see add_sums): operands that are laid out afresh are cut into fewer slices than
     // the register-staged kernels cut them into, and without the moves fp32 results were up to 1.8 times less exact for that (4350 x 430 over
     // 1968 1.5e-7 -> 2.6e-7).  The larger shapes have no registers for it.
-    constexpr bool kMoves = SPAN && WNB == 1;
+    constexpr bool kMoves = SPAN && WNB == 1 && sizeof(TO) == 4;
     constexpr int kSumSteps = 16;
     f32x16 acc[WNB][WMB], sum[kMoves ? WNB : 1][kMoves ? WMB : 1];
     clear<WMB, WNB>(acc);
