@@ -281,6 +281,14 @@ int32_t submit(nnt_ctx* ctx, const std::vector<Access>& acc,
     return NNT_OK;
 }
 
+// Gives up scratch memory that a larger one takes the place of: freed here unless a graph holds it.
+static void replace_mem(nnt_ctx* ctx, std::shared_ptr<Scratch>* mem) {
+    std::vector<std::weak_ptr<Scratch>>& old = ctx->replaced_mem;
+    old.erase(std::remove_if(old.begin(), old.end(), [](const std::weak_ptr<Scratch>& w) { return w.expired(); }), old.end());
+    if (mem->use_count() > 1) old.push_back(*mem);
+    mem->reset();
+}
+
 // Makes `*buf` (the memory of `*mem`) at least `elems` floats for each of `parts` users; contents are not kept.
 static int32_t grow_scratch(nnt_ctx* ctx, float** buf, int64_t* have, std::shared_ptr<Scratch>* mem, int64_t elems, int parts) {
     if (elems <= *have) return NNT_OK;
@@ -289,10 +297,7 @@ static int32_t grow_scratch(nnt_ctx* ctx, float** buf, int64_t* have, std::share
     if (rc != NNT_OK) return rc;
     *buf = nullptr;
     *have = 0;
-    std::vector<std::weak_ptr<Scratch>>& old = ctx->replaced_mem;
-    old.erase(std::remove_if(old.begin(), old.end(), [](const std::weak_ptr<Scratch>& w) { return w.expired(); }), old.end());
-    if (mem->use_count() > 1) old.push_back(*mem);
-    mem->reset();      // freed here unless a graph holds it
+    replace_mem(ctx, mem);
     const int64_t want = std::max<int64_t>((elems + 63) / 64 * 64, 1 << 20);
     std::shared_ptr<Scratch> fresh(new Scratch());
     fresh->bytes = parts * want * (int64_t)sizeof(float);
@@ -300,6 +305,30 @@ static int32_t grow_scratch(nnt_ctx* ctx, float** buf, int64_t* have, std::share
     *buf = fresh->p;
     *have = want;
     *mem = std::move(fresh);
+    return NNT_OK;
+}
+
+int32_t share_pack_space(nnt_ctx* ctx, int64_t bytes, std::shared_ptr<PackSpace>* out) {
+    out->reset();
+    std::shared_ptr<PackSpace> sp = ctx->pack_space.lock();
+    if (!sp) sp = std::make_shared<PackSpace>();
+    const int64_t part = (bytes + 255) / 256 * 256;
+    if (part > sp->part) {
+        std::shared_ptr<Scratch> fresh(new Scratch());
+        fresh->bytes = ctx->n_streams * part;
+        if (hipMalloc((void**)&fresh->p, (size_t)fresh->bytes) != hipSuccess) {
+            fresh->p = nullptr;
+            (void)hipGetLastError();
+            return NNT_OK;
+        }
+        const int32_t rc = sync_all(ctx);
+        if (rc != NNT_OK) return rc;
+        if (sp->mem) replace_mem(ctx, &sp->mem);
+        sp->mem = std::move(fresh);
+        sp->part = part;
+    }
+    ctx->pack_space = sp;
+    *out = std::move(sp);
     return NNT_OK;
 }
 int32_t ensure_scratch(nnt_ctx* ctx, int64_t elems) { return grow_scratch(ctx, &ctx->red_scratch, &ctx->red_scratch_elems, &ctx->red_mem, elems, 1); }
@@ -315,7 +344,7 @@ struct nnt_graph {
     nnt_ctx* ctx;
     hipGraph_t graph;
     hipGraphExec_t exec;
-    std::shared_ptr<Scratch> mem[2];     // what its tasks write partial sums to: kept also where the context takes larger buffers
+    std::shared_ptr<Scratch> mem[3];     // what its tasks write partial sums and operands to: kept also where the context takes larger buffers
 };
 
 extern "C" {
@@ -465,6 +494,7 @@ int32_t nnt_ctx_stats(nnt_ctx* ctx, nnt_exec_stats* out) {
     out->plans = (int64_t)ctx->gemm_plans.size();
     out->device_table_bytes = ctx->table_bytes;
     out->device_workspace_bytes = (ctx->red_mem ? ctx->red_mem->bytes : 0) + (ctx->stream_mem ? ctx->stream_mem->bytes : 0);
+    if (const std::shared_ptr<PackSpace> pack = ctx->pack_space.lock()) out->device_workspace_bytes += pack->mem->bytes;
     for (const std::weak_ptr<Scratch>& w : ctx->replaced_mem)
         if (const std::shared_ptr<Scratch> m = w.lock()) out->device_workspace_bytes += m->bytes;
     plan_device_bytes(ctx, &out->device_table_bytes, &out->device_workspace_bytes);
@@ -559,7 +589,8 @@ int32_t nnt_capture_end(nnt_ctx* ctx, nnt_graph** out) {
     hipGraphExec_t exec;
     NNT_HIP(ctx, hipGraphInstantiate(&exec, graph, nullptr, nullptr, 0));
     if (trace) fprintf(stderr, "nnt: capture_end: instantiated\n");
-    nnt_graph* g = new (std::nothrow) nnt_graph{ctx, graph, exec, {ctx->red_mem, ctx->stream_mem}};
+    const std::shared_ptr<PackSpace> pack = ctx->pack_space.lock();
+    nnt_graph* g = new (std::nothrow) nnt_graph{ctx, graph, exec, {ctx->red_mem, ctx->stream_mem, pack ? pack->mem : nullptr}};
     if (!g) return NNT_ENOMEM;
     *out = g;
     return NNT_OK;

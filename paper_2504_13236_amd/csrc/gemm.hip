@@ -147,12 +147,12 @@ struct GemmPlan {
     std::vector<GemmWg> wgs_ts;
     int64_t slice_elems_ts = 0;
     // Whole-operation launches of operands that only the register-staged kernels could read as they are: the operands are
-    // laid out afresh in `d_pack` first and the macro-tiles lie on one grid over all of C, with tables of its own.  Such a plan has
+    // laid out afresh in the context's pack space first and the macro-tiles lie on one grid over all of C, with tables of its own.  Such a plan has
     // nothing else: launches tile by tile of the same product have a plan to themselves.
     bool packed = false;
     PackOperand pack[2] = {};
     int pack_cfg = 0;
-    char* d_pack = nullptr;
+    std::shared_ptr<PackSpace> pack_space;
     char* d_pack_tables = nullptr;
     GemmArgs pack_args = {};
     const SplitReduce* pack_red = nullptr;
@@ -162,7 +162,7 @@ struct GemmPlan {
     float* d_ws_ts = nullptr;
     ~GemmPlan() {
         for (void* p : {(void*)d_tasks, (void*)d_chunks, (void*)d_wgs, (void*)d_wgs_op, (void*)d_red, (void*)d_ws, (void*)d_wgs_ts,
-                        (void*)d_red_ts, (void*)d_ws_ts, (void*)d_pack, (void*)d_pack_tables})
+                        (void*)d_red_ts, (void*)d_ws_ts, (void*)d_pack_tables})
             if (p) (void)hipFree(p);
     }
 };
@@ -585,7 +585,8 @@ std::vector<int64_t> group_starts(const nnt_tensor* t, const std::vector<int>& a
 // 10 us (fp32) or 15 us (bf16) and 3 TB/s.  1217 random products of 128 to 5000 rows, columns and contraction on tiles of 256 to 1024, both forms
 // of each timed: fp32 80 of 640 take the copy, 1.29 times faster, none slower (at 7 us 3 of 104 by up to 9 %; at 3.5 us 37 of 173 by up to
 // 29 %, 1538 x 359 over 469 20 -> 24 us); bf16 57 of 577, 1.59 times (3204 x 3811 over 808 135 -> 45 us), none slower (at 10 us 7 of 73, by up to
-// 42 %).
+// 42 %).  Layers of odd sizes, whose products overlap on two streams: 66 in fp32 the same within 0.5 % at any price from 6 us on, with the copy or without
+// (1153 x 1337 over 648 tokens 113 -> 100 us at 8, others slower), 41 in bf16 6 % faster.
 int32_t try_packed(nnt_ctx* ctx, const AxisMap& ax, nnt_tensor* A, nnt_tensor* B, nnt_tensor* C, nnt_tensor* bias, nnt_tensor* R, GemmPlan* P, const ShapeChoice& as_is,
                    int64_t as_is_wgs) {
     const bool bf = A->dtype == NNT_BF16;
@@ -660,20 +661,23 @@ int32_t try_packed(nnt_ctx* ctx, const AxisMap& ax, nnt_tensor* A, nnt_tensor* B
     std::vector<int32_t> line0;
     const std::vector<int64_t>* lines[2] = {P->akf ? &rows : &ks, P->bkf ? &cols : &ks};
     for (const std::vector<int64_t>* l : lines) line0.insert(line0.end(), l->begin(), l->end());
-    // (where there is no memory for them the product runs on the operands as they are)
     const int64_t cut_part = ((Kp + sc.s - 1) / sc.s + 63) / 64 * 64, n_cut = sc.s > 1 ? std::min<int64_t>(sc.n_split, gm * gn) : 0;
     const int S = n_cut > 0 ? (int)((Kp + cut_part - 1) / cut_part) : 1;
     const int64_t slice = (int64_t)bm * bn;
-    // (four floats more: the sum reads whole vectors, also of parts that do not begin at one)
-    const size_t pack_bytes = (size_t)((a_elems + b_elems) * elem), cut_bytes = n_cut > 0 ? ((size_t)n_cut * S * slice + 4) * sizeof(float) : 0;
-    if (hipMalloc((void**)&P->d_pack, pack_bytes) != hipSuccess || (cut_bytes && hipMalloc((void**)&P->d_ws, cut_bytes) != hipSuccess)) {
+    // (where there is no memory for them the product runs on the operands as they are; four floats more: the sum reads whole vectors, also of
+    // parts that do not begin at one)
+    const size_t cut_bytes = n_cut > 0 ? ((size_t)n_cut * S * slice + 4) * sizeof(float) : 0;
+    auto none = [&]() {
         (void)hipGetLastError();
-        if (P->d_pack) (void)hipFree(P->d_pack);
-        P->d_pack = nullptr;
+        for (void* p : {(void*)P->d_ws, (void*)P->d_pack_tables}) if (p) (void)hipFree(p);
         P->d_ws = nullptr;
-        return NNT_OK;
-    }
-    P->ws_bytes += (int64_t)(pack_bytes + cut_bytes);
+        P->d_pack_tables = nullptr;
+        P->pack_space.reset();
+        return (int32_t)NNT_OK;
+    };
+    const int32_t src = share_pack_space(ctx, (a_elems + b_elems) * elem, &P->pack_space);
+    if (src != NNT_OK) return src;
+    if (!P->pack_space || (cut_bytes && hipMalloc((void**)&P->d_ws, cut_bytes) != hipSuccess)) return none();
     for (int o = 0; o < 2; o++) {
         nnt_tensor* const t = o ? B : A;
         const bool kf = o ? P->bkf : P->akf;
@@ -681,7 +685,7 @@ int32_t try_packed(nnt_ctx* ctx, const AxisMap& ax, nnt_tensor* A, nnt_tensor* B
         const int cx = (*contig[o])[0];
         PackOperand& p = P->pack[o];
         p.tiles = t->d_tiles;
-        p.dst = P->d_pack + (o ? a_elems * elem : 0);
+        p.dst = (void*)(o ? a_elems * elem : 0);      // (an offset, as the chunks' are: which stream's part it is, a launch knows)
         p.ntc = (int32_t)t->grid[cx];
         p.ntl = (int32_t)lines[o]->size() - 1;
         p.base = (int32_t)t->base[cx];
@@ -714,8 +718,8 @@ int32_t try_packed(nnt_ctx* ctx, const AxisMap& ax, nnt_tensor* A, nnt_tensor* B
         const int64_t part = cut_part;
         for (int q = 0; q < S; q++) {
             GemmChunk c = whole;
-            c.A = static_cast<const char*>(whole.A) + q * part * (P->akf ? 1 : whole.lda) * elem;
-            c.B = static_cast<const char*>(whole.B) + q * part * (P->bkf ? 1 : whole.ldb) * elem;
+            c.A = (const void*)((intptr_t)whole.A + q * part * (P->akf ? 1 : whole.lda) * elem);
+            c.B = (const void*)((intptr_t)whole.B + q * part * (P->bkf ? 1 : whole.ldb) * elem);
             c.k = (int32_t)std::min(part, Kp - q * part);
             chunks.push_back(c);
         }
@@ -756,10 +760,6 @@ int32_t try_packed(nnt_ctx* ctx, const AxisMap& ax, nnt_tensor* A, nnt_tensor* B
                 }
         }
         deal_slices(by_slice, wgs);
-        P->splits = S;
-        P->n_split = (int64_t)red.size();
-        P->slice_elems = slice * n_cut / (int64_t)red.size();
-        P->red_blocks = (int)((slice / 4 + 255) / 256);
     }
     // all tables in one piece: an allocation and a copy cost some 15 us each in the first call on new tensors
     std::vector<char> blob;
@@ -772,9 +772,16 @@ int32_t try_packed(nnt_ctx* ctx, const AxisMap& ax, nnt_tensor* A, nnt_tensor* B
     const size_t at_lines = put(line0.data(), line0.size() * sizeof(int32_t)), at_red = put(red.data(), red.size() * sizeof(SplitReduce)),
                  at_spans = put(spans.data(), spans.size() * sizeof(GemmSpan)), at_tasks = put(tasks.data(), tasks.size() * sizeof(GemmTask)),
                  at_chunks = put(chunks.data(), chunks.size() * sizeof(GemmChunk)), at_wgs = put(wgs.data(), wgs.size() * sizeof(GemmWg));
-    NNT_HIP(ctx, hipMalloc((void**)&P->d_pack_tables, blob.size()));
-    P->table_bytes += (int64_t)blob.size();
+    if (hipMalloc((void**)&P->d_pack_tables, blob.size()) != hipSuccess) return none();
     NNT_HIP(ctx, hipMemcpy(P->d_pack_tables, blob.data(), blob.size(), hipMemcpyHostToDevice));
+    P->table_bytes += (int64_t)blob.size();
+    P->ws_bytes += (int64_t)cut_bytes;
+    if (n_cut > 0) {
+        P->splits = S;
+        P->n_split = (int64_t)red.size();
+        P->slice_elems = slice * n_cut / (int64_t)red.size();
+        P->red_blocks = (int)((slice / 4 + 255) / 256);
+    }
     const int32_t* const d_lines = reinterpret_cast<const int32_t*>(P->d_pack_tables + at_lines);
     P->pack[0].line0 = d_lines;
     P->pack[1].line0 = d_lines + lines[0]->size();
@@ -1289,14 +1296,18 @@ int32_t gemm_core(nnt_ctx* ctx, float alpha, int32_t opA, nnt_tensor* A, int32_t
             g = P->pack_args;
             g.alpha = alpha;
             g.beta = beta;
-            acc.push_back(Access{&P->ws_dep, 1, kReadWrite});
+            if (P->n_split > 0) acc.push_back(Access{&P->ws_dep, 1, kReadWrite});
             const double red_bytes = (double)P->n_split * P->slice_elems * 4.0 * (P->splits + 1);
             return submit(ctx, acc, [=](hipStream_t st) {
                 const bool bf16 = P->dtype_in == NNT_BF16;
-                int32_t rc = pack_operands(st, bf16, P->pack[0], P->pack[1]);
+                GemmArgs ga = g;
+                ga.pack_base = reinterpret_cast<char*>(P->pack_space->mem->p) + ctx->cur_stream * P->pack_space->part;
+                PackOperand o[2] = {P->pack[0], P->pack[1]};
+                for (PackOperand& p : o) p.dst = ga.pack_base + (intptr_t)p.dst;
+                int32_t rc = pack_operands(st, bf16, o[0], o[1]);
                 if (rc != NNT_OK) return rc;
-                rc = bf16 ? launch_gemm_bf16_span(st, P->dtype_out == NNT_F32, P->akf, P->bkf, P->pack_cfg, g, P->pack_nwg)
-                          : launch_gemm_f32_span(st, P->akf, P->bkf, P->pack_cfg, g, P->pack_nwg);
+                rc = bf16 ? launch_gemm_bf16_span(st, P->dtype_out == NNT_F32, P->akf, P->bkf, P->pack_cfg, ga, P->pack_nwg)
+                          : launch_gemm_f32_span(st, P->akf, P->bkf, P->pack_cfg, ga, P->pack_nwg);
                 if (rc != NNT_OK || P->n_split == 0) return rc;
                 profile_mark(ctx, st, "splitk_reduce", red_bytes, true);
                 launch_splitk_reduce(st, P, P->pack_red, alpha, beta);

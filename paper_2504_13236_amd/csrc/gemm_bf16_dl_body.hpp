@@ -266,8 +266,8 @@ __device__ __forceinline__ void dl_body(const GemmArgs& g, char* lds) {
         auto set_chunk = [&](const ChunkS& ch) {
             chk = ch.k;
             const int lda = (int)ch.lda, ldb = (int)ch.ldb;
-            const uint16_t* Ab = reinterpret_cast<const uint16_t*>(ch.A) + (int64_t)bat_lo * ch.strideA + (int64_t)bat_hi * ch.strideA2;
-            const uint16_t* Bb = reinterpret_cast<const uint16_t*>(ch.B) + (int64_t)bat_lo * ch.strideB + (int64_t)bat_hi * ch.strideB2;
+            const uint16_t* Ab = reinterpret_cast<const uint16_t*>(ch.A + (SPAN ? reinterpret_cast<uint64_t>(g.pack_base) : 0)) + (int64_t)bat_lo * ch.strideA + (int64_t)bat_hi * ch.strideA2;
+            const uint16_t* Bb = reinterpret_cast<const uint16_t*>(ch.B + (SPAN ? reinterpret_cast<uint64_t>(g.pack_base) : 0)) + (int64_t)bat_lo * ch.strideB + (int64_t)bat_hi * ch.strideB2;
             baseA = reinterpret_cast<const char*>(AKF ? Ab + (int64_t)m0 * lda : Ab + m0);
             baseB = reinterpret_cast<const char*>(BKF ? Bb + (int64_t)n0 * ldb : Bb + n0);
             advA = AKF ? kBK * 2 : (int64_t)kBK * lda * 2;

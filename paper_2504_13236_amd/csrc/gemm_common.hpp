@@ -74,6 +74,7 @@ struct GemmArgs {
     int32_t grid_m, grid_n; // macro-tile grid of the single product
     float alpha, beta;
     const GemmSpan* spans;  // kernels on a grid over all of C: one record per macro-tile, grid_m of them per column of macro-tiles
+    char* pack_base;        // ... and where their operands have been laid out: their chunks hold offsets from here
 };
 
 // Macro-tile configurations.  M counts rows of C (first, fastest axis), N columns.

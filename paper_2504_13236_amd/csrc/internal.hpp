@@ -117,6 +117,12 @@ struct Scratch {
     Scratch& operator=(const Scratch&) = delete;
     ~Scratch() { if (p) (void)hipFree(p); }
 };
+// Where the operands of products are laid out afresh: `part` bytes per stream, for as long as a plan needs them.  All plans of a context share it:
+// a copy is written and read inside one task.
+struct PackSpace {
+    std::shared_ptr<Scratch> mem;
+    int64_t part = 0;
+};
 }  // namespace nnt
 
 struct nnt_ctx {
@@ -158,6 +164,7 @@ struct nnt_ctx {
     float* stream_scratch = nullptr;
     int64_t stream_scratch_elems = 0;        // per stream
     std::shared_ptr<nnt::Scratch> stream_mem;
+    std::weak_ptr<nnt::PackSpace> pack_space;
     std::vector<std::weak_ptr<nnt::Scratch>> replaced_mem;      // some of it may still be held by graphs
     int cur_stream = 0;                      // stream of the task whose launches are being issued
     // per-task timing (nnt_profile_*): what the operation being submitted is called and
@@ -213,6 +220,8 @@ int32_t ensure_scratch(nnt_ctx* ctx, int64_t elems);
 int32_t ensure_stream_scratch(nnt_ctx* ctx, int64_t elems);
 // inside a task's launch function: the part of the stream it has been given (as large as every ensure_stream_scratch so far)
 inline float* stream_scratch_of(const nnt_ctx* ctx) { return ctx->stream_scratch + ctx->cur_stream * ctx->stream_scratch_elems; }
+// Space of at least `bytes` per stream for operands laid out afresh; an empty pointer where there is no memory for it.
+int32_t share_pack_space(nnt_ctx* ctx, int64_t bytes, std::shared_ptr<PackSpace>* out);
 int32_t static_scratch_setup();      // looks up the current device's address of the static scratch array (norm.hip)
 
 // Adam on several parameter tensors in one launch (elementwise.hip); the group owns small device tables.

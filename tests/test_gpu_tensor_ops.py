@@ -1074,6 +1074,58 @@ def test_graph_keeps_the_scratch_it_was_captured_with(mods):
         assert both - held() == first             # what only the graph still held, and not before
 
 
+def test_products_of_odd_sizes_share_the_space_of_their_copies(mods):
+    """The operands that products lay out afresh lie in one space per context, a part per stream as large as the largest of them needs, for as long as
+    one of the products lives.  A graph captured before the space grew replays on the space it was captured with."""
+    capi, tiled = mods
+    r = rng(59)
+    up = lambda x, q: (x + q - 1) // q * q
+    part = lambda m, n, k: (up(m, 256) + up(n, 256)) * up(k, 64) * 2
+    sizes = [(2001, 1333, 2068, 500), (1333, 2068, 2001, 500), (2001, 2068, 1333, 500), (2509, 2523, 3643, 300)]
+    with tiled.Context(n_streams=2) as ctx:
+        held = lambda: ctx.stats()["device_workspace_bytes"]
+        cases = []
+        for m, n, k, t in sizes:
+            A, B = (r.integers(-32, 33, s).astype(np.float32) / 16 for s in ((m, k), (k, n)))
+            cases.append((T(tiled, ctx, A, (t, t), "bf16"), T(tiled, ctx, B, (t, t), "bf16"), tiled.TiledTensor(ctx, "bf16", (m, n), (t, t)),
+                          A.astype(np.float64) @ B.astype(np.float64)))
+        run = lambda c: capi.nnt_gemm(ctx.h, 1.0, 0, c[0].h, 0, c[1].h, 0.0, c[2].h, 1, 0, None)
+        ctx.profile(True)
+        for i in range(3):
+            run(cases[i])
+            assert held() == 2 * max(part(*s[:3]) for s in sizes[:i + 1])
+        assert all("_span_" in x for x in ctx.profile_read())
+        ctx.profile(False)
+        before = held()
+        g = C.c_void_p()
+        capi.nnt_capture_begin(ctx.h)
+        for c in cases[:3]:
+            run(c)
+        capi.nnt_capture_end(ctx.h, C.byref(g))
+        run(cases[3])
+        assert held() == before + 2 * part(*sizes[3][:3])
+        for _ in range(3):
+            for c in cases[:3]:
+                capi.nnt_fill(ctx.h, 0.0, c[2].h)
+            capi.nnt_graph_launch(g)
+            run(cases[3])
+            for c in cases:
+                check(c[2].download(), c[3], "bf16", "shared space")
+        capi.nnt_graph_destroy(g)
+        assert held() == 2 * part(*sizes[3][:3])
+        for c in cases:
+            run(c)
+        for c in cases:
+            check(c[2].download(), c[3], "bf16", "shared space, grown")
+        for c in cases[1:]:
+            for x in c[:3]:
+                x.close()
+        assert held() == 2 * part(*sizes[3][:3])
+        for x in cases[0][:3]:
+            x.close()
+        assert held() == 0
+
+
 @pytest.mark.parametrize("n_streams", [1, 4])
 def test_per_task_timing_records(mods, n_streams):
     """nnt_profile_*: every task is bracketed by timing events; the records come back aggregated per
