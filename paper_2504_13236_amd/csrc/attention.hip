@@ -904,15 +904,15 @@ AttnGeom rows_for(AttnKernel which, int dtype, AttnGeom g) {
     if (g.split) g.nblk = (g.bs + kHalfRows - 1) / kHalfRows;
     // reverse order for the second workgroups of the units: where two of them fit on one (not dK and dV in bf16 and any fp32 kernel
     // of head size 128) and every row block exists (short last tiles put empty workgroups first, which shifts the order: 576 of 128
-    // rows in tiles of 300, 313 -> 335 us). fp32: 24 pairs of 1024 positions 266 -> 233 us, 36 of 1000 290 -> 263 (283 -> 269 where calls
-    // on two streams overlap), 8 of 3000 701 -> 606,
-    // 64 of 1024 (1024 workgroups) 423 -> 400; bf16 up to 512 workgroups the same or 1 % slower, 1024 of head size 128 (32 pairs of 4096) forward
-    // and dQ 437 -> 422.  Beyond 1024 the short ones even out whatever comes first.
+    // rows in tiles of 300, 313 -> 335 us).  Forward and backward, without and with it, over 90 sizes of 768 to 4096 positions: fp32 from 257 workgroups on 1 to 25 %
+    // faster (17 pairs of 2048 536 -> 457 us, 33 969 -> 775, 68 of 1024 514 -> 434), bf16 from 513 on 0 to 5 % (49 pairs of 2048 211 -> 202, 92 of 1024
+    // 126 -> 122, head size 128 61 of 2048 476 -> 466), up to 512 1 % either way.  Not where each unit gets just three: the third ones would come to all units
+    // at the same time (fp32 48 pairs of 2048 1049 -> 1072, bf16 head size 128 354 -> 358).  Beyond 1024 the launch is left as it was.
     const bool bf = dtype == NNT_BF16;
     const int64_t n = (int64_t)g.Nb * g.Nh * g.gs * g.nblk;
     const bool two = bf ? !(which == kAttnDkv && g.H == 128) : g.H == 64;
     const int rows = g.split ? kHalfRows : kWgRows, last = g.Ns - (g.gs - 1) * g.bs;
-    if (g.causal && two && (last + rows - 1) / rows == g.nblk && n > (bf ? 2 * kUnits : kUnits) && n <= 1024) g.fold = (int)std::min<int64_t>(n, 2 * kUnits);
+    if (g.causal && two && (last + rows - 1) / rows == g.nblk && n > (bf ? 2 * kUnits : kUnits) && n <= 1024 && n != 3 * kUnits) g.fold = (int)std::min<int64_t>(n, 2 * kUnits);
     return g;
 }
 

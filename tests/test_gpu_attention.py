@@ -48,6 +48,7 @@ CASES = [
     ((64, 256, 5, 51), 128, 1, 51),
     ((64, 384, 3, 57), 192, 3, 57),
     ((128, 256, 4, 65), 256, 4, 65),
+    ((64, 256, 3, 128), 256, 3, 128),      # 768: three per compute unit, in their own order
 ]
 
 
