@@ -794,7 +794,8 @@ int32_t launch_ln_bwd(hipStream_t st, bool vec, int nv_needed, const TiledView& 
     if (!vec) hipLaunchKernelGGL((ln_bwd_fused<T, 1, 0>), quarter, block, 0, st, X, S, G, dY, dR, dX, has_res, ncols);
     else if (nv_needed <= kLnShareAbove) hipLaunchKernelGGL((ln_bwd_fused<T, V, 4>), quarter, block, 0, st, X, S, G, dY, dR, dX, has_res, ncols);
     else if (nv_needed <= 16) hipLaunchKernelGGL((ln_bwd_fused<T, V, 4, 4>), dim3((unsigned)ncols), block, 0, st, X, S, G, dY, dR, dX, has_res, ncols);
-    else hipLaunchKernelGGL((ln_bwd_fused<T, V, 0, 4>), dim3((unsigned)ncols), dim3(256), 0, st, X, S, G, dY, dR, dX, has_res, ncols);
+    else if (nv_needed <= 32) hipLaunchKernelGGL((ln_bwd_fused<T, V, 8, 4>), dim3((unsigned)ncols), block, 0, st, X, S, G, dY, dR, dX, has_res, ncols);
+    else hipLaunchKernelGGL((ln_bwd_fused<T, V, 0, 4>), dim3((unsigned)ncols), block, 0, st, X, S, G, dY, dR, dX, has_res, ncols);
     return hipGetLastError() == hipSuccess ? NNT_OK : NNT_EHIP;
 }
 

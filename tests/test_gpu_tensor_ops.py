@@ -626,7 +626,7 @@ def test_layernorm_backward_in_one_pass(mods, dtype, shape, base):
 
 
 @pytest.mark.parametrize("tokens", [255, 256, 257, 512, 513, 768, 769, 1025])
-@pytest.mark.parametrize("dtype,rows,base", [("f32", 2048, 128), ("bf16", 3848, 264), ("f32", 79, 5), ("bf16", 8200, 8200)])
+@pytest.mark.parametrize("dtype,rows,base", [("f32", 2048, 128), ("bf16", 3848, 264), ("f32", 79, 5), ("bf16", 8200, 8200), ("f32", 4100, 4100), ("bf16", 8201, 4000)])
 def test_layernorm_backward_of_one_to_five_tokens_per_workgroup(mods, dtype, rows, base, tokens):
     """All waves of a workgroup on one token, 256 workgroups: the rounds in which a workgroup has one, two or more tokens left, workgroups without
     one in the last round, whole vectors, odd extents and the longest form.  The last token is full of large values and the input gradient takes
@@ -670,6 +670,26 @@ def test_layernorm_backward_sums_over_many_tokens(mods, rows, base, tokens):
         for t, ref, what in zip(out, ((dY * xh).sum(1), dY.sum(1, dtype=np.float64)), ("dgamma", "dbeta")):
             e = float(np.linalg.norm(t.download() - ref) / np.linalg.norm(ref))
             assert e <= 2e-7, (what, e)
+
+
+@pytest.mark.parametrize("dtype,rows,base", [("f32", 1088, 64), ("f32", 2048, 64), ("f32", 2112, 64), ("bf16", 1700, 100), ("bf16", 1920, 64)])
+def test_layernorm_backward_of_many_tokens_on_narrow_tiles(mods, dtype, rows, base):
+    """Two passes on tiles that fill less than half of a wave: 17 and 32 vectors per lane, the forms that keep the token in registers, and 33."""
+    capi, tiled = mods
+    r = rng(61)
+    X, dY, dR = [quant(r.standard_normal((rows, 1100)), dtype) for _ in range(3)]
+    gamma = (1 + 0.1 * r.standard_normal(rows)).astype(np.float32)
+    _, mean, rstd = D.layernorm_fwd(X, gamma, 0 * gamma, 1e-5)
+    dXref, dgref, dbref = D.layernorm_bwd(X, gamma, mean, rstd, dY)
+    with tiled.Context(n_streams=2) as ctx:
+        tX, tdY, tR, tg = [T(tiled, ctx, a, (base, 400), dtype) for a in (X, dY, dR)] + [T(tiled, ctx, gamma, (base,), "f32")]
+        tS, tdX = tiled.TiledTensor.from_numpy(ctx, np.stack([mean, rstd]).astype(np.float32), (2, 400)), tiled.TiledTensor(ctx, dtype, X.shape, (base, 400))
+        out = [tiled.TiledTensor(ctx, "f32", (rows,), (base,)) for _ in range(2)]
+        capi.nnt_layernorm_bwd(ctx.h, tX.h, tS.h, tg.h, tdY.h, tR.h, tdX.h, out[0].h, out[1].h)
+        e = relerr(tdX.download(), dXref + dR)
+        assert e <= TOL[dtype], e
+        check(out[0].download(), dgref, "f32", "ln dgamma")
+        check(out[1].download(), dbref, "f32", "ln dbeta")
 
 
 @pytest.mark.parametrize("rows,base,tokens,passes", [(256, 256, 40, 1), (16384, 4096, 40, 2), (256, 32, 40, 1), (256, 32, 1025, 2), (255, 51, 1025, 1)])
