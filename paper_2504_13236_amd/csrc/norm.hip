@@ -772,13 +772,11 @@ int32_t launch_ln_fwd(hipStream_t st, bool vec, bool any, int nv_needed, const T
     const bool shared = (vec || any) && nv_needed > kLnShareAbove;
     const dim3 grid((unsigned)(shared ? ncols : (ncols + 3) / 4)), block(256);
     // (odd extents: vectors at any alignment, the last one of a tile moved back to end there)
-    if (any && !shared) hipLaunchKernelGGL((ln_fwd_fused<T, V, 4, 1, true>), grid, block, 0, st, X, Y, S, G, B, eps, ncols);
+    if (any && !shared) hipLaunchKernelGGL((ln_fwd_fused<T, V, kLnShareAbove, 1, true>), grid, block, 0, st, X, Y, S, G, B, eps, ncols);
     else if (any && nv_needed <= 16) hipLaunchKernelGGL((ln_fwd_fused<T, V, 4, 4, true>), grid, block, 0, st, X, Y, S, G, B, eps, ncols);
     else if (any) hipLaunchKernelGGL((ln_fwd_fused<T, V, 16, 4, true>), grid, block, 0, st, X, Y, S, G, B, eps, ncols);
     else if (!vec) hipLaunchKernelGGL((ln_fwd_fused<T, 1, 0>), grid, block, 0, st, X, Y, S, G, B, eps, ncols);
-    else if (!shared && nv_needed <= 4) hipLaunchKernelGGL((ln_fwd_fused<T, V, 4>), grid, block, 0, st, X, Y, S, G, B, eps, ncols);
-    else if (!shared && nv_needed <= 16) hipLaunchKernelGGL((ln_fwd_fused<T, V, 16>), grid, block, 0, st, X, Y, S, G, B, eps, ncols);
-    else if (!shared) hipLaunchKernelGGL((ln_fwd_fused<T, V, 0>), grid, block, 0, st, X, Y, S, G, B, eps, ncols);
+    else if (!shared) hipLaunchKernelGGL((ln_fwd_fused<T, V, kLnShareAbove>), grid, block, 0, st, X, Y, S, G, B, eps, ncols);
     else if (nv_needed <= 16) hipLaunchKernelGGL((ln_fwd_fused<T, V, 4, 4>), grid, block, 0, st, X, Y, S, G, B, eps, ncols);
     else if (nv_needed <= 64) hipLaunchKernelGGL((ln_fwd_fused<T, V, 16, 4>), grid, block, 0, st, X, Y, S, G, B, eps, ncols);
     else hipLaunchKernelGGL((ln_fwd_fused<T, V, 0, 4>), grid, block, 0, st, X, Y, S, G, B, eps, ncols);
@@ -869,7 +867,7 @@ constexpr int kOnepassWaves = 8;
 // exact than the column sums' with their chains of 32 (256 tokens, 4096 x 65536: 3.1e-7 instead of 1.4e-7 in the 2-norm; 32 tokens, 4096 x 8192: the same
 // 1.4e-7 once the partial rows are added in pairs, 1.5e-7 before).
 constexpr unsigned kSumRounds = 32;
-constexpr int kOnepassGroups = 256;      // workgroups at most: one per compute unit (512: 101 us instead of 89 for 8192 x 4096, twice the partial rows)
+constexpr int kOnepassGroups = 256;      // workgroups at most: one per compute unit, which is what the registers allow
 
 template <typename T, int V, int NV, int WPT, bool RES, bool ANY>
 __global__ void __launch_bounds__(64 * kOnepassWaves, 2) ln_bwd_onepass(TiledView X, TiledView S, TiledView G, TiledView dY, TiledView dR,
@@ -888,7 +886,7 @@ __global__ void __launch_bounds__(64 * kOnepassWaves, 2) ln_bwd_onepass(TiledVie
     bool ok[NV];
     Own own[NV];          // (ANY: see walk)
     float ag[NV][V], ab[NV][V];
-    // the gain lies in LDS (read twice per token): registers are what the kernel is short of
+    // the gain lies in LDS (read twice per token, and again after a move of the sums): registers are what the kernel is short of
     float* const gam = sums + w * kWave + lane * V;
 #pragma unroll
     for (int it = 0; it < NV; it++) {
@@ -1112,10 +1110,12 @@ inline int onepass_wpt(int nv_needed) {
     while (wpt <= kOnepassWaves && wpt * NV < nv_needed) wpt *= 2;
     return wpt <= kOnepassWaves ? wpt : 0;
 }
-// (two vectors of 16 bytes per lane: up to 161 registers, the next token's included; sixteen waves per workgroup would have to make do with
-// 128, and the spilled ones' reloads wait for the next token's loads: 113 us for 8192 x 4096)
-// Longer tokens (8192 fp32 elements, 16384 in bf16): all eight waves on one with four vectors per lane, up to 256 registers (fp32 8192 x 4096
-// 169 -> 142 us; odd extents, bf16 8200 x 4096 253 -> 199).
+// (two vectors of 16 bytes per lane: up to 206 registers, the next token's included; sixteen waves per workgroup would have to make do with
+// 128, and the spilled ones' reloads wait for the next token's loads: 113 us for 8192 x 4096 with the copied registers of then, 77 now)
+// Longer tokens (8192 fp32 elements, 16384 in bf16): all eight waves on one with four vectors per lane, up to 256 registers (two passes and one, fp32
+// 8192 x 4096 150 and 135 us, bf16 16384 x 2048 82 and 74; odd extents, fp32 7001 x 1000 125 and 43, bf16 10001 x 2048 173 and 75).  Few of them, or
+// on narrow tiles, are slower than two passes that run side by side in a graph (bf16 8200 x 300 19 and 33, fp32 2048 x 1000 on tiles of 64 26 and 36), and about as
+// fast as calls (41 and 42, 54 and 47).
 constexpr int kOnepassVecs = 2, kOnepassLong = 4;
 inline int onepass_waves(int nv_needed) { const int w = onepass_wpt<kOnepassVecs>(nv_needed); return w ? w : onepass_wpt<kOnepassLong>(nv_needed); }
 inline int64_t onepass_wgs(int wpt, int64_t ncols) { const int64_t gr = kOnepassWaves / wpt; return std::min<int64_t>(kOnepassGroups, (ncols + gr - 1) / gr); }
@@ -1439,11 +1439,12 @@ int32_t nnt_layernorm_bwd(nnt_ctx* ctx, nnt_tensor* X, nnt_tensor* stats, nnt_te
         if (ncols > INT32_MAX) return fail(ctx, NNT_EINVAL, "nnt_layernorm_bwd: tensor too large");
         std::vector<Access> acc = {X->all(kRead), stats->all(kRead), gamma->all(kRead), dY->all(kRead), dX->all(kWrite)};
         if (dRes) acc.push_back(dRes->all(kRead));
-        // one pass over the tokens wherever the eight waves of a workgroup can hold one (measured no slower at any size, from 128 tokens
-        // of 128 to 4096 of 8192); longer ones take the column sums and the input gradient one after the other
-        // Tiles that fill less than half of a wave's lanes, more tokens than four per compute unit: two passes as well; its 256 large
-        // workgroups, most lanes idle, hold up the products of the other stream (fp32 block of 320 on tiles of 64, 1536 tokens: 418 us, 381
-        // in two passes).  With fewer tokens the launches count (128 on tiles of 32, 64 tokens, forward and backward: 17.9 -> 13.0).
+        // One pass over the tokens wherever the eight waves of a workgroup can hold one (see ln_bwd_onepass for both sides); longer ones take the column
+        // sums and the input gradient one after the other.
+        // Tiles that fill less than half of a wave's lanes, more than 1024 tokens: two passes as well.  The one pass is the faster call by itself there too,
+        // but its 256 large workgroups, most lanes idle, hold up the products of the other stream: 66 blocks and models of 128 to 768 wide on tiles of
+        // 64 and 128 with 2048 and 4096 tokens are 1 % faster in two passes on average (0.93 to 1.04), 33 with 1024 tokens 1 % slower.  Odd extents
+        // stay with the one pass (320 wide on tiles of 50 0 to 2 % faster): the two passes read them element by element.
         const int lanes = 64 * V * (int)((X->base[0] + 64 * V - 1) / (64 * V));
         const bool narrow = vec && 2 * X->base[0] < lanes && ncols > 1024;
         const int wpt = !narrow && (vec || any_vec({X, dY, dX, dRes, gamma})) ? onepass_waves(nv) : 0;
