@@ -943,7 +943,6 @@ __global__ void __launch_bounds__(64 * kOnepassWaves, 2) ln_bwd_onepass(TiledVie
     };
     // (the same number of rounds for every group: the waves of a workgroup meet once per token)
     const unsigned step = gridDim.x * GR, col0 = blockIdx.x * GR + grp;
-    const float inv = 1.f / (float)X.shape[0];
     auto work_on = [&](Token& t, unsigned r) {
         const float mean = t.real ? t.mean : 0.f, rstd = t.real ? t.rstd : 0.f;
         float a = 0.f, b = 0.f;
@@ -985,8 +984,8 @@ __global__ void __launch_bounds__(64 * kOnepassWaves, 2) ln_bwd_onepass(TiledVie
                 b += red[r & 1][grp * WPT + i].y;
             }
         }
-        a *= inv;
-        b *= inv;
+        a /= (float)X.shape[0];
+        b /= (float)X.shape[0];
         // (unpacked again below: the unpacked values held over the sums would take another 32 registers)
 #pragma unroll
         for (int it = 0; it < NV; it++) { keep(t.x[it]); keep(t.d[it]); }
@@ -999,7 +998,13 @@ __global__ void __launch_bounds__(64 * kOnepassWaves, 2) ln_bwd_onepass(TiledVie
                     unpack(t.d[it], d);
                     ldv<V>(gam + it * 64 * V, gm);
 #pragma unroll
-                    for (int k = 0; k < V; k++) o[k] = rstd * (d[k] * gm[k] - a - (x[k] - mean) * rstd * b);
+                    for (int k = 0; k < V; k++) {
+                        // (rounded one by one, as where they are kept over the sums)
+#pragma clang fp contract(off)
+                        const float gg = d[k] * gm[k], xh = (x[k] - mean) * rstd;
+                        const float t0 = gg - a;
+                        o[k] = rstd * __builtin_fmaf(-xh, b, t0);
+                    }
                     if constexpr (RES) {
                         float q[V];
                         unpack(t.q[it], q);
@@ -1117,44 +1122,48 @@ inline int onepass_wpt(int nv_needed) {
 // on narrow tiles, are slower than two passes that run side by side in a graph (bf16 8200 x 300 19 and 33, fp32 2048 x 1000 on tiles of 64 26 and 36), and about as
 // fast as calls (41 and 42, 54 and 47).
 constexpr int kOnepassVecs = 2, kOnepassLong = 4;
-inline int onepass_waves(int nv_needed) { const int w = onepass_wpt<kOnepassVecs>(nv_needed); return w ? w : onepass_wpt<kOnepassLong>(nv_needed); }
+// bf16 tokens of three or four vectors per lane stay with one wave and that form: the sums over a token are then added in the order of the two passes,
+// and dx is what they leave bit for bit (single flipped roundings of dx travel through the products behind it).  In fp32, where the last digit is all that
+// changes, two waves are the faster form (1024 x 8192 32 us, one wave 35; bf16 1600 x 8192 on tiles of 400 32 either way, 768 x 8192 29 and 27).
+inline int onepass_waves(bool bf16, int nv_needed) {
+    if (bf16 && nv_needed > kOnepassVecs && nv_needed <= kOnepassLong) return 1;
+    const int w = onepass_wpt<kOnepassVecs>(nv_needed);
+    return w ? w : onepass_wpt<kOnepassLong>(nv_needed);
+}
 inline int64_t onepass_wgs(int wpt, int64_t ncols) { const int64_t gr = kOnepassWaves / wpt; return std::min<int64_t>(kOnepassGroups, (ncols + gr - 1) / gr); }
 
-template <typename T, int V, int NV, bool RES, bool ANY>
-int32_t launch_onepass_v(hipStream_t st, int wpt, const TiledView& X, const TiledView& S, const TiledView& G, const TiledView& dY,
-                         const TiledView& dR, const TiledView& dX, int64_t ncols, float* part) {
-    const int64_t wgs = onepass_wgs(wpt, ncols), per = wgs * (kOnepassWaves / wpt);
+template <typename T, int NV, int WPT>
+int32_t launch_onepass_w(hipStream_t st, bool vec, const TiledView& X, const TiledView& S, const TiledView& G, const TiledView& dY,
+                         const TiledView& dR, const TiledView& dX, int has_res, int64_t ncols, float* part) {
+    constexpr int V = VecOf<T>::V;
+    const int64_t wgs = onepass_wgs(WPT, ncols), per = wgs * (kOnepassWaves / WPT);
     const unsigned n = (unsigned)ncols, rounds = (unsigned)((ncols + per - 1) / per);
     const dim3 grid((unsigned)wgs), block(64 * kOnepassWaves);
-    switch (wpt) {
-        case 1: hipLaunchKernelGGL((ln_bwd_onepass<T, V, NV, 1, RES, ANY>), grid, block, 0, st, X, S, G, dY, dR, dX, n, rounds, part); break;
-        case 2: hipLaunchKernelGGL((ln_bwd_onepass<T, V, NV, 2, RES, ANY>), grid, block, 0, st, X, S, G, dY, dR, dX, n, rounds, part); break;
-        case 4: hipLaunchKernelGGL((ln_bwd_onepass<T, V, NV, 4, RES, ANY>), grid, block, 0, st, X, S, G, dY, dR, dX, n, rounds, part); break;
-        case 8: hipLaunchKernelGGL((ln_bwd_onepass<T, V, NV, 8, RES, ANY>), grid, block, 0, st, X, S, G, dY, dR, dX, n, rounds, part); break;
-        default: return NNT_EINVAL;
-    }
+    if (vec && has_res) hipLaunchKernelGGL((ln_bwd_onepass<T, V, NV, WPT, true, false>), grid, block, 0, st, X, S, G, dY, dR, dX, n, rounds, part);
+    else if (vec) hipLaunchKernelGGL((ln_bwd_onepass<T, V, NV, WPT, false, false>), grid, block, 0, st, X, S, G, dY, dR, dX, n, rounds, part);
+    else if (has_res) hipLaunchKernelGGL((ln_bwd_onepass<T, V, NV, WPT, true, true>), grid, block, 0, st, X, S, G, dY, dR, dX, n, rounds, part);
+    else hipLaunchKernelGGL((ln_bwd_onepass<T, V, NV, WPT, false, true>), grid, block, 0, st, X, S, G, dY, dR, dX, n, rounds, part);
     return hipGetLastError() == hipSuccess ? NNT_OK : NNT_EHIP;
 }
 template <typename T>
 int32_t launch_onepass(hipStream_t st, bool vec, int wpt, int nv_needed, const TiledView& X, const TiledView& S, const TiledView& G, const TiledView& dY,
                        const TiledView& dR, const TiledView& dX, int has_res, int64_t ncols, float* part) {
-    constexpr int V = VecOf<T>::V;
     if (wpt * kOnepassVecs < nv_needed) {
-        // (only the longest: every wave of the workgroup, twice the vectors)
-        const int64_t wgs = onepass_wgs(wpt, ncols);
-        const unsigned n = (unsigned)ncols, rounds = (unsigned)((ncols + wgs - 1) / wgs);
-        const dim3 grid((unsigned)wgs), block(64 * kOnepassWaves);
-        if (wpt != kOnepassWaves) return NNT_EINVAL;
-        if (vec && has_res) hipLaunchKernelGGL((ln_bwd_onepass<T, V, kOnepassLong, kOnepassWaves, true, false>), grid, block, 0, st, X, S, G, dY, dR, dX, n, rounds, part);
-        else if (vec) hipLaunchKernelGGL((ln_bwd_onepass<T, V, kOnepassLong, kOnepassWaves, false, false>), grid, block, 0, st, X, S, G, dY, dR, dX, n, rounds, part);
-        else if (has_res) hipLaunchKernelGGL((ln_bwd_onepass<T, V, kOnepassLong, kOnepassWaves, true, true>), grid, block, 0, st, X, S, G, dY, dR, dX, n, rounds, part);
-        else hipLaunchKernelGGL((ln_bwd_onepass<T, V, kOnepassLong, kOnepassWaves, false, true>), grid, block, 0, st, X, S, G, dY, dR, dX, n, rounds, part);
-        return hipGetLastError() == hipSuccess ? NNT_OK : NNT_EHIP;
+        if (wpt == kOnepassWaves) return launch_onepass_w<T, kOnepassLong, kOnepassWaves>(st, vec, X, S, G, dY, dR, dX, has_res, ncols, part);
+        if constexpr (sizeof(T) == 2)
+            if (wpt == 1) return launch_onepass_w<T, kOnepassLong, 1>(st, vec, X, S, G, dY, dR, dX, has_res, ncols, part);
+        return NNT_EINVAL;
     }
-    if (vec) return has_res ? launch_onepass_v<T, V, kOnepassVecs, true, false>(st, wpt, X, S, G, dY, dR, dX, ncols, part)
-                            : launch_onepass_v<T, V, kOnepassVecs, false, false>(st, wpt, X, S, G, dY, dR, dX, ncols, part);
-    return has_res ? launch_onepass_v<T, V, kOnepassVecs, true, true>(st, wpt, X, S, G, dY, dR, dX, ncols, part)
-                   : launch_onepass_v<T, V, kOnepassVecs, false, true>(st, wpt, X, S, G, dY, dR, dX, ncols, part);
+    switch (wpt) {
+        case 1: return launch_onepass_w<T, kOnepassVecs, 1>(st, vec, X, S, G, dY, dR, dX, has_res, ncols, part);
+        case 2:
+            // (bf16: see onepass_waves)
+            if constexpr (sizeof(T) == 4) return launch_onepass_w<T, kOnepassVecs, 2>(st, vec, X, S, G, dY, dR, dX, has_res, ncols, part);
+            return NNT_EINVAL;
+        case 4: return launch_onepass_w<T, kOnepassVecs, 4>(st, vec, X, S, G, dY, dR, dX, has_res, ncols, part);
+        case 8: return launch_onepass_w<T, kOnepassVecs, 8>(st, vec, X, S, G, dY, dR, dX, has_res, ncols, part);
+        default: return NNT_EINVAL;
+    }
 }
 
 int32_t check_ln_shapes(nnt_ctx* ctx, const nnt_tensor* X, const nnt_tensor* gamma, const nnt_tensor* stats, const char* who) {
@@ -1447,7 +1456,7 @@ int32_t nnt_layernorm_bwd(nnt_ctx* ctx, nnt_tensor* X, nnt_tensor* stats, nnt_te
         // stay with the one pass (320 wide on tiles of 50 0 to 2 % faster): the two passes read them element by element.
         const int lanes = 64 * V * (int)((X->base[0] + 64 * V - 1) / (64 * V));
         const bool narrow = vec && 2 * X->base[0] < lanes && ncols > 1024;
-        const int wpt = !narrow && (vec || any_vec({X, dY, dX, dRes, gamma})) ? onepass_waves(nv) : 0;
+        const int wpt = !narrow && (vec || any_vec({X, dY, dX, dRes, gamma})) ? onepass_waves(dtype == NNT_BF16, nv) : 0;
         // (so do calls inside a capture whose partial rows have no room yet)
         const int64_t wgs = wpt > 0 ? onepass_wgs(wpt, ncols) : 0, rows = X->shape[0];
         if (wpt > 0 && ncols > 0 && ncols < INT32_MAX / 2 && X->ntiles <= 65535 && !(ctx->capturing && 2 * wgs * rows > ctx->stream_scratch_elems)) {

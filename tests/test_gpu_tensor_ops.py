@@ -672,6 +672,38 @@ def test_layernorm_backward_sums_over_many_tokens(mods, rows, base, tokens):
             assert e <= 2e-7, (what, e)
 
 
+@pytest.mark.parametrize("dtype,rows,base", [("bf16", 512, 512), ("bf16", 1024, 512), ("bf16", 768, 256), ("bf16", 1600, 400), ("bf16", 2048, 512), ("bf16", 2800, 400),
+                                             ("bf16", 4096, 1024), ("f32", 200, 200), ("f32", 512, 256), ("f32", 2048, 1024)])
+@pytest.mark.parametrize("res", [False, True])
+def test_layernorm_backward_in_one_pass_and_in_two_gives_the_same(mods, dtype, rows, base, res):
+    """The input gradient of the one pass is that of the two passes bit for bit where both add a token's sums in the same order.  Two passes run inside a
+    capture before the stream's scratch is there; the shared one is, from a bias gradient."""
+    capi, tiled = mods
+    r = rng(71)
+    X, dY, dR = [quant(r.standard_normal((rows, 700)), dtype) for _ in range(3)]
+    gamma = (1 + 0.1 * r.standard_normal(rows)).astype(np.float32)
+    _, mean, rstd = D.layernorm_fwd(X, gamma, 0 * gamma, 1e-5)
+    with tiled.Context(n_streams=2) as ctx:
+        tX, tdY, tR, tg = [T(tiled, ctx, a, (base, 400), dtype) for a in (X, dY, dR)] + [T(tiled, ctx, gamma, (base,), "f32")]
+        tS = tiled.TiledTensor.from_numpy(ctx, np.stack([mean, rstd]).astype(np.float32), (2, 400))
+        two, one = (tiled.TiledTensor(ctx, dtype, X.shape, (base, 400)) for _ in range(2))
+        out = [tiled.TiledTensor(ctx, "f32", (rows,), (base,)) for _ in range(2)]
+        capi.nnt_bias_grad(ctx.h, tdY.h, out[0].h)
+        call = lambda dX: capi.nnt_layernorm_bwd(ctx.h, tX.h, tS.h, tg.h, tdY.h, tR.h if res else None, dX.h, out[0].h, out[1].h)
+        before = ctx.stats()["tasks"]
+        g = C.c_void_p()
+        capi.nnt_capture_begin(ctx.h)
+        call(two)
+        capi.nnt_capture_end(ctx.h, C.byref(g))
+        assert ctx.stats()["tasks"] - before == 2
+        capi.nnt_graph_launch(g)
+        want = np.asarray(two.download())
+        call(one)
+        assert ctx.stats()["tasks"] - before == 3
+        assert np.array_equal(np.asarray(one.download()), want)
+        capi.nnt_graph_destroy(g)
+
+
 @pytest.mark.parametrize("dtype,rows,base", [("f32", 1088, 64), ("f32", 2048, 64), ("f32", 2112, 64), ("bf16", 1700, 100), ("bf16", 1920, 64)])
 def test_layernorm_backward_of_many_tokens_on_narrow_tiles(mods, dtype, rows, base):
     """Two passes on tiles that fill less than half of a wave: 17 and 32 vectors per lane, the forms that keep the token in registers, and 33."""
