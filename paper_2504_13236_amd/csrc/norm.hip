@@ -906,18 +906,14 @@ __global__ void __launch_bounds__(64 * kOnepassWaves, 2) ln_bwd_onepass(TiledVie
     }
     auto load_gain = [&]() {
         if (grp != 0) return;
+        float gm[NV][V];
 #pragma unroll
-        for (int it = 0; it < NV; it++) {
-            float gm[V];
+        for (int it = 0; it < NV; it++) ldn<ANY, V>(table_entry<const float>(G.tiles, l[it]) + e[it], ext[it], gm[it]);
 #pragma unroll
-            for (int k = 0; k < V; k++) gm[k] = 0.f;
-            if (ok[it]) ldn<ANY, V>(table_entry<const float>(G.tiles, l[it]) + e[it], ext[it], gm);
+        for (int it = 0; it < NV; it++)
 #pragma unroll
-            for (int k = 0; k < V; k++) gam[it * 64 * V + k] = gm[k];
-        }
+            for (int k = 0; k < V; k++) gam[it * 64 * V + k] = ok[it] ? gm[it][k] : 0.f;
     };
-    load_gain();
-    __syncthreads();
     struct Token {
         R x[NV], d[NV], q[RES ? NV : 1];
         float mean, rstd;
@@ -1066,6 +1062,8 @@ __global__ void __launch_bounds__(64 * kOnepassWaves, 2) ln_bwd_onepass(TiledVie
     };
     Token t0, t1;
     fetch(col0, t0);
+    load_gain();
+    __syncthreads();
     unsigned r = 0, moved = 0;
     if constexpr (kTwoSets) {
         while (rounds - r > 2) {
@@ -1122,11 +1120,12 @@ inline int onepass_wpt(int nv_needed) {
 // on narrow tiles, are slower than two passes that run side by side in a graph (bf16 8200 x 300 19 and 33, fp32 2048 x 1000 on tiles of 64 26 and 36), and about as
 // fast as calls (41 and 42, 54 and 47).
 constexpr int kOnepassVecs = 2, kOnepassLong = 4;
-// bf16 tokens of three or four vectors per lane stay with one wave and that form: the sums over a token are then added in the order of the two passes,
-// and dx is what they leave bit for bit (single flipped roundings of dx travel through the products behind it).  In fp32, where the last digit is all that
-// changes, two waves are the faster form (1024 x 8192 32 us, one wave 35; bf16 1600 x 8192 on tiles of 400 32 either way, 768 x 8192 29 and 27).
-inline int onepass_waves(bool bf16, int nv_needed) {
-    if (bf16 && nv_needed > kOnepassVecs && nv_needed <= kOnepassLong) return 1;
+// bf16 tokens of three or four whole vectors per lane stay with one wave and that form: the sums over a token are then added in the order of the two
+// passes, and dx is what they leave bit for bit (single flipped roundings of dx travel through the products behind it).  In fp32, where the last digit is all
+// that changes, and on odd extents, which the two passes take element by element, two waves are the faster form (fp32 1024 x 8192 32 us, one wave 35; bf16 1120 x 128
+// on tiles of 300 13 and 17; whole vectors, 1600 x 8192 on tiles of 400 32 either way, 768 x 8192 29 and 27, 2048 x 8192 on tiles of 512 38 and 42).
+inline int onepass_waves(bool bf16_vec, int nv_needed) {
+    if (bf16_vec && nv_needed > kOnepassVecs && nv_needed <= kOnepassLong) return 1;
     const int w = onepass_wpt<kOnepassVecs>(nv_needed);
     return w ? w : onepass_wpt<kOnepassLong>(nv_needed);
 }
@@ -1136,13 +1135,20 @@ template <typename T, int NV, int WPT>
 int32_t launch_onepass_w(hipStream_t st, bool vec, const TiledView& X, const TiledView& S, const TiledView& G, const TiledView& dY,
                          const TiledView& dR, const TiledView& dX, int has_res, int64_t ncols, float* part) {
     constexpr int V = VecOf<T>::V;
+    // (whole vectors only, or odd extents only: see onepass_waves)
+    constexpr bool kVec = !(sizeof(T) == 2 && NV == kOnepassVecs && WPT == 2), kAny = !(NV == kOnepassLong && WPT == 1);
     const int64_t wgs = onepass_wgs(WPT, ncols), per = wgs * (kOnepassWaves / WPT);
     const unsigned n = (unsigned)ncols, rounds = (unsigned)((ncols + per - 1) / per);
     const dim3 grid((unsigned)wgs), block(64 * kOnepassWaves);
-    if (vec && has_res) hipLaunchKernelGGL((ln_bwd_onepass<T, V, NV, WPT, true, false>), grid, block, 0, st, X, S, G, dY, dR, dX, n, rounds, part);
-    else if (vec) hipLaunchKernelGGL((ln_bwd_onepass<T, V, NV, WPT, false, false>), grid, block, 0, st, X, S, G, dY, dR, dX, n, rounds, part);
-    else if (has_res) hipLaunchKernelGGL((ln_bwd_onepass<T, V, NV, WPT, true, true>), grid, block, 0, st, X, S, G, dY, dR, dX, n, rounds, part);
-    else hipLaunchKernelGGL((ln_bwd_onepass<T, V, NV, WPT, false, true>), grid, block, 0, st, X, S, G, dY, dR, dX, n, rounds, part);
+    if (vec ? !kVec : !kAny) return NNT_EINVAL;
+    if constexpr (kVec) {
+        if (vec && has_res) hipLaunchKernelGGL((ln_bwd_onepass<T, V, NV, WPT, true, false>), grid, block, 0, st, X, S, G, dY, dR, dX, n, rounds, part);
+        else if (vec) hipLaunchKernelGGL((ln_bwd_onepass<T, V, NV, WPT, false, false>), grid, block, 0, st, X, S, G, dY, dR, dX, n, rounds, part);
+    }
+    if constexpr (kAny) {
+        if (!vec && has_res) hipLaunchKernelGGL((ln_bwd_onepass<T, V, NV, WPT, true, true>), grid, block, 0, st, X, S, G, dY, dR, dX, n, rounds, part);
+        else if (!vec) hipLaunchKernelGGL((ln_bwd_onepass<T, V, NV, WPT, false, true>), grid, block, 0, st, X, S, G, dY, dR, dX, n, rounds, part);
+    }
     return hipGetLastError() == hipSuccess ? NNT_OK : NNT_EHIP;
 }
 template <typename T>
@@ -1156,10 +1162,7 @@ int32_t launch_onepass(hipStream_t st, bool vec, int wpt, int nv_needed, const T
     }
     switch (wpt) {
         case 1: return launch_onepass_w<T, kOnepassVecs, 1>(st, vec, X, S, G, dY, dR, dX, has_res, ncols, part);
-        case 2:
-            // (bf16: see onepass_waves)
-            if constexpr (sizeof(T) == 4) return launch_onepass_w<T, kOnepassVecs, 2>(st, vec, X, S, G, dY, dR, dX, has_res, ncols, part);
-            return NNT_EINVAL;
+        case 2: return launch_onepass_w<T, kOnepassVecs, 2>(st, vec, X, S, G, dY, dR, dX, has_res, ncols, part);
         case 4: return launch_onepass_w<T, kOnepassVecs, 4>(st, vec, X, S, G, dY, dR, dX, has_res, ncols, part);
         case 8: return launch_onepass_w<T, kOnepassVecs, 8>(st, vec, X, S, G, dY, dR, dX, has_res, ncols, part);
         default: return NNT_EINVAL;
@@ -1456,7 +1459,7 @@ int32_t nnt_layernorm_bwd(nnt_ctx* ctx, nnt_tensor* X, nnt_tensor* stats, nnt_te
         // stay with the one pass (320 wide on tiles of 50 0 to 2 % faster): the two passes read them element by element.
         const int lanes = 64 * V * (int)((X->base[0] + 64 * V - 1) / (64 * V));
         const bool narrow = vec && 2 * X->base[0] < lanes && ncols > 1024;
-        const int wpt = !narrow && (vec || any_vec({X, dY, dX, dRes, gamma})) ? onepass_waves(dtype == NNT_BF16, nv) : 0;
+        const int wpt = !narrow && (vec || any_vec({X, dY, dX, dRes, gamma})) ? onepass_waves(vec && dtype == NNT_BF16, nv) : 0;
         // (so do calls inside a capture whose partial rows have no room yet)
         const int64_t wgs = wpt > 0 ? onepass_wgs(wpt, ncols) : 0, rows = X->shape[0];
         if (wpt > 0 && ncols > 0 && ncols < INT32_MAX / 2 && X->ntiles <= 65535 && !(ctx->capturing && 2 * wgs * rows > ctx->stream_scratch_elems)) {
