@@ -463,6 +463,70 @@ def test_products_of_odd_sizes(mods, m, n, k, tm, tn, tk, form, din):
         check(tD.download(), want, dt, form + ", tile by tile")
 
 
+@pytest.mark.parametrize("form", ["NN", "TN", "NT"])
+@pytest.mark.parametrize("din,m,n,k,tile,kernel,cut", [
+    ("bf16", 1537, 4611, 515, 300, "gemm_bf16_span_wide_kernel<float", False), ("bf16", 1501, 1503, 3001, 300, "gemm_bf16_span_tall_kernel<float", True),
+    ("bf16", 4097, 4099, 1033, 1024, "gemm_bf16_span", None),
+    ("f32", 4001, 4099, 2049, 1024, "gemm_f32_span_kernel<%s, 2, 2>", True), ("f32", 1051, 1033, 5001, 400, "gemm_f32_span_kernel<%s, 1, 2>", True),
+    ("f32", 1501, 1503, 3001, 300, "gemm_f32_span_kernel<%s, 1, 1>", True),
+])
+def test_forms_of_products_that_lay_their_operands_out_afresh(mods, din, m, n, k, tile, kernel, cut, form):
+    """The kernel that runs, by its record, in the three operand orders; with and without k-slices."""
+    capi, tiled = mods
+    r = rng(m + n + k)
+    opA, opB = ("NT".index(c) for c in form)
+    draw = lambda shape: r.integers(-32, 33, shape).astype(np.float32) / 16
+    with tiled.Context(n_streams=1) as ctx:
+        A, B = draw((k, m) if opA else (m, k)), draw((n, k) if opB else (k, n))
+        tA, tB, tC = T(tiled, ctx, A, (tile, tile), din), T(tiled, ctx, B, (tile, tile), din), tiled.TiledTensor(ctx, "f32", (m, n), (tile, tile))
+        ctx.profile(True)
+        capi.nnt_gemm(ctx.h, 1.0, opA, tA.h, opB, tB.h, 0.0, tC.h, 1, 0, None)
+        labels = list(ctx.profile_read())
+        ctx.profile(False)
+        order = {"NN": "false, true", "TN": "true, true", "NT": "false, false"}[form]
+        assert any((kernel % order if "%" in kernel else kernel) in x and order in x for x in labels), labels
+        assert cut is None or ("splitk_reduce" in labels) == cut, labels
+        check(tC.download(), (A.T if opA else A).astype(np.float64) @ (B.T if opB else B).astype(np.float64), "f32", form)
+
+
+@pytest.mark.parametrize("din", ["bf16", "f32"])
+@pytest.mark.parametrize("case", ["forward", "weights", "narrow"])
+def test_operands_laid_out_afresh_of_several_axes_and_of_narrow_tiles(mods, din, case):
+    """Lines that belong to two axes, ragged along both, free (a layer's forward pass, with bias and residual) and contracted (its weight
+    gradient), and tiles narrower than a vector along the contiguous axis."""
+    capi, tiled = mods
+    r = rng(83)
+    draw = lambda shape: r.integers(-32, 33, shape).astype(np.float32) / 16
+    m, n, s, b = 2001, 1333, 517, 4
+    base = lambda x: (300, 200, 3) if len(x) == 3 else (300, 300)
+    with tiled.Context(n_streams=1) as ctx:
+        if case == "forward":
+            W, X, R, bias = draw((m, n)), draw((n, s, b)), draw((m, s, b)), draw((m,))
+            ts = [T(tiled, ctx, W, base(W.shape), din), T(tiled, ctx, X, base(X.shape), din), T(tiled, ctx, bias, (300,), "f32"), T(tiled, ctx, R, base(R.shape), din)]
+            tY = tiled.TiledTensor(ctx, din, (m, s, b), base((m, s, b)))
+            call = lambda: capi.nnt_gemm_res(ctx.h, 1.0, 0, ts[0].h, 0, ts[1].h, 1.0, tY.h, 1, 0, ts[2].h, ts[3].h)
+            want = np.einsum("mn,nsb->msb", W.astype(np.float64), X.astype(np.float64), optimize=True) + bias[:, None, None] + R
+        elif case == "weights":
+            dY, X = draw((m, s, b)), draw((n, s, b))
+            ts = [T(tiled, ctx, dY, base(dY.shape), din), T(tiled, ctx, X, base(X.shape), din)]
+            tY = tiled.TiledTensor(ctx, "f32", (m, n), (300, 300))
+            call = lambda: capi.nnt_gemm(ctx.h, 1.0, 0, ts[0].h, 1, ts[1].h, 0.0, tY.h, 2, 0, None)
+            want = dY.reshape(m, -1).astype(np.float64) @ X.reshape(n, -1).T.astype(np.float64)
+        else:
+            m, n, k = 3201, 2803, 1501
+            A, B = draw((k, m)), draw((k, n))
+            ts = [T(tiled, ctx, A, (3, 700), din), T(tiled, ctx, B, (3, 700), din)]
+            tY = tiled.TiledTensor(ctx, "f32", (m, n), (700, 700))
+            call = lambda: capi.nnt_gemm(ctx.h, 1.0, 1, ts[0].h, 0, ts[1].h, 0.0, tY.h, 1, 0, None)
+            want = A.T.astype(np.float64) @ B.astype(np.float64)
+        ctx.profile(True)
+        call()
+        labels = list(ctx.profile_read())
+        ctx.profile(False)
+        assert any("_span_" in x for x in labels), labels
+        check(tY.download(), want, din if case == "forward" else "f32", case)
+
+
 @pytest.mark.parametrize("m,n,k,tile,din,bound", [
     (3778, 896, 4736, 300, "f32", 2.4e-7),       # a move every 128 k: 2.1e-7; every 256 k 2.6e-7 to 2.9e-7
     (2688, 3072, 2145, 400, "f32", 2.4e-7),
@@ -557,7 +621,7 @@ def test_gemm_rejects_mismatched_tilings(mods):
                                         # long tokens, shared by the wavefronts of a workgroup: register-cached and looping forms
                                         ((8192, 5, 2), (1024, 5, 1)), ((2560, 7, 1), (512, 7, 1)), ((20000, 3, 1), (5000, 3, 1)),
                                         # odd extents: a last tile of one element, tiles shorter than a vector, tokens shared by wavefronts, the longest
-                                        # (8192 vectors of 4, 4096 of 8) and the next
+                                        # (4096 vectors) and the next
                                         ((2001, 9, 2), (500, 4, 2)), ((13, 7, 2), (5, 7, 1)), ((3001, 33, 1), (1024, 33, 1)), ((9001, 5, 1), (9001, 5, 1)),
                                         ((16381, 3, 1), (16381, 3, 1)), ((33001, 2, 1), (33001, 2, 1))])
 def test_layernorm_tensor(mods, gran, dtype, shape, base):
