@@ -24,13 +24,15 @@
  *    least 4 MiB each once used; a smaller one that it replaces stays as long as a
  *    graph lives that was captured with it); (c)
  *    for products whose contraction is cut into k-slices, an fp32 workspace of
- *    slices x macro-tile partial sums per cached plan, and for products whose
- *    operands have odd leading dimensions or tiles a padded copy of both operands
- *    per cached plan (at most 2 GiB each; a plan that would need more is built
- *    without them).  nnt_ctx_stats
- *    reports the bytes held for (a) and for (b) + (c).  Tables and workspaces of a
- *    plan are released when one of its tensors or the context is destroyed, the
- *    rest in the matching destroy call.
+ *    slices x macro-tile partial sums per cached plan (at most 2 GiB each; a plan
+ *    that would need more is built without them); and (d) for products whose
+ *    operands have odd leading dimensions or tiles the space for a padded copy of
+ *    both operands, one part per stream as large as the largest of these products
+ *    needs, at most 2 GiB each (a product that would need more, or for which there
+ *    is no memory, reads its operands as they are), for as long as one of them or a
+ *    graph captured with it lives.  nnt_ctx_stats reports the bytes held for (a) and
+ *    for (b) to (d).  Tables and workspaces of a plan are released when one of its
+ *    tensors or the context is destroyed, the rest in the matching destroy call.
  *  - Element types: NNT_F32 (IEEE binary32) and NNT_BF16 (bfloat16, converted
  *    with round-to-nearest-even).  All arithmetic, reductions and accumulation
  *    are in fp32 whatever the storage type.
@@ -119,8 +121,10 @@ typedef struct nnt_exec_stats {
     int64_t event_waits;    /* cross-stream dependencies turned into event waits    */
     int64_t plans;          /* product plans (descriptor tables) built and cached   */
     int64_t device_table_bytes;      /* device memory held for descriptor tables             */
-    int64_t device_workspace_bytes;  /* device memory held for reduction scratch and the
-                                        k-slice workspaces of the cached product plans       */
+    int64_t device_workspace_bytes;  /* device memory held for reduction scratch, the
+                                        k-slice workspaces of the cached product plans and
+                                        the copies of operands, replaced ones that graphs
+                                        hold included                                        */
 } nnt_exec_stats;
 NNT_API int32_t nnt_ctx_stats(nnt_ctx* ctx, nnt_exec_stats* out);
 

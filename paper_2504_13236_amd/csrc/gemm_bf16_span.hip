@@ -4,7 +4,7 @@
 // padded, and the direct-load kernels run on that, with macro-tiles on one grid over all of C, so that neither the tiles'
 // edges nor their alignment cost anything in the loop.  Their result path sorts the results into C's tiles.
 // The copy moves 4 bytes per element of A and B; the three products of a layer of 1333 x 2001 over 2068 tokens on tiles of 500, copies
-// included: 81 -> 53, 76 -> 44 and 51 -> 42 us, the layer 168 -> 92.
+// included: 79 -> 54, 81 -> 48 and 55 -> 43 us, the layer 172 -> 93.
 #include "gemm_bf16_dl_body.hpp"
 
 namespace nnt {

@@ -808,8 +808,8 @@ int32_t launch_ln_bwd(hipStream_t st, bool vec, int nv_needed, const TiledView& 
 // 256 rows, which rowsum_stage2 adds in a fixed order).  Against the two passes, which in a captured graph run side by side on two streams,
 // adjoints back to back: fp32 1024 x 8192 37 -> 35 us, 4096 x 8192 140 -> 122, 8192 x 8192 326 -> 235, odd extents (vectors at any alignment instead of single
 // elements) 777 x 2664 27 -> 24, 1370 x 1672 35 -> 22; slower where less than half of the lanes have a vector or the longest tokens are few (bf16 768 x 8192
-// on tiles of 256 25 -> 28, 8192 x 4096 72 -> 77, fp32 5840 x 387 22 -> 28).  Called one by one, forward and backward, all of these are faster:
-// 49 -> 36, 126 -> 104, 49 -> 36; 65 sizes between 128 x 128 and 8192 x 8192: 1.24 times in graphs, 1.55 by calls.
+// on tiles of 256 25 -> 27, 8192 x 4096 72 -> 77, fp32 5840 x 387 22 -> 28).  Called one by one, forward and backward, all of these are faster:
+// 49 -> 36, 126 -> 104, 49 -> 36; 75 sizes between 128 x 128 and 8192 x 8192: 1.26 times in graphs, 1.56 by calls.
 template <typename T, int V> struct RawVec;
 template <> struct RawVec<float, 4> { using R = float4; };
 template <> struct RawVec<bf16_t, 8> { using R = uint4; };
