@@ -621,11 +621,23 @@ constexpr int kColsPerBlock = 128;
 
 int64_t scratch_elems(int64_t m, int64_t n, int mode) { return ((n + kColsPerBlock - 1) / kColsPerBlock) * m * (mode ? 2 : 1); }
 
+// How the first stage reads: whole vectors, vectors at any alignment, or single elements.  On odd extents vectors are the faster form on tiles of more than 64
+// rows (fp32 1031 x 4000 on tiles of 129 12.4 -> 9.9 us, 8007 x 8000 61 -> 50), in bf16 from two million elements on (1607 x 4000 on tiles of 201 16.4 -> 11.3, 8007 x
+// 8000 57 -> 29).  Tiles of up to 64 rows are one step of a wavefront either way (fp32 295 x 4000 on tiles of 37 8.8 and 9.8, bf16 9.8 and 11.2), and a small bf16 launch
+// waits for its few vectors longer than for single elements (201 x 1200 7.5 and 8.8, 1001 x 1200 8.1 and 8.8).
+enum SumForm { kSumVec, kSumAny, kSumScalar };
+inline SumForm sum_form(bool vec, bool bf16, int64_t ext, int64_t rows, int64_t ncols) {
+    return vec ? kSumVec : ext > 64 && (!bf16 || rows * ncols >= 2000000) ? kSumAny : kSumScalar;
+}
+// (ext: rows of the largest tile)
 template <typename T, int MODE>
-int32_t launch_rowsum_t(hipStream_t st, const RowsumGeom& g, int vpt, int64_t ntiles, bool vec, float* part) {
+int32_t launch_rowsum_t(hipStream_t st, const RowsumGeom& g, int64_t ext, int64_t ntiles, SumForm form, float* part) {
     constexpr int V = VecOf<T>::V;
-    if (vec) hipLaunchKernelGGL((rowsum_stage1<T, V, MODE>), dim3(vpt, g.splits, (unsigned)ntiles), dim3(256), 0, st, g, part);
-    else hipLaunchKernelGGL((rowsum_stage1<T, V, MODE, true>), dim3(vpt, g.splits, (unsigned)ntiles), dim3(256), 0, st, g, part);
+    const int per = 64 * (form == kSumScalar ? 1 : V);
+    const dim3 grid((unsigned)((ext + per - 1) / per), g.splits, (unsigned)ntiles), block(256);
+    if (form == kSumVec) hipLaunchKernelGGL((rowsum_stage1<T, V, MODE>), grid, block, 0, st, g, part);
+    else if (form == kSumAny) hipLaunchKernelGGL((rowsum_stage1<T, V, MODE, true>), grid, block, 0, st, g, part);
+    else hipLaunchKernelGGL((rowsum_stage1<T, 1, MODE>), grid, block, 0, st, g, part);
     return hipGetLastError() == hipSuccess ? NNT_OK : NNT_EHIP;
 }
 
@@ -642,11 +654,10 @@ int32_t rowsum_single(hipStream_t st, int dtype, int mode, int64_t m, int64_t n,
     g.rows_total = m;
     g.nslots = g.splits;
     const int V = dtype == NNT_F32 ? 4 : 8;
-    const bool vec = m % V == 0 && aligned16(dy) && (!x || aligned16(x));
-    const int vv = (int)((m + 64 * V - 1) / (64 * V));
+    const SumForm form = sum_form(m % V == 0 && aligned16(dy) && (!x || aligned16(x)), dtype == NNT_BF16, m, m, n);
     int32_t rc;
-    if (dtype == NNT_F32) rc = mode ? launch_rowsum_t<float, 1>(st, g, vv, 1, vec, scratch) : launch_rowsum_t<float, 0>(st, g, vv, 1, vec, scratch);
-    else rc = mode ? launch_rowsum_t<bf16_t, 1>(st, g, vv, 1, vec, scratch) : launch_rowsum_t<bf16_t, 0>(st, g, vv, 1, vec, scratch);
+    if (dtype == NNT_F32) rc = mode ? launch_rowsum_t<float, 1>(st, g, m, 1, form, scratch) : launch_rowsum_t<float, 0>(st, g, m, 1, form, scratch);
+    else rc = mode ? launch_rowsum_t<bf16_t, 1>(st, g, m, 1, form, scratch) : launch_rowsum_t<bf16_t, 0>(st, g, m, 1, form, scratch);
     if (rc != NNT_OK) return rc;
     const unsigned blocks = (unsigned)((m + kStage2Rows - 1) / kStage2Rows);
     hipLaunchKernelGGL(rowsum_stage2, dim3(blocks, mode ? 2 : 1), dim3(256), 0, st, scratch, (int64_t)g.splits, m, nullptr, out0, 1,
@@ -718,7 +729,8 @@ int32_t rowsum_tensor(nnt_ctx* ctx, int mode, nnt_tensor* dY, nnt_tensor* X, nnt
     int32_t rc = ensure_scratch(ctx, nslots * g.rows_total * (mode ? 2 : 1));
     if (rc != NNT_OK) return rc;
     if (dY->ntiles > 65535 || g.splits > 65535) return fail(ctx, NNT_EINVAL, "column sum: too many tiles");
-    const int vv = (int)((dY->base[0] + 64 * V - 1) / (64 * V));
+    const int64_t ext = dY->base[0];
+    const SumForm form = sum_form(vec, dY->dtype == NNT_BF16, ext, dY->shape[0], ncols);
     float* scratch = ctx->red_scratch;
     const int dtype = dY->dtype;
     const int64_t ntiles = dY->ntiles, rows = g.rows_total;
@@ -733,8 +745,8 @@ int32_t rowsum_tensor(nnt_ctx* ctx, int mode, nnt_tensor* dY, nnt_tensor* X, nnt
     if (out1) acc.push_back(out1->all(kWrite));
     return submit(ctx, acc, [=](hipStream_t st) {
         int32_t r;
-        if (dtype == NNT_F32) r = mode ? launch_rowsum_t<float, 1>(st, g, vv, ntiles, vec, scratch) : launch_rowsum_t<float, 0>(st, g, vv, ntiles, vec, scratch);
-        else r = mode ? launch_rowsum_t<bf16_t, 1>(st, g, vv, ntiles, vec, scratch) : launch_rowsum_t<bf16_t, 0>(st, g, vv, ntiles, vec, scratch);
+        if (dtype == NNT_F32) r = mode ? launch_rowsum_t<float, 1>(st, g, ext, ntiles, form, scratch) : launch_rowsum_t<float, 0>(st, g, ext, ntiles, form, scratch);
+        else r = mode ? launch_rowsum_t<bf16_t, 1>(st, g, ext, ntiles, form, scratch) : launch_rowsum_t<bf16_t, 0>(st, g, ext, ntiles, form, scratch);
         if (r != NNT_OK) return r;
         return launch_stage2(st, scratch, nslots, rows, o0, mode ? o1 : nullptr, base0);
     }, 2);
@@ -768,7 +780,17 @@ int32_t launch_ln_fwd(hipStream_t st, bool vec, bool any, int nv_needed, const T
                       const TiledView& G, const TiledView& B, float eps, int64_t ncols) {
     constexpr int V = VecOf<T>::V;
     // tokens of more than `kLnShareAbove` vectors per lane are shared by the four wavefronts of a workgroup
-    any = any && !vec && nv_needed <= 64;
+    // Odd extents: vectors at any alignment where they save enough of the steps in which 64 lanes take 64 single elements of a tile.  Measured on tiles of 5 to
+    // 2003, one to eight per token, 100 to 8000 tokens: with a third of the steps or less 1.0 to 4 times faster in fp32, with a quarter or less in bf16 (1.0 to 5.9); with 2 of 5
+    // in fp32 where a token has 16 vectors per lane or more (1.2 to 2.2), with half where it has 32 (3000 on tiles of 75 x 4000 tokens 87 -> 80 us).  Tiles of up to 63
+    // take as many steps either way, which single elements do faster (bf16 999 on tiles of 37 x 4000 31 us and 88, 320 on tiles of 50 12 and 20).  With few tokens what counts is
+    // that four wavefronts come to share one: more than four vectors per lane up to 1200 tokens (1.0 to 1.5 times), up to 256 where
+    // that would be many slots of few elements (bf16 255 on tiles of 51 x 1000 7.7 us and 9.0, 1600 on tiles of 25 41 and 49).
+    const int vecs = (X.base[0] + 64 * V - 1) / (64 * V), singles = (X.base[0] + 63) / 64;
+    const bool fewer_steps = V == 4 ? singles >= 3 * vecs || (nv_needed >= 16 && 2 * singles >= 5 * vecs) || (nv_needed >= 32 && singles >= 2 * vecs) : singles >= 4 * vecs;
+    const bool wide_slots = V == 8 ? nv_needed <= 16 && singles > vecs : nv_needed >= 8 || singles > vecs;
+    const bool few_tokens = nv_needed > kLnShareAbove && ncols <= (wide_slots ? 1200 : 256);
+    any = any && !vec && nv_needed <= 64 && (fewer_steps || few_tokens);
     const bool shared = (vec || any) && nv_needed > kLnShareAbove;
     const dim3 grid((unsigned)(shared ? ncols : (ncols + 3) / 4)), block(256);
     // (odd extents: vectors at any alignment, the last one of a tile moved back to end there)

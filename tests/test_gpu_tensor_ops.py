@@ -843,6 +843,29 @@ def test_bias_grad_in_one_launch(mods, dtype, shape, base):
         check(db.download(), np.asarray(dY, np.float64).reshape(shape[0], -1).sum(1), "f32", "bias grad")
 
 
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("rows,base,tokens", [(63, 63, 90), (129, 129, 90), (193, 193, 90), (501, 50, 1200), (501, 50, 1201), (386, 129, 1201), (513, 257, 90), (4111, 257, 1201), (770, 257, 1201),
+                                              (602, 201, 1300), (37, 5, 1300), (1499, 1499, 1100), (1500, 600, 1100), (255, 51, 1599), (1823, 65, 1097), (1823, 65, 1098), (200, 25, 1000), (65 * 25, 25, 70), (17 * 25, 25, 256), (17 * 25, 25, 257), (2049, 75, 1300)])
+def test_odd_extents_by_vectors_and_by_single_elements(mods, dtype, rows, base, tokens):
+    """Both sides of the rules that say whether layer norm and the column sums take odd extents by vectors or element by element."""
+    capi, tiled = mods
+    r = rng(89)
+    X, dY = [quant(r.standard_normal((rows, tokens)), dtype) for _ in range(2)]
+    gamma, beta = (1 + 0.1 * r.standard_normal(rows)).astype(np.float32), r.standard_normal(rows).astype(np.float32)
+    Yref, mean, rstd = D.layernorm_fwd(X, gamma, beta, 1e-5)
+    with tiled.Context(n_streams=2) as ctx:
+        tX, tdY = T(tiled, ctx, X, (base, 700), dtype), T(tiled, ctx, dY, (base, 700), dtype)
+        tg, tb = T(tiled, ctx, gamma, (base,), "f32"), T(tiled, ctx, beta, (base,), "f32")
+        tY, tdX = (tiled.TiledTensor(ctx, dtype, (rows, tokens), (base, 700)) for _ in range(2))
+        tS = tiled.TiledTensor(ctx, "f32", (2, tokens), (2, 700))
+        db = tiled.TiledTensor(ctx, "f32", (rows,), (base,))
+        capi.nnt_layernorm_fwd(ctx.h, tX.h, tg.h, tb.h, 1e-5, tY.h, tS.h)
+        capi.nnt_bias_grad(ctx.h, tdY.h, db.h)
+        check(tY.download(), Yref, dtype, "ln")
+        check(tS.download(), np.stack([mean, rstd]), "f32", "statistics")
+        check(db.download(), np.asarray(dY, np.float64).sum(1), "f32", "bias grad")
+
+
 @pytest.mark.parametrize("shape,base,launches", [((300, 64), (100, 64), 1), ((300, 64), (100, 33), 1), ((300, 64), (100, 30), 2), ((300, 16, 8), (300, 16, 4), 1),
                                                  ((300, 16, 8), (300, 16, 2), 2), ((40, 1024), (40, 1), 2), ((301, 8, 64), (75, 8, 1), 2)])
 def test_bias_grad_of_many_tiles_takes_two_launches(mods, shape, base, launches):
