@@ -1477,10 +1477,12 @@ int32_t nnt_layernorm_bwd(nnt_ctx* ctx, nnt_tensor* X, nnt_tensor* stats, nnt_te
         // sums and the input gradient one after the other.
         // Tiles that fill less than half of a wave's lanes, more than 1024 tokens: two passes as well.  The one pass is the faster call by itself there too,
         // but its 256 large workgroups, most lanes idle, hold up the products of the other stream: 66 blocks and models of 128 to 768 wide on tiles of
-        // 64 and 128 with 2048 and 4096 tokens are 1 % faster in two passes on average (0.93 to 1.04), 33 with 1024 tokens 1 % slower.  Odd extents
-        // stay with the one pass (320 wide on tiles of 50 0 to 2 % faster): the two passes read them element by element.
+        // 64 and 128 with 2048 and 4096 tokens are 1 % faster in two passes on average (0.93 to 1.04), 33 with 1024 tokens 1 % slower.
+        // Odd extents: the two passes take them element by element, 64 to a step, which is slower (4097 x 1000 on tiles of 1024 1.8 times) but for tiles of up to 64 rows: more than
+        // 1024 tokens, or more than 256 of more than eight vectors per lane (bf16 500 x 4000 on tiles of 50 23 us and 56, 63 x 1000 on tiles of 5 20 and 35, fp32 500 x 4000
+        // 25 and 44; with fewer 1.0 to 1.6 times the other way round).
         const int lanes = 64 * V * (int)((X->base[0] + 64 * V - 1) / (64 * V));
-        const bool narrow = vec && 2 * X->base[0] < lanes && ncols > 1024;
+        const bool narrow = vec ? 2 * X->base[0] < lanes && ncols > 1024 : X->base[0] <= 64 && (ncols > 1024 || (nv > 8 && ncols > 256));
         const int wpt = !narrow && (vec || any_vec({X, dY, dX, dRes, gamma})) ? onepass_waves(vec && dtype == NNT_BF16, nv) : 0;
         // (so do calls inside a capture whose partial rows have no room yet)
         const int64_t wgs = wpt > 0 ? onepass_wgs(wpt, ncols) : 0, rows = X->shape[0];
