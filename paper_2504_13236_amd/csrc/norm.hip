@@ -1142,12 +1142,13 @@ inline int onepass_wpt(int nv_needed) {
 // on narrow tiles, are slower than two passes that run side by side in a graph (bf16 8200 x 300 19 and 33, fp32 2048 x 1000 on tiles of 64 26 and 36), and about as
 // fast as calls (41 and 42, 54 and 47).
 constexpr int kOnepassVecs = 2, kOnepassLong = 4;
-// bf16 tokens of three or four whole vectors per lane stay with one wave and that form: the sums over a token are then added in the order of the two
-// passes, and dx is what they leave bit for bit (single flipped roundings of dx travel through the products behind it).  In fp32, where the last digit is all
-// that changes, and on odd extents, which the two passes take element by element, two waves are the faster form (fp32 1024 x 8192 32 us, one wave 35; bf16 1120 x 128
-// on tiles of 300 13 and 17; whole vectors, 1600 x 8192 on tiles of 400 32 either way, 768 x 8192 29 and 27, 2048 x 8192 on tiles of 512 38 and 42).
-inline int onepass_waves(bool bf16_vec, int nv_needed) {
-    if (bf16_vec && nv_needed > kOnepassVecs && nv_needed <= kOnepassLong) return 1;
+// 4096 bf16 tokens and more of three or four whole vectors per lane stay with one wave and that form: the sums over a token are then added in the order of the
+// two passes, and dx is what they leave bit for bit (single flipped roundings of dx travel through the products behind it).  Two waves are the faster form for
+// fewer tokens (1664 x 2319 on tiles of 512, forward and backward, 20 us, one wave 23; 4096 and more: 1600 x 8192 on tiles of 400 32 either way, 768 x 8192 29 and 27, 2048 x 8192 on tiles of
+// 512 38 and 42), in fp32, where the last digit is all that changes (1024 x 8192 32 us, one wave 35), and on odd extents, which the two passes take element by element
+// (bf16 1120 x 128 on tiles of 300 13 and 17).
+inline int onepass_waves(bool bf16_vec, int nv_needed, int64_t ncols) {
+    if (bf16_vec && nv_needed > kOnepassVecs && nv_needed <= kOnepassLong && ncols >= 4096) return 1;
     const int w = onepass_wpt<kOnepassVecs>(nv_needed);
     return w ? w : onepass_wpt<kOnepassLong>(nv_needed);
 }
@@ -1157,16 +1158,13 @@ template <typename T, int NV, int WPT>
 int32_t launch_onepass_w(hipStream_t st, bool vec, const TiledView& X, const TiledView& S, const TiledView& G, const TiledView& dY,
                          const TiledView& dR, const TiledView& dX, int has_res, int64_t ncols, float* part) {
     constexpr int V = VecOf<T>::V;
-    // (whole vectors only, or odd extents only: see onepass_waves)
-    constexpr bool kVec = !(sizeof(T) == 2 && NV == kOnepassVecs && WPT == 2), kAny = !(NV == kOnepassLong && WPT == 1);
+    constexpr bool kAny = !(NV == kOnepassLong && WPT == 1);       // (whole vectors only: see onepass_waves)
     const int64_t wgs = onepass_wgs(WPT, ncols), per = wgs * (kOnepassWaves / WPT);
     const unsigned n = (unsigned)ncols, rounds = (unsigned)((ncols + per - 1) / per);
     const dim3 grid((unsigned)wgs), block(64 * kOnepassWaves);
-    if (vec ? !kVec : !kAny) return NNT_EINVAL;
-    if constexpr (kVec) {
-        if (vec && has_res) hipLaunchKernelGGL((ln_bwd_onepass<T, V, NV, WPT, true, false>), grid, block, 0, st, X, S, G, dY, dR, dX, n, rounds, part);
-        else if (vec) hipLaunchKernelGGL((ln_bwd_onepass<T, V, NV, WPT, false, false>), grid, block, 0, st, X, S, G, dY, dR, dX, n, rounds, part);
-    }
+    if (!vec && !kAny) return NNT_EINVAL;
+    if (vec && has_res) hipLaunchKernelGGL((ln_bwd_onepass<T, V, NV, WPT, true, false>), grid, block, 0, st, X, S, G, dY, dR, dX, n, rounds, part);
+    else if (vec) hipLaunchKernelGGL((ln_bwd_onepass<T, V, NV, WPT, false, false>), grid, block, 0, st, X, S, G, dY, dR, dX, n, rounds, part);
     if constexpr (kAny) {
         if (!vec && has_res) hipLaunchKernelGGL((ln_bwd_onepass<T, V, NV, WPT, true, true>), grid, block, 0, st, X, S, G, dY, dR, dX, n, rounds, part);
         else if (!vec) hipLaunchKernelGGL((ln_bwd_onepass<T, V, NV, WPT, false, true>), grid, block, 0, st, X, S, G, dY, dR, dX, n, rounds, part);
@@ -1483,7 +1481,7 @@ int32_t nnt_layernorm_bwd(nnt_ctx* ctx, nnt_tensor* X, nnt_tensor* stats, nnt_te
         // 25 and 44; with fewer 1.0 to 1.6 times the other way round).
         const int lanes = 64 * V * (int)((X->base[0] + 64 * V - 1) / (64 * V));
         const bool narrow = vec ? 2 * X->base[0] < lanes && ncols > 1024 : X->base[0] <= 64 && (ncols > 1024 || (nv > 8 && ncols > 256));
-        const int wpt = !narrow && (vec || any_vec({X, dY, dX, dRes, gamma})) ? onepass_waves(vec && dtype == NNT_BF16, nv) : 0;
+        const int wpt = !narrow && (vec || any_vec({X, dY, dX, dRes, gamma})) ? onepass_waves(vec && dtype == NNT_BF16, nv, ncols) : 0;
         // (so do calls inside a capture whose partial rows have no room yet)
         const int64_t wgs = wpt > 0 ? onepass_wgs(wpt, ncols) : 0, rows = X->shape[0];
         if (wpt > 0 && ncols > 0 && ncols < INT32_MAX / 2 && X->ntiles <= 65535 && !(ctx->capturing && 2 * wgs * rows > ctx->stream_scratch_elems)) {
