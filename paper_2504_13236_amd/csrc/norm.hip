@@ -1490,7 +1490,7 @@ int32_t nnt_layernorm_bwd(nnt_ctx* ctx, nnt_tensor* X, nnt_tensor* stats, nnt_te
             rc = ensure_stream_scratch(ctx, 2 * wgs * rows);
             if (rc != NNT_OK) return rc;
             // (what the records say; for the choice of a stream the operation keeps the weight of two passes, being as long as a pass over that much:
-            // 11 to 16 us with its second launch where x, dy, the residual and dx are 10 to 16 MB.  Counted by those bytes it would be a small task: 27
+            // 11 to 16 us with its second launch where x, dy, the residual and dx are 10 to 16 MB.  Counted by those bytes it would be a small task: 20
             // blocks and models with such adjoints 0.4 % slower, bf16 768 x 2048 580 -> 595 us, fp32 1024 x 896 3060 -> 3115)
             ctx->cur_work = bytes * (3 + (dRes ? 1 : 0));
             void* const* og = dgamma->d_tiles;
